@@ -120,7 +120,13 @@ void release(fmm_plan* pl) {
       if (lv.Mt) (void)hipFree(lv.Mt);
       if (lv.L) (void)hipFree(lv.L);
       if (lv.Lt) (void)hipFree(lv.Lt);
+      if (lv.Lw) (void)hipFree(lv.Lw);
+      if (lv.Lc) (void)hipFree(lv.Lc);
     }
+  for (auto& f : pl->fld)
+    if (f.rho_copy) (void)hipFree(f.rho_copy);
+  for (auto w : pl->wblk)
+    if (w) (void)hipFree(w);
   auto free_st = [](fmm::SegTable& st) {
     if (st.dev) (void)hipFree(st.dev);
     st = fmm::SegTable{};
@@ -131,6 +137,8 @@ void release(fmm_plan* pl) {
   for (auto& st : pl->s_conv) free_st(st);
   for (auto& st : pl->s_l2l) free_st(st);
   for (auto& a : pl->s_bot)
+    for (auto& st : a) free_st(st);
+  for (auto& a : pl->s_blk)
     for (auto& st : a) free_st(st);
   for (auto& st : pl->s_red) free_st(st);
   release_adj(pl->adj);
@@ -356,7 +364,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2];
+  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -368,7 +376,7 @@ int build_schedule(fmm_plan* pl) {
     // gets its typed copy alone
     sg.b = pl->dl == 1 && bottom_low(pl, F) ? nullptr : (double*)fd.lev[F].M;
     sg.t = fd.lev[F].Mt;
-    p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
+    if (!block_field(pl, F)) p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
     // FMM-1: the multipoles of level F - 1 straight from the 4^3 unigrid
     // cells of each cell (as FMM-2's P2M), which reads the density instead
     // of the 8x larger level-F grid; M2M then starts at level F - 1
@@ -413,6 +421,22 @@ int build_schedule(fmm_plan* pl) {
       l.a = (const double*)fd.lev[k - 1].L;
       l.b = (double*)fd.lev[k].L;
       l2l[k].add(l, cdiv((long long)l.n * l.n * l.n, fmm::L2L_ROWS));
+    }
+    if (block_field(pl, F)) {
+      const int x = bottom_low(pl, F) ? 1 : 0, nb = fd.n >> 2;
+      Seg b{};
+      b.n = fd.n;
+      b.tpa = (int)cdiv(nb, 4);
+      b.field = f;
+      b.t = fd.rho_copy;
+      b.u = F >= 3 ? fd.lev[F].Lw : nullptr;
+      b.d = F >= 4 ? fd.lev[F - 1].Lc : nullptr;
+      for (int v = 0; v < 3; ++v) {
+        b.tz = (int)cdiv(nb, 1 << v);
+        blk[x][v].add(b, (long long)b.tpa * b.tpa * b.tz);
+      }
+      pl->blk_rows[x] += (long long)b.tpa * b.tpa * nb;
+      continue;
     }
     for (int z = 0; z < 2; ++z) {
       Seg b{};
@@ -493,6 +517,7 @@ int build_schedule(fmm_plan* pl) {
       for (auto& c : cl.v)
         if (c.u) lt[c.field] = c.u;
     pl->lt_live = false;
+    for (auto p : lt) pl->lt_live = pl->lt_live || p;
     for (auto& bs : bot)
       for (auto& bl : bs)
         for (auto& b : bl.v) {
@@ -513,6 +538,8 @@ int build_schedule(fmm_plan* pl) {
     if ((rc = upload_segs(pl, pl->s_red[x], red[x]))) return rc;
     for (int z = 0; z < 2; ++z)
       if ((rc = upload_segs(pl, pl->s_bot[x][z], bot[x][z]))) return rc;
+    for (int v = 0; v < 3; ++v)
+      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v]))) return rc;
   }
   return FMM_OK;
 }
@@ -874,6 +901,24 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
         }
       }
     }
+  }
+  for (auto& fd : pl->fld) {
+    if (!fmm::block_field(pl, fd.F)) continue;
+    const int F = fd.F;
+    const bool low = fmm::bottom_low(pl, F);
+    const size_t hr = (size_t)((p + 1) * (p + 1) + 3) / 4 * 4;
+    if (!low) {
+      const size_t b = (size_t)fd.n * fd.n * fd.n * (pl->precision == 0 ? sizeof(double) : sizeof(float));
+      if (dev_alloc(pl, &fd.rho_copy, b)) return bail();
+      if (hipMemset(fd.rho_copy, 0, b) != hipSuccess) {
+        fail(FMM_ERR_DEVICE, "hipMemset failed");
+        return bail();
+      }
+    }
+    if (F >= 3 && dev_alloc(pl, &fd.lev[F].Lw, (size_t)fd.lev[F].ncell * hr * (low ? sizeof(float) : sizeof(double))))
+      return bail();
+    if (F >= 4 && dev_alloc(pl, (void**)&fd.lev[F - 1].Lc, (size_t)fd.lev[F - 1].ncell * hr * sizeof(double)))
+      return bail();
   }
   const std::vector<int> dl = build_dlists();
   if (dl.size() != 8 * (size_t)fmm::NLIST_PAD) {
@@ -1499,6 +1544,42 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   const int nch = (nt + 3) / 4;
   if (!out || count < (size_t)lv.ncell * nt) return fail(FMM_ERR_INVALID_ARG, "out must hold %lld doubles", lv.ncell * nt);
   const int nk = lv.nk;
+  if (which == 0 && level == plan->F && fmm::block_field(plan, plan->F)) {
+    // the block kernel forms no level-F multipoles: derive them from the
+    // copy of the density it left (P2M: sum_q rho_q (s_q / 4)^a / a!)
+    const int n = plan->n;
+    const size_t N = (size_t)n * n * n;
+    std::vector<double> rho(N);
+    hipError_t e;
+    if (plan->precision == 0) {
+      e = hipMemcpy(rho.data(), plan->fld[0].rho_copy, N * sizeof(double), hipMemcpyDeviceToHost);
+    } else {
+      std::vector<float> r32(N);
+      e = hipMemcpy(r32.data(), plan->fld[0].rho_copy, N * sizeof(float), hipMemcpyDeviceToHost);
+      std::copy(r32.begin(), r32.end(), rho.begin());
+    }
+    if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
+    std::vector<int> mi(3 * fmm::nterms(plan->p));
+    fmm_multi_index(plan->p, mi.data(), mi.size());
+    auto fact = [](int k) { double f = 1; for (int i = 2; i <= k; ++i) f *= i; return f; };
+    for (long long cidx = 0; cidx < lv.ncell; ++cidx) {
+      const int c2 = (int)(cidx % nk), c1 = (int)((cidx / nk) % nk), c0 = (int)(cidx / ((long long)nk * nk));
+      double v[8];
+      for (int q = 0; q < 8; ++q)
+        v[q] = rho[((size_t)(2 * c0 + ((q >> 2) & 1)) * n + 2 * c1 + ((q >> 1) & 1)) * n + 2 * c2 + (q & 1)];
+      for (int t = 0; t < nt; ++t) {
+        const int *ex = &mi[3 * t], pat = ((ex[0] & 1) << 2) | ((ex[1] & 1) << 1) | (ex[2] & 1);
+        double s = 0.0;
+        for (int q = 0; q < 8; ++q) {
+          int b = q & pat;
+          b ^= b >> 2;
+          s += ((b ^ (b >> 1)) & 1) ? -v[q] : v[q];
+        }
+        out[cidx * nt + t] = std::ldexp(s / (fact(ex[0]) * fact(ex[1]) * fact(ex[2])), -2 * (ex[0] + ex[1] + ex[2]));
+      }
+    }
+    return ok();
+  }
   if (which == 0) {
     std::vector<double> host((size_t)nch * lv.ncellp * 4);
     hipError_t e = hipMemcpy(host.data(), lv.M, host.size() * sizeof(double), hipMemcpyDeviceToHost);

@@ -1,0 +1,491 @@
+// Mirror-folded kernels of the finest level.  Included by fmm_impl.h (needs
+// its constant tables and helpers).
+//
+// An oct (the 8 children of one cell, Sec. 2.2) is its own mirror image about
+// its centre along each axis, and so are the 6^3 cells that hold the sources
+// of its targets.  With t a target and s a source in the positive octant of
+// the oct's centre, and tau, sigma in {+1,-1}^3 their mirror signs,
+//   out(tau t, b) = sum_{s, sigma} K(tau t - sigma s) in(sigma s, a)
+// and, as a derivative of 1/r of order g picks up the sign of an axis where
+// g is odd, K[g](tau t - sigma s) = tau^g K[g](t - tau sigma s).  The sum over
+// sigma is a convolution over the group {+1,-1}^3: Walsh sums over the 8
+// mirror images turn it into 8 independent products, one per parity pattern e,
+//   IN(e; s, a)  = sum_sigma chi_e(sigma) sigma^a in(sigma s, a)
+//   OUT(e; t, b) = sum_{s, a} K^(e; t, b; s, a) IN(e; s, a)
+//   tau^b out(tau t, b) = 1/8 sum_e chi_e(tau) OUT(e; t, b)
+// with 1/8 of the multiply-adds of the unfolded sum (chi_e(sigma) = -1 for
+// each axis with e = 1 and sigma = -1).  Pairs that the interaction list
+// excludes have zero K; the exclusion is mirror-symmetric too.
+#pragma once
+
+// ---------------------------------------------------------------------------
+// Harmonic terms.  D[g] = -d^g (1/r) obeys Laplace's equation away from the
+// source, D[x, y, z + 2] = -D[x + 2, y, z] - D[x, y + 2, z], so an expansion
+// is fixed by its terms with z exponent 0 or 1: (m + 1)^2 up to degree m.
+// Reduced index: by degree m, then z = 0 (x ascending), then z = 1.
+// ---------------------------------------------------------------------------
+constexpr __host__ __device__ int hterms(int m) { return m < 0 ? 0 : (m + 1) * (m + 1); }
+constexpr __host__ __device__ int h_degree(int i) {
+  int m = 0;
+  while ((m + 1) * (m + 1) <= i) ++m;
+  return m;
+}
+// exponents x | y << 8 | z << 16 of reduced term i
+constexpr __host__ __device__ int h_exp(int i) {
+  const int m = h_degree(i), r = i - m * m;
+  return r <= m ? (r | (m - r) << 8) : ((r - m - 1) | (m - 1 - (r - m - 1)) << 8 | 1 << 16);
+}
+constexpr __host__ __device__ int h_index(int x, int y, int z) {
+  const int m = x + y + z;
+  return m * m + (z ? m + 1 + x : x);
+}
+constexpr __host__ __device__ int binom(int n, int k) {
+  int b = 1;
+  for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i;
+  return b;
+}
+// Moments (or evaluation coefficients) f of the full expansion carried over to
+// reduced term (x, y, e): sum over the full terms that the recurrence sends
+// there, (x - 2l, y - 2m, 2(l + m) + e) with weight (-1)^(l+m) C(l+m, l).
+template <typename F>
+__device__ __forceinline__ double h_reduce(int i, F&& f) {
+  const int ex = h_exp(i), x = mi_a(ex), y = mi_b(ex), e = mi_c(ex);
+  double s = 0.0;
+  for (int l = 0; 2 * l <= x; ++l)
+    for (int m = 0; 2 * m <= y; ++m) {
+      const double w = (double)(((l + m) & 1) ? -binom(l + m, l) : binom(l + m, l));
+      s += w * f(mi_index(x - 2 * l, y - 2 * m, 2 * (l + m) + e));
+    }
+  return s;
+}
+constexpr __host__ __device__ int h_parity(int i) {
+  const int ex = h_exp(i);
+  return ((ex & 1) << 2) | (((ex >> 8) & 1) << 1) | ((ex >> 16) & 1);
+}
+
+// chi_e(sigma) with sigma given by its minus bits
+__host__ __device__ __forceinline__ double chi(int e, int minus) {
+  int b = e & minus;
+  b ^= b >> 2;
+  return ((b ^ (b >> 1)) & 1) ? -1.0 : 1.0;
+}
+
+// ---------------------------------------------------------------------------
+// Finest block kernel.  A block is 4^3 unigrid cells: an oct of level F
+// (FMM-1).  Its sources are the 12^3 unigrid cells of the 6^3 level-F cells
+// around: M2P of a level-F source is a linear map of its 8 densities (P2M,
+// then M2P: 8 numbers fix all its multipoles), so P2M, M2P (Sec. 4) and the
+// near field, eq. (direct), are one matrix of 12^3 sources by 64 targets x
+// (phi, g), tabulated once per plan for the order and truncation.  Folded, it
+// is 8 products of K = 216 by 32 columns.  L2P adds K rows to them:
+//  - the own locals (M2L part of the 8 level-F cells), Walsh-folded over the
+//    children, K = (p + 1)^2 harmonic terms, the same table for every e;
+//  - the level F-1 local of the block's own cell (L2L then L2P as one exact
+//    evaluation): only terms of parity e enter pattern e.
+// ---------------------------------------------------------------------------
+constexpr int BLK_K = 216, BLK_STEPS = BLK_K / 4;
+constexpr int BLK_THREADS = 512;
+// LDS tile of densities: (4 NX + 8) x 24 x 24 cells, z rows of 28 (16 lanes
+// 4 octs apart in y and z, 4 consecutive z each, then hit distinct banks)
+constexpr int BLK_ROW = 28, BLK_PLANE = 24 * BLK_ROW;
+constexpr __host__ __device__ int blk_tile(int nx) { return (4 * nx + 8) * BLK_PLANE; }
+
+// row stride of the folded locals per (parent, pattern), in terms
+constexpr __host__ __device__ int hrow(int P) { return (hterms(P) + 3) / 4 * 4; }
+// K steps of the own-local part: whole groups of 16 terms (a lane takes 4
+// consecutive terms, one vector load), then steps of 4
+constexpr __host__ __device__ int blk_lsteps(int P) { return (hterms(P) + 3) / 4; }
+// reduced term of K index (step s, k group kq) of the own-local part
+constexpr __host__ __device__ int blk_lterm(int P, int s, int kq) {
+  const int full = hterms(P) / 16 * 4;  // steps in whole groups
+  return s < full ? (s / 4) * 16 + 4 * kq + s % 4 : 4 * s + kq;
+}
+// K steps of the level F-1 part: the most terms of one parity pattern
+constexpr __host__ __device__ int blk_psteps(int P) {
+  int most = 0;
+  for (int e = 0; e < 8; ++e) {
+    int c = 0;
+    for (int i = 0; i < hterms(P); ++i) c += h_parity(i) == e;
+    most = c > most ? c : most;
+  }
+  return (most + 3) / 4;
+}
+// the k-th reduced term of parity e, or -1
+constexpr __host__ __device__ int blk_pterm(int P, int e, int k) {
+  for (int i = 0; i < hterms(P); ++i)
+    if (h_parity(i) == e && k-- == 0) return i;
+  return -1;
+}
+// table layout (elements): the folded stencil [54][8][2][64], the own locals
+// [steps][2][64], the level F-1 locals [8][steps][2][64]
+constexpr __host__ __device__ int blk_off_l() { return BLK_STEPS * 8 * 2 * 64; }
+constexpr __host__ __device__ int blk_off_p(int P) { return blk_off_l() + blk_lsteps(P) * 2 * 64; }
+constexpr __host__ __device__ int blk_table(int P) { return blk_off_p(P) + 8 * blk_psteps(P) * 2 * 64; }
+
+// The unfolded stencil G[t][v][o], t in the positive octant (bits: 1/2 or 3/2
+// from the centre), v = (12 v0 + v1) 12 + v2 the source, in the units of the
+// bottom accumulators (phi = dx^2/2 acc, g = -dx/4 acc).
+__global__ void k_blk_green(const double* __restrict__ Dtab, double* __restrict__ G, int NMX, int ND) {
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= 8 * 1728 * 4) return;
+  const int o = id & 3, v = (id >> 2) % 1728, t = (id >> 2) / 1728;
+  const int vv[3] = {v / 144, (v / 12) % 12, v % 12};
+  const int tb[3] = {(t >> 2) & 1, (t >> 1) & 1, t & 1};
+  int d[3];
+  bool near = true;
+  for (int a = 0; a < 3; ++a) {
+    d[a] = 3 - (vv[a] >> 1);
+    near = near && d[a] >= -1 && d[a] <= 1;
+  }
+  double x = 0.0;
+  if (near) {
+    const int dt = (9 + tb[0] - vv[0]) * 49 + (9 + tb[1] - vv[1]) * 7 + (9 + tb[2] - vv[2]);
+    x = o == 0 ? 2.0 * c_p2p_phi[dt] : -4.0 * c_p2p_g[(o - 1) * 343 + dt];
+  } else {
+    const int dd = (d[0] + 3) * 49 + (d[1] + 3) * 7 + d[2] + 3;
+    const double* D = Dtab + ((size_t)dd * 8 + t) * ND;
+    for (int al = 0; al < NMX; ++al) {
+      const int ex = c_mi_exp[al];
+      const int ax = mi_a(ex), ay = mi_b(ex), az = mi_c(ex);
+      double c = ldexp(c_mi_invfact[al], -2 * (ax + ay + az));
+      if (((vv[0] & ax) + (vv[1] & ay) + (vv[2] & az)) & 1) c = -c;
+      x = fma(c, D[mi_index(ax + (o == 1), ay + (o == 2), az + (o == 3))], x);
+    }
+  }
+  G[id] = x;
+}
+
+// The block kernel's B table in the compute type (layout above); lane = j +
+// 16 kq, column 16 tile + j = (t, o).  The 1/8 of the inverse Walsh sum is
+// left to the epilogue.
+template <typename H>
+__global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int P) {
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= blk_table(P)) return;
+  const int lane = id & 63, tile = (id >> 6) & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
+  const int t = col >> 2, o = col & 3;
+  double x = 0.0;
+  if (id < blk_off_l()) {
+    const int e = (id >> 7) & 7, k = 4 * (id >> 10) + kq;
+    const int jj[3] = {k / 36, (k / 6) % 6, k % 6};
+    for (int minus = 0; minus < 8; ++minus) {
+      int v = 0;
+      for (int a = 0; a < 3; ++a) v = v * 12 + (((minus >> (2 - a)) & 1) ? 5 - jj[a] : 6 + jj[a]);
+      x += chi(e, minus) * G[((size_t)t * 1728 + v) * 4 + o];
+    }
+  } else if (id < blk_off_p(P)) {
+    const int b = blk_lterm(P, (id - blk_off_l()) >> 7, kq);
+    if (b < hterms(P)) x = h_reduce(b, [&](int bt) { return l2p_coef(bt, t, o); });
+  } else {
+    const int s = (id - blk_off_p(P)) >> 7, np = blk_psteps(P), e = s / np;
+    const int b = blk_pterm(P, e, 4 * (s % np) + kq);
+    if (b >= 0) x = 8.0 * h_reduce(b, [&](int bt) { return l2p_parent_coef(bt, 7, t, o); });
+  }
+  W[id] = static_cast<H>(x);
+}
+
+// Walsh sums of the 8 mirror images r[minus bits] for the NE patterns
+// NE eg .. NE eg + NE - 1, with s[axis] = chi of the axes fixed by eg.
+template <int NE, typename H>
+__device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[NE]) {
+  H x[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = fma(sx, r[4 + q], r[q]);
+  if constexpr (NE == 4) {
+    const H p0 = x[0] + x[2], p1 = x[1] + x[3], m0 = x[0] - x[2], m1 = x[1] - x[3];
+    a[0] = p0 + p1;
+    a[1] = p0 - p1;
+    a[2] = m0 + m1;
+    a[3] = m0 - m1;
+  } else {
+    const H y0 = fma(sy, x[2], x[0]), y1 = fma(sy, x[3], x[1]);
+    if constexpr (NE == 2) {
+      a[0] = y0 + y1;
+      a[1] = y0 - y1;
+    } else {
+      a[0] = fma(sz, y1, y0);
+    }
+  }
+}
+
+// Segments: n = unigrid cells per axis, tpa = tiles along y and z, tz = tiles
+// along x, field, t = copy of the density to leave in the plan (or null),
+// u = own locals [block][8][hrow] in the compute type (or null: F = 2),
+// d = level F-1 locals [block][hrow] (or null: F < 4).
+// Tile: NX x 4 x 4 blocks; wave w takes row tile X = w % NX (the 4 x 4 blocks
+// of plane X) and the NX patterns from NX (w / NX).
+// What bounds it: the matrix cores (54 + 13 + 3 K steps of 16 products per row
+// tile at p = 6).  A lane reads the 8 mirror images of its operand from the LDS
+// tile and folds them itself (12 adds for 8 products); B is read through the
+// caches, each fragment once per wave, the NX waves of a plane sharing it.
+template <int P, typename CT, typename TI, typename TO, int NX>
+__global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>::H) > 80000 ? 2 : 4)) void k_block(const Seg* __restrict__ segs, int nseg, IoArg io,
+                                                          const typename Mf<CT>::H* __restrict__ W,
+                                                          unsigned int* __restrict__ stamp_cnt,
+                                                          unsigned long long* __restrict__ stamp_done) {
+  using M = Mf<CT>;
+  using H = typename M::H;
+  using Acc = typename M::Acc;
+  constexpr int NE = NX, HR = hrow(P), NLS = blk_lsteps(P), NPS = blk_psteps(P);
+  // epilogue image of the block's results, [8][NX * 16][33]
+  constexpr int EP = 8 * NX * 16 * 33, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
+  __shared__ __attribute__((aligned(16))) H lds[SZ];
+  __shared__ int spt[8 * NPS * 4];
+  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
+  const int n = sg.n, nb = n >> 2;
+  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
+  TO* __restrict__ phi = io_phi<TO>(io, sg.field);
+  TO* __restrict__ g = io_g<TO>(io, sg.field);
+  TI* __restrict__ keep = static_cast<TI*>(sg.t);
+  const int lb = blockIdx.x - sg.first_block;
+  const int bx0 = (lb / (sg.tpa * sg.tpa)) * NX, by0 = ((lb / sg.tpa) % sg.tpa) * 4, bz0 = (lb % sg.tpa) * 4;
+  for (int t = threadIdx.x; t < 8 * NPS * 4; t += BLK_THREADS) spt[t] = blk_pterm(P, t / (NPS * 4), t % (NPS * 4));
+  // the densities of the tile and 4 cells around, zero outside the grid
+  {
+    constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
+    const int x0 = 4 * bx0 - 4, y0 = 4 * by0 - 4, z0 = 4 * bz0 - 4;
+    const auto grho = gmem(rho);
+#pragma unroll 1
+    for (int e0 = threadIdx.x; e0 < CNT; e0 += FB * BLK_THREADS) {
+      TI v[FB];
+#pragma unroll
+      for (int u = 0; u < FB; ++u) {
+        const int e = e0 + u * BLK_THREADS, z = z0 + e % 24, y = y0 + (e / 24) % 24, x = x0 + e / 576;
+        const bool in = e < CNT && x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
+        v[u] = in ? grho[((long long)x * n + y) * n + z] : TI(0);
+      }
+#pragma unroll
+      for (int u = 0; u < FB; ++u) {
+        const int e = e0 + u * BLK_THREADS, tz = e % 24, ty = (e / 24) % 24, tx = e / 576;
+        if (e < CNT) {
+          lds[tx * BLK_PLANE + ty * BLK_ROW + tz] = static_cast<H>(v[u]);
+          if (keep && tx >= 4 && tx < 4 * NX + 4 && ty >= 4 && ty < 20 && tz >= 4 && tz < 20 && x0 + tx < n &&
+              y0 + ty < n && z0 + tz < n)
+            keep[((long long)(x0 + tx) * n + y0 + ty) * n + z0 + tz] = v[u];
+        }
+      }
+    }
+  }
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, eg = w / NX, e0 = eg * NE;
+  const H sx = (e0 & 4) ? H(-1) : H(1), sy = (e0 & 2) ? H(-1) : H(1), sz = (e0 & 1) ? H(-1) : H(1);
+  Acc acc[NE][2];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) acc[e][0] = acc[e][1] = Acc{0, 0, 0, 0};
+  __syncthreads();
+  // ---- the 12^3 densities: K index k = (36 jx + 6 jy + jz), image "plus" at
+  // centre + j, "minus" at centre - 1 - j along each axis
+  {
+    const H* ctr = lds + (4 * X + 6) * BLK_PLANE + (4 * (i >> 2) + 6) * BLK_ROW + 4 * (i & 3) + 6;
+    int jx = 0, jy = 0, jz = kq;
+    auto aread = [&](H (&r)[8]) {
+      const int px = jx * BLK_PLANE, mx = -BLK_PLANE - px, py = jy * BLK_ROW, my = -BLK_ROW - py;
+      const H *pp = ctr + px + py, *pm = ctr + px + my, *mp = ctr + mx + py, *mm = ctr + mx + my;
+      r[0] = pp[jz];
+      r[1] = pp[-1 - jz];
+      r[2] = pm[jz];
+      r[3] = pm[-1 - jz];
+      r[4] = mp[jz];
+      r[5] = mp[-1 - jz];
+      r[6] = mm[jz];
+      r[7] = mm[-1 - jz];
+      jz += 4;
+      if (jz >= 6) {
+        jz -= 6;
+        if (++jy == 6) {
+          jy = 0;
+          jx = jx < 5 ? jx + 1 : 5;  // (past the last step: a read that is not used)
+        }
+      }
+    };
+    const auto wb = gmem(W + e0 * 128 + lane);
+    auto bread = [&](int s, H (&b)[NE][2]) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) b[e][t] = wb[s * 1024 + e * 128 + t * 64];
+    };
+    H r[2][8], b[2][NE][2], a[NE];
+    aread(r[0]);
+    bread(0, b[0]);
+#pragma unroll 1
+    for (int s = 0; s < BLK_STEPS; s += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int sn = s + u + 1 < BLK_STEPS ? s + u + 1 : BLK_STEPS - 1;
+        bread(sn, b[u ^ 1]);
+        aread(r[u ^ 1]);
+        fold8<NE>(r[u], sx, sy, sz, a);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          acc[e][0] = M::op(a[e], b[u][e][0], acc[e][0]);
+          acc[e][1] = M::op(a[e], b[u][e][1], acc[e][1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  // ---- L2P; the lane's block, clamped into the grid
+  const int cx = min(bx0 + X, nb - 1), cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1);
+  const long long cell = ((long long)cx * nb + cy) * nb + cz;
+  if (sg.u) {
+    typedef H h4 __attribute__((ext_vector_type(4)));
+    const auto own = gmem(static_cast<const H*>(sg.u) + (cell * 8 + e0) * HR);
+    const H* wl = W + blk_off_l() + lane;
+    constexpr int FULL = hterms(P) / 16;
+#pragma unroll 1
+    for (int c = 0; c < FULL; ++c) {
+      h4 a[NE];
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+        a[e] = *(const __attribute__((address_space(1))) h4*)(own + e * HR + 16 * c + 4 * kq);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const H b0 = wl[(4 * c + v) * 128], b1 = wl[(4 * c + v) * 128 + 64];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          acc[e][0] = M::op(a[e][v], b0, acc[e][0]);
+          acc[e][1] = M::op(a[e][v], b1, acc[e][1]);
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 4 * FULL; s < NLS; ++s) {
+      const H b0 = wl[s * 128], b1 = wl[s * 128 + 64];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const H a = own[e * HR + 4 * s + kq];
+        acc[e][0] = M::op(a, b0, acc[e][0]);
+        acc[e][1] = M::op(a, b1, acc[e][1]);
+      }
+    }
+  }
+  if (sg.d) {
+    const auto par = gmem(sg.d + cell * HR);
+    const H* wp = W + blk_off_p(P) + e0 * (NPS * 128) + lane;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int s = 0; s < NPS; ++s) {
+        const int bt = spt[(e0 + e) * (NPS * 4) + 4 * s + kq];
+        const double v = par[bt >= 0 ? bt : 0];
+        const H a = bt >= 0 ? static_cast<H>(v) : H(0);
+        acc[e][0] = M::op(a, wp[(e * NPS + s) * 128], acc[e][0]);
+        acc[e][1] = M::op(a, wp[(e * NPS + s) * 128 + 64], acc[e][1]);
+      }
+  }
+  // ---- inverse Walsh sums over the patterns: results to LDS as [pattern]
+  // [block][33], each thread transforms whole octets in place, then the block
+  // writes z runs of 16 unigrid cells
+  __syncthreads();
+  constexpr int NR = NX * 16, ES = NR * 33;
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) lds[(e0 + e) * ES + (16 * X + M::row(v, kq)) * 33 + 16 * t + i] = acc[e][t][v];
+  __syncthreads();
+#pragma unroll 1
+  for (int q = threadIdx.x; q < NR * 32; q += BLK_THREADS) {
+    H* x = lds + (q >> 5) * 33 + (q & 31);
+    H y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = x[e * ES];
+#pragma unroll
+    for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (!(e & bit)) {
+          const H u = y[e], v = y[e | bit];
+          y[e] = u + v;
+          y[e | bit] = u - v;
+        }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
+  }
+  __syncthreads();
+  // phi = dx^2/16 sum, g_d = -dx/32 tau_d sum (with the Walsh sum's 1/8)
+  const double dx = 1.0 / n;
+  const long long N = (long long)n * n * n;
+  const int ncomp = g ? 4 : 1;
+#pragma unroll 1
+  for (int q = threadIdx.x; q < 4 * NX * 256 * ncomp; q += BLK_THREADS) {
+    const int z = q & 15, y = (q >> 4) & 15, x = (q >> 8) % (4 * NX), o = (q >> 8) / (4 * NX);
+    const int ux = 4 * bx0 + x, uy = 4 * by0 + y, uz = 4 * bz0 + z;
+    if (ux >= n || uy >= n || uz >= n) continue;
+    // position in the block 0..3: the minus images are 0, 1 (3/2, 1/2 out)
+    const int qx = x & 3, qy = y & 3, qz = z & 3;
+    const int minus = ((qx < 2) << 2) | ((qy < 2) << 1) | (qz < 2);
+    const int t = ((qx == 0 || qx == 3) << 2) | ((qy == 0 || qy == 3) << 1) | (qz == 0 || qz == 3);
+    const int row = 16 * (x >> 2) + 4 * (y >> 2) + (z >> 2);
+    const double val = (double)lds[minus * ES + row * 33 + 4 * t + o];
+    const long long u = ((long long)ux * n + uy) * n + uz;
+    if (o == 0)
+      phi[u] = (TO)(dx * dx * 0.0625 * val);
+    else
+      g[(o - 1) * N + u] = (TO)(((minus >> (3 - o)) & 1 ? 1.0 : -1.0) * 0.03125 * dx * val);
+  }
+  if (stamp_cnt) {
+    // the field's last block records when the field is complete
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();
+      if (atomicAdd(stamp_cnt + sg.field, 1u) == (unsigned int)(sg.tpa * sg.tpa * sg.tz) - 1)
+        stamp_done[sg.field] = wall_clock64();
+    }
+  }
+}
+
+// Locals of one level carried from the M2L's rows [parent][loc_stride] to the
+// block kernel's form.  own: Walsh sums over the children, harmonic terms only,
+// [parent][8][hrow] in the compute type.  compact: the harmonic terms of each
+// cell, [cell][hrow].
+template <int P, typename H, typename HS>
+__global__ __launch_bounds__(256) void k_lfold_own(const HS* __restrict__ L, H* __restrict__ out, long long cnt) {
+  constexpr int HR = hrow(P), RS = loc_stride(P);
+  const long long id = blockIdx.x * 256LL + threadIdx.x;
+  if (id >= cnt * HR) return;
+  const int b = (int)(id % HR);
+  const long long p = id / HR;
+  double y[8];
+  int par = 0;
+  if (b < hterms(P)) {
+    const int ex = h_exp(b), m = h_degree(b), bt = mi_index(mi_a(ex), mi_b(ex), mi_c(ex));
+    par = h_parity(b);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[7 - q] = chi(par, 7 - q) * (double)L[p * RS + m2l_col(q, bt, m)];
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[q] = 0.0;
+  }
+#pragma unroll
+  for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (!(e & bit)) {
+        const double u = y[e], v = y[e | bit];
+        y[e] = u + v;
+        y[e | bit] = u - v;
+      }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) out[(p * 8 + e) * HR + b] = static_cast<H>(y[e]);
+}
+template <int P>
+__global__ __launch_bounds__(256) void k_lfold_compact(const double* __restrict__ L, double* __restrict__ out, int nk) {
+  constexpr int HR = hrow(P), RS = loc_stride(P);
+  const long long id = blockIdx.x * 256LL + threadIdx.x;
+  if (id >= (long long)nk * nk * nk * HR) return;
+  const int b = (int)(id % HR), np = nk >> 1;
+  const long long c = id / HR;
+  const int c2 = (int)(c % nk), c1 = (int)((c / nk) % nk), c0 = (int)(c / ((long long)nk * nk));
+  const long long p = ((long long)(c0 >> 1) * np + (c1 >> 1)) * np + (c2 >> 1);
+  const int q = ((c0 & 1) << 2) | ((c1 & 1) << 1) | (c2 & 1);
+  double v = 0.0;
+  if (b < hterms(P)) {
+    const int ex = h_exp(b);
+    v = L[p * RS + m2l_col(q, mi_index(mi_a(ex), mi_b(ex), mi_c(ex)), h_degree(b))];
+  }
+  out[id] = v;
+}

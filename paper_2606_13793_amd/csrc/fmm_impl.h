@@ -577,6 +577,7 @@ __device__ __forceinline__ double p2p2_coef(int k, int grp, int q, int o) {
 }
 
 #include "fmm_mfma.h"
+#include "fmm_fold.h"
 
 // ---------------------------------------------------------------------------
 // L2L, eq. (L2L), for one level k: Lhat_k[T] += shift of Lhat_{k-1}[parent(T)]
@@ -1375,6 +1376,27 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   }
   const bool m2l64 = pl->s_conv[0].nseg > 0, m2llow = pl->s_conv[1].nseg > 0;
   const bool bot64 = pl->s_bot[0][0].nseg > 0, botlow = pl->s_bot[1][0].nseg > 0;
+  if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
+    double* G = nullptr;
+    if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND);
+    e = hipGetLastError();
+    const int cnt = blk_table(pl->p);
+    for (int x = 0; x < 2 && e == hipSuccess; ++x) {
+      if (!pl->s_blk[x][0].nseg) continue;
+      const size_t b = (size_t)cnt * (x ? sizeof(float) : sizeof(double));
+      if ((e = hipMalloc(&pl->wblk[x], b)) != hipSuccess) break;
+      pl->bytes += b;
+      if (x)
+        hipLaunchKernelGGL(k_blk_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (float*)pl->wblk[x], pl->p);
+      else
+        hipLaunchKernelGGL(k_blk_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (double*)pl->wblk[x], pl->p);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    (void)hipFree(G);
+    if (e != hipSuccess) return e;
+  }
   if ((e = build_tables_t<double>(pl, bot64, m2l64, s)) != hipSuccess) return e;
   if (pl->precision == 1) e = build_tables_t<float>(pl, botlow, m2llow, s);
   if (pl->precision == 2) e = build_tables_t<bf16_tag>(pl, botlow, m2llow, s);
@@ -1459,7 +1481,10 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
     hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 16, 2>), dim3(st.blocks, 8), dim3(bottom_threads<CT>()), 0, s, st.dev,
                        st.nseg, io, (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X],
                        (const H*)pl->wp2p[X], pl->dlists, nck, cnt, done);
-  } else if (z == 0)
+    return hipGetLastError();
+  }
+  if constexpr (X != 2) return hipErrorInvalidValue;  // FMM-1 in FP64 and FP32: k_block
+  else if (z == 0)
     hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 16, 1>), dim3(st.blocks), dim3(bottom_threads<CT>()), 0, s, st.dev, st.nseg, io,
                        (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X],
                        pl->dlists, nck, cnt, done);
@@ -1467,6 +1492,45 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
     hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 8, 1>), dim3(st.blocks), dim3(bottom_threads<CT>()), 0, s, st.dev, st.nseg, io,
                        (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X],
                        pl->dlists, nck, cnt, done);
+  return hipGetLastError();
+}
+
+// Finest blocks (k_block) of site x (0 FP64, 1 low precision).  Tiles of 4
+// rows of blocks share each B fragment between 4 waves; fewer rows where they
+// would leave compute units idle.
+template <int P, typename CT, typename TI, typename TO>
+hipError_t launch_block(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
+  using H = typename Mf<CT>::H;
+  if (!pl->s_blk[x][0].nseg) return hipSuccess;
+  const long long rows = pl->blk_rows[x];
+  int v = rows >= 8LL * pl->cus ? 2 : rows >= 4LL * pl->cus ? 1 : 0;
+  if ((pl->force_bz ? pl->force_bz : pl->tune.bz) == 8 && v > 0) --v;
+  unsigned int* cnt = pl->stamps ? pl->stamp_cnt : nullptr;
+  unsigned long long* done = pl->stamps ? pl->stamp_time + 1 : nullptr;
+  // the locals in the kernel's form
+  for (auto& fd : pl->fld) {
+    if (!block_field(pl, fd.F) || (bottom_low(pl, fd.F) ? 1 : 0) != x || fd.F < 3) continue;
+    const Level& lf = fd.lev[fd.F];
+    const long long np = lf.ncell / 8;
+    if (lf.Lt)
+      hipLaunchKernelGGL((k_lfold_own<P, H, H>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s, (const H*)lf.Lt,
+                         (H*)lf.Lw, np);
+    else
+      hipLaunchKernelGGL((k_lfold_own<P, H, double>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s,
+                         (const double*)lf.L, (H*)lf.Lw, np);
+    if (fd.F >= 4)
+      hipLaunchKernelGGL((k_lfold_compact<P>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s,
+                         (const double*)fd.lev[fd.F - 1].L, fd.lev[fd.F - 1].Lc, fd.lev[fd.F - 1].nk);
+  }
+  const SegTable& st = pl->s_blk[x][v];
+  StageScope sc(pl, ST_BOTTOM, 1, s);
+  const H* w = (const H*)pl->wblk[x];
+  if (v == 2)
+    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 4>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
+  else if (v == 1)
+    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 2>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
+  else
+    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 1>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
   return hipGetLastError();
 }
 
@@ -1483,10 +1547,12 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   {
     StageScope sc(pl, ST_P2M, 1, s);
     // terms past nmax are written as zero
-    if (pl->dl == 2)
+    if (!pl->s_p2m.nseg)
+      ;
+    else if (pl->dl == 2)
       hipLaunchKernelGGL((k_p2m2<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
                          io, pl->NMX);
-    else
+    else if constexpr (Mf<CT>::IDX == 2)
       hipLaunchKernelGGL((k_p2m<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
                          io, pl->NMX);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1516,6 +1582,9 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
     StageScope sc(pl, ST_L2L, pl->s_l2l[k].nseg ? 1 : 0, s);
     if ((e = launch_l2l_site<P>(pl, pl->s_l2l[k], s)) != hipSuccess) return e;
   }
+  if ((e = launch_block<P, double, TI, TO>(pl, 0, io, s)) != hipSuccess) return e;
+  if constexpr (std::is_same<CT, float>::value)
+    if ((e = launch_block<P, float, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;
   if ((e = launch_bottom<P, double, TI, TO>(pl, 0, io, s)) != hipSuccess) return e;
   if constexpr (!std::is_same<CT, double>::value)
     if ((e = launch_bottom<P, CT, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;

@@ -179,6 +179,12 @@ struct Level {
   // null elsewhere.  Only the bottom kernel reads it, and it rounds its
   // operands to that type anyway.
   void* Lt = nullptr;
+  // finest level of a field on the folded block kernel (k_block): the same
+  // locals Walsh-folded over the children, [parent][8][hrow] in the compute
+  // type
+  void* Lw = nullptr;
+  // level below it: the harmonic terms of each cell's local, [cell][hrow]
+  double* Lc = nullptr;
 };
 
 // one density field of a plan (a single-field plan has one)
@@ -186,6 +192,10 @@ struct Field {
   int n = 0, L = 0, F = 0;  // unigrid cells per axis, log2 n, finest FMM level L - 1
   double dx = 0.0;
   Level lev[16];
+  // a copy of the last solve's density (I/O type), left by the block kernel
+  // of a field with an FP64 bottom: the level-F multipoles, which that kernel
+  // never forms, are derived from it when they are asked for
+  void* rho_copy = nullptr;
 };
 
 // I/O buffers of one field for one call
@@ -323,6 +333,9 @@ struct fmm_plan {
   fmm::SegTable s_conv[2];          // forward M2L: [0] FP64 levels, [1] low-precision levels
   fmm::SegTable s_l2l[16];          // L2L into level k (index k)
   fmm::SegTable s_bot[2][2];        // bottom [FP64 | low][tile depth 16 | 8]
+  fmm::SegTable s_blk[2][3];        // finest blocks [FP64 | low][1, 2 or 4 rows of blocks per tile]
+  long long blk_rows[2] = {0, 0};   // their row tiles of 16 blocks
+  void* wblk[2] = {nullptr, nullptr};  // the block kernel's B table, FP64 and FP32
   fmm::SegTable s_red[2];           // reductions of split forward M2L partial sums
   double* conv_part = nullptr;      // partial sums of split forward M2L segments
   // per convolution kind and compute type: (K chunks, first fragment) of
@@ -401,6 +414,12 @@ hipError_t finish_locals(fmm_plan* pl, int level, hipStream_t s);
 int build_schedule(fmm_plan* pl);
 // which levels run in which compute type (same rule for every field)
 inline bool bottom_low(const fmm_plan* pl, int F) { return pl->precision != 0 && F > pl->coarse_fp64_levels; }
+// Whether a field's finest level runs on the folded block kernel: FMM-1 in
+// FP64 or FP32.  BF16 bottoms keep k_bottom, whose results carry the rounding
+// of every BF16 multipole: the block kernel has no multipoles to round.
+inline bool block_field(const fmm_plan* pl, int F) {
+  return pl->dl == 1 && !(pl->precision == 2 && bottom_low(pl, F));
+}
 bool finest_locals_typed(const fmm_plan* pl, const Field& fd);
 inline int m2l_low_from(const fmm_plan* pl) {
   return pl->precision == 0 ? 64 : (pl->coarse_fp64_levels + 1 > 3 ? pl->coarse_fp64_levels + 1 : 3);
@@ -410,7 +429,7 @@ inline int m2l_low_from(const fmm_plan* pl) {
 // low-precision M2L into level k + 1 reads level k
 inline bool typed_level(const fmm_plan* pl, int F, int k) {
   if (pl->precision == 0) return false;
-  return (k == F && bottom_low(pl, F)) || (k < F && k + 1 >= m2l_low_from(pl));
+  return (k == F && bottom_low(pl, F) && !block_field(pl, F)) || (k < F && k + 1 >= m2l_low_from(pl));
 }
 
 // Records an event pair around a stage when the plan is profiling.
