@@ -122,11 +122,15 @@ void release(fmm_plan* pl) {
       if (lv.Lt) (void)hipFree(lv.Lt);
       if (lv.Lw) (void)hipFree(lv.Lw);
       if (lv.Lc) (void)hipFree(lv.Lc);
+      if (lv.Mh) (void)hipFree(lv.Mh);
     }
   for (auto& f : pl->fld)
     if (f.rho_copy) (void)hipFree(f.rho_copy);
   for (auto w : pl->wblk)
     if (w) (void)hipFree(w);
+  for (auto w : pl->wm2lf)
+    if (w) (void)hipFree(w);
+  if (pl->m2lf_tiles) (void)hipFree(pl->m2lf_tiles);
   auto free_st = [](fmm::SegTable& st) {
     if (st.dev) (void)hipFree(st.dev);
     st = fmm::SegTable{};
@@ -140,6 +144,9 @@ void release(fmm_plan* pl) {
     for (auto& st : a) free_st(st);
   for (auto& a : pl->s_blk)
     for (auto& st : a) free_st(st);
+  for (auto& a : pl->s_m2lf)
+    for (auto& st : a) free_st(st);
+  for (auto& st : pl->s_l2lf) free_st(st);
   for (auto& st : pl->s_red) free_st(st);
   release_adj(pl->adj);
   if (pl->conv_part) (void)hipFree(pl->conv_part);
@@ -364,7 +371,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3];
+  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -387,6 +394,8 @@ int build_schedule(fmm_plan* pl) {
       s2.field = f;
       s2.b = (double*)fd.lev[F - 1].M;
       s2.t = fd.lev[F - 1].Mt;
+      s2.u = fd.lev[F - 1].Mh;
+      s2.split = harmonic_float(pl, F - 1);
       const long long nc = 1LL << (3 * (F - 1));
       p2m2.add(s2, cdiv(nc, 256));
       top = F - 1;
@@ -398,10 +407,38 @@ int build_schedule(fmm_plan* pl) {
       m.a = (const double*)fd.lev[k].M;
       m.b = (double*)fd.lev[k - 1].M;
       m.t = fd.lev[k - 1].Mt;
+      m.u = fd.lev[k - 1].Mh;
+      m.split = harmonic_float(pl, k - 1);
       // parents per block of k_m2m: 16 up to 56 terms, else 8
       m2m[k].add(m, cdiv(1LL << (3 * (k - 1)), pl->NM <= 56 ? 16 : 8));
     }
-    for (int k = 3; k <= F; ++k) {
+    if (block_field(pl, F)) {
+      for (int k = F; k >= 3; --k) {  // the finest first: its blocks are the bulk of the launch
+        Seg c{};
+        c.n = 1 << (k - 1);
+        const int no = c.n >> 1;
+        c.tpa = (int)cdiv(no, 4);
+        c.field = f;
+        c.a = (const double*)fd.lev[k - 1].Mh;
+        const bool low = harmonic_float(pl, k - 1);
+        c.b = low && k == F ? nullptr : (double*)fd.lev[k].Lw;
+        c.u = low && k == F ? fd.lev[k].Lw : nullptr;
+        for (int v = 0; v < 3; ++v) {
+          c.tz = (int)cdiv(no, 1 << v);
+          m2lf[low ? 1 : 0][v].add(c, (long long)c.tpa * c.tpa * c.tz);
+        }
+      }
+      for (int k = 3; k <= F - 1; ++k) {
+        Seg l{};
+        l.n = 1 << (k - 1);
+        l.field = f;
+        l.a = k > 3 ? fd.lev[k - 1].Lc : nullptr;
+        l.c = (const double*)fd.lev[k].Lw;
+        l.b = fd.lev[k].Lc;
+        l2lf[k].add(l, cdiv((long long)l.n * l.n * l.n, 16));
+      }
+    }
+    for (int k = 3; k <= F && !block_field(pl, F); ++k) {
       Seg c{};
       c.n = 1 << (k - 1);
       c.tpa = (int)cdiv(c.n, kConvTile);
@@ -414,7 +451,7 @@ int build_schedule(fmm_plan* pl) {
       c.u = k == F ? fd.lev[F].Lt : nullptr;
       conv[k >= klow ? 1 : 0].add(c, (long long)c.tpa * c.tpa * c.tz);
     }
-    for (int k = 4; k <= F - 1; ++k) {
+    for (int k = 4; k <= F - 1 && !block_field(pl, F); ++k) {
       Seg l{};
       l.n = 1 << (k - 1);
       l.field = f;
@@ -531,6 +568,7 @@ int build_schedule(fmm_plan* pl) {
   for (int k = 0; k < 16; ++k) {
     if ((rc = upload_segs(pl, pl->s_m2m[k], m2m[k]))) return rc;
     if ((rc = upload_segs(pl, pl->s_l2l[k], l2l[k]))) return rc;
+    if ((rc = upload_segs(pl, pl->s_l2lf[k], l2lf[k]))) return rc;
   }
   for (int x = 0; x < 2; ++x) {
     if ((rc = upload_segs(pl, pl->s_conv[x], conv[x]))) return rc;
@@ -539,7 +577,8 @@ int build_schedule(fmm_plan* pl) {
     for (int z = 0; z < 2; ++z)
       if ((rc = upload_segs(pl, pl->s_bot[x][z], bot[x][z]))) return rc;
     for (int v = 0; v < 3; ++v)
-      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v]))) return rc;
+      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v])) || (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])))
+        return rc;
   }
   return FMM_OK;
 }
@@ -887,7 +926,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
           return bail();
         }
       }
-      if (k >= 3) {
+      if (k >= 3 && !fmm::block_field(pl, fd.F)) {
         // the finest level of a low-precision bottom keeps its locals in the
         // compute type only (Level::Lt)
         const bool typed = k == fd.F && fmm::finest_locals_typed(pl, fd);
@@ -915,10 +954,19 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
         return bail();
       }
     }
-    if (F >= 3 && dev_alloc(pl, &fd.lev[F].Lw, (size_t)fd.lev[F].ncell * hr * (low ? sizeof(float) : sizeof(double))))
-      return bail();
-    if (F >= 4 && dev_alloc(pl, (void**)&fd.lev[F - 1].Lc, (size_t)fd.lev[F - 1].ncell * hr * sizeof(double)))
-      return bail();
+    auto zalloc = [&](void** ptr, size_t bytes) {
+      if (dev_alloc(pl, ptr, bytes)) return false;
+      if (hipMemset(*ptr, 0, bytes) == hipSuccess) return true;
+      fail(FMM_ERR_DEVICE, "hipMemset failed");
+      return false;
+    };
+    for (int k = 2; k <= F; ++k) {
+      fmm::Level& lv = fd.lev[k];
+      if (k >= 3 && !zalloc(&lv.Lw, (size_t)lv.ncell * hr * (k == F && low ? sizeof(float) : sizeof(double)))) return bail();
+      if (k >= 3 && k < F && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
+      if (k < F && !zalloc(&lv.Mh, (size_t)lv.ncellp * hr * (fmm::harmonic_float(pl, k) ? sizeof(float) : sizeof(double))))
+        return bail();
+    }
   }
   const std::vector<int> dl = build_dlists();
   if (dl.size() != 8 * (size_t)fmm::NLIST_PAD) {
@@ -1532,6 +1580,77 @@ int fmm_fd_force(int n, const double* phi, double* f, void* stream) {
   return ok();
 }
 
+// The complete locals of one level of a field on the folded kernels, [cell]
+// [full term]: the harmonic terms the plan keeps, and the others by Laplace's
+// equation.  The finest level keeps its M2L part only, Walsh-folded over each
+// parent's children: unfolded here, plus the shift of the level above.
+static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
+  const fmm::Level& lv = plan->lev[level];
+  const int p = plan->p, nk = lv.nk, ht = (p + 1) * (p + 1), hr = (ht + 3) / 4 * 4, nl = plan->NL;
+  auto hidx = [](int x, int y, int z) { return (x + y + z) * (x + y + z) + (z ? x + y + z + 1 + x : x); };
+  auto choose = [](int n, int k) { double b = 1; for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i; return b; };
+  std::vector<int> mi(3 * nl);
+  fmm_multi_index(p, mi.data(), mi.size());
+  auto full = [&](const double* h, double* f) {
+    for (int t = 0; t < nl; ++t) {
+      const int x = mi[3 * t], y = mi[3 * t + 1], z = mi[3 * t + 2], k = z >> 1;
+      double v = 0.0;
+      for (int l = 0; l <= k; ++l) v += choose(k, l) * h[hidx(x + 2 * l, y + 2 * (k - l), z & 1)];
+      f[t] = k & 1 ? -v : v;
+    }
+  };
+  auto fetch = [&](const void* dev, size_t cnt, bool f32, std::vector<double>* v) {
+    v->resize(cnt);
+    if (!f32) return hipMemcpy(v->data(), dev, cnt * sizeof(double), hipMemcpyDeviceToHost);
+    std::vector<float> w(cnt);
+    const hipError_t e = hipMemcpy(w.data(), dev, cnt * sizeof(float), hipMemcpyDeviceToHost);
+    std::copy(w.begin(), w.end(), v->begin());
+    return e;
+  };
+  std::vector<double> own, par;
+  const bool finest = level == plan->F;
+  hipError_t e = hipDeviceSynchronize();
+  if (e == hipSuccess)
+    e = fetch(finest ? lv.Lw : lv.Lc, (size_t)lv.ncell * hr, finest && fmm::bottom_low(plan, plan->F), &own);
+  if (e == hipSuccess && finest && level > 3)
+    e = fetch(plan->lev[level - 1].Lc, (size_t)plan->lev[level - 1].ncell * hr, false, &par);
+  if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
+  std::vector<double> h(hr), pf(nl);
+  const int np = nk / 2;
+  for (long long c = 0; c < lv.ncell; ++c) {
+    if (!finest) {
+      full(&own[(size_t)c * hr], out + c * nl);
+      continue;
+    }
+    const int c2 = (int)(c % nk), c1 = (int)((c / nk) % nk), c0 = (int)(c / ((long long)nk * nk));
+    const size_t P = ((size_t)(c0 >> 1) * np + (c1 >> 1)) * np + (c2 >> 1);
+    const int minus = 7 - (((c0 & 1) << 2) | ((c1 & 1) << 1) | (c2 & 1));
+    auto odd = [](int b) { b ^= b >> 2; return (b ^ (b >> 1)) & 1; };
+    for (int z = 0; z < 2; ++z)
+      for (int x = 0; x <= p; ++x)
+        for (int y = 0; x + y + z <= p; ++y) {
+          const int b = hidx(x, y, z), pb = ((x & 1) << 2) | ((y & 1) << 1) | (z & 1);
+          double v = 0.0;
+          for (int k = 0; k < 8; ++k) v += (odd((k ^ pb) & minus) ? -0.125 : 0.125) * own[(P * 8 + k) * hr + b];
+          h[b] = v;
+        }
+    full(h.data(), out + c * nl);
+    if (level <= 3) continue;
+    full(&par[P * hr], pf.data());
+    auto fact = [](int k) { double f = 1; for (int i = 2; i <= k; ++i) f *= i; return f; };
+    for (int t = 0; t < nl; ++t)
+      for (int s = t; s < nl; ++s) {
+        const int gx = mi[3 * s] - mi[3 * t], gy = mi[3 * s + 1] - mi[3 * t + 1], gz = mi[3 * s + 2] - mi[3 * t + 2];
+        if (gx < 0 || gy < 0 || gz < 0) continue;
+        const int mt = mi[3 * t] + mi[3 * t + 1] + mi[3 * t + 2];
+        const int neg = odd((((gx & 1) << 2) | ((gy & 1) << 1) | (gz & 1)) & minus);
+        const double w = std::ldexp(1.0 / (fact(gx) * fact(gy) * fact(gz)), -(mt + 1) - 2 * (gx + gy + gz));
+        out[c * nl + t] += (neg ? -w : w) * pf[s];
+      }
+  }
+  return ok();
+}
+
 int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size_t count) {
   if (!plan) return fail(FMM_ERR_INVALID_ARG, "plan is NULL");
   if (which != 0 && which != 1) return fail(FMM_ERR_INVALID_ARG, "which must be 0 or 1");
@@ -1591,8 +1710,9 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
     }
     return ok();
   }
-  if (level == plan->F && plan->lt_live)
+  if (level == plan->F && (fmm::block_field(plan, plan->F) ? fmm::finest_locals_typed(plan, plan->fld[0]) : plan->lt_live))
     return fail(FMM_ERR_UNSUPPORTED, "a low-precision bottom keeps the level-%d locals in its compute type only", level);
+  if (fmm::block_field(plan, plan->F)) return export_harmonic_locals(plan, level, out);
   hipError_t fe = fmm::finish_locals(plan, level, nullptr);
   if (fe == hipSuccess) fe = hipDeviceSynchronize();
   if (fe != hipSuccess) return fail(FMM_ERR_DEVICE, "completing locals failed: %s", hipGetErrorString(fe));

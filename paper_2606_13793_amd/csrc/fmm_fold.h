@@ -18,51 +18,6 @@
 // excludes have zero K; the exclusion is mirror-symmetric too.
 #pragma once
 
-// ---------------------------------------------------------------------------
-// Harmonic terms.  D[g] = -d^g (1/r) obeys Laplace's equation away from the
-// source, D[x, y, z + 2] = -D[x + 2, y, z] - D[x, y + 2, z], so an expansion
-// is fixed by its terms with z exponent 0 or 1: (m + 1)^2 up to degree m.
-// Reduced index: by degree m, then z = 0 (x ascending), then z = 1.
-// ---------------------------------------------------------------------------
-constexpr __host__ __device__ int hterms(int m) { return m < 0 ? 0 : (m + 1) * (m + 1); }
-constexpr __host__ __device__ int h_degree(int i) {
-  int m = 0;
-  while ((m + 1) * (m + 1) <= i) ++m;
-  return m;
-}
-// exponents x | y << 8 | z << 16 of reduced term i
-constexpr __host__ __device__ int h_exp(int i) {
-  const int m = h_degree(i), r = i - m * m;
-  return r <= m ? (r | (m - r) << 8) : ((r - m - 1) | (m - 1 - (r - m - 1)) << 8 | 1 << 16);
-}
-constexpr __host__ __device__ int h_index(int x, int y, int z) {
-  const int m = x + y + z;
-  return m * m + (z ? m + 1 + x : x);
-}
-constexpr __host__ __device__ int binom(int n, int k) {
-  int b = 1;
-  for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i;
-  return b;
-}
-// Moments (or evaluation coefficients) f of the full expansion carried over to
-// reduced term (x, y, e): sum over the full terms that the recurrence sends
-// there, (x - 2l, y - 2m, 2(l + m) + e) with weight (-1)^(l+m) C(l+m, l).
-template <typename F>
-__device__ __forceinline__ double h_reduce(int i, F&& f) {
-  const int ex = h_exp(i), x = mi_a(ex), y = mi_b(ex), e = mi_c(ex);
-  double s = 0.0;
-  for (int l = 0; 2 * l <= x; ++l)
-    for (int m = 0; 2 * m <= y; ++m) {
-      const double w = (double)(((l + m) & 1) ? -binom(l + m, l) : binom(l + m, l));
-      s += w * f(mi_index(x - 2 * l, y - 2 * m, 2 * (l + m) + e));
-    }
-  return s;
-}
-constexpr __host__ __device__ int h_parity(int i) {
-  const int ex = h_exp(i);
-  return ((ex & 1) << 2) | (((ex >> 8) & 1) << 1) | ((ex >> 16) & 1);
-}
-
 // chi_e(sigma) with sigma given by its minus bits
 __host__ __device__ __forceinline__ double chi(int e, int minus) {
   int b = e & minus;
@@ -185,23 +140,25 @@ __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int
 }
 
 // Walsh sums of the 8 mirror images r[minus bits] for the NE patterns
-// NE eg .. NE eg + NE - 1, with s[axis] = chi of the axes fixed by eg.
+// NE eg .. NE eg + NE - 1: s = the weight of the minus images along each axis,
+// chi of the axis where eg fixes it (x; y for NE <= 2; z for NE = 1) times the
+// images' own sign.
 template <int NE, typename H>
 __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[NE]) {
   H x[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) x[q] = fma(sx, r[4 + q], r[q]);
   if constexpr (NE == 4) {
-    const H p0 = x[0] + x[2], p1 = x[1] + x[3], m0 = x[0] - x[2], m1 = x[1] - x[3];
-    a[0] = p0 + p1;
-    a[1] = p0 - p1;
-    a[2] = m0 + m1;
-    a[3] = m0 - m1;
+    const H p0 = fma(sy, x[2], x[0]), p1 = fma(sy, x[3], x[1]), m0 = fma(-sy, x[2], x[0]), m1 = fma(-sy, x[3], x[1]);
+    a[0] = fma(sz, p1, p0);
+    a[1] = fma(-sz, p1, p0);
+    a[2] = fma(sz, m1, m0);
+    a[3] = fma(-sz, m1, m0);
   } else {
     const H y0 = fma(sy, x[2], x[0]), y1 = fma(sy, x[3], x[1]);
     if constexpr (NE == 2) {
-      a[0] = y0 + y1;
-      a[1] = y0 - y1;
+      a[0] = fma(sz, y1, y0);
+      a[1] = fma(-sz, y1, y0);
     } else {
       a[0] = fma(sz, y1, y0);
     }
@@ -315,7 +272,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
         const int sn = s + u + 1 < BLK_STEPS ? s + u + 1 : BLK_STEPS - 1;
         bread(sn, b[u ^ 1]);
         aread(r[u ^ 1]);
-        fold8<NE>(r[u], sx, sy, sz, a);
+        fold8<NE>(r[u], sx, NE <= 2 ? sy : H(1), NE == 1 ? sz : H(1), a);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
@@ -438,54 +395,359 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
   }
 }
 
-// Locals of one level carried from the M2L's rows [parent][loc_stride] to the
-// block kernel's form.  own: Walsh sums over the children, harmonic terms only,
-// [parent][8][hrow] in the compute type.  compact: the harmonic terms of each
-// cell, [cell][hrow].
-template <int P, typename H, typename HS>
-__global__ __launch_bounds__(256) void k_lfold_own(const HS* __restrict__ L, H* __restrict__ out, long long cnt) {
-  constexpr int HR = hrow(P), RS = loc_stride(P);
-  const long long id = blockIdx.x * 256LL + threadIdx.x;
-  if (id >= cnt * HR) return;
-  const int b = (int)(id % HR);
-  const long long p = id / HR;
-  double y[8];
-  int par = 0;
-  if (b < hterms(P)) {
-    const int ex = h_exp(b), m = h_degree(b), bt = mi_index(mi_a(ex), mi_b(ex), mi_c(ex));
-    par = h_parity(b);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) y[7 - q] = chi(par, 7 - q) * (double)L[p * RS + m2l_col(q, bt, m)];
-  } else {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) y[q] = 0.0;
+// ---------------------------------------------------------------------------
+// M2L, eq. (M2L), folded.  Rows are the octs O of the source grid (level
+// k - 1); the sources are the 6^3 cells around (27 in the positive octant),
+// the targets the 64 level-k children of the oct's 8 cells P.  Both sides keep
+// harmonic terms only, and |a| + |b| <= p.
+// Columns (kappa, b): the targets of the positive octant are the 8 children of
+// its cell P; their Walsh pattern kappa over those children takes the place of
+// the child, so that a row of the result is already folded the way k_block
+// reads it:
+//   Lw[P][kappa][b] = sum_children chi_kappa(sigma) sigma^b L(child, b)
+//                   = chi_kappa(tau) sum_e chi_e(tau) OUT(e; kappa, b) / 8,
+// P the cell tau of the oct.  Columns are sorted by |b| (kappa slow inside a
+// degree), K by |a| (K index 27 a + source), so a tile of 16 columns needs a
+// prefix of K: ceil(27 (p - |b| + 1)^2 / 4) steps.
+// ---------------------------------------------------------------------------
+constexpr __host__ __device__ int m2lf_ntiles(int P) { return (8 * hterms(P) + 15) / 16; }
+constexpr __host__ __device__ int m2lf_steps(int P, int nmax, int t) {
+  const int m = h_degree(16 * t / 8);
+  const int q = P - m < nmax ? P - m : nmax;
+  return (27 * hterms(q) + 3) / 4;
+}
+// (pattern, term) of column col, packed pattern << 8 | term; -1 past the last
+constexpr __host__ __device__ int m2lf_col(int P, int col) {
+  if (col >= 8 * hterms(P)) return -1;
+  const int m = h_degree(col / 8), in = col - 8 * m * m;
+  return (in / (2 * m + 1)) << 8 | (m * m + in % (2 * m + 1));
+}
+
+// B fragments in the compute type, [fragment (tile, step)][8 patterns][64];
+// tiles[t] = (steps, first fragment).
+template <typename H>
+__global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __restrict__ tiles, H* __restrict__ W, int P,
+                             int nmax, int ND, long long cnt) {
+  const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= cnt) return;
+  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  int t = 0;
+  while (tiles[t].y + tiles[t].x <= f) ++t;
+  const int k = 4 * (f - tiles[t].y) + (lane >> 4), cb = m2lf_col(P, 16 * t + (lane & 15));
+  const int a = k / 27, s = k % 27, kap = cb >> 8, b = cb & 255;
+  double x = 0.0;
+  if (cb >= 0 && a < hterms(nmax) && h_degree(a) + h_degree(b) <= P) {
+    const int ea = h_exp(a), eb = h_exp(b), pa = h_parity(a), pb = h_parity(b);
+    const int g = mi_index(mi_a(ea) + mi_a(eb), mi_b(ea) + mi_b(eb), mi_c(ea) + mi_c(eb));
+    const int j[3] = {s / 9, (s / 3) % 3, s % 3};
+    for (int minus = 0; minus < 8; ++minus) {
+      int dd = 0;
+      bool near = true;
+      for (int ax = 0; ax < 3; ++ax) {
+        const int d = (minus >> (2 - ax)) & 1 ? j[ax] + 1 : -j[ax];
+        near = near && d >= -1 && d <= 1;
+        dd = dd * 7 + d + 3;
+      }
+      if (near) continue;
+      double y = 0.0;
+      for (int q = 0; q < 8; ++q) y += chi(kap ^ pb, 7 - q) * Dtab[((size_t)dd * 8 + q) * ND + g];
+      x += chi(e ^ pa, minus) * y;
+    }
+    x = ldexp(x, -(h_degree(b) + 1) - 3);
   }
+  W[id] = static_cast<H>(x);
+}
+
+// Segments: n = source grid cells per axis, tpa = tiles along y and z, tz =
+// tiles along x, a = harmonic multipoles of the source grid in the compute
+// type, [term][(n + 6)^3] (terms padded to a multiple of 4), u = result in the
+// compute type or b = result in FP64, [n^3][8][hrow].
+// Tile: MT x 4 x 4 octs.  8 waves: 8 / NE groups of NE patterns, KS slices of
+// the K steps, MT / NR groups of NR row tiles (a row tile: the 4 x 4 octs of a
+// plane).  A block sums NT column tiles over all 8 patterns, so the inverse
+// Walsh sums happen in its epilogue.  Blocks: column groups x T tiles, the
+// heaviest group (lowest degrees) first.
+// What bounds it: the matrix cores.  LDS holds 4 terms of the tile's cells and
+// 2 around; a lane reads the 8 mirror images of an operand and folds them (8
+// adds for two patterns), which NT products amortise; each B fragment is read
+// from L2 once per wave for NR row tiles.
+template <int P, typename CT, int MT, int NT, int NE, int KS>
+__global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, int nseg, int T,
+                                                 const int2* __restrict__ tiles,
+                                                 const typename Mf<CT>::H* __restrict__ W) {
+  using M = Mf<CT>;
+  using H = typename M::H;
+  using Acc = typename M::Acc;
+  constexpr int NR = MT * KS / NE, NG = 8 / NE, NX = MT / NR, HR = hrow(P);
+  static_assert(NG * KS * NX == 8, "8 waves");
+  constexpr int CELLS = (2 * MT + 4) * 144, CS = 16 * NT + 1;
+  constexpr int EP = KS * NX * 8 * 16 * CS, SZ = EP > 4 * CELLS ? EP : 4 * CELLS;
+  __shared__ __attribute__((aligned(16))) H lds[SZ];
+  __shared__ int4 ktab[108];  // per K index of a chunk: plus image, and the distances to the minus ones
+  __shared__ float4 tsg[HR];  // per term: (-1)^exponent along each axis, the sign of a minus image
+  __shared__ int scol[16 * NT];
+  const int grp = (int)blockIdx.x / T, T0 = grp * NT, lbk = (int)blockIdx.x - grp * T;
+  const Seg& sg = find_seg(segs, nseg, lbk);
+  const int ns = sg.n, nsp = ns + 6, no = ns >> 1, tb = lbk - sg.first_block;
+  const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
+  const long long ncellp = (long long)nsp * nsp * nsp;
+  const auto src = gmem(reinterpret_cast<const H*>(sg.a));
+  int vt[NT], off[NT];
 #pragma unroll
-  for (int bit = 1; bit < 8; bit <<= 1)
+  for (int t = 0; t < NT; ++t) {
+    const int2 e = tiles[T0 + t];
+    vt[t] = e.x;
+    off[t] = e.y;
+  }
+  for (int k = threadIdx.x; k < 108; k += 512) {
+    const int s = k % 27, jx = s / 9, jy = (s / 3) % 3, jz = s % 3;
+    ktab[k] = int4{(k / 27) * CELLS + jx * 144 + jy * 12 + jz, (2 * jx + 1) * 144, (2 * jy + 1) * 12, 2 * jz + 1};
+  }
+  for (int c = threadIdx.x; c < 16 * NT; c += 512) scol[c] = m2lf_col(P, 16 * T0 + c);
+  for (int t = threadIdx.x; t < HR; t += 512) {
+    const int ex = h_exp(t);
+    tsg[t] = float4{mi_a(ex) & 1 ? -1.f : 1.f, mi_b(ex) & 1 ? -1.f : 1.f, mi_c(ex) & 1 ? -1.f : 1.f, 0.f};
+  }
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e0 = (w % NG) * NE, ks = (w / NG) % KS, xg = w / (NG * KS);
+  const H sx = (e0 & 4) ? H(-1) : H(1), sy = (e0 & 2) ? H(-1) : H(1), sz = (e0 & 1) ? H(-1) : H(1);
+  // the lane's oct: image "plus 0" of the wave's first row tile
+  const H* ctr = lds + (2 * xg * NR + 3) * 144 + (2 * (i >> 2) + 3) * 12 + 2 * (i & 3) + 3;
+  Acc acc[NR][NE][NT];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (!(e & bit)) {
-        const double u = y[e], v = y[e | bit];
-        y[e] = u + v;
-        y[e | bit] = u - v;
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[r][e][t] = Acc{0, 0, 0, 0};
+  const H* we = W + e0 * 64 + lane;
+  // K steps [sa, sb) of chunk c (steps 27 c ..), column tiles 0 .. NA - 1
+  auto run = [&](auto nac, int c, int sa, int sb) {
+    constexpr int NA = decltype(nac)::value;
+    int s = sa + (ks - sa % KS + KS) % KS;
+    if (s >= sb) return;
+    auto aread = [&](int st, H (&r)[NR][8], float (&g)[3]) {
+      const int k = 4 * (st - 27 * c) + kq;  // < 108
+      const int4 q = ktab[k];
+      const float4 sg4 = tsg[4 * c + ((k * 38) >> 10)];  // k / 27
+      g[0] = sg4.x;
+      g[1] = sg4.y;
+      g[2] = sg4.z;
+      const H *p0 = ctr + q.x, *p1 = p0 - q.z, *p2 = p0 - q.y, *p3 = p1 - q.y;
+#pragma unroll
+      for (int m = 0; m < NR; ++m) {
+        r[m][0] = p0[m * 288];
+        r[m][1] = p0[m * 288 - q.w];
+        r[m][2] = p1[m * 288];
+        r[m][3] = p1[m * 288 - q.w];
+        r[m][4] = p2[m * 288];
+        r[m][5] = p2[m * 288 - q.w];
+        r[m][6] = p3[m * 288];
+        r[m][7] = p3[m * 288 - q.w];
+      }
+    };
+    auto bread = [&](int st, H (&b)[NE][NA]) {
+#pragma unroll
+      for (int t = 0; t < NA; ++t) {
+        const auto p = gmem(we + (size_t)(off[t] + st) * 512);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) b[e][t] = p[e * 64];
+      }
+    };
+    H r[2][NR][8], b[2][NE][NA], a[NE];
+    float g[2][3];
+    aread(s, r[0], g[0]);
+    bread(s, b[0]);
+#pragma unroll 1
+    for (; s < sb; s += 2 * KS) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int st = s + u * KS, sn = st + KS < sb ? st + KS : s;
+        if (u == 0 || st < sb) {
+          bread(sn, b[u ^ 1]);
+          aread(sn, r[u ^ 1], g[u ^ 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          const H gx = sx * (H)g[u][0], gy = NE <= 2 ? sy * (H)g[u][1] : (H)g[u][1], gz = NE == 1 ? sz * (H)g[u][2] : (H)g[u][2];
+#pragma unroll
+          for (int m = 0; m < NR; ++m) {
+            fold8<NE>(r[u][m], gx, gy, gz, a);
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+#pragma unroll
+              for (int t = 0; t < NA; ++t) acc[m][e][t] = M::op(a[e], b[u][e][t], acc[m][e][t]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  };
+  // terms 4 c .. 4 c + 3 per chunk: 27 K steps
+  for (int c = 0; 27 * c < vt[0]; ++c) {
+    __syncthreads();
+    constexpr int CNT = 4 * CELLS, FB = 7;
+#pragma unroll 1
+    for (int q0 = threadIdx.x; q0 < CNT; q0 += FB * 512) {
+      H v[FB];
+#pragma unroll
+      for (int u = 0; u < FB; ++u) {
+        const int q = q0 + u * 512, cell = q % CELLS, z = 2 * oz0 + 1 + cell % 12, y = 2 * oy0 + 1 + (cell / 12) % 12,
+                  x = 2 * ox0 + 1 + cell / 144;
+        v[u] = q < CNT && x < nsp && y < nsp && z < nsp
+                   ? src[(4 * c + q / CELLS) * ncellp + ((long long)x * nsp + y) * nsp + z]
+                   : H(0);
       }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) out[(p * 8 + e) * HR + b] = static_cast<H>(y[e]);
-}
-template <int P>
-__global__ __launch_bounds__(256) void k_lfold_compact(const double* __restrict__ L, double* __restrict__ out, int nk) {
-  constexpr int HR = hrow(P), RS = loc_stride(P);
-  const long long id = blockIdx.x * 256LL + threadIdx.x;
-  if (id >= (long long)nk * nk * nk * HR) return;
-  const int b = (int)(id % HR), np = nk >> 1;
-  const long long c = id / HR;
-  const int c2 = (int)(c % nk), c1 = (int)((c / nk) % nk), c0 = (int)(c / ((long long)nk * nk));
-  const long long p = ((long long)(c0 >> 1) * np + (c1 >> 1)) * np + (c2 >> 1);
-  const int q = ((c0 & 1) << 2) | ((c1 & 1) << 1) | (c2 & 1);
-  double v = 0.0;
-  if (b < hterms(P)) {
-    const int ex = h_exp(b);
-    v = L[p * RS + m2l_col(q, mi_index(mi_a(ex), mi_b(ex), mi_c(ex)), h_degree(b))];
+      for (int u = 0; u < FB; ++u)
+        if (q0 + u * 512 < CNT) lds[q0 + u * 512] = v[u];
+    }
+    __syncthreads();
+    const int end = min(27 * c + 27, vt[0]);
+    int cur = 27 * c;
+    count_down<NT>([&](auto nac) {
+      constexpr int NA = decltype(nac)::value;
+      const int to = min(end, vt[NA - 1]);
+      if (to > cur) {
+        run(nac, c, cur, to);
+        cur = to;
+      }
+    });
   }
-  out[id] = v;
+  // inverse Walsh sums, one row tile of each row group at a time
+  H* const ut = static_cast<H*>(sg.u);
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          lds[(((ks * NX + xg) * 8 + e0 + e) * 16 + M::row(v, kq)) * CS + 16 * t + i] = acc[r][e][t][v];
+    __syncthreads();
+#pragma unroll 1
+    for (int q = threadIdx.x; q < NX * 16 * 16 * NT; q += 512) {
+      const int col = q % (16 * NT), row = (q / (16 * NT)) & 15, xr = q / (256 * NT);
+      const int cb = scol[col];
+      const int ox = ox0 + xr * NR + r, oy = oy0 + (row >> 2), oz = oz0 + (row & 3);
+      if (cb < 0 || ox >= no || oy >= no || oz >= no) continue;
+      double y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        double x = 0.0;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) x += (double)lds[(((k * NX + xr) * 8 + e) * 16 + row) * CS + col];
+        y[e] = x;
+      }
+#pragma unroll
+      for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!(e & bit)) {
+            const double u = y[e], v = y[e | bit];
+            y[e] = u + v;
+            y[e | bit] = u - v;
+          }
+      const int kap = cb >> 8, b = cb & 255;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        // cell tau of the oct: minus bits m
+        const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
+                            (2 * oz + 1 - (m & 1));
+        const double v = chi(kap, m) * y[m];
+        if (ut)
+          ut[(p * 8 + kap) * HR + b] = static_cast<H>(v);
+        else
+          sg.b[(p * 8 + kap) * HR + b] = v;
+      }
+    }
+  }
+}
+
+// L2L, eq. (L2L), in harmonic terms: the complete locals of the cells of one
+// level, [cell][hrow], from the M2L's rows (Walsh-folded over the children) and
+// the complete locals of the level above (null: the coarsest level).  With
+// S[b][pat] the shift's partial sum over the g of parity pattern pat
+// (coefficient lists of plan time, over the full terms b + g, which a block
+// expands once from the harmonic ones),
+//   L(child, b) = chi_b(sigma) sum_kappa chi_kappa(sigma) (Lw[kappa][b] / 8 + S[b][kappa ^ parity(b)]).
+// Thread (parent of 16, slot of 32): terms slot, slot + 32, ...
+// Segments: n = cells per axis of level k - 1, a = its complete locals (or
+// null), c = M2L rows of level k, b = the result.
+constexpr int L2LF_ROWS = 16, L2LF_THREADS = 512;
+template <int P>
+__global__ __launch_bounds__(L2LF_THREADS) void k_l2lf(const Seg* __restrict__ segs, int nseg,
+                                                       const int* __restrict__ cs, const int* __restrict__ cidx,
+                                                       const double* __restrict__ ccoef) {
+  constexpr int NL = nterms(P), HT = hterms(P), HR = hrow(P), E = l2l_entries(P), SS = NL + 1;
+  __shared__ int s_cs[8 * NL + 1];
+  __shared__ int s_idx[E];
+  __shared__ double s_coef[E];
+  __shared__ double s_src[L2LF_ROWS * SS];
+  __shared__ double s_h[L2LF_ROWS * HR];
+  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
+  const int ns = sg.n;
+  const long long nps = (long long)ns * ns * ns, P0 = (long long)(blockIdx.x - sg.first_block) * L2LF_ROWS;
+  const bool up = sg.a != nullptr;
+  if (up) {
+    for (int t = threadIdx.x; t <= 8 * NL; t += L2LF_THREADS) s_cs[t] = cs[t];
+    for (int t = threadIdx.x; t < E; t += L2LF_THREADS) {
+      s_idx[t] = cidx[t];
+      s_coef[t] = ccoef[t];
+    }
+    for (int t = threadIdx.x; t < L2LF_ROWS * HR; t += L2LF_THREADS)
+      s_h[t] = P0 + t / HR < nps ? sg.a[P0 * HR + t] : 0.0;
+    __syncthreads();
+    // full terms: (x, y, 2k + e) = (-1)^k sum_l C(k, l) (x + 2l, y + 2(k - l), e)
+    for (int t = threadIdx.x; t < L2LF_ROWS * NL; t += L2LF_THREADS) {
+      const int r = t / NL, f = t - r * NL, ex = c_mi_exp[f], z = mi_c(ex), k = z >> 1;
+      double v = 0.0;
+      for (int l = 0; l <= k; ++l)
+        v += (double)binom(k, l) * s_h[r * HR + h_index(mi_a(ex) + 2 * l, mi_b(ex) + 2 * (k - l), z & 1)];
+      s_src[r * SS + f] = (k & 1) ? -v : v;
+    }
+    __syncthreads();
+  }
+  const int slot = threadIdx.x & 31, r = threadIdx.x >> 5;
+  const long long Pc = P0 + r;
+  if (Pc >= nps) return;
+  const int p2 = (int)(Pc % ns), p1 = (int)((Pc / ns) % ns), p0 = (int)(Pc / ((long long)ns * ns));
+  const double* __restrict__ row = sg.c + Pc * 8 * HR;
+  const double* src = s_src + r * SS;
+  double* __restrict__ out = sg.b;
+  for (int b = slot; b < HT; b += 32) {
+    const int ex = h_exp(b), bt = mi_index(mi_a(ex), mi_b(ex), mi_c(ex)), pb = h_parity(b);
+    double y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) y[k] = row[k * HR + b];
+    double S[8];
+#pragma unroll
+    for (int pat = 0; pat < 8; ++pat) {
+      double x = 0.0;
+      if (up)
+#pragma unroll 2
+        for (int j = s_cs[8 * bt + pat]; j < s_cs[8 * bt + pat + 1]; ++j) x = fma(s_coef[j], src[s_idx[j]], x);
+      S[pat] = x;
+    }
+    // S over the patterns of the full shift; its Walsh index is kappa = pat ^ pb,
+    // so transform both sums apart and give S its sign chi_b
+#pragma unroll
+    for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (!(e & bit)) {
+          const double u = y[e], v = y[e | bit], a = S[e], c = S[e | bit];
+          y[e] = u + v;
+          y[e | bit] = u - v;
+          S[e] = a + c;
+          S[e | bit] = a - c;
+        }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const long long c = ((long long)(2 * p0 + 1 - ((m >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((m >> 1) & 1))) * (2 * ns) +
+                          (2 * p2 + 1 - (m & 1));
+      out[c * HR + b] = fma(0.125 * chi(pb, m), y[m], S[m]);
+    }
+  }
 }

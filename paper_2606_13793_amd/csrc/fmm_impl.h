@@ -238,6 +238,8 @@ struct TypedChunk {
   }
 };
 
+#include "fmm_harmonic.h"
+
 template <int P, typename TI, typename CT>
 __global__ __launch_bounds__(256) void k_p2m(const Seg* __restrict__ segs, int nseg, IoArg io, int NM) {
   constexpr int NT = nterms(P), NC = (NT + 3) / 4;
@@ -331,13 +333,16 @@ __global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int 
   const long long ncellp = (long long)nFp * nFp * nFp;
   const long long cp = ((long long)(t0 + 3) * nFp + (t1 + 3)) * nFp + (t2 + 3);
   double tv[TypedChunk<CT>::KC];  // the typed chunk being filled
-  static_for<NC>([&](auto cc) {
-    constexpr int c = decltype(cc)::value;
-    d4 o;
-    static_for<4>([&](auto ec) {
-      constexpr int al = 4 * c + decltype(ec)::value;
+  d4 o = d4{0, 0, 0, 0};
+  // degree by degree: the full terms, written in chunks of 4, and from those
+  // of one degree its harmonic terms
+  static_for<P + 1>([&](auto dc) {
+    constexpr int m = decltype(dc)::value;
+    double d[ndeg(m)];
+    static_for<ndeg(m)>([&](auto ec) {
+      constexpr int al = nterms(m - 1) + decltype(ec)::value, c = al / 4;
       double val = 0.0;
-      if constexpr (al < NT) {
+      {
         constexpr int ex = mi_exp_of(al);
         constexpr int ax = ex & 255, ay = (ex >> 8) & 255, az = ex >> 16;
         constexpr int base = 16 * 2 * (ax & 1) + 4 * 2 * (ay & 1) + 2 * (az & 1);
@@ -350,11 +355,24 @@ __global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int 
         constexpr double sc = 1.0 / (fact_d(ax) * fact_d(ay) * fact_d(az) * (double)(1LL << (3 * (ax + ay + az))));
         if (al < NM) val = sc * x;
       }
-      o[decltype(ec)::value] = val;
+      d[decltype(ec)::value] = val;
+      o[al % 4] = val;
+      if constexpr (al % 4 == 3 || al == NT - 1) {
+        *reinterpret_cast<d4*>(M + (c * ncellp + cp) * 4) = o;
+        TypedChunk<CT>::template put<c, NC>(tv, o, sg.t, ncellp, cp);
+        o = d4{0, 0, 0, 0};
+      }
     });
-    *reinterpret_cast<d4*>(M + (c * ncellp + cp) * 4) = o;
-    TypedChunk<CT>::template put<c, NC>(tv, o, sg.t, ncellp, cp);
-    // (one chunk at a time: the scheduler would otherwise form every term
+    if (sg.u)
+      static_for<2 * m + 1>([&](auto rc) {
+        constexpr int i = m * m + decltype(rc)::value;
+        const double v = h_reduce_deg<i>(d);
+        if (sg.split)
+          static_cast<float*>(sg.u)[i * ncellp + cp] = (float)v;
+        else
+          static_cast<double*>(sg.u)[i * ncellp + cp] = v;
+      });
+    // (one degree at a time: the scheduler would otherwise form every term
     // before the first store and hold them all in registers)
     __builtin_amdgcn_sched_barrier(0);
   });
@@ -394,6 +412,7 @@ __global__ __launch_bounds__(M2MShape<PO>::THREADS) void k_m2m(const Seg* __rest
   __shared__ int sstart[NM + 1];
   __shared__ int soff[NE];
   __shared__ double scoef[NE];
+  __shared__ double out[M2M_PAR * NM];
   const Seg& sg = find_seg(segs, nseg, blockIdx.x);
   const double* __restrict__ Mc = sg.a;
   double* __restrict__ Mp = sg.b;
@@ -453,11 +472,27 @@ __global__ __launch_bounds__(M2MShape<PO>::THREADS) void k_m2m(const Seg* __rest
     const int p2 = (int)(P % np), p1 = (int)((P / np) % np), p0 = (int)(P / ((long long)np * np));
     const long long cp = ((long long)(p0 + 3) * npp + (p1 + 3)) * npp + (p2 + 3);
     const double v = al < nmx ? acc : 0.0;  // truncation at nmax
+    out[pl * NM + al] = v;
     Mp[((al >> 2) * ncp_p + cp) * 4 + (al & 3)] = v;
     if constexpr (Mf<CT>::IDX != 0) {
       constexpr int KC = Mf<CT>::KC;
       if (sg.t) ((typename Mf<CT>::H*)sg.t)[((al / KC) * ncp_p + cp) * KC + al % KC] = static_cast<typename Mf<CT>::H>(v);
     }
+  }
+  if (!sg.u) return;
+  // the harmonic terms
+  __syncthreads();
+  for (int w = threadIdx.x; w < M2M_PAR * hterms(PO); w += M2M_THREADS) {
+    const int pl = w % M2M_PAR, i = w / M2M_PAR;
+    const long long P = P0 + pl;
+    if (P >= nP) continue;
+    const double v = h_reduce(i, [&](int al) { return out[pl * NM + al]; });
+    const int p2 = (int)(P % np), p1 = (int)((P / np) % np), p0 = (int)(P / ((long long)np * np));
+    const long long x = i * ncp_p + ((long long)(p0 + 3) * npp + (p1 + 3)) * npp + (p2 + 3);
+    if (sg.split)
+      static_cast<float*>(sg.u)[x] = (float)v;
+    else
+      static_cast<double*>(sg.u)[x] = v;
   }
 }
 
@@ -1364,6 +1399,34 @@ hipError_t build_tables_t(fmm_plan* pl, bool bottom, bool m2l, hipStream_t s) {
   return hipSuccess;
 }
 
+// column tiles and B fragments of the folded M2L (x: 0 FP64, 1 FP32)
+hipError_t build_m2lf(fmm_plan* pl, int x, hipStream_t s) {
+  const int nt = m2lf_ntiles(pl->p);
+  std::vector<int2> t(nt + 8, int2{0, 0});  // a group may run past the last tile
+  long long f = 0;
+  for (int i = 0; i < nt; ++i) {
+    t[i] = int2{m2lf_steps(pl->p, pl->nmax, i), (int)f};
+    f += t[i].x;
+  }
+  hipError_t e;
+  if (!pl->m2lf_tiles) {
+    if ((e = hipMalloc(&pl->m2lf_tiles, t.size() * sizeof(int2))) != hipSuccess) return e;
+    pl->bytes += t.size() * sizeof(int2);
+    if ((e = hipMemcpy(pl->m2lf_tiles, t.data(), t.size() * sizeof(int2), hipMemcpyHostToDevice)) != hipSuccess) return e;
+  }
+  const long long cnt = f * 512;
+  const size_t b = (size_t)cnt * (x ? sizeof(float) : sizeof(double));
+  if ((e = hipMalloc(&pl->wm2lf[x], b)) != hipSuccess) return e;
+  pl->bytes += b;
+  if (x)
+    hipLaunchKernelGGL(k_m2lf_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, pl->m2lf_tiles,
+                       (float*)pl->wm2lf[x], pl->p, pl->nmax, pl->ND, cnt);
+  else
+    hipLaunchKernelGGL(k_m2lf_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, pl->m2lf_tiles,
+                       (double*)pl->wm2lf[x], pl->p, pl->nmax, pl->ND, cnt);
+  return hipGetLastError();
+}
+
 // every launch site's compute type: levels k < m2l_low_from and bottoms of
 // fields with F <= coarse_fp64_levels run in FP64
 hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
@@ -1376,6 +1439,8 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   }
   const bool m2l64 = pl->s_conv[0].nseg > 0, m2llow = pl->s_conv[1].nseg > 0;
   const bool bot64 = pl->s_bot[0][0].nseg > 0, botlow = pl->s_bot[1][0].nseg > 0;
+  for (int x = 0; x < 2; ++x)
+    if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, s)) != hipSuccess) return e;
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
     double* G = nullptr;
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
@@ -1495,6 +1560,28 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int P, typename CT, int MT, int NT, int NE, int KS>
+hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s) {
+  StageScope sc(pl, ST_M2L, 1, s);
+  constexpr int G = (m2lf_ntiles(P) + NT - 1) / NT;
+  hipLaunchKernelGGL((k_m2lf<P, CT, MT, NT, NE, KS>), dim3((unsigned)G * st.blocks), dim3(512), 0, s, st.dev, st.nseg,
+                     st.blocks, pl->m2lf_tiles, (const typename Mf<CT>::H*)pl->wm2lf[x]);
+  return hipGetLastError();
+}
+
+// Folded M2L of site x (0 FP64, 1 FP32): the largest tile that still gives
+// every compute unit blocks.
+template <int P, typename CT>
+hipError_t launch_m2lf(fmm_plan* pl, int x, hipStream_t s) {
+  if (!pl->s_m2lf[x][0].nseg) return hipSuccess;
+  int v = pl->s_m2lf[x][2].blocks >= pl->cus ? 2 : pl->s_m2lf[x][1].blocks >= pl->cus / 4 ? 1 : 0;
+  if (pl->tune.grp == 1 && v > 0) --v;
+  const SegTable& st = pl->s_m2lf[x][v];
+  if (v == 2) return launch_m2lf_v<P, CT, 4, 4, 2, 1>(pl, x, st, s);
+  if (v == 1) return launch_m2lf_v<P, CT, 2, 4, 2, 1>(pl, x, st, s);
+  return launch_m2lf_v<P, CT, 1, 1, 4, 4>(pl, x, st, s);
+}
+
 // Finest blocks (k_block) of site x (0 FP64, 1 low precision).  Tiles of 4
 // rows of blocks share each B fragment between 4 waves; fewer rows where they
 // would leave compute units idle.
@@ -1507,21 +1594,6 @@ hipError_t launch_block(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   if ((pl->force_bz ? pl->force_bz : pl->tune.bz) == 8 && v > 0) --v;
   unsigned int* cnt = pl->stamps ? pl->stamp_cnt : nullptr;
   unsigned long long* done = pl->stamps ? pl->stamp_time + 1 : nullptr;
-  // the locals in the kernel's form
-  for (auto& fd : pl->fld) {
-    if (!block_field(pl, fd.F) || (bottom_low(pl, fd.F) ? 1 : 0) != x || fd.F < 3) continue;
-    const Level& lf = fd.lev[fd.F];
-    const long long np = lf.ncell / 8;
-    if (lf.Lt)
-      hipLaunchKernelGGL((k_lfold_own<P, H, H>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s, (const H*)lf.Lt,
-                         (H*)lf.Lw, np);
-    else
-      hipLaunchKernelGGL((k_lfold_own<P, H, double>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s,
-                         (const double*)lf.L, (H*)lf.Lw, np);
-    if (fd.F >= 4)
-      hipLaunchKernelGGL((k_lfold_compact<P>), dim3(blocks_for(np * hrow(P), 256)), dim3(256), 0, s,
-                         (const double*)fd.lev[fd.F - 1].L, fd.lev[fd.F - 1].Lc, fd.lev[fd.F - 1].nk);
-  }
   const SegTable& st = pl->s_blk[x][v];
   StageScope sc(pl, ST_BOTTOM, 1, s);
   const H* w = (const H*)pl->wblk[x];
@@ -1570,6 +1642,9 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
                        pl->m2m_start, pl->m2m_off, pl->m2m_coef, pl->NMX);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  if ((e = launch_m2lf<P, double>(pl, 0, s)) != hipSuccess) return e;
+  if constexpr (std::is_same<CT, float>::value)
+    if ((e = launch_m2lf<P, float>(pl, 1, s)) != hipSuccess) return e;
   if ((e = launch_conv<P, double, CV_M2L>(pl, pl->s_conv[0], pl->wm2l[0], s)) != hipSuccess) return e;
   if ((e = launch_split_reduce(pl, pl->s_red[0], s)) != hipSuccess) return e;
   if constexpr (!std::is_same<CT, double>::value) {
@@ -1578,8 +1653,17 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   }
   // L2L down to level F - 1 of each field; level F's far field is taken from
   // Lhat_{F-1} directly by the bottom kernel
+  for (int k = 3; k <= pl->maxF - 1; ++k) {
+    const SegTable& st = pl->s_l2lf[k];
+    if (!st.nseg) continue;
+    StageScope sc(pl, ST_L2L, 1, s);
+    hipLaunchKernelGGL(k_l2lf<P>, dim3(st.blocks), dim3(L2LF_THREADS), 0, s, st.dev, st.nseg, pl->l2l_start,
+                       pl->l2l_idx, pl->l2l_coef);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   for (int k = 4; k <= pl->maxF - 1; ++k) {
-    StageScope sc(pl, ST_L2L, pl->s_l2l[k].nseg ? 1 : 0, s);
+    if (!pl->s_l2l[k].nseg) continue;
+    StageScope sc(pl, ST_L2L, 1, s);
     if ((e = launch_l2l_site<P>(pl, pl->s_l2l[k], s)) != hipSuccess) return e;
   }
   if ((e = launch_block<P, double, TI, TO>(pl, 0, io, s)) != hipSuccess) return e;

@@ -179,12 +179,15 @@ struct Level {
   // null elsewhere.  Only the bottom kernel reads it, and it rounds its
   // operands to that type anyway.
   void* Lt = nullptr;
-  // finest level of a field on the folded block kernel (k_block): the same
-  // locals Walsh-folded over the children, [parent][8][hrow] in the compute
-  // type
+  // fields on the folded kernels (fmm_fold.h), in place of L: the M2L part of
+  // the locals of level k >= 3, Walsh-folded over the children, [parent][8]
+  // [hrow], FP64 (the finest level: the block kernel's compute type)
   void* Lw = nullptr;
-  // level below it: the harmonic terms of each cell's local, [cell][hrow]
+  // levels 3 .. F - 1: the complete locals' harmonic terms, [cell][hrow]
   double* Lc = nullptr;
+  // harmonic multipoles of levels 2 .. F - 1, [term][ncellp] with a zero halo,
+  // in the compute type of the M2L into the next level
+  void* Mh = nullptr;
 };
 
 // one density field of a plan (a single-field plan has one)
@@ -335,6 +338,10 @@ struct fmm_plan {
   fmm::SegTable s_bot[2][2];        // bottom [FP64 | low][tile depth 16 | 8]
   fmm::SegTable s_blk[2][3];        // finest blocks [FP64 | low][1, 2 or 4 rows of blocks per tile]
   long long blk_rows[2] = {0, 0};   // their row tiles of 16 blocks
+  fmm::SegTable s_m2lf[2][3];       // folded M2L [FP64 | low][1, 2 or 4 rows of octs per tile]
+  fmm::SegTable s_l2lf[16];         // folded L2L: complete locals of level k
+  void* wm2lf[2] = {nullptr, nullptr};  // the folded M2L's B fragments, FP64 and FP32
+  int2* m2lf_tiles = nullptr;       // (K steps, first fragment) of each column tile
   void* wblk[2] = {nullptr, nullptr};  // the block kernel's B table, FP64 and FP32
   fmm::SegTable s_red[2];           // reductions of split forward M2L partial sums
   double* conv_part = nullptr;      // partial sums of split forward M2L segments
@@ -424,12 +431,16 @@ bool finest_locals_typed(const fmm_plan* pl, const Field& fd);
 inline int m2l_low_from(const fmm_plan* pl) {
   return pl->precision == 0 ? 64 : (pl->coarse_fp64_levels + 1 > 3 ? pl->coarse_fp64_levels + 1 : 3);
 }
+// whether a folded field's harmonic multipoles of level k are FP32 (the M2L
+// into level k + 1 runs in FP32)
+inline bool harmonic_float(const fmm_plan* pl, int k) { return pl->precision == 1 && k + 1 >= m2l_low_from(pl); }
 // whether the multipoles of level k (of a field with finest level F) get a
 // copy in the compute type: the low-precision bottom reads level F, the
 // low-precision M2L into level k + 1 reads level k
 inline bool typed_level(const fmm_plan* pl, int F, int k) {
   if (pl->precision == 0) return false;
-  return (k == F && bottom_low(pl, F) && !block_field(pl, F)) || (k < F && k + 1 >= m2l_low_from(pl));
+  if (block_field(pl, F)) return false;
+  return (k == F && bottom_low(pl, F)) || (k < F && k + 1 >= m2l_low_from(pl));
 }
 
 // Records an event pair around a stage when the plan is profiling.
