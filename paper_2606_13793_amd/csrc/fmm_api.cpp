@@ -99,7 +99,11 @@ void release_adj(fmm::AdjWs& w) {
     if (a) (void)hipFree(a);
   if (w.part) (void)hipFree(w.part);
   if (w.near) (void)hipFree(w.near);
-  for (fmm::SegTable* st : {&w.m2lt[0], &w.m2lt[1], &w.m2pt, &w.m2lt_red, &w.p2pt})
+  for (auto a : w.lb)
+    if (a) (void)hipFree(a);
+  for (auto a : w.lc)
+    if (a) (void)hipFree(a);
+  for (fmm::SegTable* st : {&w.m2lt[0], &w.m2lt[1], &w.m2pt, &w.m2lt_red, &w.p2pt, &w.m2ltf[0], &w.m2ltf[1]})
     if (st->dev) (void)hipFree(st->dev);
   w = fmm::AdjWs{};
 }
@@ -130,7 +134,12 @@ void release(fmm_plan* pl) {
     if (w) (void)hipFree(w);
   for (auto w : pl->wm2lf)
     if (w) (void)hipFree(w);
+  for (auto w : pl->wm2lf_adj)
+    if (w) (void)hipFree(w);
   if (pl->m2lf_tiles) (void)hipFree(pl->m2lf_tiles);
+  if (pl->m2lf_adj_tiles) (void)hipFree(pl->m2lf_adj_tiles);
+  if (pl->wblk_adj) (void)hipFree(pl->wblk_adj);
+  if (pl->m2lf_part) (void)hipFree(pl->m2lf_part);
   auto free_st = [](fmm::SegTable& st) {
     if (st.dev) (void)hipFree(st.dev);
     st = fmm::SegTable{};
@@ -639,6 +648,42 @@ struct AdjSegs {
   SegArr lt[2], pt, ltr, p2pt;
 };
 
+// Folded fields: bytes of each workspace buffer, and the segments of the
+// transposed M2L over workspace w (the finest level first), whose results go
+// to the plan's multipole grids as planes of harmonic terms.
+struct FoldAdjLayout {
+  size_t lb[16] = {}, lc[16] = {};
+};
+FoldAdjLayout fold_adj_layout(const fmm_plan* pl) {
+  FoldAdjLayout l;
+  const size_t ht = (size_t)(pl->p + 1) * (pl->p + 1), hr = (ht + 3) / 4 * 4;
+  for (int k = 3; k <= pl->F; ++k) {
+    const size_t np = ((size_t)1 << (k - 1)) + 6;
+    l.lb[k] = 8 * ht * np * np * np * (fmm::harmonic_float(pl, k - 1) ? sizeof(float) : sizeof(double));
+    if (k < pl->F) l.lc[k] = ((size_t)1 << (3 * k)) * hr * sizeof(double);
+  }
+  return l;
+}
+void fold_adj_segments(const fmm_plan* pl, const fmm::AdjWs& w, SegArr (&out)[2], int (&variant)[2]) {
+  SegArr s[2][3];
+  for (int k = pl->F; k >= 3; --k) {
+    fmm::Seg c{};
+    c.n = 1 << (k - 1);
+    const int no = c.n >> 1, x = fmm::harmonic_float(pl, k - 1) ? 1 : 0;
+    c.tpa = (int)cdiv(no, 4);
+    c.a = (const double*)w.lb[k];
+    c.b = (double*)pl->lev[k - 1].M;
+    for (int v = 0; v < 3; ++v) {
+      c.tz = (int)cdiv(no, 1 << v);
+      s[x][v].add(c, (long long)c.tpa * c.tpa * c.tz);
+    }
+  }
+  for (int x = 0; x < 2; ++x) {
+    variant[x] = fmm::m2lf_variant(pl, s[x][1].blocks, s[x][2].blocks);
+    out[x] = s[x][variant[x]];
+  }
+}
+
 // Segments of the transposed convolutions over workspace w: M2L^T rows are
 // the sources of every target level (the finest first, so its long blocks
 // start first; FP64 levels and low-precision levels in separate launches),
@@ -911,10 +956,12 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
       lv.ncell = 1LL << (3 * k);
       lv.ncellp = (long long)lv.nkp * lv.nkp * lv.nkp;
       const size_t mb = (size_t)pl->NC * lv.ncellp * 4 * sizeof(double);
-      if (dev_alloc(pl, &lv.M, mb)) return bail();
-      if (hipMemset(lv.M, 0, mb) != hipSuccess) {
-        fail(FMM_ERR_DEVICE, "hipMemset failed");
-        return bail();
+      if (k < fd.F || !fmm::block_field(pl, fd.F)) {  // folded fields form no finest multipoles
+        if (dev_alloc(pl, &lv.M, mb)) return bail();
+        if (hipMemset(lv.M, 0, mb) != hipSuccess) {
+          fail(FMM_ERR_DEVICE, "hipMemset failed");
+          return bail();
+        }
       }
       if (fmm::typed_level(pl, fd.F, k)) {
         // the copy in the compute type: BF16 chunks of 16 terms, FP32 of 4
@@ -985,12 +1032,13 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     return bail();
   }
   if (!batch) {
+    const bool folded = fmm::block_field(pl, pl->F);
     // the backward pass's tables: coefficients of the transposed L2P steps
     // (one set per group of 8 unigrid cells), the transposed convolutions'
     // B fragments and, for FMM-2, the near-field transpose's offset lists
     const size_t ng = pl->dl == 2 ? 8 : 1;
-    if (dev_alloc(pl, (void**)&pl->adj_l2p, ng * pl->NL * 32 * sizeof(double)) ||
-        dev_alloc(pl, (void**)&pl->adj_l2p2, ng * 8 * pl->NL * 32 * sizeof(double)))
+    if (!folded && (dev_alloc(pl, (void**)&pl->adj_l2p, ng * pl->NL * 32 * sizeof(double)) ||
+        dev_alloc(pl, (void**)&pl->adj_l2p2, ng * 8 * pl->NL * 32 * sizeof(double))))
       return bail();
     if (pl->dl == 2) {
       const std::vector<int> lp = build_dlists_p2p();
@@ -1391,8 +1439,21 @@ static int ensure_adjoint(fmm_plan* pl) {
     }
     return FMM_OK;
   };
-  const AdjLayout lay = adj_layout(pl);
   int rc;
+  if (fmm::block_field(pl, pl->F)) {
+    const FoldAdjLayout fl = fold_adj_layout(pl);
+    for (int k = 3; k <= pl->F; ++k) {
+      if ((rc = zalloc((double**)&w.lb[k], fl.lb[k]))) return bail(rc);
+      if (fl.lc[k] && (rc = zalloc(&w.lc[k], fl.lc[k]))) return bail(rc);
+    }
+    SegArr sa[2];
+    fold_adj_segments(pl, w, sa, w.m2ltf_v);
+    if ((rc = upload_arr(pl, w.m2ltf[0], sa[0])) || (rc = upload_arr(pl, w.m2ltf[1], sa[1]))) return bail(rc);
+    pl->adj = w;
+    pl->adj_ready = 1;
+    return FMM_OK;
+  }
+  const AdjLayout lay = adj_layout(pl);
   if ((rc = zalloc(&w.ybar, lay.ybar))) return bail(rc);
   for (int k = 3; k <= pl->F; ++k)
     if ((rc = zalloc(&w.abar[k], lay.abar[k]))) return bail(rc);
@@ -1468,6 +1529,40 @@ int fmm_solve_backward_noalloc(fmm_plan* plan, const void* dphi, const void* dg,
   }
   char* b = (char*)base;
   fmm::AdjWs w;
+  if (fmm::block_field(plan, plan->F)) {
+    // the folded workspace, which is smaller than the bound checked above
+    const FoldAdjLayout fl = fold_adj_layout(plan);
+    size_t fat = fmm::kNoallocSegBytes;
+    for (int k = plan->F; k >= 3; --k) {
+      w.lb[k] = b + fat;
+      fat += al(fl.lb[k]);
+      if (fl.lc[k]) w.lc[k] = (double*)(b + fat);
+      fat += al(fl.lc[k]);
+    }
+    if (fat > fmm::kNoallocBytes) return fail(FMM_ERR_DEVICE, "internal: folded backward workspace of %zu bytes", fat);
+    SegArr sa[2];
+    fold_adj_segments(plan, w, sa, w.m2ltf_v);
+    fmm::Seg* sd = (fmm::Seg*)b;
+    for (int x = 0; x < 2 && e == hipSuccess; ++x) {
+      if (!sa[x].n) continue;
+      w.m2ltf[x].dev = sd;
+      w.m2ltf[x].nseg = sa[x].n;
+      w.m2ltf[x].blocks = (int)sa[x].blocks;
+      e = fmm::noalloc_put_segs(sa[x].v, sa[x].n, sd, s);
+      sd += sa[x].n;
+    }
+    if (e == hipSuccess && fat > fmm::kNoallocSegBytes)
+      e = fmm::noalloc_zero((double*)(b + fmm::kNoallocSegBytes), (long long)((fat - fmm::kNoallocSegBytes) / sizeof(double)), s);
+    const int prof = plan->profiling;
+    plan->profiling = 0;
+    if (e == hipSuccess) e = fmm::launch_backward(plan, w, dphi, dg, drho, s);
+    plan->profiling = prof;
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(FMM_ERR_DEVICE, "backward launch failed: %s", hipGetErrorString(e));
+    }
+    return ok();
+  }
   w.ybar = (double*)(b + y_off);
   for (int k = 3; k <= plan->F; ++k) w.abar[k] = (double*)(b + a_off[k]);
   if (lay.near) w.near = (double*)(b + n_off);

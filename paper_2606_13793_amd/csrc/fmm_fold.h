@@ -139,16 +139,73 @@ __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int
   W[id] = static_cast<H>(x);
 }
 
+// (pattern, term) of folded-local column col (columns sorted by the degree of
+// the term, the pattern slow inside a degree), packed pattern << 8 | term; -1
+// past the last
+constexpr __host__ __device__ int m2lf_col(int P, int col) {
+  if (col >= 8 * hterms(P)) return -1;
+  const int m = h_degree(col / 8), in = col - 8 * m * m;
+  return (in / (2 * m + 1)) << 8 | (m * m + in % (2 * m + 1));
+}
+// Index tables of the folded kernels of one order.
+template <int P>
+struct FoldTab {
+  short col[8 * hterms(P)];             // m2lf_col
+  unsigned char full[hterms(P)];        // full-term index of a reduced term
+  unsigned char par[hterms(P)];         // its parity pattern
+  signed char pt[8][4 * blk_psteps(P)];  // blk_pterm
+  constexpr FoldTab() : col(), full(), par(), pt() {
+    for (int i = 0; i < 8 * hterms(P); ++i) col[i] = (short)m2lf_col(P, i);
+    int cnt[8] = {};
+    for (auto& row : pt)
+      for (auto& v : row) v = -1;
+    for (int i = 0; i < hterms(P); ++i) {
+      const int ex = h_exp(i), e = h_parity(i);
+      full[i] = (unsigned char)mi_index(ex & 255, (ex >> 8) & 255, ex >> 16);
+      par[i] = (unsigned char)e;
+      pt[e][cnt[e]++] = (signed char)i;
+    }
+  }
+};
+template <int P>
+__constant__ const FoldTab<P> c_ft = FoldTab<P>();
+
+// in-place Walsh transform of 8 values
+template <typename H>
+__device__ __forceinline__ void walsh8(H (&y)[8]) {
+#pragma unroll
+  for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (!(e & bit)) {
+        const H u = y[e], v = y[e | bit];
+        y[e] = u + v;
+        y[e | bit] = u - v;
+      }
+}
+
 // Walsh sums of the 8 mirror images r[minus bits] for the NE patterns
 // NE eg .. NE eg + NE - 1: s = the weight of the minus images along each axis,
-// chi of the axis where eg fixes it (x; y for NE <= 2; z for NE = 1) times the
+// chi of the axis where eg fixes it (x for NE <= 4; y for NE <= 2; z for NE = 1) times the
 // images' own sign.
 template <int NE, typename H>
 __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[NE]) {
   H x[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) x[q] = fma(sx, r[4 + q], r[q]);
-  if constexpr (NE == 4) {
+  if constexpr (NE == 8) {
+    H y[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = h ? fma(-sx, r[4 + q], r[q]) : x[q];
+      const H p0 = fma(sy, y[2], y[0]), p1 = fma(sy, y[3], y[1]), m0 = fma(-sy, y[2], y[0]), m1 = fma(-sy, y[3], y[1]);
+      a[4 * h] = fma(sz, p1, p0);
+      a[4 * h + 1] = fma(-sz, p1, p0);
+      a[4 * h + 2] = fma(sz, m1, m0);
+      a[4 * h + 3] = fma(-sz, m1, m0);
+    }
+  } else if constexpr (NE == 4) {
     const H p0 = fma(sy, x[2], x[0]), p1 = fma(sy, x[3], x[1]), m0 = fma(-sy, x[2], x[0]), m1 = fma(-sy, x[3], x[1]);
     a[0] = fma(sz, p1, p0);
     a[1] = fma(-sz, p1, p0);
@@ -184,6 +241,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
   using H = typename M::H;
   using Acc = typename M::Acc;
   constexpr int NE = NX, HR = hrow(P), NLS = blk_lsteps(P), NPS = blk_psteps(P);
+  constexpr int OFF_L = blk_off_l(), OFF_P = blk_off_p(P);
   // epilogue image of the block's results, [8][NX * 16][33]
   constexpr int EP = 8 * NX * 16 * 33, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
@@ -196,7 +254,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
   TI* __restrict__ keep = static_cast<TI*>(sg.t);
   const int lb = blockIdx.x - sg.first_block;
   const int bx0 = (lb / (sg.tpa * sg.tpa)) * NX, by0 = ((lb / sg.tpa) % sg.tpa) * 4, bz0 = (lb % sg.tpa) * 4;
-  for (int t = threadIdx.x; t < 8 * NPS * 4; t += BLK_THREADS) spt[t] = blk_pterm(P, t / (NPS * 4), t % (NPS * 4));
+  for (int t = threadIdx.x; t < 8 * NPS * 4; t += BLK_THREADS) spt[t] = c_ft<P>.pt[t / (NPS * 4)][t % (NPS * 4)];
   // the densities of the tile and 4 cells around, zero outside the grid
   {
     constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
@@ -289,7 +347,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
   if (sg.u) {
     typedef H h4 __attribute__((ext_vector_type(4)));
     const auto own = gmem(static_cast<const H*>(sg.u) + (cell * 8 + e0) * HR);
-    const H* wl = W + blk_off_l() + lane;
+    const H* wl = W + OFF_L + lane;
     constexpr int FULL = hterms(P) / 16;
 #pragma unroll 1
     for (int c = 0; c < FULL; ++c) {
@@ -320,7 +378,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
   }
   if (sg.d) {
     const auto par = gmem(sg.d + cell * HR);
-    const H* wp = W + blk_off_p(P) + e0 * (NPS * 128) + lane;
+    const H* wp = W + OFF_P + e0 * (NPS * 128) + lane;
 #pragma unroll
     for (int e = 0; e < NE; ++e)
 #pragma unroll
@@ -350,15 +408,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
     H y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = x[e * ES];
-#pragma unroll
-    for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (!(e & bit)) {
-          const H u = y[e], v = y[e | bit];
-          y[e] = u + v;
-          y[e | bit] = u - v;
-        }
+    walsh8(y);
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
   }
@@ -416,13 +466,6 @@ constexpr __host__ __device__ int m2lf_steps(int P, int nmax, int t) {
   const int q = P - m < nmax ? P - m : nmax;
   return (27 * hterms(q) + 3) / 4;
 }
-// (pattern, term) of column col, packed pattern << 8 | term; -1 past the last
-constexpr __host__ __device__ int m2lf_col(int P, int col) {
-  if (col >= 8 * hterms(P)) return -1;
-  const int m = h_degree(col / 8), in = col - 8 * m * m;
-  return (in / (2 * m + 1)) << 8 | (m * m + in % (2 * m + 1));
-}
-
 // B fragments in the compute type, [fragment (tile, step)][8 patterns][64];
 // tiles[t] = (steps, first fragment).
 template <typename H>
@@ -458,37 +501,88 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
   W[id] = static_cast<H>(x);
 }
 
+// OP 1 is the transpose: rows are the octs of source cells J, the operands the
+// cotangents of the Lw rows of the 27 x 8 cells P around (K index 27 column +
+// P, columns sorted by |b|; an image's sign is chi_kappa), columns the terms a
+// of one J, the results M_bar(J = sigma, a) = sigma^a sum_e chi_e(sigma) OUT(e; a).
+//
 // Segments: n = source grid cells per axis, tpa = tiles along y and z, tz =
-// tiles along x, a = harmonic multipoles of the source grid in the compute
+// tiles along x; OP 0: a = harmonic multipoles of the source grid in the compute
 // type, [term][(n + 6)^3] (terms padded to a multiple of 4), u = result in the
-// compute type or b = result in FP64, [n^3][8][hrow].
+// compute type or b = result in FP64, [n^3][8][hrow]; OP 1: a = cotangent planes
+// [column][(n + 6)^3] in the compute type, b = result, planes [term][(n + 6)^3].
 // Tile: MT x 4 x 4 octs.  8 waves: 8 / NE groups of NE patterns, KS slices of
 // the K steps, MT / NR groups of NR row tiles (a row tile: the 4 x 4 octs of a
 // plane).  A block sums NT column tiles over all 8 patterns, so the inverse
 // Walsh sums happen in its epilogue.  Blocks: column groups x T tiles, the
-// heaviest group (lowest degrees) first.
+// heaviest group (lowest degrees) first; a group whose K loop is long against
+// the launch shares it among several blocks (grid.parts), each summing a run
+// of chunks: they leave their sums in `part`, which k_m2lf_sum adds in order.
 // What bounds it: the matrix cores.  LDS holds 4 terms of the tile's cells and
 // 2 around; a lane reads the 8 mirror images of an operand and folds them (8
 // adds for two patterns), which NT products amortise; each B fragment is read
 // from L2 once per wave for NR row tiles.
-template <int P, typename CT, int MT, int NT, int NE, int KS>
+//
+// result q of a group of row tiles: consecutive threads take the columns of a
+// row, or for planes the rows
+template <int OP, int NT>
+__device__ __forceinline__ int m2lf_qcol(int q) { return OP ? (q >> 4) % (16 * NT) : q % (16 * NT); }
+template <int OP, int NT>
+__device__ __forceinline__ int m2lf_qrow(int q) { return OP ? q & 15 : (q / (16 * NT)) & 15; }
+// inverse Walsh sum over the patterns, to the 8 cells of the oct of `row`
+template <int P, typename H, int OP>
+__device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox, int oy0, int oz0, int row, double (&y)[8]) {
+  constexpr int HR = hrow(P);
+  const int ns = sg.n, nsp = ns + 6, no = ns >> 1, oy = oy0 + (row >> 2), oz = oz0 + (row & 3);
+  if (cb < 0 || ox >= no || oy >= no || oz >= no) return;
+  walsh8(y);
+  if constexpr (OP == 1) {
+    const int pa = c_ft<P>.par[cb];
+    const long long ncellp = (long long)nsp * nsp * nsp;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const long long c = ((long long)(2 * ox + 4 - ((m >> 2) & 1)) * nsp + (2 * oy + 4 - ((m >> 1) & 1))) * nsp +
+                          (2 * oz + 4 - (m & 1));
+      sg.b[cb * ncellp + c] = chi(pa, m) * y[m];
+    }
+  } else {
+    const int kap = cb >> 8, b = cb & 255;
+    H* const ut = static_cast<H*>(sg.u);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      // cell tau of the oct: minus bits m
+      const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
+                          (2 * oz + 1 - (m & 1));
+      const double v = chi(kap, m) * y[m];
+      if (ut)
+        ut[(p * 8 + kap) * HR + b] = static_cast<H>(v);
+      else
+        sg.b[(p * 8 + kap) * HR + b] = v;
+    }
+  }
+}
+template <int P, typename CT, int OP, int MT, int NT, int NE, int KS>
 __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, int nseg, int T,
                                                  const int2* __restrict__ tiles,
-                                                 const typename Mf<CT>::H* __restrict__ W) {
+                                                 const typename Mf<CT>::H* __restrict__ W, const M2lGrid grid,
+                                                 double* __restrict__ part) {
   using M = Mf<CT>;
   using H = typename M::H;
   using Acc = typename M::Acc;
-  constexpr int NR = MT * KS / NE, NG = 8 / NE, NX = MT / NR, HR = hrow(P);
+  constexpr int NR = MT * KS / NE, NG = 8 / NE, NX = MT / NR;
   static_assert(NG * KS * NX == 8, "8 waves");
   constexpr int CELLS = (2 * MT + 4) * 144, CS = 16 * NT + 1;
   constexpr int EP = KS * NX * 8 * 16 * CS, SZ = EP > 4 * CELLS ? EP : 4 * CELLS;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
   __shared__ int4 ktab[108];  // per K index of a chunk: plus image, and the distances to the minus ones
-  __shared__ float4 tsg[HR];  // per term: (-1)^exponent along each axis, the sign of a minus image
+  constexpr int NTERM = OP ? 8 * hterms(P) : hrow(P);
+  __shared__ float4 tsg[NTERM];  // per K term: the sign of a minus image along each axis
   __shared__ int scol[16 * NT];
-  const int grp = (int)blockIdx.x / T, T0 = grp * NT, lbk = (int)blockIdx.x - grp * T;
+  int grp = 0;
+  while (grp + 1 < grid.ng && (int)blockIdx.x >= grid.first[grp + 1]) ++grp;
+  const int T0 = grp * NT, np = grid.parts[grp], rb = (int)blockIdx.x - grid.first[grp], lbk = rb / np, ip = rb % np;
   const Seg& sg = find_seg(segs, nseg, lbk);
-  const int ns = sg.n, nsp = ns + 6, no = ns >> 1, tb = lbk - sg.first_block;
+  const int nsp = sg.n + 6, tb = lbk - sg.first_block;
   const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
   const long long ncellp = (long long)nsp * nsp * nsp;
   const auto src = gmem(reinterpret_cast<const H*>(sg.a));
@@ -503,10 +597,13 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
     const int s = k % 27, jx = s / 9, jy = (s / 3) % 3, jz = s % 3;
     ktab[k] = int4{(k / 27) * CELLS + jx * 144 + jy * 12 + jz, (2 * jx + 1) * 144, (2 * jy + 1) * 12, 2 * jz + 1};
   }
-  for (int c = threadIdx.x; c < 16 * NT; c += 512) scol[c] = m2lf_col(P, 16 * T0 + c);
-  for (int t = threadIdx.x; t < HR; t += 512) {
-    const int ex = h_exp(t);
-    tsg[t] = float4{mi_a(ex) & 1 ? -1.f : 1.f, mi_b(ex) & 1 ? -1.f : 1.f, mi_c(ex) & 1 ? -1.f : 1.f, 0.f};
+  for (int c = threadIdx.x; c < 16 * NT; c += 512) {
+    const int col = 16 * T0 + c;
+    scol[c] = col >= (OP ? 1 : 8) * hterms(P) ? -1 : OP ? col : c_ft<P>.col[col];
+  }
+  for (int t = threadIdx.x; t < NTERM; t += 512) {
+    const int e = OP ? c_ft<P>.col[t] >> 8 : t < hterms(P) ? c_ft<P>.par[t] : 0;
+    tsg[t] = float4{e & 4 ? -1.f : 1.f, e & 2 ? -1.f : 1.f, e & 1 ? -1.f : 1.f, 0.f};
   }
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -568,7 +665,7 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
           bread(sn, b[u ^ 1]);
           aread(sn, r[u ^ 1], g[u ^ 1]);
           __builtin_amdgcn_sched_barrier(0);
-          const H gx = sx * (H)g[u][0], gy = NE <= 2 ? sy * (H)g[u][1] : (H)g[u][1], gz = NE == 1 ? sz * (H)g[u][2] : (H)g[u][2];
+          const H gx = NE <= 4 ? sx * (H)g[u][0] : (H)g[u][0], gy = NE <= 2 ? sy * (H)g[u][1] : (H)g[u][1], gz = NE == 1 ? sz * (H)g[u][2] : (H)g[u][2];
 #pragma unroll
           for (int m = 0; m < NR; ++m) {
             fold8<NE>(r[u][m], gx, gy, gz, a);
@@ -583,7 +680,8 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
     }
   };
   // terms 4 c .. 4 c + 3 per chunk: 27 K steps
-  for (int c = 0; 27 * c < vt[0]; ++c) {
+  const int nch = (vt[0] + 26) / 27, c1 = (ip + 1) * nch / np;
+  for (int c = ip * nch / np; c < c1; ++c) {
     __syncthreads();
     constexpr int CNT = 4 * CELLS, FB = 7;
 #pragma unroll 1
@@ -613,10 +711,11 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
       }
     });
   }
-  // inverse Walsh sums, one row tile of each row group at a time
-  H* const ut = static_cast<H*>(sg.u);
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
+  // the 8 patterns' sums of result q of row tile r, through LDS (one row tile
+  // of each row group at a time), then from all parts of the K loop
+  constexpr int NQ = NX * 16 * 16 * NT;
+  double* const slot = part + (size_t)blockIdx.x * (NR * NQ * 8);
+  auto stage = [&](int r) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < NE; ++e)
@@ -626,43 +725,107 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
         for (int v = 0; v < 4; ++v)
           lds[(((ks * NX + xg) * 8 + e0 + e) * 16 + M::row(v, kq)) * CS + 16 * t + i] = acc[r][e][t][v];
     __syncthreads();
+  };
+  auto load = [&](int q, double (&y)[8]) {
+    const int col = m2lf_qcol<OP, NT>(q), row = m2lf_qrow<OP, NT>(q), xr = q / (256 * NT);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      double x = 0.0;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) x += (double)lds[(((k * NX + xr) * 8 + e) * 16 + row) * CS + col];
+      y[e] = x;
+    }
+  };
+  if (np > 1) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      stage(r);
 #pragma unroll 1
-    for (int q = threadIdx.x; q < NX * 16 * 16 * NT; q += 512) {
-      const int col = q % (16 * NT), row = (q / (16 * NT)) & 15, xr = q / (256 * NT);
-      const int cb = scol[col];
-      const int ox = ox0 + xr * NR + r, oy = oy0 + (row >> 2), oz = oz0 + (row & 3);
-      if (cb < 0 || ox >= no || oy >= no || oz >= no) continue;
-      double y[8];
+      for (int q = threadIdx.x; q < NQ; q += 512) {
+        double y[8];
+        load(q, y);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        double x = 0.0;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) x += (double)lds[(((k * NX + xr) * 8 + e) * 16 + row) * CS + col];
-        y[e] = x;
-      }
-#pragma unroll
-      for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (!(e & bit)) {
-            const double u = y[e], v = y[e | bit];
-            y[e] = u + v;
-            y[e | bit] = u - v;
-          }
-      const int kap = cb >> 8, b = cb & 255;
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        // cell tau of the oct: minus bits m
-        const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
-                            (2 * oz + 1 - (m & 1));
-        const double v = chi(kap, m) * y[m];
-        if (ut)
-          ut[(p * 8 + kap) * HR + b] = static_cast<H>(v);
-        else
-          sg.b[(p * 8 + kap) * HR + b] = v;
+        for (int e = 0; e < 8; ++e) slot[(size_t)(r * 8 + e) * NQ + q] = y[e];
       }
     }
+    return;
   }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    stage(r);
+#pragma unroll 1
+    for (int q = threadIdx.x; q < NQ; q += 512) {
+      const int cb = scol[m2lf_qcol<OP, NT>(q)];
+      double y[8];
+      load(q, y);
+      m2lf_put<P, H, OP>(sg, cb, ox0 + (q / (256 * NT)) * NR + r, oy0, oz0, m2lf_qrow<OP, NT>(q), y);
+    }
+  }
+}
+
+// Adds the parts of the shared groups of a k_m2lf launch, in order.  Blocks:
+// (group, tile), the groups with several parts only (sum_first: first block).
+template <int P, typename H, int OP, int MT, int NT, int NR>
+__global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, int nseg, int T, const M2lGrid grid,
+                                                  const double* __restrict__ part) {
+  constexpr int NQ = MT / NR * 256 * NT;
+  int g = 0, left = (int)blockIdx.x / T;  // (a tile per T blocks of each shared group)
+  while (grid.parts[g] == 1 || left-- > 0) ++g;
+  const int lbk = (int)blockIdx.x % T, np = grid.parts[g];
+  const Seg& sg = find_seg(segs, nseg, lbk);
+  const int tb = lbk - sg.first_block;
+  const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
+  const double* slot = part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NQ * 8);
+  for (int x = blockIdx.y * 256 + threadIdx.x; x < NR * NQ; x += gridDim.y * 256) {
+    const int r = x / NQ, q = x % NQ, col = 16 * NT * g + m2lf_qcol<OP, NT>(q);
+    const int cb = col >= (OP ? 1 : 8) * hterms(P) ? -1 : OP ? col : c_ft<P>.col[col];
+    if (cb < 0) continue;
+    double y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = slot[(size_t)(r * 8 + e) * NQ + q];
+    for (int k = 1; k < np; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] += slot[(size_t)k * (NR * NQ * 8) + (size_t)(r * 8 + e) * NQ + q];
+    m2lf_put<P, H, OP>(sg, cb, ox0 + (q / (256 * NT)) * NR + r, oy0, oz0, m2lf_qrow<OP, NT>(q), y);
+  }
+}
+
+// The transpose's steps and B fragments (OP 1), as k_m2lf_table.
+constexpr __host__ __device__ int m2lfa_steps(int P, int nmax, int t) {
+  const int m = h_degree(16 * t);
+  return m > nmax ? 0 : 54 * hterms(P - m);
+}
+template <typename H>
+__global__ void k_m2lf_adj_table(const double* __restrict__ Dtab, const int2* __restrict__ tiles, H* __restrict__ W,
+                                 int P, int nmax, int ND, long long cnt) {
+  const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= cnt) return;
+  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  int t = 0;
+  while (tiles[t].y + tiles[t].x <= f) ++t;
+  const int k = 4 * (f - tiles[t].y) + (lane >> 4), s = k % 27, cb = m2lf_col(P, k / 27), a = 16 * t + (lane & 15);
+  const int kap = cb >> 8, b = cb & 255;
+  double x = 0.0;
+  if (cb >= 0 && a < hterms(nmax) && h_degree(a) + h_degree(b) <= P) {
+    const int ea = h_exp(a), eb = h_exp(b), pb = h_parity(b);
+    const int g = mi_index(mi_a(ea) + mi_a(eb), mi_b(ea) + mi_b(eb), mi_c(ea) + mi_c(eb));
+    const int j[3] = {s / 9, (s / 3) % 3, s % 3};
+    for (int minus = 0; minus < 8; ++minus) {
+      int dd = 0;
+      bool near = true;
+      for (int ax = 0; ax < 3; ++ax) {
+        const int d = (minus >> (2 - ax)) & 1 ? -j[ax] - 1 : j[ax];  // P - J
+        near = near && d >= -1 && d <= 1;
+        dd = dd * 7 + d + 3;
+      }
+      if (near) continue;
+      double y = 0.0;
+      for (int q = 0; q < 8; ++q) y += chi(kap ^ pb, 7 - q) * Dtab[((size_t)dd * 8 + q) * ND + g];
+      x += chi(e ^ kap, minus) * y;
+    }
+    x = ldexp(x, -(h_degree(b) + 1) - 3);
+  }
+  W[id] = static_cast<H>(x);
 }
 
 // L2L, eq. (L2L), in harmonic terms: the complete locals of the cells of one
@@ -717,7 +880,7 @@ __global__ __launch_bounds__(L2LF_THREADS) void k_l2lf(const Seg* __restrict__ s
   const double* src = s_src + r * SS;
   double* __restrict__ out = sg.b;
   for (int b = slot; b < HT; b += 32) {
-    const int ex = h_exp(b), bt = mi_index(mi_a(ex), mi_b(ex), mi_c(ex)), pb = h_parity(b);
+    const int bt = c_ft<P>.full[b], pb = c_ft<P>.par[b];
     double y[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) y[k] = row[k * HR + b];

@@ -1,0 +1,434 @@
+// Transposes of the folded kernels (fmm_fold.h).  Included by fmm_impl.h.
+//
+// The solve on the folded kernels is, with all maps linear,
+//   Mh_{F-1} = harmonic P2M rho, Mh_{k-1} = M2M Mh_k,
+//   Lw_k = M2L Mh_{k-1} (Walsh-folded over children), Lc_k = unfold Lw_k + L2L Lc_{k-1},
+//   (phi, g) = unfold(block stencil fold(rho) + L2P Lw_F + L2P' Lc_{F-1}).
+// The backward pass runs the transposes in reverse:
+//   k_blk_adj_l    cotangents -> Lw_bar_F, Lc_bar_{F-1}          (L2P^T)
+//   k_l2lf_adj     Lc_bar_k -> Lw_bar_k, Lc_bar_{k-1}, k = F-1..3
+//   k_m2lf (OP 1)  Lw_bar_k -> Mh_bar_{k-1}, every level           (M2L^T)
+//   k_m2mf_adj     Mh_bar_{k-1} -> Mh_bar_k (+=), k = 3..F-1
+//   k_block_adj    cotangents, Mh_bar_{F-1} -> rho_bar           (stencil^T, P2M^T)
+// The interaction relation is symmetric and mirror-symmetric, so each
+// transpose gathers over the same 6^3 cells (12^3 unigrid cells) around an oct
+// and folds the same way.  L2P^T, the stencil and the chains are FP64 in every
+// plan, M2L^T runs in the compute type of the forward M2L of its level.
+#pragma once
+
+// column tiles of the stencil transpose: [4 outputs][54 steps][8 patterns][64],
+// 8 live columns (the sources of the positive octant); then P2M^T,
+// [8][blk_psteps][64]
+constexpr __host__ __device__ int blka_off_p() { return 4 * BLK_STEPS * 8 * 64; }
+constexpr __host__ __device__ int blka_off_l(int P) { return blka_off_p() + 8 * blk_psteps(P) * 64; }
+// L2P^T: own locals [8 steps][tiles][64], level F-1 [8 patterns][8 steps][64]
+constexpr __host__ __device__ int blka_ltiles(int P) { return (hterms(P) + 15) / 16; }
+constexpr __host__ __device__ int blka_off_lp(int P) { return blka_off_l(P) + 8 * blka_ltiles(P) * 64; }
+constexpr __host__ __device__ int blka_table(int P) { return blka_off_lp(P) + 64 * 64; }
+
+__global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int P, int nmax) {
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= blka_table(P)) return;
+  const int lane = id & 63, j = lane & 15, kq = lane >> 4;
+  double x = 0.0;
+  if (id < blka_off_p()) {
+    // source sp of the positive octant, targets at y = the 8 images of u
+    const int e = (id >> 6) & 7, s = (id >> 9) % BLK_STEPS, o = (id >> 9) / BLK_STEPS, k = 4 * s + kq;
+    const int jj[3] = {k / 36, (k / 6) % 6, k % 6};
+    if (j < 8)
+      for (int minus = 0; minus < 8; ++minus) {
+        int t = 0, v = 0, neg = 0;  // the target's place in its own block, the source seen from there, tau
+        for (int a = 0; a < 3; ++a) {
+          const int u2 = (minus >> (2 - a)) & 1 ? -(2 * jj[a] + 1) : 2 * jj[a] + 1;  // 2 y
+          const int B = (u2 + 4 + 16) / 8 - 2, r2 = u2 - 8 * B;                      // block offset, 2 (y - 4 B)
+          const int sp2 = 2 * ((j >> (2 - a)) & 1) + 1;
+          const int v2 = r2 < 0 ? 8 * B - sp2 : sp2 - 8 * B;
+          neg = neg << 1 | (r2 < 0);
+          t = t << 1 | (r2 > 2 || r2 < -2);
+          v = v * 12 + (v2 + 11) / 2;
+        }
+        const int eo = o ? 8 >> o : 0;  // the axis of output o
+        x += chi(e, minus) * chi(eo, minus) * chi(eo, neg) * G[((size_t)t * 1728 + v) * 4 + o];
+      }
+  } else if (id < blka_off_l(P)) {
+    const int s = (id - blka_off_p()) >> 6, np = blk_psteps(P), e = s / np;
+    const int b = blk_pterm(P, e, 4 * (s % np) + kq);
+    if (j < 8 && b >= 0 && h_degree(b) <= nmax) {
+      // P2M weights w^a / a!, w = -(1/8 or 3/8)
+      const double w[3] = {(j & 4) ? -0.375 : -0.125, (j & 2) ? -0.375 : -0.125, (j & 1) ? -0.375 : -0.125};
+      x = 8.0 * h_reduce(b, [&](int bt) {
+            const int ex = c_mi_exp[bt];
+            double m = c_mi_invfact[bt];
+            for (int i = 0; i < mi_a(ex); ++i) m *= w[0];
+            for (int i = 0; i < mi_b(ex); ++i) m *= w[1];
+            for (int i = 0; i < mi_c(ex); ++i) m *= w[2];
+            return m;
+          });
+    }
+  } else if (id < blka_off_lp(P)) {
+    const int f = (id - blka_off_l(P)) >> 6, s = f / blka_ltiles(P), b = 16 * (f % blka_ltiles(P)) + j;
+    if (b < hterms(P)) x = 0.125 * h_reduce(b, [&](int bt) { return l2p_coef(bt, s, kq); });
+  } else {
+    const int f = (id - blka_off_lp(P)) >> 6, e = f >> 3, s = f & 7;
+    const int b = blk_pterm(P, e, j);
+    if (b >= 0) x = h_reduce(b, [&](int bt) { return l2p_parent_coef(bt, 7, s, kq); });
+  }
+  W[id] = x;
+}
+
+// L2P^T.  A block takes 16 consecutive 4^3 blocks (C order), folds their
+// scaled cotangents into Y(e; t, o), and wave e multiplies pattern e by the
+// transposed tables: Lw_bar_F columns (e, b) to padded planes
+// [column][(nb + 6)^3] in the compute type of the transposed M2L, and the
+// terms of parity e of Lc_bar_{F-1}, [block][hrow].  Bound by its traffic
+// (reads 4 values a cell, writes 8 (p + 1)^2 a block); rows consecutive along
+// z make every plane's store a run of 16.
+template <int P, typename TI, typename H>
+__global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, const TI* __restrict__ dg, int n,
+                                                   const double* __restrict__ W, H* __restrict__ lb,
+                                                   double* __restrict__ lc) {
+  constexpr int HR = hrow(P), NT = blka_ltiles(P), HT = hterms(P), NPT = 4 * blk_psteps(P);
+  constexpr int OFF_L = blka_off_l(P), OFF_P = blka_off_lp(P);
+  constexpr int YS = 33, RS = 17;  // LDS row strides
+  constexpr int SZ = 8 * 16 * YS > 8 * (HT + 16) * RS ? 8 * 16 * YS : 8 * (HT + 16) * RS;
+  __shared__ double lds[SZ];
+  const int nb = n >> 2, nbp = nb + 6;
+  const long long nblk = (long long)nb * nb * nb, N = (long long)n * n * n, ncp = (long long)nbp * nbp * nbp;
+  const long long B0 = (long long)blockIdx.x * 16;
+  const double dx = 1.0 / n, sphi = 0.5 * dx * dx, sgr = -0.25 * dx;
+  {
+    // thread (o, t, block): blocks fastest
+    const int bl = threadIdx.x & 15, t = (threadIdx.x >> 4) & 7, o = threadIdx.x >> 7;
+    const long long B = B0 + bl;
+    double y[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) y[m] = 0.0;
+    if (B < nblk && (o == 0 || dg)) {
+      const int b2 = (int)(B % nb), b1 = (int)((B / nb) % nb), b0 = (int)(B / ((long long)nb * nb));
+      const TI* src = o == 0 ? dphi : dg + (o - 1) * N;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int x = m & 4 ? 1 - ((t >> 2) & 1) : 2 + ((t >> 2) & 1), yy = m & 2 ? 1 - ((t >> 1) & 1) : 2 + ((t >> 1) & 1),
+                  z = m & 1 ? 1 - (t & 1) : 2 + (t & 1);
+        y[m] = (double)src[((long long)(4 * b0 + x) * n + 4 * b1 + yy) * n + 4 * b2 + z];
+      }
+    }
+    walsh8(y);
+    const double sc = o == 0 ? sphi : sgr;
+    const int eo = o ? 8 >> o : 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // (a constant register index: the exchange e ^ eo is done by the LDS address)
+      lds[((e ^ eo) * 16 + bl) * YS + 4 * t + o] = sc * y[e];
+    }
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int e = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  d4 acc[NT], ap = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const double a = lds[(e * 16 + i) * YS + 4 * s + kq];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_L + (s * NT + t) * 64 + lane], acc[t], 0, 0, 0);
+    if (lc) ap = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_P + (e * 8 + s) * 64 + lane], ap, 0, 0, 0);
+  }
+  __syncthreads();
+  // results by column, blocks along a row
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (16 * t + i < HT) lds[(e * (HT + 16) + 16 * t + i) * RS + 4 * v + kq] = acc[t][v];
+    lds[(e * (HT + 16) + HT + i) * RS + 4 * v + kq] = ap[v];
+  }
+  __syncthreads();
+  {
+    const int bl = threadIdx.x & 15;
+    const long long B = B0 + bl;
+    if (B < nblk) {
+      const int b2 = (int)(B % nb), b1 = (int)((B / nb) % nb), b0 = (int)(B / ((long long)nb * nb));
+      const long long cp = ((long long)(b0 + 3) * nbp + b1 + 3) * nbp + b2 + 3;
+      for (int c = threadIdx.x >> 4; c < 8 * HT; c += 32) {
+        const int q = c_ft<P>.col[c], k = q >> 8, b = q & 255;
+        lb[c * ncp + cp] = static_cast<H>(lds[(k * (HT + 16) + b) * RS + bl]);
+      }
+    }
+  }
+  if (lc) {
+    for (int q = threadIdx.x; q < 16 * 128; q += 512) {
+      const int j = q & 15, pe = (q >> 4) & 7, bl = q >> 7;
+      const int b = j < NPT ? c_ft<P>.pt[pe][j] : -1;
+      if (b >= 0 && B0 + bl < nblk) lc[(B0 + bl) * HR + b] = lds[(pe * (HT + 16) + HT + j) * RS + bl];
+    }
+  }
+}
+
+// L2L^T for one level k: from the complete locals' cotangents of its cells
+// ([cell][hrow]) to those of the M2L's rows (planes over the parents, Walsh
+// sums over the children / 8) and, unless k is the coarsest, to those of the
+// level above.  With W[b][pat] = sum_children sigma^pat Lc_bar(child, b), the
+// shift's transpose is the M2M's coefficient list at half weight over the
+// harmonic b, and the expansion to full terms transposes to h_reduce.
+template <int P>
+struct L2LAdj {
+  static constexpr int NL = nterms(P), HT = hterms(P), PAR = NL <= 56 ? 16 : 8;
+};
+template <int P, typename H>
+__global__ __launch_bounds__(256) void k_l2lf_adj(const double* __restrict__ lc, H* __restrict__ lb,
+                                                  double* __restrict__ lup, int ns, const int* __restrict__ cstart,
+                                                  const int* __restrict__ coff, const double* __restrict__ ccoef) {
+  constexpr int NL = L2LAdj<P>::NL, HT = L2LAdj<P>::HT, PAR = L2LAdj<P>::PAR, HR = hrow(P), WS = 8 * NL + 1;
+  __shared__ double W[PAR * WS];
+  __shared__ double full[PAR * NL];
+  const long long nps = (long long)ns * ns * ns, P0 = (long long)blockIdx.x * PAR;
+  const int nsp = ns + 6;
+  const long long ncp = (long long)nsp * nsp * nsp;
+  if (lup)
+    for (int q = threadIdx.x; q < PAR * WS; q += 256) W[q] = 0.0;
+  __syncthreads();
+  for (int q = threadIdx.x; q < PAR * HT; q += 256) {
+    const int b = q % HT, pl = q / HT;
+    const long long p = P0 + pl;
+    double y[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) y[m] = 0.0;
+    if (p < nps) {
+      const int p2 = (int)(p % ns), p1 = (int)((p / ns) % ns), p0 = (int)(p / ((long long)ns * ns));
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const long long c = ((long long)(2 * p0 + 1 - ((m >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((m >> 1) & 1))) * (2 * ns) +
+                            (2 * p2 + 1 - (m & 1));
+        y[m] = lc[c * HR + b];
+      }
+    }
+    walsh8(y);
+    const int bt = c_ft<P>.full[b];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) W[pl * WS + 8 * bt + k] = y[k];
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < PAR * 8 * HT; q += 256) {
+    const int pl = q % PAR, c = q / PAR;
+    const long long p = P0 + pl;
+    if (p >= nps) continue;
+    const int cb = c_ft<P>.col[c], b = cb & 255, bt = c_ft<P>.full[b];
+    const int p2 = (int)(p % ns), p1 = (int)((p / ns) % ns), p0 = (int)(p / ((long long)ns * ns));
+    lb[c * ncp + ((long long)(p0 + 3) * nsp + p1 + 3) * nsp + p2 + 3] =
+        static_cast<H>(0.125 * W[pl * WS + 8 * bt + ((cb >> 8) ^ c_ft<P>.par[b])]);
+  }
+  if (!lup) return;
+  for (int q = threadIdx.x; q < PAR * NL; q += 256) {
+    const int pl = q % PAR, e = q / PAR;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int j = cstart[e]; j < cstart[e + 1]; ++j) acc = fma(ccoef[j], W[pl * WS + coff[j]], acc);
+    full[pl * NL + e] = 0.5 * acc;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < PAR * HT; q += 256) {
+    const int b = q % HT, pl = q / HT;
+    // transpose of the expansion to full terms: the same weights as h_reduce
+    if (P0 + pl < nps) lup[(P0 + pl) * HR + b] = h_reduce(b, [&](int t) { return full[pl * NL + t]; });
+  }
+}
+
+// M2M^T for one level k in harmonic terms: Mh_bar_k[child][b] += sum over the
+// full terms a = b + g of the parent, whose cotangents are those of its
+// harmonic terms expanded by Laplace's equation (the transpose of h_reduce).
+// Planes [term][(n + 6)^3]; np = cells per axis of level k - 1.
+constexpr int M2MA_PAR = 16;
+template <int P>
+__global__ __launch_bounds__(256) void k_m2mf_adj(const double* __restrict__ Mp, double* __restrict__ Mc, int np,
+                                                  const int* __restrict__ lstart, const int* __restrict__ la,
+                                                  const double* __restrict__ lcoef) {
+  constexpr int NM = nterms(P), HT = hterms(P), MS = NM | 1;
+  __shared__ double mh[M2MA_PAR * HT];
+  __shared__ double mrow[M2MA_PAR * MS];
+  const int npp = np + 6, nk = 2 * np, nkp = nk + 6;
+  const long long ncp = (long long)npp * npp * npp, nck = (long long)nkp * nkp * nkp, nps = (long long)np * np * np;
+  const long long P0 = (long long)blockIdx.x * M2MA_PAR;
+  for (int q = threadIdx.x; q < M2MA_PAR * HT; q += 256) {
+    const int pl = q % M2MA_PAR, t = q / M2MA_PAR;
+    const long long p = P0 + pl;
+    double v = 0.0;
+    if (p < nps) {
+      const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np));
+      v = Mp[t * ncp + ((long long)(p0 + 3) * npp + p1 + 3) * npp + p2 + 3];
+    }
+    mh[pl * HT + t] = v;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < M2MA_PAR * NM; q += 256) {
+    const int pl = q % M2MA_PAR, f = q / M2MA_PAR, ex = c_mi_exp[f], z = mi_c(ex), k = z >> 1;
+    double v = 0.0;
+    for (int l = 0; l <= k; ++l)
+      v += (double)binom(k, l) * mh[pl * HT + h_index(mi_a(ex) + 2 * l, mi_b(ex) + 2 * (k - l), z & 1)];
+    mrow[pl * MS + f] = (k & 1) ? -v : v;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < M2MA_PAR * HT; q += 256) {
+    const int pl = q % M2MA_PAR, b = q / M2MA_PAR;
+    const long long p = P0 + pl;
+    if (p >= nps) continue;
+    const int bt = c_ft<P>.full[b];
+    const double* mr = mrow + pl * MS;
+    double S[8];
+#pragma unroll
+    for (int pat = 0; pat < 8; ++pat) {
+      double x = 0.0;
+      for (int j = lstart[bt * 8 + pat]; j < lstart[bt * 8 + pat + 1]; ++j) x = fma(lcoef[j], mr[la[j]], x);
+      S[pat] = x;
+    }
+    walsh8(S);  // child c takes sum_pat (-1)^popc(c & pat) S[pat]
+    const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np));
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const long long cc = ((long long)(2 * p0 + ((c >> 2) & 1) + 3) * nkp + (2 * p1 + ((c >> 1) & 1) + 3)) * nkp +
+                           (2 * p2 + (c & 1) + 3);
+      Mc[b * nck + cc] += S[c];
+    }
+  }
+}
+
+// Transpose of the block stencil (P2P^T, M2P^T and the finest P2M^T), plus the
+// P2M^T of level F - 1: rho_bar of a 4^3 block from the cotangents of the 12^3
+// cells around, one output (phi, gx, gy, gz) in the LDS tile at a time, and
+// the adjoint harmonic multipoles of its own level F-1 cell (planes; or null).
+// Tiles and folding as in k_block; 8 of the 16 columns of a product are live.
+template <int P, typename TI, typename TO, int NX>
+__global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restrict__ dphi, const TI* __restrict__ dg,
+                                                              const double* __restrict__ W,
+                                                              const double* __restrict__ Mb, TO* __restrict__ drho,
+                                                              int n, int tpa) {
+  constexpr int NE = 4, KS = 4 / NX, NPS = blk_psteps(P), CS = 9;
+  constexpr int EP = KS * 8 * NX * 16 * CS, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
+  __shared__ __attribute__((aligned(16))) double lds[SZ];
+  const int nb = n >> 2, lb = blockIdx.x;
+  const int bx0 = (lb / (tpa * tpa)) * NX, by0 = ((lb / tpa) % tpa) * 4, bz0 = (lb % tpa) * 4;
+  const long long N = (long long)n * n * n;
+  const double dx = 1.0 / n;
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, ks = (w / NX) % KS, e0 = (w / 4) * NE;
+  const double sx0 = e0 ? -1.0 : 1.0;
+  constexpr int OFF_P = blka_off_p();
+  d4 acc[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) acc[e] = d4{0, 0, 0, 0};
+  const double* ctr = lds + (4 * X + 6) * BLK_PLANE + (4 * (i >> 2) + 6) * BLK_ROW + 4 * (i & 3) + 6;
+#pragma unroll 1
+  for (int o = 0; o < (dg ? 4 : 1); ++o) {
+    __syncthreads();
+    {
+      constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
+      const int x0 = 4 * bx0 - 4, y0 = 4 * by0 - 4, z0 = 4 * bz0 - 4;
+      const auto gs = gmem(o == 0 ? dphi : dg + (o - 1) * N);
+      const double sc = o == 0 ? 0.0625 * dx * dx : -0.03125 * dx;  // with the Walsh sum's 1/8
+#pragma unroll 1
+      for (int q0 = threadIdx.x; q0 < CNT; q0 += FB * BLK_THREADS) {
+        TI v[FB];
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+          const int e = q0 + u * BLK_THREADS, z = z0 + e % 24, y = y0 + (e / 24) % 24, x = x0 + e / 576;
+          const bool in = e < CNT && x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
+          v[u] = in ? gs[((long long)x * n + y) * n + z] : TI(0);
+        }
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+          const int e = q0 + u * BLK_THREADS;
+          if (e < CNT) lds[(e / 576) * BLK_PLANE + ((e / 24) % 24) * BLK_ROW + e % 24] = sc * (double)v[u];
+        }
+      }
+    }
+    __syncthreads();
+    // the sign of a minus image along the output's own axis
+    const double sx = o == 1 ? -sx0 : sx0, sy = o == 2 ? -1.0 : 1.0, sz = o == 3 ? -1.0 : 1.0;
+    const auto wb = gmem(W + o * (BLK_STEPS * 512) + e0 * 64 + lane);
+    auto aread = [&](int s, double (&r)[8]) {
+      const int k = 4 * s + kq, jx = k / 36, jy = (k / 6) % 6, jz = k % 6;
+      const int px = jx * BLK_PLANE, mx = -BLK_PLANE - px, py = jy * BLK_ROW, my = -BLK_ROW - py;
+      const double *pp = ctr + px + py, *pm = ctr + px + my, *mp = ctr + mx + py, *mm = ctr + mx + my;
+      r[0] = pp[jz];
+      r[1] = pp[-1 - jz];
+      r[2] = pm[jz];
+      r[3] = pm[-1 - jz];
+      r[4] = mp[jz];
+      r[5] = mp[-1 - jz];
+      r[6] = mm[jz];
+      r[7] = mm[-1 - jz];
+    };
+    auto bread = [&](int s, double (&b)[NE]) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) b[e] = wb[s * 512 + e * 64];
+    };
+    double r[2][8], b[2][NE], a[NE];
+    aread(ks, r[0]);
+    bread(ks, b[0]);
+#pragma unroll 1
+    for (int s = ks; s < BLK_STEPS; s += 2 * KS) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int st = s + u * KS, sn = st + KS < BLK_STEPS ? st + KS : ks;
+        if (u == 0 || st < BLK_STEPS) {
+          bread(sn, b[u ^ 1]);
+          aread(sn, r[u ^ 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          fold8<NE>(r[u], sx, sy, sz, a);
+#pragma unroll
+          for (int e = 0; e < NE; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[u][e], acc[e], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  }
+  if (Mb && ks == 0) {
+    const int cx = min(bx0 + X, nb - 1), cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1), nbp = nb + 6;
+    const long long ncp = (long long)nbp * nbp * nbp, cell = ((long long)(cx + 3) * nbp + cy + 3) * nbp + cz + 3;
+    const double* wp = W + OFF_P + e0 * (NPS * 64) + lane;
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int s = 0; s < NPS; ++s) {
+        const int bt = c_ft<P>.pt[e0 + e][4 * s + kq];
+        // (the stencil's accumulators carry the Walsh sum's 1/8)
+        const double v = Mb[(bt >= 0 ? bt : 0) * ncp + cell];
+        acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(bt >= 0 ? 0.125 * v : 0.0, wp[(e * NPS + s) * 64], acc[e], 0, 0, 0);
+      }
+  }
+  __syncthreads();
+  constexpr int NR = NX * 16, ES = NR * CS;
+  if (i < 8) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) lds[(ks * 8 + e0 + e) * ES + (16 * X + 4 * v + kq) * CS + i] = acc[e][v];
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < NR * 8; q += BLK_THREADS) {
+    double* x = lds + (q >> 3) * CS + (q & 7);
+    double y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      y[e] = x[e * ES];
+#pragma unroll
+      for (int k = 1; k < KS; ++k) y[e] += x[(k * 8 + e) * ES];
+    }
+    walsh8(y);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int q = threadIdx.x; q < 4 * NX * 256; q += BLK_THREADS) {
+    const int z = q & 15, y = (q >> 4) & 15, x = q >> 8;
+    const int ux = 4 * bx0 + x, uy = 4 * by0 + y, uz = 4 * bz0 + z;
+    if (ux >= n || uy >= n || uz >= n) continue;
+    const int qx = x & 3, qy = y & 3, qz = z & 3;
+    const int minus = ((qx < 2) << 2) | ((qy < 2) << 1) | (qz < 2);
+    const int t = ((qx == 0 || qx == 3) << 2) | ((qy == 0 || qy == 3) << 1) | (qz == 0 || qz == 3);
+    drho[((long long)ux * n + uy) * n + uz] = (TO)lds[minus * ES + (16 * (x >> 2) + 4 * (y >> 2) + (z >> 2)) * CS + t];
+  }
+}

@@ -613,6 +613,7 @@ __device__ __forceinline__ double p2p2_coef(int k, int grp, int q, int o) {
 
 #include "fmm_mfma.h"
 #include "fmm_fold.h"
+#include "fmm_fold_adj.h"
 
 // ---------------------------------------------------------------------------
 // L2L, eq. (L2L), for one level k: Lhat_k[T] += shift of Lhat_{k-1}[parent(T)]
@@ -1400,30 +1401,34 @@ hipError_t build_tables_t(fmm_plan* pl, bool bottom, bool m2l, hipStream_t s) {
 }
 
 // column tiles and B fragments of the folded M2L (x: 0 FP64, 1 FP32)
-hipError_t build_m2lf(fmm_plan* pl, int x, hipStream_t s) {
-  const int nt = m2lf_ntiles(pl->p);
+hipError_t build_m2lf(fmm_plan* pl, int x, bool adj, hipStream_t s) {
+  const int nt = adj ? (hterms(pl->p) + 15) / 16 : m2lf_ntiles(pl->p);
+  int2*& tiles = adj ? pl->m2lf_adj_tiles : pl->m2lf_tiles;
+  void*& w = adj ? pl->wm2lf_adj[x] : pl->wm2lf[x];
   std::vector<int2> t(nt + 8, int2{0, 0});  // a group may run past the last tile
   long long f = 0;
   for (int i = 0; i < nt; ++i) {
-    t[i] = int2{m2lf_steps(pl->p, pl->nmax, i), (int)f};
+    t[i] = int2{adj ? m2lfa_steps(pl->p, pl->nmax, i) : m2lf_steps(pl->p, pl->nmax, i), (int)f};
     f += t[i].x;
   }
   hipError_t e;
-  if (!pl->m2lf_tiles) {
-    if ((e = hipMalloc(&pl->m2lf_tiles, t.size() * sizeof(int2))) != hipSuccess) return e;
+  if (!tiles) {
+    if ((e = hipMalloc(&tiles, t.size() * sizeof(int2))) != hipSuccess) return e;
     pl->bytes += t.size() * sizeof(int2);
-    if ((e = hipMemcpy(pl->m2lf_tiles, t.data(), t.size() * sizeof(int2), hipMemcpyHostToDevice)) != hipSuccess) return e;
+    if ((e = hipMemcpy(tiles, t.data(), t.size() * sizeof(int2), hipMemcpyHostToDevice)) != hipSuccess) return e;
   }
   const long long cnt = f * 512;
   const size_t b = (size_t)cnt * (x ? sizeof(float) : sizeof(double));
-  if ((e = hipMalloc(&pl->wm2lf[x], b)) != hipSuccess) return e;
+  if ((e = hipMalloc(&w, b)) != hipSuccess) return e;
   pl->bytes += b;
+  auto* k32 = adj ? k_m2lf_adj_table<float> : k_m2lf_table<float>;
+  auto* k64 = adj ? k_m2lf_adj_table<double> : k_m2lf_table<double>;
   if (x)
-    hipLaunchKernelGGL(k_m2lf_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, pl->m2lf_tiles,
-                       (float*)pl->wm2lf[x], pl->p, pl->nmax, pl->ND, cnt);
+    hipLaunchKernelGGL(k32, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, tiles, (float*)w, pl->p, pl->nmax,
+                       pl->ND, cnt);
   else
-    hipLaunchKernelGGL(k_m2lf_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, pl->m2lf_tiles,
-                       (double*)pl->wm2lf[x], pl->p, pl->nmax, pl->ND, cnt);
+    hipLaunchKernelGGL(k64, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, tiles, (double*)w, pl->p, pl->nmax,
+                       pl->ND, cnt);
   return hipGetLastError();
 }
 
@@ -1440,7 +1445,7 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   const bool m2l64 = pl->s_conv[0].nseg > 0, m2llow = pl->s_conv[1].nseg > 0;
   const bool bot64 = pl->s_bot[0][0].nseg > 0, botlow = pl->s_bot[1][0].nseg > 0;
   for (int x = 0; x < 2; ++x)
-    if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, s)) != hipSuccess) return e;
+    if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, false, s)) != hipSuccess) return e;
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
     double* G = nullptr;
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
@@ -1560,26 +1565,114 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int P, typename CT, int MT, int NT, int NE, int KS>
+// Tile shapes of the folded M2L by variant (rows of octs, column tiles per
+// group, patterns per wave, K slices): OP 0 forward, 1 transpose, whose few
+// column tiles are dominated by the first.
+template <int OP, int V>
+struct M2lShape;
+template <> struct M2lShape<0, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
+template <> struct M2lShape<0, 1> { static constexpr int MT = 2, NT = 4, NE = 2, KS = 1; };
+template <> struct M2lShape<0, 2> { static constexpr int MT = 4, NT = 4, NE = 2, KS = 1; };
+template <> struct M2lShape<1, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
+template <> struct M2lShape<1, 1> { static constexpr int MT = 2, NT = 1, NE = 8, KS = 4; };
+template <> struct M2lShape<1, 2> { static constexpr int MT = 4, NT = 2, NE = 4, KS = 1; };
+
+// Grid of a launch over T tiles.  A block's K loop is cut where it would take
+// more than a quarter of what each compute unit has to do in the whole launch
+// (the last blocks to start would otherwise set its length), down to one
+// chunk of 27 steps.
+template <int P, int OP, int V>
+M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
+  using S = M2lShape<OP, V>;
+  const int nt = OP ? (hterms(P) + 15) / 16 : m2lf_ntiles(P);
+  M2lGrid g;
+  g.ng = (nt + S::NT - 1) / S::NT;
+  long long cost[kM2lGroups] = {}, longest[kM2lGroups] = {}, total = 0;
+  for (int t = 0; t < nt; ++t) {
+    const int st = OP ? m2lfa_steps(P, pl->nmax, t) : m2lf_steps(P, pl->nmax, t);
+    cost[t / S::NT] += st;
+    longest[t / S::NT] = std::max<long long>(longest[t / S::NT], st);
+    total += st;
+  }
+  const long long lim = std::max<long long>(27, total * T / pl->cus / 4);
+  for (int i = 0; i < g.ng; ++i) {
+    const long long chunks = (longest[i] + 26) / 27, want = (cost[i] + lim - 1) / lim;
+    g.parts[i] = (int)std::max<long long>(1, std::min<long long>({want, chunks, 32}));
+    g.shared += g.parts[i] > 1;
+    g.first[i] = (int)g.blocks;
+    g.blocks += (long long)T * g.parts[i];
+  }
+  return g;
+}
+// doubles of partial sums of such a launch
+template <int P, int OP, int V>
+void m2lf_need(const fmm_plan* pl, int T, size_t* part) {
+  using S = M2lShape<OP, V>;
+  const M2lGrid g = m2lf_grid<P, OP, V>(pl, T);
+  if (!g.shared) return;
+  *part = std::max(*part, (size_t)g.blocks * S::MT * 16 * 16 * S::NT * 8);
+}
+template <int P, typename CT, int OP, int V>
 hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s) {
-  StageScope sc(pl, ST_M2L, 1, s);
-  constexpr int G = (m2lf_ntiles(P) + NT - 1) / NT;
-  hipLaunchKernelGGL((k_m2lf<P, CT, MT, NT, NE, KS>), dim3((unsigned)G * st.blocks), dim3(512), 0, s, st.dev, st.nseg,
-                     st.blocks, pl->m2lf_tiles, (const typename Mf<CT>::H*)pl->wm2lf[x]);
+  using S = M2lShape<OP, V>;
+  using H = typename Mf<CT>::H;
+  const M2lGrid g = m2lf_grid<P, OP, V>(pl, st.blocks);
+  StageScope sc(pl, ST_M2L, g.shared ? 2 : 1, s);
+  hipLaunchKernelGGL((k_m2lf<P, CT, OP, S::MT, S::NT, S::NE, S::KS>), dim3((unsigned)g.blocks), dim3(512), 0, s, st.dev,
+                     st.nseg, st.blocks, OP ? pl->m2lf_adj_tiles : pl->m2lf_tiles,
+                     (const H*)(OP ? pl->wm2lf_adj[x] : pl->wm2lf[x]), g, pl->m2lf_part);
+  if (g.shared)
+    hipLaunchKernelGGL((k_m2lf_sum<P, H, OP, S::MT, S::NT, S::MT * S::KS / S::NE>),
+                       dim3((unsigned)(g.shared * st.blocks), S::MT * S::NT), dim3(256), 0, s, st.dev, st.nseg, st.blocks,
+                       g, pl->m2lf_part);
   return hipGetLastError();
 }
 
-// Folded M2L of site x (0 FP64, 1 FP32): the largest tile that still gives
-// every compute unit blocks.
+// Folded M2L of site x (0 FP64, 1 FP32).
 template <int P, typename CT>
 hipError_t launch_m2lf(fmm_plan* pl, int x, hipStream_t s) {
   if (!pl->s_m2lf[x][0].nseg) return hipSuccess;
-  int v = pl->s_m2lf[x][2].blocks >= pl->cus ? 2 : pl->s_m2lf[x][1].blocks >= pl->cus / 4 ? 1 : 0;
+  int v = m2lf_variant(pl, pl->s_m2lf[x][1].blocks, pl->s_m2lf[x][2].blocks);
   if (pl->tune.grp == 1 && v > 0) --v;
   const SegTable& st = pl->s_m2lf[x][v];
-  if (v == 2) return launch_m2lf_v<P, CT, 4, 4, 2, 1>(pl, x, st, s);
-  if (v == 1) return launch_m2lf_v<P, CT, 2, 4, 2, 1>(pl, x, st, s);
-  return launch_m2lf_v<P, CT, 1, 1, 4, 4>(pl, x, st, s);
+  if (v == 2) return launch_m2lf_v<P, CT, 0, 2>(pl, x, st, s);
+  if (v == 1) return launch_m2lf_v<P, CT, 0, 1>(pl, x, st, s);
+  return launch_m2lf_v<P, CT, 0, 0>(pl, x, st, s);
+}
+
+// Its transpose.
+template <int P, typename CT>
+hipError_t launch_m2lf_adj(fmm_plan* pl, const AdjWs& w, int x, hipStream_t s) {
+  const SegTable& st = w.m2ltf[x];
+  if (!st.nseg) return hipSuccess;
+  if (w.m2ltf_v[x] == 2) return launch_m2lf_v<P, CT, 1, 2>(pl, x, st, s);
+  if (w.m2ltf_v[x] == 1) return launch_m2lf_v<P, CT, 1, 1>(pl, x, st, s);
+  return launch_m2lf_v<P, CT, 1, 0>(pl, x, st, s);
+}
+
+// The workspace those launches share.  The transpose's launches have the
+// forward ones' tiles (one field).
+template <int P>
+hipError_t alloc_m2lf_part(fmm_plan* pl) {
+  size_t part = 0;
+  for (int x = 0; x < 2; ++x) {
+    const auto& st = pl->s_m2lf[x];
+    if (!st[0].nseg) continue;
+    const int v = m2lf_variant(pl, st[1].blocks, st[2].blocks);
+    // (a batch's autotuner may take the next smaller variant)
+    if (v == 2) m2lf_need<P, 0, 2>(pl, st[2].blocks, &part);
+    if (v >= 1) m2lf_need<P, 0, 1>(pl, st[1].blocks, &part);
+    if (v <= 1) m2lf_need<P, 0, 0>(pl, st[0].blocks, &part);
+    if (pl->batch) continue;
+    if (v == 2) m2lf_need<P, 1, 2>(pl, st[2].blocks, &part);
+    if (v == 1) m2lf_need<P, 1, 1>(pl, st[1].blocks, &part);
+    if (v == 0) m2lf_need<P, 1, 0>(pl, st[0].blocks, &part);
+  }
+  if (!part) return hipSuccess;
+  hipError_t e;
+  if ((e = hipMalloc(&pl->m2lf_part, part * sizeof(double))) != hipSuccess) return e;
+  pl->bytes += part * sizeof(double);
+  return hipSuccess;
 }
 
 // Finest blocks (k_block) of site x (0 FP64, 1 low precision).  Tiles of 4
@@ -1697,6 +1790,21 @@ hipError_t adjoint_bottom_tables(fmm_plan* pl, hipStream_t s) {
 hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
   hipError_t e;
   const int NL = pl->NL;
+  if (block_field(pl, pl->F)) {
+    for (int x = 0; x < 2; ++x)
+      if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, true, s)) != hipSuccess) return e;
+    double* G = nullptr;
+    const int cnt = blka_table(pl->p);
+    if ((e = hipMalloc(&pl->wblk_adj, cnt * sizeof(double))) != hipSuccess) return e;
+    pl->bytes += cnt * sizeof(double);
+    if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND);
+    hipLaunchKernelGGL(k_blk_adj_table, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, pl->wblk_adj, pl->p, pl->nmax);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    (void)hipFree(G);
+    return e;
+  }
   if (pl->dl == 2)
     hipLaunchKernelGGL(k_adj_coef2, dim3(blocks_for(72LL * NL * 32, 256)), dim3(256), 0, s, pl->adj_l2p,
                        pl->adj_l2p2, NL);
@@ -1725,8 +1833,62 @@ hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
   return adjoint_bottom_tables<bf16_tag>(pl, s);
 }
 
+// The backward pass of a field on the folded kernels (field 0).
+template <int P, typename CT, typename TI>
+hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TI* drho, hipStream_t s) {
+  const int n = pl->n, F = pl->F, nb = n >> 2;
+  const long long nblk = (long long)nb * nb * nb;
+  hipError_t e;
+  if (F >= 3) {
+    double* lc = F >= 4 ? w.lc[F - 1] : nullptr;
+    if (harmonic_float(pl, F - 1))
+      hipLaunchKernelGGL((k_blk_adj_l<P, TI, float>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
+                         pl->wblk_adj, (float*)w.lb[F], lc);
+    else
+      hipLaunchKernelGGL((k_blk_adj_l<P, TI, double>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
+                         pl->wblk_adj, (double*)w.lb[F], lc);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (int k = F - 1; k >= 3; --k) {
+      const int ns = 1 << (k - 1);
+      const unsigned g = blocks_for((long long)ns * ns * ns, L2LAdj<P>::PAR);
+      double* up = k > 3 ? w.lc[k - 1] : nullptr;
+      if (harmonic_float(pl, k - 1))
+        hipLaunchKernelGGL((k_l2lf_adj<P, float>), dim3(g), dim3(256), 0, s, w.lc[k], (float*)w.lb[k], up, ns,
+                           pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+      else
+        hipLaunchKernelGGL((k_l2lf_adj<P, double>), dim3(g), dim3(256), 0, s, w.lc[k], (double*)w.lb[k], up, ns,
+                           pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if ((e = launch_m2lf_adj<P, double>(pl, w, 0, s)) != hipSuccess) return e;
+    if constexpr (std::is_same<CT, float>::value)
+      if ((e = launch_m2lf_adj<P, float>(pl, w, 1, s)) != hipSuccess) return e;
+    for (int k = 3; k <= F - 1; ++k) {
+      const int np = 1 << (k - 1);
+      hipLaunchKernelGGL((k_m2mf_adj<P>), dim3(blocks_for((long long)np * np * np, M2MA_PAR)), dim3(256), 0, s,
+                         (const double*)pl->lev[k - 1].M, (double*)pl->lev[k].M, np, pl->m2mt_start, pl->m2mt_a,
+                         pl->m2mt_coef);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+  }
+  const double* mb = F >= 3 ? (const double*)pl->lev[F - 1].M : nullptr;
+  const long long rows = (long long)nb * ((nb + 3) / 4) * ((nb + 3) / 4);
+  const int tpa = (nb + 3) / 4, t2 = tpa * tpa;
+  if (rows >= 8LL * pl->cus)
+    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 4>), dim3(t2 * ((nb + 3) / 4)), dim3(BLK_THREADS), 0, s, dphi, dg,
+                       pl->wblk_adj, mb, drho, n, tpa);
+  else if (rows >= 4LL * pl->cus)
+    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 2>), dim3(t2 * ((nb + 1) / 2)), dim3(BLK_THREADS), 0, s, dphi, dg,
+                       pl->wblk_adj, mb, drho, n, tpa);
+  else
+    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 1>), dim3(t2 * nb), dim3(BLK_THREADS), 0, s, dphi, dg, pl->wblk_adj, mb,
+                       drho, n, tpa);
+  return hipGetLastError();
+}
+
 template <int P, typename CT, typename TI, typename TO>
 hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TO* drho, hipStream_t s) {
+  if (block_field(pl, pl->F)) return backward_fold<P, CT, TI>(pl, w, dphi, dg, drho, s);
   constexpr int NL = nterms(P);
   const int n = pl->n, F = pl->F, dl = pl->dl, nF = n >> dl;
   const double dx = pl->dx;
@@ -1816,7 +1978,8 @@ hipError_t Impl<P>::upload_constants() {
 
 template <int P>
 hipError_t Impl<P>::tables(fmm_plan* pl, hipStream_t s) {
-  return tables_all(pl, s);
+  const hipError_t e = alloc_m2lf_part<P>(pl);
+  return e == hipSuccess ? tables_all(pl, s) : e;
 }
 
 template <int P>

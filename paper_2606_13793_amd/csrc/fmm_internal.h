@@ -257,12 +257,28 @@ struct AdjWs {
   double* part = nullptr;    // split partial sums of the transposed M2L (null: unsplit)
   double* near = nullptr;    // FMM-2: the near-field transpose per finest cell, [16][(nF+6)^3][4]
   SegTable m2lt[2], m2pt, m2lt_red, p2pt;
+  // a field on the folded kernels (fmm_fold_adj.h) has these instead
+  void* lb[16] = {};     // level k: the M2L rows' cotangents, planes [8 (p+1)^2][(2^(k-1)+6)^3] in the M2L's type
+  double* lc[16] = {};   // level k < F: the complete locals' cotangents, [cell][hrow]
+  SegTable m2ltf[2];     // folded transposed M2L [FP64 | FP32]
+  int m2ltf_v[2] = {0, 0};  // and its tile (rows of octs: 1, 2 or 4)
 };
 // Static workspace of fmm_solve_backward_noalloc (bytes per device) and the
 // most segments its tables hold.
 constexpr size_t kNoallocBytes = (size_t)96 << 20;
 constexpr size_t kNoallocSegBytes = 4096;
 constexpr int kMaxAdjSegs = 12;
+
+// Column groups of a folded M2L launch: group g has the blocks from first[g],
+// parts[g] of them per tile, each summing a share of the K loop.
+constexpr int kM2lGroups = 48;
+struct M2lGrid {
+  int ng = 0;
+  int first[kM2lGroups] = {};
+  int parts[kM2lGroups] = {};
+  long long blocks = 0;
+  int shared = 0;  // groups with more than one part
+};
 
 // launch-shape choices picked by the batch autotuner
 struct Tuning {
@@ -341,6 +357,12 @@ struct fmm_plan {
   fmm::SegTable s_m2lf[2][3];       // folded M2L [FP64 | low][1, 2 or 4 rows of octs per tile]
   fmm::SegTable s_l2lf[16];         // folded L2L: complete locals of level k
   void* wm2lf[2] = {nullptr, nullptr};  // the folded M2L's B fragments, FP64 and FP32
+  void* wm2lf_adj[2] = {nullptr, nullptr};  // the same of its transpose
+  int2* m2lf_adj_tiles = nullptr;
+  // partial sums of folded M2L launches that share their K loops, sized for
+  // every launch of the plan
+  double* m2lf_part = nullptr;
+  double* wblk_adj = nullptr;       // table of the block kernel's transposes
   int2* m2lf_tiles = nullptr;       // (K steps, first fragment) of each column tile
   void* wblk[2] = {nullptr, nullptr};  // the block kernel's B table, FP64 and FP32
   fmm::SegTable s_red[2];           // reductions of split forward M2L partial sums
@@ -434,6 +456,11 @@ inline int m2l_low_from(const fmm_plan* pl) {
 // whether a folded field's harmonic multipoles of level k are FP32 (the M2L
 // into level k + 1 runs in FP32)
 inline bool harmonic_float(const fmm_plan* pl, int k) { return pl->precision == 1 && k + 1 >= m2l_low_from(pl); }
+// Tile of a folded M2L launch (0, 1, 2: 1, 2 or 4 rows of octs), from its
+// block counts: the largest that still gives every compute unit blocks.
+inline int m2lf_variant(const fmm_plan* pl, long long blocks2, long long blocks4) {
+  return blocks4 >= pl->cus ? 2 : blocks2 >= pl->cus / 4 ? 1 : 0;
+}
 // whether the multipoles of level k (of a field with finest level F) get a
 // copy in the compute type: the low-precision bottom reads level F, the
 // low-precision M2L into level k + 1 reads level k

@@ -53,3 +53,36 @@ def test_finest_blocks(F, orc, precision, n, p, nmax, tile):
     e = rel(phi, phi_o), rel(g, g_o)
     print(f"  phi {e[0]:.2e} g {e[1]:.2e}", flush=True)
     assert e[0] <= BARS[precision][0] and e[1] <= BARS[precision][1], e
+
+
+# the transposes: the coarsest grids (no M2L; one M2L level), one and several
+# L2L levels, truncation, both types of a mixed plan, tiles of every height
+@pytest.mark.parametrize("precision,n,p,nmax", [
+    ("fp64", 8, 4, None), ("fp64", 16, 8, 3), ("fp64", 32, 7, None), ("fp64", 64, 3, 0),
+    ("fp32", 16, 5, None), ("fp32", 64, 4, 2), ("fp64", 128, 2, None),
+])
+def test_folded_backward(F, orc, precision, n, p, nmax):
+    import torch
+    print(f"case backward {precision} n={n} p={p} nmax={nmax}", flush=True)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n + p)
+    dphi = torch.randn((n, n, n), dtype=dt, device="cuda", generator=gen)
+    dg = torch.randn((3, n, n, n), dtype=dt, device="cuda", generator=gen)
+    plan = F.Plan(n, p, precision, nmax=nmax, coarse_fp64_levels=3)
+    drho = plan.backward(dphi, dg)
+    dphi_only = plan.backward(dphi)
+    if n <= 32:
+        want = orc.adjoint(dphi.double().cpu().numpy(), dg.double().cpu().numpy(), p, nmax=nmax)
+        e = rel(drho.double().cpu().numpy(), want)
+        print(f"  {e:.2e}", flush=True)
+        assert e <= BARS[precision][1], e
+    # <A rho, y> = <rho, A^T y> against the forward solve, with and without dg
+    rho = torch.as_tensor(fi.plummer_density(n, fi.multi_plummer_params(12, 77 + n))).to("cuda", dt)
+    phi, g = plan.solve(rho)
+    torch.cuda.synchronize()
+    for lhs, grad, scale in (((phi.double() * dphi).sum() + (g.double() * dg).sum(), drho,
+                              phi.double().norm() * dphi.double().norm() + g.double().norm() * dg.double().norm()),
+                             ((phi.double() * dphi).sum(), dphi_only, phi.double().norm() * dphi.double().norm())):
+        d = float((lhs - (rho.double() * grad.double()).sum()).abs() / scale)
+        print(f"  identity {d:.2e}", flush=True)
+        assert d <= (1e-13 if precision == "fp64" else 1e-5), d
