@@ -99,11 +99,12 @@ void release_adj(fmm::AdjWs& w) {
     if (a) (void)hipFree(a);
   if (w.part) (void)hipFree(w.part);
   if (w.near) (void)hipFree(w.near);
+  if (w.yb) (void)hipFree(w.yb);
   for (auto a : w.lb)
     if (a) (void)hipFree(a);
   for (auto a : w.lc)
     if (a) (void)hipFree(a);
-  for (fmm::SegTable* st : {&w.m2lt[0], &w.m2lt[1], &w.m2pt, &w.m2lt_red, &w.p2pt, &w.m2ltf[0], &w.m2ltf[1]})
+  for (fmm::SegTable* st : {&w.m2lt[0], &w.m2lt[1], &w.m2pt, &w.m2lt_red, &w.p2pt, &w.m2ltf[0], &w.m2ltf[1], &w.m2ptf})
     if (st->dev) (void)hipFree(st->dev);
   w = fmm::AdjWs{};
 }
@@ -129,15 +130,17 @@ void release(fmm_plan* pl) {
       if (lv.Mh) (void)hipFree(lv.Mh);
     }
   for (auto& f : pl->fld)
+  {
     if (f.rho_copy) (void)hipFree(f.rho_copy);
+    if (f.m2p) (void)hipFree(f.m2p);
+  }
   for (auto w : pl->wblk)
     if (w) (void)hipFree(w);
-  for (auto w : pl->wm2lf)
-    if (w) (void)hipFree(w);
-  for (auto w : pl->wm2lf_adj)
-    if (w) (void)hipFree(w);
-  if (pl->m2lf_tiles) (void)hipFree(pl->m2lf_tiles);
-  if (pl->m2lf_adj_tiles) (void)hipFree(pl->m2lf_adj_tiles);
+  for (auto& ws : pl->fold_w)
+    for (auto w : ws)
+      if (w) (void)hipFree(w);
+  for (auto t : pl->fold_tiles)
+    if (t) (void)hipFree(t);
   if (pl->wblk_adj) (void)hipFree(pl->wblk_adj);
   if (pl->m2lf_part) (void)hipFree(pl->m2lf_part);
   auto free_st = [](fmm::SegTable& st) {
@@ -154,6 +157,8 @@ void release(fmm_plan* pl) {
   for (auto& a : pl->s_blk)
     for (auto& st : a) free_st(st);
   for (auto& a : pl->s_m2lf)
+    for (auto& st : a) free_st(st);
+  for (auto& a : pl->s_m2pf)
     for (auto& st : a) free_st(st);
   for (auto& st : pl->s_l2lf) free_st(st);
   for (auto& st : pl->s_red) free_st(st);
@@ -380,7 +385,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], l2lf[16];
+  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -392,7 +397,11 @@ int build_schedule(fmm_plan* pl) {
     // gets its typed copy alone
     sg.b = pl->dl == 1 && bottom_low(pl, F) ? nullptr : (double*)fd.lev[F].M;
     sg.t = fd.lev[F].Mt;
-    if (!block_field(pl, F)) p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
+    if (pl->dl == 2) {
+      sg.u = fd.lev[F].Mh;
+      sg.split = harmonic_float(pl, F, F);
+    }
+    if (!block_field(pl, F) || pl->dl == 2) p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
     // FMM-1: the multipoles of level F - 1 straight from the 4^3 unigrid
     // cells of each cell (as FMM-2's P2M), which reads the density instead
     // of the 8x larger level-F grid; M2M then starts at level F - 1
@@ -404,7 +413,7 @@ int build_schedule(fmm_plan* pl) {
       s2.b = (double*)fd.lev[F - 1].M;
       s2.t = fd.lev[F - 1].Mt;
       s2.u = fd.lev[F - 1].Mh;
-      s2.split = harmonic_float(pl, F - 1);
+      s2.split = harmonic_float(pl, F, F - 1);
       const long long nc = 1LL << (3 * (F - 1));
       p2m2.add(s2, cdiv(nc, 256));
       top = F - 1;
@@ -417,7 +426,7 @@ int build_schedule(fmm_plan* pl) {
       m.b = (double*)fd.lev[k - 1].M;
       m.t = fd.lev[k - 1].Mt;
       m.u = fd.lev[k - 1].Mh;
-      m.split = harmonic_float(pl, k - 1);
+      m.split = harmonic_float(pl, F, k - 1);
       // parents per block of k_m2m: 16 up to 56 terms, else 8
       m2m[k].add(m, cdiv(1LL << (3 * (k - 1)), pl->NM <= 56 ? 16 : 8));
     }
@@ -429,15 +438,27 @@ int build_schedule(fmm_plan* pl) {
         c.tpa = (int)cdiv(no, 4);
         c.field = f;
         c.a = (const double*)fd.lev[k - 1].Mh;
-        const bool low = harmonic_float(pl, k - 1);
-        c.b = low && k == F ? nullptr : (double*)fd.lev[k].Lw;
-        c.u = low && k == F ? fd.lev[k].Lw : nullptr;
+        const bool low = harmonic_float(pl, F, k - 1), typed = low && k == F && pl->dl == 1;
+        c.b = typed ? nullptr : (double*)fd.lev[k].Lw;
+        c.u = typed ? fd.lev[k].Lw : nullptr;
         for (int v = 0; v < 3; ++v) {
           c.tz = (int)cdiv(no, 1 << v);
           m2lf[low ? 1 : 0][v].add(c, (long long)c.tpa * c.tpa * c.tz);
         }
       }
-      for (int k = 3; k <= F - 1; ++k) {
+      if (pl->dl == 2) {
+        Seg c{};
+        c.n = nF;
+        c.tpa = (int)cdiv(nF / 2, 4);
+        c.field = f;
+        c.a = (const double*)fd.lev[F].Mh;
+        c.u = fd.m2p;
+        for (int v = 0; v < 3; ++v) {
+          c.tz = (int)cdiv(nF / 2, 1 << v);
+          m2pf[bottom_low(pl, F) ? 1 : 0][v].add(c, (long long)c.tpa * c.tpa * c.tz);
+        }
+      }
+      for (int k = 3; k <= block_level(pl, F); ++k) {
         Seg l{};
         l.n = 1 << (k - 1);
         l.field = f;
@@ -474,9 +495,11 @@ int build_schedule(fmm_plan* pl) {
       b.n = fd.n;
       b.tpa = (int)cdiv(nb, 4);
       b.field = f;
+      const int lb = block_level(pl, F);
       b.t = fd.rho_copy;
-      b.u = F >= 3 ? fd.lev[F].Lw : nullptr;
-      b.d = F >= 4 ? fd.lev[F - 1].Lc : nullptr;
+      b.u = F >= 3 && pl->dl == 1 ? fd.lev[F].Lw : nullptr;
+      b.d = lb >= 3 ? fd.lev[lb].Lc : nullptr;
+      b.c = (const double*)fd.m2p;
       for (int v = 0; v < 3; ++v) {
         b.tz = (int)cdiv(nb, 1 << v);
         blk[x][v].add(b, (long long)b.tpa * b.tpa * b.tz);
@@ -586,7 +609,8 @@ int build_schedule(fmm_plan* pl) {
     for (int z = 0; z < 2; ++z)
       if ((rc = upload_segs(pl, pl->s_bot[x][z], bot[x][z]))) return rc;
     for (int v = 0; v < 3; ++v)
-      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v])) || (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])))
+      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v])) || (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])) ||
+          (rc = upload_segs(pl, pl->s_m2pf[x][v], m2pf[x][v])))
         return rc;
   }
   return FMM_OK;
@@ -652,24 +676,29 @@ struct AdjSegs {
 // transposed M2L over workspace w (the finest level first), whose results go
 // to the plan's multipole grids as planes of harmonic terms.
 struct FoldAdjLayout {
-  size_t lb[16] = {}, lc[16] = {};
+  size_t lb[16] = {}, lc[16] = {}, yb = 0;
 };
 FoldAdjLayout fold_adj_layout(const fmm_plan* pl) {
   FoldAdjLayout l;
   const size_t ht = (size_t)(pl->p + 1) * (pl->p + 1), hr = (ht + 3) / 4 * 4;
   for (int k = 3; k <= pl->F; ++k) {
     const size_t np = ((size_t)1 << (k - 1)) + 6;
-    l.lb[k] = 8 * ht * np * np * np * (fmm::harmonic_float(pl, k - 1) ? sizeof(float) : sizeof(double));
-    if (k < pl->F) l.lc[k] = ((size_t)1 << (3 * k)) * hr * sizeof(double);
+    l.lb[k] = 8 * ht * np * np * np * (fmm::harmonic_float(pl, pl->F, k - 1) ? sizeof(float) : sizeof(double));
+    if (k <= fmm::block_level(pl, pl->F)) l.lc[k] = ((size_t)1 << (3 * k)) * hr * sizeof(double);
+  }
+  if (pl->dl == 2) {
+    const size_t np = ((size_t)1 << pl->F) + 6;
+    l.yb = 256 * np * np * np * (fmm::bottom_low(pl, pl->F) ? sizeof(float) : sizeof(double));
   }
   return l;
 }
-void fold_adj_segments(const fmm_plan* pl, const fmm::AdjWs& w, SegArr (&out)[2], int (&variant)[2]) {
-  SegArr s[2][3];
+// out[2]: FMM-2's transposed M2P
+void fold_adj_segments(const fmm_plan* pl, const fmm::AdjWs& w, SegArr (&out)[3], int (&variant)[3]) {
+  SegArr s[3][3];
   for (int k = pl->F; k >= 3; --k) {
     fmm::Seg c{};
     c.n = 1 << (k - 1);
-    const int no = c.n >> 1, x = fmm::harmonic_float(pl, k - 1) ? 1 : 0;
+    const int no = c.n >> 1, x = fmm::harmonic_float(pl, pl->F, k - 1) ? 1 : 0;
     c.tpa = (int)cdiv(no, 4);
     c.a = (const double*)w.lb[k];
     c.b = (double*)pl->lev[k - 1].M;
@@ -678,7 +707,18 @@ void fold_adj_segments(const fmm_plan* pl, const fmm::AdjWs& w, SegArr (&out)[2]
       s[x][v].add(c, (long long)c.tpa * c.tpa * c.tz);
     }
   }
-  for (int x = 0; x < 2; ++x) {
+  if (pl->dl == 2) {
+    fmm::Seg c{};
+    c.n = 1 << pl->F;
+    c.tpa = (int)cdiv(c.n / 2, 4);
+    c.a = (const double*)w.yb;
+    c.b = (double*)pl->lev[pl->F].M;
+    for (int v = 0; v < 3; ++v) {
+      c.tz = (int)cdiv(c.n / 2, 1 << v);
+      s[2][v].add(c, (long long)c.tpa * c.tpa * c.tz);
+    }
+  }
+  for (int x = 0; x < 3; ++x) {
     variant[x] = fmm::m2lf_variant(pl, s[x][1].blocks, s[x][2].blocks);
     out[x] = s[x][variant[x]];
   }
@@ -956,7 +996,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
       lv.ncell = 1LL << (3 * k);
       lv.ncellp = (long long)lv.nkp * lv.nkp * lv.nkp;
       const size_t mb = (size_t)pl->NC * lv.ncellp * 4 * sizeof(double);
-      if (k < fd.F || !fmm::block_field(pl, fd.F)) {  // folded fields form no finest multipoles
+      if (k <= fmm::block_level(pl, fd.F) || !fmm::block_field(pl, fd.F)) {  // (folded FMM-1 forms no finest multipoles)
         if (dev_alloc(pl, &lv.M, mb)) return bail();
         if (hipMemset(lv.M, 0, mb) != hipSuccess) {
           fail(FMM_ERR_DEVICE, "hipMemset failed");
@@ -993,7 +1033,9 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     const int F = fd.F;
     const bool low = fmm::bottom_low(pl, F);
     const size_t hr = (size_t)((p + 1) * (p + 1) + 3) / 4 * 4;
-    if (!low) {
+    if (pl->dl == 2 && dev_alloc(pl, &fd.m2p, 4 * (size_t)fd.n * fd.n * fd.n * (low ? sizeof(float) : sizeof(double))))
+      return bail();
+    if (!low && pl->dl == 1) {
       const size_t b = (size_t)fd.n * fd.n * fd.n * (pl->precision == 0 ? sizeof(double) : sizeof(float));
       if (dev_alloc(pl, &fd.rho_copy, b)) return bail();
       if (hipMemset(fd.rho_copy, 0, b) != hipSuccess) {
@@ -1009,9 +1051,10 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     };
     for (int k = 2; k <= F; ++k) {
       fmm::Level& lv = fd.lev[k];
-      if (k >= 3 && !zalloc(&lv.Lw, (size_t)lv.ncell * hr * (k == F && low ? sizeof(float) : sizeof(double)))) return bail();
-      if (k >= 3 && k < F && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
-      if (k < F && !zalloc(&lv.Mh, (size_t)lv.ncellp * hr * (fmm::harmonic_float(pl, k) ? sizeof(float) : sizeof(double))))
+      if (k >= 3 && !zalloc(&lv.Lw, (size_t)lv.ncell * hr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
+      const bool upto = k <= fmm::block_level(pl, F);
+      if (k >= 3 && upto && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
+      if (upto && !zalloc(&lv.Mh, (size_t)lv.ncellp * hr * (fmm::harmonic_float(pl, F, k) ? sizeof(float) : sizeof(double))))
         return bail();
     }
   }
@@ -1040,7 +1083,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     if (!folded && (dev_alloc(pl, (void**)&pl->adj_l2p, ng * pl->NL * 32 * sizeof(double)) ||
         dev_alloc(pl, (void**)&pl->adj_l2p2, ng * 8 * pl->NL * 32 * sizeof(double))))
       return bail();
-    if (pl->dl == 2) {
+    if (pl->dl == 2 && !folded) {
       const std::vector<int> lp = build_dlists_p2p();
       if (dev_alloc(pl, (void**)&pl->dlists_p2p, lp.size() * sizeof(int))) return bail();
       if ((e = hipMemcpy(pl->dlists_p2p, lp.data(), lp.size() * sizeof(int), hipMemcpyHostToDevice)) != hipSuccess) {
@@ -1446,9 +1489,16 @@ static int ensure_adjoint(fmm_plan* pl) {
       if ((rc = zalloc((double**)&w.lb[k], fl.lb[k]))) return bail(rc);
       if (fl.lc[k] && (rc = zalloc(&w.lc[k], fl.lc[k]))) return bail(rc);
     }
-    SegArr sa[2];
-    fold_adj_segments(pl, w, sa, w.m2ltf_v);
-    if ((rc = upload_arr(pl, w.m2ltf[0], sa[0])) || (rc = upload_arr(pl, w.m2ltf[1], sa[1]))) return bail(rc);
+    if (fl.yb && (rc = zalloc((double**)&w.yb, fl.yb))) return bail(rc);
+    SegArr sa[3];
+    int v[3];
+    fold_adj_segments(pl, w, sa, v);
+    if ((rc = upload_arr(pl, w.m2ltf[0], sa[0])) || (rc = upload_arr(pl, w.m2ltf[1], sa[1])) ||
+        (rc = upload_arr(pl, w.m2ptf, sa[2])))
+      return bail(rc);
+    w.m2ltf_v[0] = v[0];
+    w.m2ltf_v[1] = v[1];
+    w.m2ptf_v = v[2];
     pl->adj = w;
     pl->adj_ready = 1;
     return FMM_OK;
@@ -1539,15 +1589,22 @@ int fmm_solve_backward_noalloc(fmm_plan* plan, const void* dphi, const void* dg,
       if (fl.lc[k]) w.lc[k] = (double*)(b + fat);
       fat += al(fl.lc[k]);
     }
+    if (fl.yb) w.yb = b + fat;
+    fat += al(fl.yb);
     if (fat > fmm::kNoallocBytes) return fail(FMM_ERR_DEVICE, "internal: folded backward workspace of %zu bytes", fat);
-    SegArr sa[2];
-    fold_adj_segments(plan, w, sa, w.m2ltf_v);
+    SegArr sa[3];
+    int v[3];
+    fold_adj_segments(plan, w, sa, v);
+    w.m2ltf_v[0] = v[0];
+    w.m2ltf_v[1] = v[1];
+    w.m2ptf_v = v[2];
     fmm::Seg* sd = (fmm::Seg*)b;
-    for (int x = 0; x < 2 && e == hipSuccess; ++x) {
+    for (int x = 0; x < 3 && e == hipSuccess; ++x) {
       if (!sa[x].n) continue;
-      w.m2ltf[x].dev = sd;
-      w.m2ltf[x].nseg = sa[x].n;
-      w.m2ltf[x].blocks = (int)sa[x].blocks;
+      fmm::SegTable& st = x < 2 ? w.m2ltf[x] : w.m2ptf;
+      st.dev = sd;
+      st.nseg = sa[x].n;
+      st.blocks = (int)sa[x].blocks;
       e = fmm::noalloc_put_segs(sa[x].v, sa[x].n, sd, s);
       sd += sa[x].n;
     }
@@ -1703,7 +1760,7 @@ static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
     return e;
   };
   std::vector<double> own, par;
-  const bool finest = level == plan->F;
+  const bool finest = level > fmm::block_level(plan, plan->F);
   hipError_t e = hipDeviceSynchronize();
   if (e == hipSuccess)
     e = fetch(finest ? lv.Lw : lv.Lc, (size_t)lv.ncell * hr, finest && fmm::bottom_low(plan, plan->F), &own);
@@ -1758,7 +1815,7 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   const int nch = (nt + 3) / 4;
   if (!out || count < (size_t)lv.ncell * nt) return fail(FMM_ERR_INVALID_ARG, "out must hold %lld doubles", lv.ncell * nt);
   const int nk = lv.nk;
-  if (which == 0 && level == plan->F && fmm::block_field(plan, plan->F)) {
+  if (which == 0 && level == plan->F && plan->dl == 1 && fmm::block_field(plan, plan->F)) {
     // the block kernel forms no level-F multipoles: derive them from the
     // copy of the density it left (P2M: sum_q rho_q (s_q / 4)^a / a!)
     const int n = plan->n;

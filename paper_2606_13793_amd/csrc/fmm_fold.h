@@ -26,8 +26,8 @@ __host__ __device__ __forceinline__ double chi(int e, int minus) {
 }
 
 // ---------------------------------------------------------------------------
-// Finest block kernel.  A block is 4^3 unigrid cells: an oct of level F
-// (FMM-1).  Its sources are the 12^3 unigrid cells of the 6^3 level-F cells
+// Finest block kernel.  A block is 4^3 unigrid cells: an oct of level F for
+// FMM-1, a level-F cell for FMM-2.  FMM-1: its sources are the 12^3 unigrid cells of the 6^3 level-F cells
 // around: M2P of a level-F source is a linear map of its 8 densities (P2M,
 // then M2P: 8 numbers fix all its multipoles), so P2M, M2P (Sec. 4) and the
 // near field, eq. (direct), are one matrix of 12^3 sources by 64 targets x
@@ -35,8 +35,11 @@ __host__ __device__ __forceinline__ double chi(int e, int minus) {
 // is 8 products of K = 216 by 32 columns.  L2P adds K rows to them:
 //  - the own locals (M2L part of the 8 level-F cells), Walsh-folded over the
 //    children, K = (p + 1)^2 harmonic terms, the same table for every e;
-//  - the level F-1 local of the block's own cell (L2L then L2P as one exact
-//    evaluation): only terms of parity e enter pattern e.
+//  - the complete local of the block's own cell (level F-1 for FMM-1: L2L then
+//    L2P as one exact evaluation): only terms of parity e enter pattern e.
+// FMM-2: the 12^3 cells around are the near field, eq. (direct), the own local
+// is the level-F one, and M2P (k_m2lf, FO_M2P) comes from a buffer in the
+// epilogue.
 // ---------------------------------------------------------------------------
 constexpr int BLK_K = 216, BLK_STEPS = BLK_K / 4;
 constexpr int BLK_THREADS = 512;
@@ -80,7 +83,7 @@ constexpr __host__ __device__ int blk_table(int P) { return blk_off_p(P) + 8 * b
 // The unfolded stencil G[t][v][o], t in the positive octant (bits: 1/2 or 3/2
 // from the centre), v = (12 v0 + v1) 12 + v2 the source, in the units of the
 // bottom accumulators (phi = dx^2/2 acc, g = -dx/4 acc).
-__global__ void k_blk_green(const double* __restrict__ Dtab, double* __restrict__ G, int NMX, int ND) {
+__global__ void k_blk_green(const double* __restrict__ Dtab, double* __restrict__ G, int NMX, int ND, int dl) {
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= 8 * 1728 * 4) return;
   const int o = id & 3, v = (id >> 2) % 1728, t = (id >> 2) / 1728;
@@ -93,7 +96,9 @@ __global__ void k_blk_green(const double* __restrict__ Dtab, double* __restrict_
     near = near && d[a] >= -1 && d[a] <= 1;
   }
   double x = 0.0;
-  if (near) {
+  if (dl == 2) {
+    x = p2p2_delta_coef(6 + tb[0] - vv[0], 6 + tb[1] - vv[1], 6 + tb[2] - vv[2], o);
+  } else if (near) {
     const int dt = (9 + tb[0] - vv[0]) * 49 + (9 + tb[1] - vv[1]) * 7 + (9 + tb[2] - vv[2]);
     x = o == 0 ? 2.0 * c_p2p_phi[dt] : -4.0 * c_p2p_g[(o - 1) * 343 + dt];
   } else {
@@ -110,11 +115,19 @@ __global__ void k_blk_green(const double* __restrict__ Dtab, double* __restrict_
   G[id] = x;
 }
 
+// L2P from the complete local of the block's cell to target t of the positive
+// octant, in the units of the accumulators.
+__device__ __forceinline__ double blk_l2p(int bt, int t, int o, int dl) {
+  if (dl == 1) return l2p_parent_coef(bt, 7, t, o);
+  const double w[3] = {(t & 4) ? 0.375 : 0.125, (t & 2) ? 0.375 : 0.125, (t & 1) ? 0.375 : 0.125};
+  return l2p_w_coef(bt, w, 1.0, 1.0, o);
+}
+
 // The block kernel's B table in the compute type (layout above); lane = j +
 // 16 kq, column 16 tile + j = (t, o).  The 1/8 of the inverse Walsh sum is
 // left to the epilogue.
 template <typename H>
-__global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int P) {
+__global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int P, int dl) {
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= blk_table(P)) return;
   const int lane = id & 63, tile = (id >> 6) & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
@@ -134,7 +147,7 @@ __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int
   } else {
     const int s = (id - blk_off_p(P)) >> 7, np = blk_psteps(P), e = s / np;
     const int b = blk_pterm(P, e, 4 * (s % np) + kq);
-    if (b >= 0) x = 8.0 * h_reduce(b, [&](int bt) { return l2p_parent_coef(bt, 7, t, o); });
+    if (b >= 0) x = 8.0 * h_reduce(b, [&](int bt) { return blk_l2p(bt, t, o, dl); });
   }
   W[id] = static_cast<H>(x);
 }
@@ -225,14 +238,15 @@ __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[
 // Segments: n = unigrid cells per axis, tpa = tiles along y and z, tz = tiles
 // along x, field, t = copy of the density to leave in the plan (or null),
 // u = own locals [block][8][hrow] in the compute type (or null: F = 2),
-// d = level F-1 locals [block][hrow] (or null: F < 4).
+// d = complete locals of the blocks' cells [block][hrow] (or null), c = FMM-2:
+// M2P, [block][4][4^3] in the compute type.
 // Tile: NX x 4 x 4 blocks; wave w takes row tile X = w % NX (the 4 x 4 blocks
 // of plane X) and the NX patterns from NX (w / NX).
 // What bounds it: the matrix cores (54 + 13 + 3 K steps of 16 products per row
 // tile at p = 6).  A lane reads the 8 mirror images of its operand from the LDS
 // tile and folds them itself (12 adds for 8 products); B is read through the
 // caches, each fragment once per wave, the NX waves of a plane sharing it.
-template <int P, typename CT, typename TI, typename TO, int NX>
+template <int P, typename CT, typename TI, typename TO, int NX, int DL>
 __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>::H) > 80000 ? 2 : 4)) void k_block(const Seg* __restrict__ segs, int nseg, IoArg io,
                                                           const typename Mf<CT>::H* __restrict__ W,
                                                           unsigned int* __restrict__ stamp_cnt,
@@ -413,8 +427,9 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
     for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
   }
   __syncthreads();
-  // phi = dx^2/16 sum, g_d = -dx/32 tau_d sum (with the Walsh sum's 1/8)
-  const double dx = 1.0 / n;
+  // phi = sphi acc, g_d = sgr tau_d acc, with the Walsh sum's 1/8 in acc
+  const H* const m2p = reinterpret_cast<const H*>(sg.c);
+  const double dx = 1.0 / n, sphi = (DL == 1 ? 0.5 : 0.25) * dx * dx, sgr = (DL == 1 ? -0.25 : -0.0625) * dx;
   const long long N = (long long)n * n * n;
   const int ncomp = g ? 4 : 1;
 #pragma unroll 1
@@ -427,12 +442,15 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
     const int minus = ((qx < 2) << 2) | ((qy < 2) << 1) | (qz < 2);
     const int t = ((qx == 0 || qx == 3) << 2) | ((qy == 0 || qy == 3) << 1) | (qz == 0 || qz == 3);
     const int row = 16 * (x >> 2) + 4 * (y >> 2) + (z >> 2);
-    const double val = (double)lds[minus * ES + row * 33 + 4 * t + o];
+    double val = 0.125 * (double)lds[minus * ES + row * 33 + 4 * t + o];
+    if (o && (minus >> (3 - o)) & 1) val = -val;
+    if constexpr (DL == 2)
+      val += (double)m2p[((((long long)(ux >> 2) * nb + (uy >> 2)) * nb + (uz >> 2)) * 4 + o) * 64 + (qx * 4 + qy) * 4 + qz];
     const long long u = ((long long)ux * n + uy) * n + uz;
     if (o == 0)
-      phi[u] = (TO)(dx * dx * 0.0625 * val);
+      phi[u] = (TO)(sphi * val);
     else
-      g[(o - 1) * N + u] = (TO)(((minus >> (3 - o)) & 1 ? 1.0 : -1.0) * 0.03125 * dx * val);
+      g[(o - 1) * N + u] = (TO)(sgr * val);
   }
   if (stamp_cnt) {
     // the field's last block records when the field is complete
@@ -460,12 +478,16 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
 // degree), K by |a| (K index 27 a + source), so a tile of 16 columns needs a
 // prefix of K: ceil(27 (p - |b| + 1)^2 / 4) steps.
 // ---------------------------------------------------------------------------
-constexpr __host__ __device__ int m2lf_ntiles(int P) { return (8 * hterms(P) + 15) / 16; }
-constexpr __host__ __device__ int m2lf_steps(int P, int nmax, int t) {
-  const int m = h_degree(16 * t / 8);
-  const int q = P - m < nmax ? P - m : nmax;
-  return (27 * hterms(q) + 3) / 4;
+constexpr __host__ __device__ int fold_ntiles(int op, int P) {
+  return op == FO_M2L ? (8 * hterms(P) + 15) / 16 : op == FO_M2P ? 16 : (hterms(P) + 15) / 16;
 }
+constexpr __host__ __device__ int fold_steps(int op, int P, int nmax, int t) {
+  if (op == FO_M2P) return (27 * hterms(nmax) + 3) / 4;
+  const int m = h_degree(op == FO_M2L ? 16 * t / 8 : 16 * t);
+  if (op == FO_M2L) return (27 * hterms(P - m < nmax ? P - m : nmax) + 3) / 4;
+  return m > nmax ? 0 : op == FO_M2LT ? 54 * hterms(P - m) : 27 * 64;
+}
+
 // B fragments in the compute type, [fragment (tile, step)][8 patterns][64];
 // tiles[t] = (steps, first fragment).
 template <typename H>
@@ -505,12 +527,17 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
 // cotangents of the Lw rows of the 27 x 8 cells P around (K index 27 column +
 // P, columns sorted by |b|; an image's sign is chi_kappa), columns the terms a
 // of one J, the results M_bar(J = sigma, a) = sigma^a sum_e chi_e(sigma) OUT(e; a).
+// OP 2 is FMM-2's M2P (Sec. 4): rows are the octs of level F, K as in M2L with
+// every term, columns (o, t) the outputs at the 4^3 unigrid cells t of the
+// positive octant's cell.  OP 3 is its transpose: K index 27 (32 kappa + 4 t + o)
+// + P over the cotangents of the cells P, folded about each P's own centre.
 //
 // Segments: n = source grid cells per axis, tpa = tiles along y and z, tz =
 // tiles along x; OP 0: a = harmonic multipoles of the source grid in the compute
 // type, [term][(n + 6)^3] (terms padded to a multiple of 4), u = result in the
-// compute type or b = result in FP64, [n^3][8][hrow]; OP 1: a = cotangent planes
-// [column][(n + 6)^3] in the compute type, b = result, planes [term][(n + 6)^3].
+// compute type or b = result in FP64, [n^3][8][hrow]; OP 2: the same, u =
+// [n^3][4][4^3]; OP 1, 3: a = cotangent planes [K term][(n + 6)^3] in the compute
+// type, b = result, planes [term][(n + 6)^3].
 // Tile: MT x 4 x 4 octs.  8 waves: 8 / NE groups of NE patterns, KS slices of
 // the K steps, MT / NR groups of NR row tiles (a row tile: the 4 x 4 octs of a
 // plane).  A block sums NT column tiles over all 8 patterns, so the inverse
@@ -523,12 +550,18 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
 // adds for two patterns), which NT products amortise; each B fragment is read
 // from L2 once per wave for NR row tiles.
 //
+// what column col stands for, -1 past the last
+template <int P, int OP>
+__device__ __forceinline__ int fold_colmap(int col) {
+  if constexpr (OP == 0) return col < 8 * hterms(P) ? c_ft<P>.col[col] : -1;
+  return col < (OP == 2 ? 256 : hterms(P)) ? col : -1;
+}
 // result q of a group of row tiles: consecutive threads take the columns of a
 // row, or for planes the rows
 template <int OP, int NT>
-__device__ __forceinline__ int m2lf_qcol(int q) { return OP ? (q >> 4) % (16 * NT) : q % (16 * NT); }
+__device__ __forceinline__ int m2lf_qcol(int q) { return OP & 1 ? (q >> 4) % (16 * NT) : q % (16 * NT); }
 template <int OP, int NT>
-__device__ __forceinline__ int m2lf_qrow(int q) { return OP ? q & 15 : (q / (16 * NT)) & 15; }
+__device__ __forceinline__ int m2lf_qrow(int q) { return OP & 1 ? q & 15 : (q / (16 * NT)) & 15; }
 // inverse Walsh sum over the patterns, to the 8 cells of the oct of `row`
 template <int P, typename H, int OP>
 __device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox, int oy0, int oz0, int row, double (&y)[8]) {
@@ -536,7 +569,17 @@ __device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox, int oy0,
   const int ns = sg.n, nsp = ns + 6, no = ns >> 1, oy = oy0 + (row >> 2), oz = oz0 + (row & 3);
   if (cb < 0 || ox >= no || oy >= no || oz >= no) return;
   walsh8(y);
-  if constexpr (OP == 1) {
+  if constexpr (OP == 2) {
+    H* const ut = static_cast<H*>(sg.u);
+    const int o = cb >> 6, eo = o ? 8 >> o : 0, t0 = (cb >> 4) & 3, t1 = (cb >> 2) & 3, t2 = cb & 3;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
+                          (2 * oz + 1 - (m & 1));
+      const int pos = ((m & 4 ? 3 - t0 : t0) * 4 + (m & 2 ? 3 - t1 : t1)) * 4 + (m & 1 ? 3 - t2 : t2);
+      ut[(p * 4 + o) * 64 + pos] = static_cast<H>(m & eo ? -y[m] : y[m]);
+    }
+  } else if constexpr (OP & 1) {
     const int pa = c_ft<P>.par[cb];
     const long long ncellp = (long long)nsp * nsp * nsp;
 #pragma unroll
@@ -575,7 +618,7 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
   constexpr int EP = KS * NX * 8 * 16 * CS, SZ = EP > 4 * CELLS ? EP : 4 * CELLS;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
   __shared__ int4 ktab[108];  // per K index of a chunk: plus image, and the distances to the minus ones
-  constexpr int NTERM = OP ? 8 * hterms(P) : hrow(P);
+  constexpr int NTERM = OP == 3 ? 256 : OP == 1 ? 8 * hterms(P) : hrow(P);
   __shared__ float4 tsg[NTERM];  // per K term: the sign of a minus image along each axis
   __shared__ int scol[16 * NT];
   int grp = 0;
@@ -599,10 +642,10 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
   }
   for (int c = threadIdx.x; c < 16 * NT; c += 512) {
     const int col = 16 * T0 + c;
-    scol[c] = col >= (OP ? 1 : 8) * hterms(P) ? -1 : OP ? col : c_ft<P>.col[col];
+    scol[c] = fold_colmap<P, OP>(col);
   }
   for (int t = threadIdx.x; t < NTERM; t += 512) {
-    const int e = OP ? c_ft<P>.col[t] >> 8 : t < hterms(P) ? c_ft<P>.par[t] : 0;
+    const int e = OP == 3 ? t >> 5 : OP == 1 ? c_ft<P>.col[t] >> 8 : t < hterms(P) ? c_ft<P>.par[t] : 0;
     tsg[t] = float4{e & 4 ? -1.f : 1.f, e & 2 ? -1.f : 1.f, e & 1 ? -1.f : 1.f, 0.f};
   }
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
@@ -778,7 +821,7 @@ __global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, 
   const double* slot = part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NQ * 8);
   for (int x = blockIdx.y * 256 + threadIdx.x; x < NR * NQ; x += gridDim.y * 256) {
     const int r = x / NQ, q = x % NQ, col = 16 * NT * g + m2lf_qcol<OP, NT>(q);
-    const int cb = col >= (OP ? 1 : 8) * hterms(P) ? -1 : OP ? col : c_ft<P>.col[col];
+    const int cb = fold_colmap<P, OP>(col);
     if (cb < 0) continue;
     double y[8];
 #pragma unroll
@@ -790,11 +833,7 @@ __global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, 
   }
 }
 
-// The transpose's steps and B fragments (OP 1), as k_m2lf_table.
-constexpr __host__ __device__ int m2lfa_steps(int P, int nmax, int t) {
-  const int m = h_degree(16 * t);
-  return m > nmax ? 0 : 54 * hterms(P - m);
-}
+// The other operators' B fragments, as k_m2lf_table.
 template <typename H>
 __global__ void k_m2lf_adj_table(const double* __restrict__ Dtab, const int2* __restrict__ tiles, H* __restrict__ W,
                                  int P, int nmax, int ND, long long cnt) {
@@ -824,6 +863,55 @@ __global__ void k_m2lf_adj_table(const double* __restrict__ Dtab, const int2* __
       x += chi(e ^ kap, minus) * y;
     }
     x = ldexp(x, -(h_degree(b) + 1) - 3);
+  }
+  W[id] = static_cast<H>(x);
+}
+
+// FMM-2: M2P, and its transpose, from the derivatives at the 64 unigrid
+// positions of a level-F cell.
+template <typename H>
+__global__ void k_m2pf_table(const double* __restrict__ Dtab2, const int2* __restrict__ tiles, H* __restrict__ W, int P,
+                             int nmax, int ND, long long cnt, int adj) {
+  const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= cnt) return;
+  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  int t = 0;
+  while (tiles[t].y + tiles[t].x <= f) ++t;
+  const int k = 4 * (f - tiles[t].y) + (lane >> 4), s = k % 27, kt = k / 27, col = 16 * t + (lane & 15);
+  const int a = adj ? col : kt;
+  double x = 0.0;
+  if (a < hterms(nmax)) {
+    const int ea = h_exp(a), pa = h_parity(a), j[3] = {s / 9, (s / 3) % 3, s % 3};
+    const int o = adj ? kt & 3 : col >> 6, eo = o ? 8 >> o : 0, kap = kt >> 5;
+    const int g = mi_index(mi_a(ea) + (o == 1), mi_b(ea) + (o == 2), mi_c(ea) + (o == 3));
+    for (int minus = 0; minus < 8; ++minus) {
+      int dd = 0;
+      bool near = true;
+      for (int ax = 0; ax < 3; ++ax) {
+        const int m = (minus >> (2 - ax)) & 1;
+        const int d = adj ? (m ? -j[ax] - 1 : j[ax]) : (m ? j[ax] + 1 : -j[ax]);  // P - J
+        near = near && d >= -1 && d <= 1;
+        dd = dd * 7 + d + 3;
+      }
+      if (near) continue;
+      const double* D = Dtab2 + (size_t)dd * 64 * ND + g;
+      if (!adj) {
+        x += chi(e ^ pa, minus) * D[(size_t)(col & 63) * ND];
+      } else {
+        // the target's images about its own cell's centre: 1/2, 3/2 out on either side
+        double y = 0.0;
+        for (int im = 0; im < 8; ++im) {
+          int sub = 0;
+          for (int ax = 0; ax < 3; ++ax) {
+            const int b = (kt >> (4 - ax)) & 1;
+            sub = sub * 4 + ((im >> (2 - ax)) & 1 ? 1 - b : 2 + b);
+          }
+          y += chi(kap ^ eo, im) * D[(size_t)sub * ND];
+        }
+        x += chi(e ^ kap, minus) * y;
+      }
+    }
+    x *= adj ? 1.0 / 64 : 1.0 / 8;
   }
   W[id] = static_cast<H>(x);
 }

@@ -5,7 +5,8 @@
 //   Lw_k = M2L Mh_{k-1} (Walsh-folded over children), Lc_k = unfold Lw_k + L2L Lc_{k-1},
 //   (phi, g) = unfold(block stencil fold(rho) + L2P Lw_F + L2P' Lc_{F-1}).
 // The backward pass runs the transposes in reverse:
-//   k_blk_adj_l    cotangents -> Lw_bar_F, Lc_bar_{F-1}          (L2P^T)
+//   k_blk_adj_l    cotangents -> Lw_bar_F, Lc_bar_{F-1}          (L2P^T; FMM-2:
+//                  Lc_bar_F, and the folded cotangents for M2P^T, k_m2lf OP 3)
 //   k_l2lf_adj     Lc_bar_k -> Lw_bar_k, Lc_bar_{k-1}, k = F-1..3
 //   k_m2lf (OP 1)  Lw_bar_k -> Mh_bar_{k-1}, every level           (M2L^T)
 //   k_m2mf_adj     Mh_bar_{k-1} -> Mh_bar_k (+=), k = 3..F-1
@@ -26,7 +27,7 @@ constexpr __host__ __device__ int blka_ltiles(int P) { return (hterms(P) + 15) /
 constexpr __host__ __device__ int blka_off_lp(int P) { return blka_off_l(P) + 8 * blka_ltiles(P) * 64; }
 constexpr __host__ __device__ int blka_table(int P) { return blka_off_lp(P) + 64 * 64; }
 
-__global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int P, int nmax) {
+__global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int P, int nmax, int dl) {
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= blka_table(P)) return;
   const int lane = id & 63, j = lane & 15, kq = lane >> 4;
@@ -71,7 +72,7 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
   } else {
     const int f = (id - blka_off_lp(P)) >> 6, e = f >> 3, s = f & 7;
     const int b = blk_pterm(P, e, j);
-    if (b >= 0) x = h_reduce(b, [&](int bt) { return l2p_parent_coef(bt, 7, s, kq); });
+    if (b >= 0) x = h_reduce(b, [&](int bt) { return blk_l2p(bt, s, kq, dl); });
   }
   W[id] = x;
 }
@@ -83,7 +84,8 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
 // terms of parity e of Lc_bar_{F-1}, [block][hrow].  Bound by its traffic
 // (reads 4 values a cell, writes 8 (p + 1)^2 a block); rows consecutive along
 // z make every plane's store a run of 16.
-template <int P, typename TI, typename H>
+// FMM-2: no own part; lb takes Y itself, planes [32 e + 4 t + o][(nb + 6)^3].
+template <int P, typename TI, typename H, int DL>
 __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, const TI* __restrict__ dg, int n,
                                                    const double* __restrict__ W, H* __restrict__ lb,
                                                    double* __restrict__ lc) {
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
   const int nb = n >> 2, nbp = nb + 6;
   const long long nblk = (long long)nb * nb * nb, N = (long long)n * n * n, ncp = (long long)nbp * nbp * nbp;
   const long long B0 = (long long)blockIdx.x * 16;
-  const double dx = 1.0 / n, sphi = 0.5 * dx * dx, sgr = -0.25 * dx;
+  const double dx = 1.0 / n, sphi = (DL == 1 ? 0.5 : 0.25) * dx * dx, sgr = (DL == 1 ? -0.25 : -0.0625) * dx;
   {
     // thread (o, t, block): blocks fastest
     const int bl = threadIdx.x & 15, t = (threadIdx.x >> 4) & 7, o = threadIdx.x >> 7;
@@ -123,6 +125,17 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
     }
   }
   __syncthreads();
+  if constexpr (DL == 2) {
+    const int bl = threadIdx.x & 15;
+    const long long B = B0 + bl;
+    if (B < nblk) {
+      const int b2 = (int)(B % nb), b1 = (int)((B / nb) % nb), b0 = (int)(B / ((long long)nb * nb));
+      const long long cp = ((long long)(b0 + 3) * nbp + b1 + 3) * nbp + b2 + 3;
+      for (int c = threadIdx.x >> 4; c < 256; c += 32)
+        lb[c * ncp + cp] = static_cast<H>(lds[((c >> 5) * 16 + bl) * YS + (c & 31)]);
+    }
+    if (!lc) return;
+  }
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const int e = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   d4 acc[NT], ap = d4{0, 0, 0, 0};
@@ -132,7 +145,7 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
   for (int s = 0; s < 8; ++s) {
     const double a = lds[(e * 16 + i) * YS + 4 * s + kq];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < NT && DL == 1; ++t)
       acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_L + (s * NT + t) * 64 + lane], acc[t], 0, 0, 0);
     if (lc) ap = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_P + (e * 8 + s) * 64 + lane], ap, 0, 0, 0);
   }
@@ -146,7 +159,7 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
     lds[(e * (HT + 16) + HT + i) * RS + 4 * v + kq] = ap[v];
   }
   __syncthreads();
-  {
+  if constexpr (DL == 1) {
     const int bl = threadIdx.x & 15;
     const long long B = B0 + bl;
     if (B < nblk) {
@@ -299,7 +312,7 @@ __global__ __launch_bounds__(256) void k_m2mf_adj(const double* __restrict__ Mp,
 // cells around, one output (phi, gx, gy, gz) in the LDS tile at a time, and
 // the adjoint harmonic multipoles of its own level F-1 cell (planes; or null).
 // Tiles and folding as in k_block; 8 of the 16 columns of a product are live.
-template <int P, typename TI, typename TO, int NX>
+template <int P, typename TI, typename TO, int NX, int DL>
 __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restrict__ dphi, const TI* __restrict__ dg,
                                                               const double* __restrict__ W,
                                                               const double* __restrict__ Mb, TO* __restrict__ drho,
@@ -326,7 +339,8 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
       constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
       const int x0 = 4 * bx0 - 4, y0 = 4 * by0 - 4, z0 = 4 * bz0 - 4;
       const auto gs = gmem(o == 0 ? dphi : dg + (o - 1) * N);
-      const double sc = o == 0 ? 0.0625 * dx * dx : -0.03125 * dx;  // with the Walsh sum's 1/8
+      // the accumulators' scale, with the Walsh sum's 1/8
+      const double sc = 0.125 * (o == 0 ? (DL == 1 ? 0.5 : 0.25) * dx * dx : (DL == 1 ? -0.25 : -0.0625) * dx);
 #pragma unroll 1
       for (int q0 = threadIdx.x; q0 < CNT; q0 += FB * BLK_THREADS) {
         TI v[FB];

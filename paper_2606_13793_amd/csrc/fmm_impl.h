@@ -1400,36 +1400,38 @@ hipError_t build_tables_t(fmm_plan* pl, bool bottom, bool m2l, hipStream_t s) {
   return hipSuccess;
 }
 
-// column tiles and B fragments of the folded M2L (x: 0 FP64, 1 FP32)
-hipError_t build_m2lf(fmm_plan* pl, int x, bool adj, hipStream_t s) {
-  const int nt = adj ? (hterms(pl->p) + 15) / 16 : m2lf_ntiles(pl->p);
-  int2*& tiles = adj ? pl->m2lf_adj_tiles : pl->m2lf_tiles;
-  void*& w = adj ? pl->wm2lf_adj[x] : pl->wm2lf[x];
+// column tiles and B fragments of a folded operator (x: 0 FP64, 1 FP32)
+hipError_t build_fold(fmm_plan* pl, int op, int x, hipStream_t s) {
+  const int nt = fold_ntiles(op, pl->p);
   std::vector<int2> t(nt + 8, int2{0, 0});  // a group may run past the last tile
   long long f = 0;
   for (int i = 0; i < nt; ++i) {
-    t[i] = int2{adj ? m2lfa_steps(pl->p, pl->nmax, i) : m2lf_steps(pl->p, pl->nmax, i), (int)f};
+    t[i] = int2{fold_steps(op, pl->p, pl->nmax, i), (int)f};
     f += t[i].x;
   }
   hipError_t e;
-  if (!tiles) {
-    if ((e = hipMalloc(&tiles, t.size() * sizeof(int2))) != hipSuccess) return e;
-    pl->bytes += t.size() * sizeof(int2);
-    if ((e = hipMemcpy(tiles, t.data(), t.size() * sizeof(int2), hipMemcpyHostToDevice)) != hipSuccess) return e;
+  if (!pl->fold_tiles[op]) {
+    const size_t b = t.size() * sizeof(int2);
+    if ((e = hipMalloc(&pl->fold_tiles[op], b)) != hipSuccess) return e;
+    pl->bytes += b;
+    if ((e = hipMemcpy(pl->fold_tiles[op], t.data(), b, hipMemcpyHostToDevice)) != hipSuccess) return e;
   }
   const long long cnt = f * 512;
   const size_t b = (size_t)cnt * (x ? sizeof(float) : sizeof(double));
-  if ((e = hipMalloc(&w, b)) != hipSuccess) return e;
+  if ((e = hipMalloc(&pl->fold_w[op][x], b)) != hipSuccess) return e;
   pl->bytes += b;
-  auto* k32 = adj ? k_m2lf_adj_table<float> : k_m2lf_table<float>;
-  auto* k64 = adj ? k_m2lf_adj_table<double> : k_m2lf_table<double>;
-  if (x)
-    hipLaunchKernelGGL(k32, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, tiles, (float*)w, pl->p, pl->nmax,
-                       pl->ND, cnt);
-  else
-    hipLaunchKernelGGL(k64, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab, tiles, (double*)w, pl->p, pl->nmax,
-                       pl->ND, cnt);
-  return hipGetLastError();
+  const dim3 g(blocks_for(cnt, 256)), th(256);
+  auto go = [&](auto* w) {
+    using H = std::remove_pointer_t<decltype(w)>;
+    if (op == FO_M2L || op == FO_M2LT)
+      hipLaunchKernelGGL((op == FO_M2L ? k_m2lf_table<H> : k_m2lf_adj_table<H>), g, th, 0, s, pl->dtab,
+                         pl->fold_tiles[op], w, pl->p, pl->nmax, pl->ND, cnt);
+    else
+      hipLaunchKernelGGL((k_m2pf_table<H>), g, th, 0, s, pl->dtab2, pl->fold_tiles[op], w, pl->p, pl->nmax, pl->ND, cnt,
+                         op == FO_M2PT);
+    return hipGetLastError();
+  };
+  return x ? go((float*)pl->fold_w[op][x]) : go((double*)pl->fold_w[op][x]);
 }
 
 // every launch site's compute type: levels k < m2l_low_from and bottoms of
@@ -1445,11 +1447,15 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   const bool m2l64 = pl->s_conv[0].nseg > 0, m2llow = pl->s_conv[1].nseg > 0;
   const bool bot64 = pl->s_bot[0][0].nseg > 0, botlow = pl->s_bot[1][0].nseg > 0;
   for (int x = 0; x < 2; ++x)
-    if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, false, s)) != hipSuccess) return e;
+  {
+    if (pl->s_m2lf[x][0].nseg && (e = build_fold(pl, FO_M2L, x, s)) != hipSuccess) return e;
+    if (pl->s_m2pf[x][0].nseg && (e = build_fold(pl, FO_M2P, x, s)) != hipSuccess) return e;
+  }
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
     double* G = nullptr;
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND);
+    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND,
+                       pl->dl);
     e = hipGetLastError();
     const int cnt = blk_table(pl->p);
     for (int x = 0; x < 2 && e == hipSuccess; ++x) {
@@ -1458,9 +1464,11 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
       if ((e = hipMalloc(&pl->wblk[x], b)) != hipSuccess) break;
       pl->bytes += b;
       if (x)
-        hipLaunchKernelGGL(k_blk_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (float*)pl->wblk[x], pl->p);
+        hipLaunchKernelGGL(k_blk_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (float*)pl->wblk[x], pl->p,
+                           pl->dl);
       else
-        hipLaunchKernelGGL(k_blk_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (double*)pl->wblk[x], pl->p);
+        hipLaunchKernelGGL(k_blk_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (double*)pl->wblk[x], pl->p,
+                           pl->dl);
       e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1553,8 +1561,7 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
                        (const H*)pl->wp2p[X], pl->dlists, nck, cnt, done);
     return hipGetLastError();
   }
-  if constexpr (X != 2) return hipErrorInvalidValue;  // FMM-1 in FP64 and FP32: k_block
-  else if (z == 0)
+  if (z == 0)
     hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 16, 1>), dim3(st.blocks), dim3(bottom_threads<CT>()), 0, s, st.dev, st.nseg, io,
                        (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X],
                        pl->dlists, nck, cnt, done);
@@ -1566,16 +1573,23 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
 }
 
 // Tile shapes of the folded M2L by variant (rows of octs, column tiles per
-// group, patterns per wave, K slices): OP 0 forward, 1 transpose, whose few
+// group, patterns per wave, K slices): forward, and transposes, whose few
 // column tiles are dominated by the first.
 template <int OP, int V>
 struct M2lShape;
 template <> struct M2lShape<0, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
 template <> struct M2lShape<0, 1> { static constexpr int MT = 2, NT = 4, NE = 2, KS = 1; };
 template <> struct M2lShape<0, 2> { static constexpr int MT = 4, NT = 4, NE = 2, KS = 1; };
+template <> struct M2lShape<2, 0> : M2lShape<0, 0> {};
+template <> struct M2lShape<2, 1> : M2lShape<0, 1> {};
+template <> struct M2lShape<2, 2> : M2lShape<0, 2> {};
 template <> struct M2lShape<1, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
 template <> struct M2lShape<1, 1> { static constexpr int MT = 2, NT = 1, NE = 8, KS = 4; };
 template <> struct M2lShape<1, 2> { static constexpr int MT = 4, NT = 2, NE = 4, KS = 1; };
+
+template <> struct M2lShape<3, 0> : M2lShape<1, 0> {};
+template <> struct M2lShape<3, 1> : M2lShape<1, 1> {};
+template <> struct M2lShape<3, 2> : M2lShape<1, 2> {};
 
 // Grid of a launch over T tiles.  A block's K loop is cut where it would take
 // more than a quarter of what each compute unit has to do in the whole launch
@@ -1584,12 +1598,12 @@ template <> struct M2lShape<1, 2> { static constexpr int MT = 4, NT = 2, NE = 4,
 template <int P, int OP, int V>
 M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
   using S = M2lShape<OP, V>;
-  const int nt = OP ? (hterms(P) + 15) / 16 : m2lf_ntiles(P);
+  const int nt = fold_ntiles(OP, P);
   M2lGrid g;
   g.ng = (nt + S::NT - 1) / S::NT;
   long long cost[kM2lGroups] = {}, longest[kM2lGroups] = {}, total = 0;
   for (int t = 0; t < nt; ++t) {
-    const int st = OP ? m2lfa_steps(P, pl->nmax, t) : m2lf_steps(P, pl->nmax, t);
+    const int st = fold_steps(OP, P, pl->nmax, t);
     cost[t / S::NT] += st;
     longest[t / S::NT] = std::max<long long>(longest[t / S::NT], st);
     total += st;
@@ -1617,10 +1631,9 @@ hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s)
   using S = M2lShape<OP, V>;
   using H = typename Mf<CT>::H;
   const M2lGrid g = m2lf_grid<P, OP, V>(pl, st.blocks);
-  StageScope sc(pl, ST_M2L, g.shared ? 2 : 1, s);
+  StageScope sc(pl, OP == FO_M2P ? ST_BOTTOM : ST_M2L, g.shared ? 2 : 1, s);
   hipLaunchKernelGGL((k_m2lf<P, CT, OP, S::MT, S::NT, S::NE, S::KS>), dim3((unsigned)g.blocks), dim3(512), 0, s, st.dev,
-                     st.nseg, st.blocks, OP ? pl->m2lf_adj_tiles : pl->m2lf_tiles,
-                     (const H*)(OP ? pl->wm2lf_adj[x] : pl->wm2lf[x]), g, pl->m2lf_part);
+                     st.nseg, st.blocks, pl->fold_tiles[OP], (const H*)pl->fold_w[OP][x], g, pl->m2lf_part);
   if (g.shared)
     hipLaunchKernelGGL((k_m2lf_sum<P, H, OP, S::MT, S::NT, S::MT * S::KS / S::NE>),
                        dim3((unsigned)(g.shared * st.blocks), S::MT * S::NT), dim3(256), 0, s, st.dev, st.nseg, st.blocks,
@@ -1628,26 +1641,21 @@ hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s)
   return hipGetLastError();
 }
 
-// Folded M2L of site x (0 FP64, 1 FP32).
-template <int P, typename CT>
-hipError_t launch_m2lf(fmm_plan* pl, int x, hipStream_t s) {
-  if (!pl->s_m2lf[x][0].nseg) return hipSuccess;
-  int v = m2lf_variant(pl, pl->s_m2lf[x][1].blocks, pl->s_m2lf[x][2].blocks);
-  if (pl->tune.grp == 1 && v > 0) --v;
-  const SegTable& st = pl->s_m2lf[x][v];
-  if (v == 2) return launch_m2lf_v<P, CT, 0, 2>(pl, x, st, s);
-  if (v == 1) return launch_m2lf_v<P, CT, 0, 1>(pl, x, st, s);
-  return launch_m2lf_v<P, CT, 0, 0>(pl, x, st, s);
-}
-
-// Its transpose.
-template <int P, typename CT>
-hipError_t launch_m2lf_adj(fmm_plan* pl, const AdjWs& w, int x, hipStream_t s) {
-  const SegTable& st = w.m2ltf[x];
+// A folded operator over the tiles of variant v.
+template <int P, typename CT, int OP>
+hipError_t launch_fold(fmm_plan* pl, int x, int v, const SegTable& st, hipStream_t s) {
   if (!st.nseg) return hipSuccess;
-  if (w.m2ltf_v[x] == 2) return launch_m2lf_v<P, CT, 1, 2>(pl, x, st, s);
-  if (w.m2ltf_v[x] == 1) return launch_m2lf_v<P, CT, 1, 1>(pl, x, st, s);
-  return launch_m2lf_v<P, CT, 1, 0>(pl, x, st, s);
+  if (v == 2) return launch_m2lf_v<P, CT, OP, 2>(pl, x, st, s);
+  if (v == 1) return launch_m2lf_v<P, CT, OP, 1>(pl, x, st, s);
+  return launch_m2lf_v<P, CT, OP, 0>(pl, x, st, s);
+}
+// Forward operators of site x (0 FP64, 1 FP32).
+template <int P, typename CT, int OP>
+hipError_t launch_fold_site(fmm_plan* pl, int x, hipStream_t s) {
+  const auto& st = OP == FO_M2P ? pl->s_m2pf[x] : pl->s_m2lf[x];
+  int v = m2lf_variant(pl, st[1].blocks, st[2].blocks);
+  if (pl->tune.grp == 1 && v > 0) --v;
+  return launch_fold<P, CT, OP>(pl, x, v, st[v], s);
 }
 
 // The workspace those launches share.  The transpose's launches have the
@@ -1655,18 +1663,22 @@ hipError_t launch_m2lf_adj(fmm_plan* pl, const AdjWs& w, int x, hipStream_t s) {
 template <int P>
 hipError_t alloc_m2lf_part(fmm_plan* pl) {
   size_t part = 0;
-  for (int x = 0; x < 2; ++x) {
-    const auto& st = pl->s_m2lf[x];
-    if (!st[0].nseg) continue;
+  auto need = [&](auto opc, auto adjc, const SegTable (&st)[3]) {
+    constexpr int OP = decltype(opc)::value, ADJ = decltype(adjc)::value;
+    if (!st[0].nseg) return;
     const int v = m2lf_variant(pl, st[1].blocks, st[2].blocks);
     // (a batch's autotuner may take the next smaller variant)
-    if (v == 2) m2lf_need<P, 0, 2>(pl, st[2].blocks, &part);
-    if (v >= 1) m2lf_need<P, 0, 1>(pl, st[1].blocks, &part);
-    if (v <= 1) m2lf_need<P, 0, 0>(pl, st[0].blocks, &part);
-    if (pl->batch) continue;
-    if (v == 2) m2lf_need<P, 1, 2>(pl, st[2].blocks, &part);
-    if (v == 1) m2lf_need<P, 1, 1>(pl, st[1].blocks, &part);
-    if (v == 0) m2lf_need<P, 1, 0>(pl, st[0].blocks, &part);
+    if (v == 2) m2lf_need<P, OP, 2>(pl, st[2].blocks, &part);
+    if (v >= 1) m2lf_need<P, OP, 1>(pl, st[1].blocks, &part);
+    if (v <= 1) m2lf_need<P, OP, 0>(pl, st[0].blocks, &part);
+    if (pl->batch) return;
+    if (v == 2) m2lf_need<P, ADJ, 2>(pl, st[2].blocks, &part);
+    if (v == 1) m2lf_need<P, ADJ, 1>(pl, st[1].blocks, &part);
+    if (v == 0) m2lf_need<P, ADJ, 0>(pl, st[0].blocks, &part);
+  };
+  for (int x = 0; x < 2; ++x) {
+    need(std::integral_constant<int, FO_M2L>{}, std::integral_constant<int, FO_M2LT>{}, pl->s_m2lf[x]);
+    need(std::integral_constant<int, FO_M2P>{}, std::integral_constant<int, FO_M2PT>{}, pl->s_m2pf[x]);
   }
   if (!part) return hipSuccess;
   hipError_t e;
@@ -1690,13 +1702,19 @@ hipError_t launch_block(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   const SegTable& st = pl->s_blk[x][v];
   StageScope sc(pl, ST_BOTTOM, 1, s);
   const H* w = (const H*)pl->wblk[x];
-  if (v == 2)
-    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 4>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
-  else if (v == 1)
-    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 2>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
-  else
-    hipLaunchKernelGGL((k_block<P, CT, TI, TO, 1>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w, cnt, done);
-  return hipGetLastError();
+  auto go = [&](auto nx) {
+    constexpr int NX = decltype(nx)::value;
+    if (pl->dl == 2)
+      hipLaunchKernelGGL((k_block<P, CT, TI, TO, NX, 2>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w,
+                         cnt, done);
+    else
+      hipLaunchKernelGGL((k_block<P, CT, TI, TO, NX, 1>), dim3(st.blocks), dim3(BLK_THREADS), 0, s, st.dev, st.nseg, io, w,
+                         cnt, done);
+    return hipGetLastError();
+  };
+  if (v == 2) return go(std::integral_constant<int, 4>{});
+  if (v == 1) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 1>{});
 }
 
 // One solve of every field of the plan.  CT is the compute type of the fine
@@ -1735,18 +1753,21 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
                        pl->m2m_start, pl->m2m_off, pl->m2m_coef, pl->NMX);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_m2lf<P, double>(pl, 0, s)) != hipSuccess) return e;
-  if constexpr (std::is_same<CT, float>::value)
-    if ((e = launch_m2lf<P, float>(pl, 1, s)) != hipSuccess) return e;
+  if ((e = launch_fold_site<P, double, FO_M2L>(pl, 0, s)) != hipSuccess) return e;
+  if ((e = launch_fold_site<P, double, FO_M2P>(pl, 0, s)) != hipSuccess) return e;
+  if constexpr (std::is_same<CT, float>::value) {
+    if ((e = launch_fold_site<P, float, FO_M2L>(pl, 1, s)) != hipSuccess) return e;
+    if ((e = launch_fold_site<P, float, FO_M2P>(pl, 1, s)) != hipSuccess) return e;
+  }
   if ((e = launch_conv<P, double, CV_M2L>(pl, pl->s_conv[0], pl->wm2l[0], s)) != hipSuccess) return e;
   if ((e = launch_split_reduce(pl, pl->s_red[0], s)) != hipSuccess) return e;
-  if constexpr (!std::is_same<CT, double>::value) {
+  if constexpr (Mf<CT>::IDX == 2) {
     if ((e = launch_conv<P, CT, CV_M2L>(pl, pl->s_conv[1], pl->wm2l[Mf<CT>::IDX], s)) != hipSuccess) return e;
     if ((e = launch_split_reduce(pl, pl->s_red[1], s)) != hipSuccess) return e;
   }
   // L2L down to level F - 1 of each field; level F's far field is taken from
   // Lhat_{F-1} directly by the bottom kernel
-  for (int k = 3; k <= pl->maxF - 1; ++k) {
+  for (int k = 3; k <= pl->maxF; ++k) {
     const SegTable& st = pl->s_l2lf[k];
     if (!st.nseg) continue;
     StageScope sc(pl, ST_L2L, 1, s);
@@ -1762,8 +1783,7 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   if ((e = launch_block<P, double, TI, TO>(pl, 0, io, s)) != hipSuccess) return e;
   if constexpr (std::is_same<CT, float>::value)
     if ((e = launch_block<P, float, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;
-  if ((e = launch_bottom<P, double, TI, TO>(pl, 0, io, s)) != hipSuccess) return e;
-  if constexpr (!std::is_same<CT, double>::value)
+  if constexpr (Mf<CT>::IDX == 2)
     if ((e = launch_bottom<P, CT, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;
   return hipSuccess;
 }
@@ -1791,15 +1811,19 @@ hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
   hipError_t e;
   const int NL = pl->NL;
   if (block_field(pl, pl->F)) {
-    for (int x = 0; x < 2; ++x)
-      if (pl->s_m2lf[x][0].nseg && (e = build_m2lf(pl, x, true, s)) != hipSuccess) return e;
+    for (int x = 0; x < 2; ++x) {
+      if (pl->s_m2lf[x][0].nseg && (e = build_fold(pl, FO_M2LT, x, s)) != hipSuccess) return e;
+      if (pl->s_m2pf[x][0].nseg && (e = build_fold(pl, FO_M2PT, x, s)) != hipSuccess) return e;
+    }
     double* G = nullptr;
     const int cnt = blka_table(pl->p);
     if ((e = hipMalloc(&pl->wblk_adj, cnt * sizeof(double))) != hipSuccess) return e;
     pl->bytes += cnt * sizeof(double);
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND);
-    hipLaunchKernelGGL(k_blk_adj_table, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, pl->wblk_adj, pl->p, pl->nmax);
+    hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND,
+                       pl->dl);
+    hipLaunchKernelGGL(k_blk_adj_table, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, pl->wblk_adj, pl->p, pl->nmax,
+                       pl->dl);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(G);
@@ -1834,61 +1858,74 @@ hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
 }
 
 // The backward pass of a field on the folded kernels (field 0).
-template <int P, typename CT, typename TI>
+template <int P, typename CT, typename TI, int DL>
 hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TI* drho, hipStream_t s) {
-  const int n = pl->n, F = pl->F, nb = n >> 2;
+  const int n = pl->n, F = pl->F, B = block_level(pl, F), nb = n >> 2;
   const long long nblk = (long long)nb * nb * nb;
   hipError_t e;
-  if (F >= 3) {
-    double* lc = F >= 4 ? w.lc[F - 1] : nullptr;
-    if (harmonic_float(pl, F - 1))
-      hipLaunchKernelGGL((k_blk_adj_l<P, TI, float>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
-                         pl->wblk_adj, (float*)w.lb[F], lc);
+  // FMM-1 without M2L levels has nothing but the block stencil
+  if (F >= 3 || DL == 2) {
+    double* lc = B >= 3 ? w.lc[B] : nullptr;
+    void* lb = DL == 2 ? w.yb : w.lb[F];
+    if (DL == 2 ? bottom_low(pl, F) && pl->precision == 1 : harmonic_float(pl, F, F - 1))
+      hipLaunchKernelGGL((k_blk_adj_l<P, TI, float, DL>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
+                         pl->wblk_adj, (float*)lb, lc);
     else
-      hipLaunchKernelGGL((k_blk_adj_l<P, TI, double>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
-                         pl->wblk_adj, (double*)w.lb[F], lc);
+      hipLaunchKernelGGL((k_blk_adj_l<P, TI, double, DL>), dim3(blocks_for(nblk, 16)), dim3(512), 0, s, dphi, dg, n,
+                         pl->wblk_adj, (double*)lb, lc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int k = F - 1; k >= 3; --k) {
-      const int ns = 1 << (k - 1);
-      const unsigned g = blocks_for((long long)ns * ns * ns, L2LAdj<P>::PAR);
-      double* up = k > 3 ? w.lc[k - 1] : nullptr;
-      if (harmonic_float(pl, k - 1))
-        hipLaunchKernelGGL((k_l2lf_adj<P, float>), dim3(g), dim3(256), 0, s, w.lc[k], (float*)w.lb[k], up, ns,
-                           pl->m2m_start, pl->m2m_off, pl->m2m_coef);
-      else
-        hipLaunchKernelGGL((k_l2lf_adj<P, double>), dim3(g), dim3(256), 0, s, w.lc[k], (double*)w.lb[k], up, ns,
-                           pl->m2m_start, pl->m2m_off, pl->m2m_coef);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if ((e = launch_m2lf_adj<P, double>(pl, w, 0, s)) != hipSuccess) return e;
-    if constexpr (std::is_same<CT, float>::value)
-      if ((e = launch_m2lf_adj<P, float>(pl, w, 1, s)) != hipSuccess) return e;
-    for (int k = 3; k <= F - 1; ++k) {
-      const int np = 1 << (k - 1);
-      hipLaunchKernelGGL((k_m2mf_adj<P>), dim3(blocks_for((long long)np * np * np, M2MA_PAR)), dim3(256), 0, s,
-                         (const double*)pl->lev[k - 1].M, (double*)pl->lev[k].M, np, pl->m2mt_start, pl->m2mt_a,
-                         pl->m2mt_coef);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
   }
-  const double* mb = F >= 3 ? (const double*)pl->lev[F - 1].M : nullptr;
-  const long long rows = (long long)nb * ((nb + 3) / 4) * ((nb + 3) / 4);
-  const int tpa = (nb + 3) / 4, t2 = tpa * tpa;
-  if (rows >= 8LL * pl->cus)
-    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 4>), dim3(t2 * ((nb + 3) / 4)), dim3(BLK_THREADS), 0, s, dphi, dg,
-                       pl->wblk_adj, mb, drho, n, tpa);
-  else if (rows >= 4LL * pl->cus)
-    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 2>), dim3(t2 * ((nb + 1) / 2)), dim3(BLK_THREADS), 0, s, dphi, dg,
-                       pl->wblk_adj, mb, drho, n, tpa);
-  else
-    hipLaunchKernelGGL((k_block_adj<P, TI, TI, 1>), dim3(t2 * nb), dim3(BLK_THREADS), 0, s, dphi, dg, pl->wblk_adj, mb,
-                       drho, n, tpa);
-  return hipGetLastError();
+  for (int k = B; k >= 3; --k) {
+    const int ns = 1 << (k - 1);
+    const unsigned g = blocks_for((long long)ns * ns * ns, L2LAdj<P>::PAR);
+    double* up = k > 3 ? w.lc[k - 1] : nullptr;
+    if (harmonic_float(pl, F, k - 1))
+      hipLaunchKernelGGL((k_l2lf_adj<P, float>), dim3(g), dim3(256), 0, s, w.lc[k], (float*)w.lb[k], up, ns,
+                         pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+    else
+      hipLaunchKernelGGL((k_l2lf_adj<P, double>), dim3(g), dim3(256), 0, s, w.lc[k], (double*)w.lb[k], up, ns,
+                         pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if ((e = launch_fold<P, double, FO_M2LT>(pl, 0, w.m2ltf_v[0], w.m2ltf[0], s)) != hipSuccess) return e;
+  if constexpr (std::is_same<CT, float>::value)
+    if ((e = launch_fold<P, float, FO_M2LT>(pl, 1, w.m2ltf_v[1], w.m2ltf[1], s)) != hipSuccess) return e;
+  if constexpr (DL == 2) {
+    bool low = false;
+    if constexpr (std::is_same<CT, float>::value) {
+      low = bottom_low(pl, F);
+      if (low && (e = launch_fold<P, float, FO_M2PT>(pl, 1, w.m2ptf_v, w.m2ptf, s)) != hipSuccess) return e;
+    }
+    if (!low && (e = launch_fold<P, double, FO_M2PT>(pl, 0, w.m2ptf_v, w.m2ptf, s)) != hipSuccess) return e;
+  }
+  for (int k = 3; k <= B; ++k) {
+    const int np = 1 << (k - 1);
+    hipLaunchKernelGGL((k_m2mf_adj<P>), dim3(blocks_for((long long)np * np * np, M2MA_PAR)), dim3(256), 0, s,
+                       (const double*)pl->lev[k - 1].M, (double*)pl->lev[k].M, np, pl->m2mt_start, pl->m2mt_a,
+                       pl->m2mt_coef);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const double* mb = B >= 2 ? (const double*)pl->lev[B].M : nullptr;
+  const int tpa = (nb + 3) / 4;
+  const long long rows = (long long)nb * tpa * tpa;
+  auto go = [&](auto nx) {
+    constexpr int NX = decltype(nx)::value;
+    hipLaunchKernelGGL((k_block_adj<P, TI, TI, NX, DL>), dim3(tpa * tpa * ((nb + NX - 1) / NX)), dim3(BLK_THREADS), 0, s,
+                       dphi, dg, pl->wblk_adj, mb, drho, n, tpa);
+    return hipGetLastError();
+  };
+  if (rows >= 8LL * pl->cus) return go(std::integral_constant<int, 4>{});
+  if (rows >= 4LL * pl->cus) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 1>{});
 }
 
 template <int P, typename CT, typename TI, typename TO>
 hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TO* drho, hipStream_t s) {
-  if (block_field(pl, pl->F)) return backward_fold<P, CT, TI>(pl, w, dphi, dg, drho, s);
+  if (block_field(pl, pl->F))
+    return pl->dl == 2 ? backward_fold<P, CT, TI, 2>(pl, w, dphi, dg, drho, s)
+                       : backward_fold<P, CT, TI, 1>(pl, w, dphi, dg, drho, s);
+  if constexpr (Mf<CT>::IDX != 2) return hipErrorInvalidValue;  // FP64 and FP32 fields are all folded
+  else {
   constexpr int NL = nterms(P);
   const int n = pl->n, F = pl->F, dl = pl->dl, nF = n >> dl;
   const double dx = pl->dx;
@@ -1921,7 +1958,7 @@ hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* d
     }
     // transposed M2L of every target level (sources k - 1 receive)
     if ((e = launch_conv<P, double, CV_M2LT>(pl, w.m2lt[0], pl->wt_m2l[0], s)) != hipSuccess) return e;
-    if constexpr (!std::is_same<CT, double>::value)
+    if constexpr (Mf<CT>::IDX == 2)
       if ((e = launch_conv<P, CT, CV_M2LT>(pl, w.m2lt[1], pl->wt_m2l[Mf<CT>::IDX], s)) != hipSuccess) return e;
     if ((e = launch_split_reduce(pl, w.m2lt_red, s)) != hipSuccess) return e;
   }
@@ -1958,6 +1995,7 @@ hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* d
   hipLaunchKernelGGL((k_adj_bottom<TO>), bgrid, dim3(16 * tz), 0, s, (const double*)pl->lev[F].M, w.ybar, drho, n,
                      pl->NMX);
   return hipGetLastError();
+  }
 }
 
 template <typename T>

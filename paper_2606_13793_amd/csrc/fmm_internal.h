@@ -183,9 +183,9 @@ struct Level {
   // the locals of level k >= 3, Walsh-folded over the children, [parent][8]
   // [hrow], FP64 (the finest level: the block kernel's compute type)
   void* Lw = nullptr;
-  // levels 3 .. F - 1: the complete locals' harmonic terms, [cell][hrow]
+  // levels 3 .. block_level: the complete locals' harmonic terms, [cell][hrow]
   double* Lc = nullptr;
-  // harmonic multipoles of levels 2 .. F - 1, [term][ncellp] with a zero halo,
+  // harmonic multipoles of levels 2 .. block_level, [term][ncellp] with a zero halo,
   // in the compute type of the M2L into the next level
   void* Mh = nullptr;
 };
@@ -199,6 +199,9 @@ struct Field {
   // of a field with an FP64 bottom: the level-F multipoles, which that kernel
   // never forms, are derived from it when they are asked for
   void* rho_copy = nullptr;
+  // FMM-2: M2P at the unigrid centres, [level-F cell][phi, g][4^3] in the
+  // bottom's compute type, added by the block kernel
+  void* m2p = nullptr;
 };
 
 // I/O buffers of one field for one call
@@ -262,6 +265,9 @@ struct AdjWs {
   double* lc[16] = {};   // level k < F: the complete locals' cotangents, [cell][hrow]
   SegTable m2ltf[2];     // folded transposed M2L [FP64 | FP32]
   int m2ltf_v[2] = {0, 0};  // and its tile (rows of octs: 1, 2 or 4)
+  void* yb = nullptr;    // FMM-2: folded cotangents of the level-F cells, planes [256][(2^F+6)^3] in the M2P's type
+  SegTable m2ptf;        // FMM-2: folded transposed M2P
+  int m2ptf_v = 0;
 };
 // Static workspace of fmm_solve_backward_noalloc (bytes per device) and the
 // most segments its tables hold.
@@ -269,6 +275,8 @@ constexpr size_t kNoallocBytes = (size_t)96 << 20;
 constexpr size_t kNoallocSegBytes = 4096;
 constexpr int kMaxAdjSegs = 12;
 
+// Operators of the folded kernel k_m2lf.
+enum FoldOp { FO_M2L = 0, FO_M2LT = 1, FO_M2P = 2, FO_M2PT = 3 };
 // Column groups of a folded M2L launch: group g has the blocks from first[g],
 // parts[g] of them per tile, each summing a share of the K loop.
 constexpr int kM2lGroups = 48;
@@ -355,15 +363,16 @@ struct fmm_plan {
   fmm::SegTable s_blk[2][3];        // finest blocks [FP64 | low][1, 2 or 4 rows of blocks per tile]
   long long blk_rows[2] = {0, 0};   // their row tiles of 16 blocks
   fmm::SegTable s_m2lf[2][3];       // folded M2L [FP64 | low][1, 2 or 4 rows of octs per tile]
+  fmm::SegTable s_m2pf[2][3];       // FMM-2: folded M2P, the same
   fmm::SegTable s_l2lf[16];         // folded L2L: complete locals of level k
-  void* wm2lf[2] = {nullptr, nullptr};  // the folded M2L's B fragments, FP64 and FP32
-  void* wm2lf_adj[2] = {nullptr, nullptr};  // the same of its transpose
-  int2* m2lf_adj_tiles = nullptr;
+  // the folded operators (FoldOp): B fragments, FP64 and FP32, and (K steps,
+  // first fragment) of each column tile
+  void* fold_w[4][2] = {};
+  int2* fold_tiles[4] = {};
   // partial sums of folded M2L launches that share their K loops, sized for
   // every launch of the plan
   double* m2lf_part = nullptr;
   double* wblk_adj = nullptr;       // table of the block kernel's transposes
-  int2* m2lf_tiles = nullptr;       // (K steps, first fragment) of each column tile
   void* wblk[2] = {nullptr, nullptr};  // the block kernel's B table, FP64 and FP32
   fmm::SegTable s_red[2];           // reductions of split forward M2L partial sums
   double* conv_part = nullptr;      // partial sums of split forward M2L segments
@@ -443,19 +452,23 @@ hipError_t finish_locals(fmm_plan* pl, int level, hipStream_t s);
 int build_schedule(fmm_plan* pl);
 // which levels run in which compute type (same rule for every field)
 inline bool bottom_low(const fmm_plan* pl, int F) { return pl->precision != 0 && F > pl->coarse_fp64_levels; }
-// Whether a field's finest level runs on the folded block kernel: FMM-1 in
-// FP64 or FP32.  BF16 bottoms keep k_bottom, whose results carry the rounding
+// Whether a field runs on the folded kernels: FP64 or FP32.  BF16 bottoms keep k_bottom, whose results carry the rounding
 // of every BF16 multipole: the block kernel has no multipoles to round.
 inline bool block_field(const fmm_plan* pl, int F) {
-  return pl->dl == 1 && !(pl->precision == 2 && bottom_low(pl, F));
+  return !(pl->precision == 2 && bottom_low(pl, F));
 }
+// the level whose cells are the block kernel's 4^3 unigrid cells
+inline int block_level(const fmm_plan* pl, int F) { return F + pl->dl - 2; }
 bool finest_locals_typed(const fmm_plan* pl, const Field& fd);
 inline int m2l_low_from(const fmm_plan* pl) {
   return pl->precision == 0 ? 64 : (pl->coarse_fp64_levels + 1 > 3 ? pl->coarse_fp64_levels + 1 : 3);
 }
-// whether a folded field's harmonic multipoles of level k are FP32 (the M2L
-// into level k + 1 runs in FP32)
-inline bool harmonic_float(const fmm_plan* pl, int k) { return pl->precision == 1 && k + 1 >= m2l_low_from(pl); }
+// whether the harmonic multipoles of level k of a folded field with finest
+// level F are FP32 (the M2L into level k + 1, for FMM-2's finest level the
+// M2P, runs in FP32)
+inline bool harmonic_float(const fmm_plan* pl, int F, int k) {
+  return pl->precision == 1 && (k == F ? bottom_low(pl, F) : k + 1 >= m2l_low_from(pl));
+}
 // Tile of a folded M2L launch (0, 1, 2: 1, 2 or 4 rows of octs), from its
 // block counts: the largest that still gives every compute unit blocks.
 inline int m2lf_variant(const fmm_plan* pl, long long blocks2, long long blocks4) {

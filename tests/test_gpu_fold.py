@@ -86,3 +86,25 @@ def test_folded_backward(F, orc, precision, n, p, nmax):
         d = float((lhs - (rho.double() * grad.double()).sum()).abs() / scale)
         print(f"  identity {d:.2e}", flush=True)
         assert d <= (1e-13 if precision == "fp64" else 1e-5), d
+
+
+# FMM-2's folded M2P and its transpose: no M2L level, one, several; both types
+@pytest.mark.parametrize("precision,n,p,nmax", [("fp64", 16, 5, None), ("fp64", 32, 8, 2), ("fp32", 64, 3, None)])
+def test_folded_fmm2(F, orc, precision, n, p, nmax):
+    import torch
+    print(f"case fmm2 {precision} n={n} p={p} nmax={nmax}", flush=True)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    rho = torch.as_tensor(fi.plummer_density(n, fi.multi_plummer_params(12, 31 + n))).to("cuda", dt)
+    gen = torch.Generator(device="cuda").manual_seed(n + p)
+    dphi = torch.randn((n, n, n), dtype=dt, device="cuda", generator=gen)
+    dg = torch.randn((3, n, n, n), dtype=dt, device="cuda", generator=gen)
+    plan = F.Plan(n, p, precision, nmax=nmax, delta_l=2, coarse_fp64_levels=3)
+    phi, g = plan.solve(rho)
+    drho = plan.backward(dphi, dg)
+    torch.cuda.synchronize()
+    h = [t.double().cpu().numpy() for t in (rho, phi, g, dphi, dg, drho)]
+    phi_o, g_o = orc.solve(h[0], p, nmax=nmax, delta_l=2)
+    e = rel(h[1], phi_o), rel(h[2], g_o), rel(h[5], orc.adjoint(h[3], h[4], p, nmax=nmax, delta_l=2))
+    print(f"  phi {e[0]:.2e} g {e[1]:.2e} drho {e[2]:.2e}", flush=True)
+    bp, bg = BARS[precision]
+    assert e[0] <= bp and e[1] <= bg and e[2] <= bg, e
