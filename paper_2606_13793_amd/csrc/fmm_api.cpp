@@ -719,8 +719,8 @@ void fold_adj_segments(const fmm_plan* pl, const fmm::AdjWs& w, SegArr (&out)[3]
     }
   }
   for (int x = 0; x < 3; ++x) {
-    variant[x] = fmm::m2lf_variant(pl, s[x][1].blocks, s[x][2].blocks);
-    out[x] = s[x][variant[x]];
+    variant[x] = fmm::fold_variant(pl, x < 2 ? fmm::FO_M2LT : fmm::FO_M2PT, s[x][2].blocks);
+    out[x] = s[x][variant[x] ? 2 : 0];
   }
 }
 
@@ -1032,7 +1032,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     if (!fmm::block_field(pl, fd.F)) continue;
     const int F = fd.F;
     const bool low = fmm::bottom_low(pl, F);
-    const size_t hr = (size_t)((p + 1) * (p + 1) + 3) / 4 * 4;
+    const size_t hr = (size_t)((p + 1) * (p + 1) + 3) / 4 * 4, fr = (size_t)((p + 1) * (p + 1) + 1) / 2 * 16;
     if (pl->dl == 2 && dev_alloc(pl, &fd.m2p, 4 * (size_t)fd.n * fd.n * fd.n * (low ? sizeof(float) : sizeof(double))))
       return bail();
     if (!low && pl->dl == 1) {
@@ -1051,7 +1051,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     };
     for (int k = 2; k <= F; ++k) {
       fmm::Level& lv = fd.lev[k];
-      if (k >= 3 && !zalloc(&lv.Lw, (size_t)lv.ncell * hr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
+      if (k >= 3 && !zalloc(&lv.Lw, (size_t)(lv.ncell / 8) * fr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
       const bool upto = k <= fmm::block_level(pl, F);
       if (k >= 3 && upto && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
       if (upto && !zalloc(&lv.Mh, (size_t)lv.ncellp * hr * (fmm::harmonic_float(pl, F, k) ? sizeof(float) : sizeof(double))))
@@ -1738,7 +1738,7 @@ int fmm_fd_force(int n, const double* phi, double* f, void* stream) {
 // parent's children: unfolded here, plus the shift of the level above.
 static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
   const fmm::Level& lv = plan->lev[level];
-  const int p = plan->p, nk = lv.nk, ht = (p + 1) * (p + 1), hr = (ht + 3) / 4 * 4, nl = plan->NL;
+  const int p = plan->p, nk = lv.nk, ht = (p + 1) * (p + 1), hr = (ht + 3) / 4 * 4, fr = (ht + 1) / 2 * 16, nl = plan->NL;
   auto hidx = [](int x, int y, int z) { return (x + y + z) * (x + y + z) + (z ? x + y + z + 1 + x : x); };
   auto choose = [](int n, int k) { double b = 1; for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i; return b; };
   std::vector<int> mi(3 * nl);
@@ -1763,7 +1763,7 @@ static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
   const bool finest = level > fmm::block_level(plan, plan->F);
   hipError_t e = hipDeviceSynchronize();
   if (e == hipSuccess)
-    e = fetch(finest ? lv.Lw : lv.Lc, (size_t)lv.ncell * hr, finest && fmm::bottom_low(plan, plan->F), &own);
+    e = fetch(finest ? lv.Lw : lv.Lc, finest ? (size_t)(lv.ncell / 8) * fr : (size_t)lv.ncell * hr, finest && fmm::bottom_low(plan, plan->F), &own);
   if (e == hipSuccess && finest && level > 3)
     e = fetch(plan->lev[level - 1].Lc, (size_t)plan->lev[level - 1].ncell * hr, false, &par);
   if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
@@ -1783,7 +1783,7 @@ static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
         for (int y = 0; x + y + z <= p; ++y) {
           const int b = hidx(x, y, z), pb = ((x & 1) << 2) | ((y & 1) << 1) | (z & 1);
           double v = 0.0;
-          for (int k = 0; k < 8; ++k) v += (odd((k ^ pb) & minus) ? -0.125 : 0.125) * own[(P * 8 + k) * hr + b];
+          for (int k = 0; k < 8; ++k) v += (odd((k ^ pb) & minus) ? -0.125 : 0.125) * own[P * fr + 16 * (b >> 1) + 2 * k + (b & 1)];
           h[b] = v;
         }
     full(h.data(), out + c * nl);

@@ -42,22 +42,40 @@ __host__ __device__ __forceinline__ double chi(int e, int minus) {
 // epilogue.
 // ---------------------------------------------------------------------------
 constexpr int BLK_K = 216, BLK_STEPS = BLK_K / 4;
-constexpr int BLK_THREADS = 512;
-// LDS tile of densities: (4 NX + 8) x 24 x 24 cells, z rows of 28 (16 lanes
-// 4 octs apart in y and z, 4 consecutive z each, then hit distinct banks)
-constexpr int BLK_ROW = 28, BLK_PLANE = 24 * BLK_ROW;
+constexpr int BLK_THREADS = 256;
+// LDS tile of densities: (4 NX + 8) x 24 x 24 cells, one element of padding
+// after every 4 rows: the 16 lanes of an operand read are 4 cells apart in z and
+// 4 rows in y, 97 elements, so in FP64 they hit 16 distinct pairs of the 32 banks
+// (with rows of 28 and no other padding, all 4 y hit the same ones).
+constexpr int BLK_PLANE = 24 * 24 + 6;
+constexpr __host__ __device__ int blk_row(int y) { return 24 * y + (y >> 2); }
 constexpr __host__ __device__ int blk_tile(int nx) { return (4 * nx + 8) * BLK_PLANE; }
 
-// row stride of the folded locals per (parent, pattern), in terms
-constexpr __host__ __device__ int hrow(int P) { return (hterms(P) + 3) / 4 * 4; }
-// K steps of the own-local part: whole groups of 16 terms (a lane takes 4
-// consecutive terms, one vector load), then steps of 4
-constexpr __host__ __device__ int blk_lsteps(int P) { return (hterms(P) + 3) / 4; }
-// reduced term of K index (step s, k group kq) of the own-local part
-constexpr __host__ __device__ int blk_lterm(int P, int s, int kq) {
-  const int full = hterms(P) / 16 * 4;  // steps in whole groups
-  return s < full ? (s / 4) * 16 + 4 * kq + s % 4 : 4 * s + kq;
+// K order of the stencil: step 6 g + jz, k-group kq: source (jx, jy, jz) with
+// 6 jx + jy = 4 g + kq.  A lane's (jx, jy) stays for 6 steps, and jz is the same
+// for all lanes, so the addresses of the mirror images cost nothing per step.
+constexpr int BLK_GROUPS = BLK_STEPS / 6;
+// place of a lane's (jx, jy): the plus image (from 6 cells before the block's
+// centre along z; bits 0-11), the distance of the minus image along y (9 bits
+// from 12) and jx (from 21)
+constexpr __host__ __device__ int blk_place(int pair) {
+  if (pair >= 36) pair = 35;
+  const int jx = pair / 6, jy = pair % 6;
+  return (jx * BLK_PLANE + blk_row(6 + jy) - blk_row(6)) | (blk_row(6 + jy) - blk_row(5 - jy)) << 12 | jx << 21;
 }
+static_assert(5 * BLK_PLANE + blk_row(11) - blk_row(6) < 4096 && blk_row(11) < 512, "bits of a place");
+
+// row stride of complete locals per cell, in terms
+constexpr __host__ __device__ int hrow(int P) { return (hterms(P) + 3) / 4 * 4; }
+// Folded locals of a parent: pairs of terms (2q, 2q + 1), 8 patterns, 2 terms.
+// A pair is a column tile of the M2L, so that its stores are whole aligned lines
+// and its K loop is as long as its lower degree needs; the block kernel reads 4
+// patterns of a pair as one run.
+constexpr __host__ __device__ int frow(int P) { return (hterms(P) + 1) / 2 * 16; }
+constexpr __host__ __device__ int fold_at(int kappa, int b) { return 16 * (b >> 1) + 2 * kappa + (b & 1); }
+// the own-local part runs two K steps at a time: k-group kq of step 2 s + v has
+// term 8 s + 2 kq + v
+constexpr __host__ __device__ int blk_lpairs(int P) { return (hterms(P) + 7) / 8; }
 // K steps of the level F-1 part: the most terms of one parity pattern
 constexpr __host__ __device__ int blk_psteps(int P) {
   int most = 0;
@@ -77,7 +95,7 @@ constexpr __host__ __device__ int blk_pterm(int P, int e, int k) {
 // table layout (elements): the folded stencil [54][8][2][64], the own locals
 // [steps][2][64], the level F-1 locals [8][steps][2][64]
 constexpr __host__ __device__ int blk_off_l() { return BLK_STEPS * 8 * 2 * 64; }
-constexpr __host__ __device__ int blk_off_p(int P) { return blk_off_l() + blk_lsteps(P) * 2 * 64; }
+constexpr __host__ __device__ int blk_off_p(int P) { return blk_off_l() + 2 * blk_lpairs(P) * 2 * 64; }
 constexpr __host__ __device__ int blk_table(int P) { return blk_off_p(P) + 8 * blk_psteps(P) * 2 * 64; }
 
 // The unfolded stencil G[t][v][o], t in the positive octant (bits: 1/2 or 3/2
@@ -134,15 +152,15 @@ __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int
   const int t = col >> 2, o = col & 3;
   double x = 0.0;
   if (id < blk_off_l()) {
-    const int e = (id >> 7) & 7, k = 4 * (id >> 10) + kq;
-    const int jj[3] = {k / 36, (k / 6) % 6, k % 6};
+    const int e = (id >> 7) & 7, st = id >> 10, pair = 4 * (st / 6) + kq;
+    const int jj[3] = {pair / 6, pair % 6, st % 6};
     for (int minus = 0; minus < 8; ++minus) {
       int v = 0;
       for (int a = 0; a < 3; ++a) v = v * 12 + (((minus >> (2 - a)) & 1) ? 5 - jj[a] : 6 + jj[a]);
       x += chi(e, minus) * G[((size_t)t * 1728 + v) * 4 + o];
     }
   } else if (id < blk_off_p(P)) {
-    const int b = blk_lterm(P, (id - blk_off_l()) >> 7, kq);
+    const int st = (id - blk_off_l()) >> 7, b = 8 * (st >> 1) + 2 * kq + (st & 1);
     if (b < hterms(P)) x = h_reduce(b, [&](int bt) { return l2p_coef(bt, t, o); });
   } else {
     const int s = (id - blk_off_p(P)) >> 7, np = blk_psteps(P), e = s / np;
@@ -152,8 +170,8 @@ __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int
   W[id] = static_cast<H>(x);
 }
 
-// (pattern, term) of folded-local column col (columns sorted by the degree of
-// the term, the pattern slow inside a degree), packed pattern << 8 | term; -1
+// (pattern, term) of column col of the transpose's K order (sorted by the degree
+// of the term, the pattern slow inside a degree), packed pattern << 8 | term; -1
 // past the last
 constexpr __host__ __device__ int m2lf_col(int P, int col) {
   if (col >= 8 * hterms(P)) return -1;
@@ -182,6 +200,14 @@ struct FoldTab {
 };
 template <int P>
 __constant__ const FoldTab<P> c_ft = FoldTab<P>();
+struct BlkPlaces {
+  int v[36];
+  constexpr BlkPlaces() : v() {
+    for (int i = 0; i < 36; ++i) v[i] = blk_place(i);
+  }
+  __device__ int operator[](int i) const { return v[i]; }
+};
+__constant__ const BlkPlaces c_blk_place = BlkPlaces();
 
 // in-place Walsh transform of 8 values
 template <typename H>
@@ -235,223 +261,298 @@ __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[
   }
 }
 
+// Stages the (4 NX + 8) x 24 x 24 cells from (x0, y0, z0) of an n^3 grid into the
+// LDS tile, times sc, zero outside the grid; keep (or null) gets a copy of the
+// block's own cells.  252 threads take 21 rows of 12 pairs at a time; the pairs
+// are aligned to their element only.
+template <int NX, typename TI, typename H, typename Val>
+__device__ __forceinline__ void stage_cells(H* __restrict__ lds, const TI* __restrict__ src, TI* __restrict__ keep, int n,
+                                            int x0, int y0, int z0, Val&& val) {
+  typedef TI ti2 __attribute__((ext_vector_type(2), aligned(sizeof(TI))));
+  constexpr int ROWS = (4 * NX + 8) * 24, FB = 7;
+  const long long at = ((long long)x0 * n + y0) * n + z0;
+  const auto g = gmem(src + at);  // (only dereferenced inside the grid)
+  const int zc = threadIdx.x % 12, r0 = threadIdx.x / 12, z = z0 + 2 * zc;
+  const bool zok = z >= 0 && z < n && threadIdx.x < 252;
+  if (threadIdx.x >= 252) return;
+#pragma unroll 1
+  for (int r = r0; r < ROWS; r += 21 * FB) {
+    ti2 v[FB];
+#pragma unroll
+    for (int u = 0; u < FB; ++u) {
+      const int row = r + 21 * u, tx = row / 24, ty = row - 24 * tx;
+      const bool in = zok && row < ROWS && (unsigned)(x0 + tx) < (unsigned)n && (unsigned)(y0 + ty) < (unsigned)n;
+      v[u] = in ? *(const __attribute__((address_space(1))) ti2*)(g + (unsigned)((tx * n + ty) * n + 2 * zc)) : ti2{0, 0};
+    }
+#pragma unroll
+    for (int u = 0; u < FB; ++u) {
+      const int row = r + 21 * u, tx = row / 24, ty = row - 24 * tx;
+      if (row >= ROWS) continue;
+      H* const to = lds + tx * BLK_PLANE + blk_row(ty) + 2 * zc;
+      to[0] = val(v[u][0]);
+      to[1] = val(v[u][1]);
+      if (keep && tx >= 4 && tx < 4 * NX + 4 && ty >= 4 && ty < 20 && zc >= 2 && zc < 10 && x0 + tx < n && y0 + ty < n &&
+          z < n)
+        *(ti2*)(keep + at + (unsigned)((tx * n + ty) * n + 2 * zc)) = v[u];
+    }
+  }
+}
+
+// The lane's pointers to the images of source (jx, jy) with x plus or minus, y
+// plus or minus, at 6 cells before the block's centre along z.
+template <typename H>
+__device__ __forceinline__ void blk_images(const H* ctr, int q, const H* (&p)[4]) {
+  const int dx = 2 * BLK_PLANE * (q >> 21) + BLK_PLANE, dy = (q >> 12) & 511;
+  p[0] = ctr + (q & 4095);
+  p[1] = p[0] - dy;
+  p[2] = p[0] - dx;
+  p[3] = p[1] - dx;
+}
+template <int JZ, typename H>
+__device__ __forceinline__ void blk_read(const H* const (&p)[4], H (&r)[8]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    r[2 * q] = p[q][6 + JZ];
+    r[2 * q + 1] = p[q][5 - JZ];
+  }
+}
+
 // Segments: n = unigrid cells per axis, tpa = tiles along y and z, tz = tiles
 // along x, field, t = copy of the density to leave in the plan (or null),
-// u = own locals [block][8][hrow] in the compute type (or null: F = 2),
+// u = own locals [block][frow] in the compute type (or null: F = 2),
 // d = complete locals of the blocks' cells [block][hrow] (or null), c = FMM-2:
 // M2P, [block][4][4^3] in the compute type.
-// Tile: NX x 4 x 4 blocks; wave w takes row tile X = w % NX (the 4 x 4 blocks
-// of plane X) and the NX patterns from NX (w / NX).
+// Tile: NX x 4 x 4 blocks; 4 waves: row tile X (the 4 x 4 blocks of plane X),
+// one half of the patterns, and for NX = 1 one of two slices of the K steps.
 // What bounds it: the matrix cores (54 + 13 + 3 K steps of 16 products per row
-// tile at p = 6).  A lane reads the 8 mirror images of its operand from the LDS
-// tile and folds them itself (12 adds for 8 products); B is read through the
-// caches, each fragment once per wave, the NX waves of a plane sharing it.
+// tile at p = 6), and, as vector operations do not run beside FP64 products,
+// everything else a wave executes.  So a lane folds the 8 mirror images of its
+// operand from the LDS tile itself (12 adds for 8 products) at addresses formed
+// once for 6 steps, B comes through the caches at a uniform base, and the
+// epilogue forms addresses once per thread.  Blocks are small so that a CU holds
+// two (FP32: four): one's staging and stores run beside the other's products.
+// blocks (of 4 waves) per compute unit
+template <typename CT, int NX>
+constexpr int blk_occ = Mf<CT>::IDX == 0 ? 2 : NX == 2 ? 3 : 4;
 template <int P, typename CT, typename TI, typename TO, int NX, int DL>
-__global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>::H) > 80000 ? 2 : 4)) void k_block(const Seg* __restrict__ segs, int nseg, IoArg io,
-                                                          const typename Mf<CT>::H* __restrict__ W,
-                                                          unsigned int* __restrict__ stamp_cnt,
-                                                          unsigned long long* __restrict__ stamp_done) {
+__global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
+    const Seg* __restrict__ segs, int nseg, IoArg io, const typename Mf<CT>::H* __restrict__ W,
+    unsigned int* __restrict__ stamp_cnt, unsigned long long* __restrict__ stamp_done) {
   using M = Mf<CT>;
   using H = typename M::H;
   using Acc = typename M::Acc;
-  constexpr int NE = NX, HR = hrow(P), NLS = blk_lsteps(P), NPS = blk_psteps(P);
-  constexpr int OFF_L = blk_off_l(), OFF_P = blk_off_p(P);
-  // epilogue image of the block's results, [8][NX * 16][33]
-  constexpr int EP = 8 * NX * 16 * 33, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
+  constexpr int NE = 4, KS = Mf<CT>::IDX == 0 ? 2 / NX : 2, NR = NX * KS / 2, HR = hrow(P), FR = frow(P);
+  constexpr int NLP = blk_lpairs(P), NPS = blk_psteps(P), OFF_L = blk_off_l(), OFF_P = blk_off_p(P);
+  // own-local pairs of steps of the last K slice, which has one group less
+  constexpr int LSPLIT = KS == 1 ? NLP : NLP < (8 + NPS + 2 * NLP) / 4 ? NLP : (8 + NPS + 2 * NLP) / 4;
+  // epilogue image of the results of NXR row tiles, [slice][half][4][NXR * 16][33]
+  constexpr int NXR = NX / NR, ES = NXR * 16 * 33;
+  constexpr int EP = KS * 8 * ES, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
   __shared__ int spt[8 * NPS * 4];
   const Seg& sg = find_seg(segs, nseg, blockIdx.x);
   const int n = sg.n, nb = n >> 2;
-  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
   TO* __restrict__ phi = io_phi<TO>(io, sg.field);
   TO* __restrict__ g = io_g<TO>(io, sg.field);
-  TI* __restrict__ keep = static_cast<TI*>(sg.t);
   const int lb = blockIdx.x - sg.first_block;
   const int bx0 = (lb / (sg.tpa * sg.tpa)) * NX, by0 = ((lb / sg.tpa) % sg.tpa) * 4, bz0 = (lb % sg.tpa) * 4;
   for (int t = threadIdx.x; t < 8 * NPS * 4; t += BLK_THREADS) spt[t] = c_ft<P>.pt[t / (NPS * 4)][t % (NPS * 4)];
-  // the densities of the tile and 4 cells around, zero outside the grid
-  {
-    constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
-    const int x0 = 4 * bx0 - 4, y0 = 4 * by0 - 4, z0 = 4 * bz0 - 4;
-    const auto grho = gmem(rho);
-#pragma unroll 1
-    for (int e0 = threadIdx.x; e0 < CNT; e0 += FB * BLK_THREADS) {
-      TI v[FB];
-#pragma unroll
-      for (int u = 0; u < FB; ++u) {
-        const int e = e0 + u * BLK_THREADS, z = z0 + e % 24, y = y0 + (e / 24) % 24, x = x0 + e / 576;
-        const bool in = e < CNT && x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
-        v[u] = in ? grho[((long long)x * n + y) * n + z] : TI(0);
-      }
-#pragma unroll
-      for (int u = 0; u < FB; ++u) {
-        const int e = e0 + u * BLK_THREADS, tz = e % 24, ty = (e / 24) % 24, tx = e / 576;
-        if (e < CNT) {
-          lds[tx * BLK_PLANE + ty * BLK_ROW + tz] = static_cast<H>(v[u]);
-          if (keep && tx >= 4 && tx < 4 * NX + 4 && ty >= 4 && ty < 20 && tz >= 4 && tz < 20 && x0 + tx < n &&
-              y0 + ty < n && z0 + tz < n)
-            keep[((long long)(x0 + tx) * n + y0 + ty) * n + z0 + tz] = v[u];
-        }
-      }
-    }
-  }
+  stage_cells<NX>(lds, io_rho<TI>(io, sg.field), static_cast<TI*>(sg.t), n, 4 * bx0 - 4, 4 * by0 - 4, 4 * bz0 - 4,
+                  [](TI v) { return static_cast<H>(v); });
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, eg = w / NX, e0 = eg * NE;
-  const H sx = (e0 & 4) ? H(-1) : H(1), sy = (e0 & 2) ? H(-1) : H(1), sz = (e0 & 1) ? H(-1) : H(1);
-  Acc acc[NE][2];
+  // the wave's first row tile, K slice and half of the patterns
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = KS == 1 ? w & 1 : 0, ks = KS == 1 ? 0 : w & 1,
+            half = w >> 1, e0 = half * NE;
+  const H sx = half ? H(-1) : H(1);
+  Acc acc[NR][NE][2];
 #pragma unroll
-  for (int e = 0; e < NE; ++e) acc[e][0] = acc[e][1] = Acc{0, 0, 0, 0};
-  __syncthreads();
-  // ---- the 12^3 densities: K index k = (36 jx + 6 jy + jz), image "plus" at
-  // centre + j, "minus" at centre - 1 - j along each axis
-  {
-    const H* ctr = lds + (4 * X + 6) * BLK_PLANE + (4 * (i >> 2) + 6) * BLK_ROW + 4 * (i & 3) + 6;
-    int jx = 0, jy = 0, jz = kq;
-    auto aread = [&](H (&r)[8]) {
-      const int px = jx * BLK_PLANE, mx = -BLK_PLANE - px, py = jy * BLK_ROW, my = -BLK_ROW - py;
-      const H *pp = ctr + px + py, *pm = ctr + px + my, *mp = ctr + mx + py, *mm = ctr + mx + my;
-      r[0] = pp[jz];
-      r[1] = pp[-1 - jz];
-      r[2] = pm[jz];
-      r[3] = pm[-1 - jz];
-      r[4] = mp[jz];
-      r[5] = mp[-1 - jz];
-      r[6] = mm[jz];
-      r[7] = mm[-1 - jz];
-      jz += 4;
-      if (jz >= 6) {
-        jz -= 6;
-        if (++jy == 6) {
-          jy = 0;
-          jx = jx < 5 ? jx + 1 : 5;  // (past the last step: a read that is not used)
-        }
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) acc[r][e][0] = acc[r][e][1] = Acc{0, 0, 0, 0};
+  auto products = [&](const H (&a)[NR][NE], const H (&b)[NE][2]) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        acc[r][e][0] = M::op(a[r][e], b[e][0], acc[r][e][0]);
+        acc[r][e][1] = M::op(a[r][e], b[e][1], acc[r][e][1]);
       }
-    };
-    const auto wb = gmem(W + e0 * 128 + lane);
+  };
+  __syncthreads();
+  // ---- the 12^3 densities
+  {
+    const H* ctr = lds + (4 * X + 6) * BLK_PLANE + blk_row(4 * (i >> 2) + 6) + 4 * (i & 3);
+    const auto wb = gmem(W + e0 * 128);  // (uniform base, the lane as a 32-bit offset)
     auto bread = [&](int s, H (&b)[NE][2]) {
 #pragma unroll
       for (int e = 0; e < NE; ++e)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) b[e][t] = wb[s * 1024 + e * 128 + t * 64];
+        for (int t = 0; t < 2; ++t) b[e][t] = (wb + s * 1024 + e * 128 + t * 64)[(unsigned)lane];
     };
-    H r[2][8], b[2][NE][2], a[NE];
-    aread(r[0]);
-    bread(0, b[0]);
-#pragma unroll 1
-    for (int s = 0; s < BLK_STEPS; s += 2) {
+    const H* p[4];
+    H r[NR][8], b[2][NE][2], a[NR][NE];
+    auto aread = [&](auto jc) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int sn = s + u + 1 < BLK_STEPS ? s + u + 1 : BLK_STEPS - 1;
-        bread(sn, b[u ^ 1]);
-        aread(r[u ^ 1]);
-        fold8<NE>(r[u], sx, NE <= 2 ? sy : H(1), NE == 1 ? sz : H(1), a);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int m = 0; m < NR; ++m)
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          acc[e][0] = M::op(a[e], b[u][e][0], acc[e][0]);
-          acc[e][1] = M::op(a[e], b[u][e][1], acc[e][1]);
+        for (int q = 0; q < 4; ++q) {
+          r[m][2 * q] = p[q][m * 4 * BLK_PLANE + 6 + decltype(jc)::value];
+          r[m][2 * q + 1] = p[q][m * 4 * BLK_PLANE + 5 - decltype(jc)::value];
         }
+    };
+    // operands are read one step ahead: images as soon as the last are folded
+    blk_images(ctr, c_blk_place[4 * ks + kq], p);
+    bread(6 * ks, b[0]);
+    aread(std::integral_constant<int, 0>{});
+#pragma unroll 1
+    for (int grp = ks; grp < BLK_GROUPS; grp += KS) {
+      const int gn = grp + KS < BLK_GROUPS ? grp + KS : ks;  // (past the last: read, not used)
+      const int pn = c_blk_place[4 * gn + kq];
+      static_for<6>([&](auto jc) {
+        constexpr int jz = decltype(jc)::value, u = jz & 1;
+#pragma unroll
+        for (int m = 0; m < NR; ++m) fold8<NE>(r[m], sx, H(1), H(1), a[m]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (jz < 5) {
+          bread(6 * grp + jz + 1, b[u ^ 1]);
+        } else {
+          bread(6 * gn, b[u ^ 1]);
+          blk_images(ctr, pn, p);
+        }
+        aread(std::integral_constant<int, (jz + 1) % 6>{});
+        __builtin_amdgcn_sched_barrier(0);
+        products(a, b[u]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+  }
+  // ---- L2P; the lane's blocks, clamped into the grid
+  long long cell[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    cell[r] = ((long long)min(bx0 + X + r, nb - 1) * nb + min(by0 + (i >> 2), nb - 1)) * nb + min(bz0 + (i & 3), nb - 1);
+  if (DL == 1 && sg.u) {
+    typedef H h8 __attribute__((ext_vector_type(8), aligned(16)));
+    const auto wl = gmem(W + OFF_L);
+    const auto own = gmem(static_cast<const H*>(sg.u) + 2 * e0);
+    h8 x[2][NR];
+    H y[2][2][2];
+    // pair of steps s: 4 patterns of 2 terms are one run
+    auto read = [&](int s, h8 (&x)[NR], H (&y)[2][2]) {
+      const int q = min(4 * s + kq, FR / 16 - 1);  // (past the last: the table is zero)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) x[r] = *(const __attribute__((address_space(1))) h8*)(own + cell[r] * FR + 16 * q);
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) y[v][t] = (wl + s * 256 + v * 128 + t * 64)[(unsigned)lane];
+    };
+    const int s0 = KS == 1 || ks ? 0 : LSPLIT, s1 = KS == 1 || !ks ? NLP : LSPLIT;
+    auto step = [&](const h8 (&x)[NR], const H (&y)[2][2]) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+          for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[r][e][t] = M::op(x[r][2 * e + v], y[v][t], acc[r][e][t]);
+    };
+    if (s0 < s1) {
+      read(s0, x[0], y[0]);
+#pragma unroll 1
+      for (int s = s0; s < s1; s += 2) {
+        read(min(s + 1, s1 - 1), x[1], y[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        step(x[0], y[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        read(min(s + 2, s1 - 1), x[0], y[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 < s1) step(x[1], y[1]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  // ---- L2P; the lane's block, clamped into the grid
-  const int cx = min(bx0 + X, nb - 1), cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1);
-  const long long cell = ((long long)cx * nb + cy) * nb + cz;
-  if (sg.u) {
-    typedef H h4 __attribute__((ext_vector_type(4)));
-    const auto own = gmem(static_cast<const H*>(sg.u) + (cell * 8 + e0) * HR);
-    const H* wl = W + OFF_L + lane;
-    constexpr int FULL = hterms(P) / 16;
-#pragma unroll 1
-    for (int c = 0; c < FULL; ++c) {
-      h4 a[NE];
+  if (sg.d && ks == 0) {
+    const auto wp = gmem(W + OFF_P + e0 * (NPS * 128));
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const auto par = gmem(sg.d + cell[r] * HR);
+      double v[NE][NPS];
 #pragma unroll
       for (int e = 0; e < NE; ++e)
-        a[e] = *(const __attribute__((address_space(1))) h4*)(own + e * HR + 16 * c + 4 * kq);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const H b0 = wl[(4 * c + v) * 128], b1 = wl[(4 * c + v) * 128 + 64];
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          acc[e][0] = M::op(a[e][v], b0, acc[e][0]);
-          acc[e][1] = M::op(a[e][v], b1, acc[e][1]);
+        for (int s = 0; s < NPS; ++s) {
+          const int bt = spt[(e0 + e) * (NPS * 4) + 4 * s + kq];
+          const double x = par[bt >= 0 ? bt : 0];
+          v[e][s] = bt >= 0 ? x : 0.0;
         }
-      }
-    }
 #pragma unroll
-    for (int s = 4 * FULL; s < NLS; ++s) {
-      const H b0 = wl[s * 128], b1 = wl[s * 128 + 64];
+      for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        const H a = own[e * HR + 4 * s + kq];
-        acc[e][0] = M::op(a, b0, acc[e][0]);
-        acc[e][1] = M::op(a, b1, acc[e][1]);
-      }
+        for (int s = 0; s < NPS; ++s) {
+          const H a = static_cast<H>(v[e][s]);
+          acc[r][e][0] = M::op(a, (wp + (e * NPS + s) * 128)[(unsigned)lane], acc[r][e][0]);
+          acc[r][e][1] = M::op(a, (wp + (e * NPS + s) * 128 + 64)[(unsigned)lane], acc[r][e][1]);
+        }
     }
   }
-  if (sg.d) {
-    const auto par = gmem(sg.d + cell * HR);
-    const H* wp = W + OFF_P + e0 * (NPS * 128) + lane;
-#pragma unroll
-    for (int e = 0; e < NE; ++e)
-#pragma unroll
-      for (int s = 0; s < NPS; ++s) {
-        const int bt = spt[(e0 + e) * (NPS * 4) + 4 * s + kq];
-        const double v = par[bt >= 0 ? bt : 0];
-        const H a = bt >= 0 ? static_cast<H>(v) : H(0);
-        acc[e][0] = M::op(a, wp[(e * NPS + s) * 128], acc[e][0]);
-        acc[e][1] = M::op(a, wp[(e * NPS + s) * 128 + 64], acc[e][1]);
-      }
-  }
-  // ---- inverse Walsh sums over the patterns: results to LDS as [pattern]
-  // [block][33], each thread transforms whole octets in place, then the block
-  // writes z runs of 16 unigrid cells
-  __syncthreads();
-  constexpr int NR = NX * 16, ES = NR * 33;
-#pragma unroll
-  for (int e = 0; e < NE; ++e)
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) lds[(e0 + e) * ES + (16 * X + M::row(v, kq)) * 33 + 16 * t + i] = acc[e][t][v];
-  __syncthreads();
-#pragma unroll 1
-  for (int q = threadIdx.x; q < NR * 32; q += BLK_THREADS) {
-    H* x = lds + (q >> 5) * 33 + (q & 31);
-    H y[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = x[e * ES];
-    walsh8(y);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
-  }
-  __syncthreads();
-  // phi = sphi acc, g_d = sgr tau_d acc, with the Walsh sum's 1/8 in acc
+  // phi = sphi acc, g_d = sgr tau_d acc, with the Walsh sum's 1/8.  Thread (y, z)
+  // of the tile's 16 x 16 columns along x; position in the block 0..3: the minus
+  // images are 0, 1 (3/2, 1/2 out)
   const H* const m2p = reinterpret_cast<const H*>(sg.c);
   const double dx = 1.0 / n, sphi = (DL == 1 ? 0.5 : 0.25) * dx * dx, sgr = (DL == 1 ? -0.25 : -0.0625) * dx;
   const long long N = (long long)n * n * n;
-  const int ncomp = g ? 4 : 1;
-#pragma unroll 1
-  for (int q = threadIdx.x; q < 4 * NX * 256 * ncomp; q += BLK_THREADS) {
-    const int z = q & 15, y = (q >> 4) & 15, x = (q >> 8) % (4 * NX), o = (q >> 8) / (4 * NX);
-    const int ux = 4 * bx0 + x, uy = 4 * by0 + y, uz = 4 * bz0 + z;
-    if (ux >= n || uy >= n || uz >= n) continue;
-    // position in the block 0..3: the minus images are 0, 1 (3/2, 1/2 out)
-    const int qx = x & 3, qy = y & 3, qz = z & 3;
-    const int minus = ((qx < 2) << 2) | ((qy < 2) << 1) | (qz < 2);
-    const int t = ((qx == 0 || qx == 3) << 2) | ((qy == 0 || qy == 3) << 1) | (qz == 0 || qz == 3);
-    const int row = 16 * (x >> 2) + 4 * (y >> 2) + (z >> 2);
-    double val = 0.125 * (double)lds[minus * ES + row * 33 + 4 * t + o];
-    if (o && (minus >> (3 - o)) & 1) val = -val;
-    if constexpr (DL == 2)
-      val += (double)m2p[((((long long)(ux >> 2) * nb + (uy >> 2)) * nb + (uz >> 2)) * 4 + o) * 64 + (qx * 4 + qy) * 4 + qz];
-    const long long u = ((long long)ux * n + uy) * n + uz;
-    if (o == 0)
-      phi[u] = (TO)(sphi * val);
-    else
-      g[(o - 1) * N + u] = (TO)(sgr * val);
-  }
+  const int z = threadIdx.x & 15, y = threadIdx.x >> 4, qy = y & 3, qz = z & 3;
+  const int uy = 4 * by0 + y, uz = 4 * bz0 + z, myz = (qy < 2) << 1 | (qz < 2);
+  const int tyz = (qy == 0 || qy == 3) << 1 | (qz == 0 || qz == 3);
+  const H* const res = lds + myz * ES + (4 * (y >> 2) + (z >> 2)) * 33 + 4 * tyz;
+  const double sc[4] = {0.125 * sphi, 0.125 * sgr, (qy < 2 ? -0.125 : 0.125) * sgr, (qz < 2 ? -0.125 : 0.125) * sgr};
+  const long long blk0 = ((long long)bx0 * nb + (uy >> 2)) * nb + (uz >> 2), pyz = qy * 4 + qz;
+  const unsigned at = (unsigned)(y * n + z);
+  static_for<NR>([&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    // inverse Walsh sums: over y and z in the wave, over x (the two halves of the
+    // patterns) when the results are read back as z runs
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const H p0 = acc[R][0][t][v] + acc[R][1][t][v], m0 = acc[R][0][t][v] - acc[R][1][t][v],
+                p1 = acc[R][2][t][v] + acc[R][3][t][v], m1 = acc[R][2][t][v] - acc[R][3][t][v];
+        H* const to = lds + (ks * 2 + half) * 4 * ES + (16 * X + M::row(v, kq)) * 33 + 16 * t + i;
+        to[0] = p0 + p1;
+        to[ES] = m0 + m1;
+        to[2 * ES] = p0 - p1;
+        to[3 * ES] = m0 - m1;
+      }
+    __syncthreads();
+    if (uy < n && uz < n)
+      static_for<4 * NXR>([&](auto xc) {
+        constexpr int x = decltype(xc)::value, qx = x & 3, XT = x >> 2, XB = R + XT;
+        constexpr int ro = (qx == 0 || qx == 3 ? 16 : 0) + 16 * XT * 33;
+        const int ux = 4 * (bx0 + XB) + qx;
+        if (ux >= n) return;
+        const long long row = ((long long)ux * n + 4 * by0) * n + 4 * bz0;  // (uniform)
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          if (o && !g) break;
+          H a = res[ro + o], c = res[4 * ES + ro + o];
+          if constexpr (KS == 2) {
+            a += res[8 * ES + ro + o];
+            c += res[12 * ES + ro + o];
+          }
+          double val = (double)(qx < 2 ? a - c : a + c) * (o == 1 && qx < 2 ? -sc[1] : sc[o]);
+          if constexpr (DL == 2)
+            val = fma((double)m2p[((blk0 + (long long)XB * nb * nb) * 4 + o) * 64 + qx * 16 + pyz], o ? sgr : sphi, val);
+          if (o == 0)
+            (phi + row)[at] = (TO)val;
+          else
+            (g + (o - 1) * N + row)[at] = (TO)val;
+        }
+      });
+  });
   if (stamp_cnt) {
     // the field's last block records when the field is complete
     __syncthreads();
@@ -472,7 +573,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
 // its cell P; their Walsh pattern kappa over those children takes the place of
 // the child, so that a row of the result is already folded the way k_block
 // reads it:
-//   Lw[P][kappa][b] = sum_children chi_kappa(sigma) sigma^b L(child, b)
+//   Lw[P][(kappa, b)] = sum_children chi_kappa(sigma) sigma^b L(child, b)
 //                   = chi_kappa(tau) sum_e chi_e(tau) OUT(e; kappa, b) / 8,
 // P the cell tau of the oct.  Columns are sorted by |b| (kappa slow inside a
 // degree), K by |a| (K index 27 a + source), so a tile of 16 columns needs a
@@ -481,11 +582,27 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_tile(NX) * sizeof(typename Mf<CT>
 constexpr __host__ __device__ int fold_ntiles(int op, int P) {
   return op == FO_M2L ? (8 * hterms(P) + 15) / 16 : op == FO_M2P ? 16 : (hterms(P) + 15) / 16;
 }
+// steps of the forward operators before the chunks, for term 0
+constexpr int FOLD_HEAD = 7;
 constexpr __host__ __device__ int fold_steps(int op, int P, int nmax, int t) {
-  if (op == FO_M2P) return (27 * hterms(nmax) + 3) / 4;
-  const int m = h_degree(op == FO_M2L ? 16 * t / 8 : 16 * t);
-  if (op == FO_M2L) return (27 * hterms(P - m < nmax ? P - m : nmax) + 3) / 4;
+  const int m = h_degree(op == FO_M2L ? 2 * t : 16 * t);
+  if (op == FO_M2L || op == FO_M2P) {
+    const int q = op == FO_M2P || nmax < P - m ? nmax : P - m;
+    return FOLD_HEAD + 27 * ((hterms(q) - 1 + 3) / 4);
+  }
   return m > nmax ? 0 : op == FO_M2LT ? 54 * hterms(P - m) : 27 * 64;
+}
+// (term, source) of k-group kq of a step; the term past the last for padding
+__host__ __device__ inline void fold_k(int op, int st, int kq, int* term, int* src) {
+  const bool head = op == FO_M2L || op == FO_M2P;
+  if (head && st < FOLD_HEAD) {
+    *term = 4 * st + kq < 27 ? 0 : 0xffff;
+    *src = (4 * st + kq) % 27;
+    return;
+  }
+  const int c = st - (head ? FOLD_HEAD : 0);
+  *term = (head ? 1 : 0) + 4 * (c / 27) + kq;
+  *src = c % 27;
 }
 
 // B fragments in the compute type, [fragment (tile, step)][8 patterns][64];
@@ -498,10 +615,11 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
   const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
-  const int k = 4 * (f - tiles[t].y) + (lane >> 4), cb = m2lf_col(P, 16 * t + (lane & 15));
-  const int a = k / 27, s = k % 27, kap = cb >> 8, b = cb & 255;
+  const int kap = (lane >> 1) & 7, b = 2 * t + (lane & 1);  // fold_at
+  int a, s;
+  fold_k(FO_M2L, f - tiles[t].y, lane >> 4, &a, &s);
   double x = 0.0;
-  if (cb >= 0 && a < hterms(nmax) && h_degree(a) + h_degree(b) <= P) {
+  if (b < hterms(P) && a < hterms(nmax) && h_degree(a) + h_degree(b) <= P) {
     const int ea = h_exp(a), eb = h_exp(b), pa = h_parity(a), pb = h_parity(b);
     const int g = mi_index(mi_a(ea) + mi_a(eb), mi_b(ea) + mi_b(eb), mi_c(ea) + mi_c(eb));
     const int j[3] = {s / 9, (s / 3) % 3, s % 3};
@@ -524,36 +642,49 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
 }
 
 // OP 1 is the transpose: rows are the octs of source cells J, the operands the
-// cotangents of the Lw rows of the 27 x 8 cells P around (K index 27 column +
-// P, columns sorted by |b|; an image's sign is chi_kappa), columns the terms a
+// cotangents of the Lw rows of the 27 x 8 cells P around (K terms: the columns,
+// sorted by |b|; an image's sign is chi_kappa), columns the terms a
 // of one J, the results M_bar(J = sigma, a) = sigma^a sum_e chi_e(sigma) OUT(e; a).
 // OP 2 is FMM-2's M2P (Sec. 4): rows are the octs of level F, K as in M2L with
 // every term, columns (o, t) the outputs at the 4^3 unigrid cells t of the
-// positive octant's cell.  OP 3 is its transpose: K index 27 (32 kappa + 4 t + o)
-// + P over the cotangents of the cells P, folded about each P's own centre.
+// positive octant's cell.  OP 3 is its transpose: K term 32 kappa + 4 t + o of
+// the cotangents of the cells P, folded about each P's own centre.
 //
 // Segments: n = source grid cells per axis, tpa = tiles along y and z, tz =
 // tiles along x; OP 0: a = harmonic multipoles of the source grid in the compute
 // type, [term][(n + 6)^3] (terms padded to a multiple of 4), u = result in the
-// compute type or b = result in FP64, [n^3][8][hrow]; OP 2: the same, u =
+// compute type or b = result in FP64, [n^3][frow]; OP 2: the same, u =
 // [n^3][4][4^3]; OP 1, 3: a = cotangent planes [K term][(n + 6)^3] in the compute
 // type, b = result, planes [term][(n + 6)^3].
-// Tile: MT x 4 x 4 octs.  8 waves: 8 / NE groups of NE patterns, KS slices of
-// the K steps, MT / NR groups of NR row tiles (a row tile: the 4 x 4 octs of a
-// plane).  A block sums NT column tiles over all 8 patterns, so the inverse
-// Walsh sums happen in its epilogue.  Blocks: column groups x T tiles, the
-// heaviest group (lowest degrees) first; a group whose K loop is long against
-// the launch shares it among several blocks (grid.parts), each summing a run
-// of chunks: they leave their sums in `part`, which k_m2lf_sum adds in order.
-// What bounds it: the matrix cores.  LDS holds 4 terms of the tile's cells and
-// 2 around; a lane reads the 8 mirror images of an operand and folds them (8
-// adds for two patterns), which NT products amortise; each B fragment is read
-// from L2 once per wave for NR row tiles.
+// Tile: MT x 4 x 4 octs.  NW waves: 8 / NE groups of NE patterns, MT / NR
+// groups of NR row tiles (a row tile: the 4 x 4 octs of a plane).  A block sums
+// NT column tiles over all 8 patterns, so the inverse Walsh sums happen in its
+// epilogue.  Blocks: column groups x T tiles, the heaviest group (lowest
+// degrees) first; a group whose K loop is long against the launch shares it
+// among several blocks (grid.parts), each summing a run of chunks: they leave
+// their sums in `part`, which k_m2lf_sum adds in order.
+// What bounds it: the matrix cores, and in FP64 every vector operation beside
+// them, as those do not overlap (an FP64 product of 16 x 16 x 4 takes 64 cycles
+// of a SIMD, a fused multiply-add 4.5).  So a lane folds the 8 mirror images of
+// its operand once for NE x NT products (12 adds for 4 patterns), its addresses
+// change every third step, B comes at a uniform base, the next step's operands
+// and the next chunk's planes are read beside the products.  Two blocks run per
+// compute unit, so that one's staging and stores lie beside the other's
+// products.  At 64^3 source cells, p = 6 (the finest level of a 256^3 grid):
+// FP64 1785 us -> 1460 us (835 us of products at 2.4 GHz), FP32 1216 -> 885 us,
+// of which the 839 (420) MB of results are 180 (90) us of copy rate.
 //
-// what column col stands for, -1 past the last
+// LDS tile of k_m2lf: rows of 12 cells along z, the even cells first (the 16
+// octs of an operand read are 2 cells apart in z and in y), with a stride of 14:
+// two rows are 28 elements, so in FP64 the 16 lanes of a read hit 16 distinct
+// pairs of the 32 banks
+constexpr int FOLD_ROW = 14, FOLD_PLANE = 12 * FOLD_ROW;
+constexpr __host__ __device__ int fold_z(int z) { return (z & 1) * 6 + (z >> 1); }
+// what column col stands for: OP 0 the column and its pattern from bit 16; -1
+// past the last
 template <int P, int OP>
 __device__ __forceinline__ int fold_colmap(int col) {
-  if constexpr (OP == 0) return col < 8 * hterms(P) ? c_ft<P>.col[col] : -1;
+  if constexpr (OP == 0) return 2 * (col >> 4) + (col & 1) < hterms(P) ? col | ((col >> 1) & 7) << 16 : -1;
   return col < (OP == 2 ? 256 : hterms(P)) ? col : -1;
 }
 // result q of a group of row tiles: consecutive threads take the columns of a
@@ -562,64 +693,70 @@ template <int OP, int NT>
 __device__ __forceinline__ int m2lf_qcol(int q) { return OP & 1 ? (q >> 4) % (16 * NT) : q % (16 * NT); }
 template <int OP, int NT>
 __device__ __forceinline__ int m2lf_qrow(int q) { return OP & 1 ? q & 15 : (q / (16 * NT)) & 15; }
-// inverse Walsh sum over the patterns, to the 8 cells of the oct of `row`
+// inverse Walsh sum over the patterns, to the 8 cells of the oct (dx, row) of the
+// tile at octs (ox0, oy0, oz0) (uniform; the lane's part of an address is a
+// 32-bit offset)
 template <int P, typename H, int OP>
-__device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox, int oy0, int oz0, int row, double (&y)[8]) {
-  constexpr int HR = hrow(P);
-  const int ns = sg.n, nsp = ns + 6, no = ns >> 1, oy = oy0 + (row >> 2), oz = oz0 + (row & 3);
-  if (cb < 0 || ox >= no || oy >= no || oz >= no) return;
+__device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox0, int oy0, int oz0, int dx, int row,
+                                         double (&y)[8]) {
+  constexpr int FR = frow(P);
+  const int ns = sg.n, nsp = ns + 6, no = ns >> 1, dy = row >> 2, dz = row & 3;
+  if (cb < 0 || ox0 + dx >= no || oy0 + dy >= no || oz0 + dz >= no) return;
   walsh8(y);
   if constexpr (OP == 2) {
     H* const ut = static_cast<H*>(sg.u);
     const int o = cb >> 6, eo = o ? 8 >> o : 0, t0 = (cb >> 4) & 3, t1 = (cb >> 2) & 3, t2 = cb & 3;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
-                          (2 * oz + 1 - (m & 1));
+      const long long p = ((long long)(2 * (ox0 + dx) + 1 - ((m >> 2) & 1)) * ns + (2 * (oy0 + dy) + 1 - ((m >> 1) & 1))) * ns +
+                          (2 * (oz0 + dz) + 1 - (m & 1));
       const int pos = ((m & 4 ? 3 - t0 : t0) * 4 + (m & 2 ? 3 - t1 : t1)) * 4 + (m & 1 ? 3 - t2 : t2);
       ut[(p * 4 + o) * 64 + pos] = static_cast<H>(m & eo ? -y[m] : y[m]);
     }
   } else if constexpr (OP & 1) {
     const int pa = c_ft<P>.par[cb];
-    const long long ncellp = (long long)nsp * nsp * nsp;
+    double* const b0 = sg.b + ((long long)(2 * ox0 + 4) * nsp + 2 * oy0 + 4) * nsp + 2 * oz0 + 4;
+    double* const bl = b0 + cb * ((long long)nsp * nsp * nsp) + (2 * (dx * nsp + dy) * nsp + 2 * dz);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const long long c = ((long long)(2 * ox + 4 - ((m >> 2) & 1)) * nsp + (2 * oy + 4 - ((m >> 1) & 1))) * nsp +
-                          (2 * oz + 4 - (m & 1));
-      sg.b[cb * ncellp + c] = chi(pa, m) * y[m];
-    }
+    for (int m = 0; m < 8; ++m)
+      bl[-(((m >> 2) & 1) * nsp + ((m >> 1) & 1)) * nsp - (m & 1)] = chi(pa, m) * y[m];
   } else {
-    const int kap = cb >> 8, b = cb & 255;
-    H* const ut = static_cast<H*>(sg.u);
+    const int kap = cb >> 16;
+    const unsigned off = (unsigned)((2 * (dx * ns + dy) * ns + 2 * dz) * FR + (cb & 0xffff));
+    const long long p0 = ((long long)2 * ox0 * ns + 2 * oy0) * ns + 2 * oz0;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       // cell tau of the oct: minus bits m
-      const long long p = ((long long)(2 * ox + 1 - ((m >> 2) & 1)) * ns + (2 * oy + 1 - ((m >> 1) & 1))) * ns +
-                          (2 * oz + 1 - (m & 1));
+      const long long p = (p0 + ((m & 4 ? 0 : 1) * ns + (m & 2 ? 0 : 1)) * ns + (m & 1 ? 0 : 1)) * FR;
       const double v = chi(kap, m) * y[m];
-      if (ut)
-        ut[(p * 8 + kap) * HR + b] = static_cast<H>(v);
+      if (sg.u)
+        (static_cast<H*>(sg.u) + p)[off] = static_cast<H>(v);
       else
-        sg.b[(p * 8 + kap) * HR + b] = v;
+        (sg.b + p)[off] = v;
     }
   }
 }
-template <int P, typename CT, int OP, int MT, int NT, int NE, int KS>
-__global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, int nseg, int T,
-                                                 const int2* __restrict__ tiles,
-                                                 const typename Mf<CT>::H* __restrict__ W, const M2lGrid grid,
-                                                 double* __restrict__ part) {
+// column tiles per pass of the epilogue
+template <int NT>
+constexpr int m2lf_nte = NT % 2 ? NT : NT / 2;
+template <int P, typename CT, int OP, int MT, int NT, int NE, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ segs, int nseg, int T,
+                                                     const int2* __restrict__ tiles,
+                                                     const typename Mf<CT>::H* __restrict__ W, const M2lGrid grid,
+                                                     double* __restrict__ part) {
   using M = Mf<CT>;
   using H = typename M::H;
   using Acc = typename M::Acc;
-  constexpr int NR = MT * KS / NE, NG = 8 / NE, NX = MT / NR;
-  static_assert(NG * KS * NX == 8, "8 waves");
-  constexpr int CELLS = (2 * MT + 4) * 144, CS = 16 * NT + 1;
-  constexpr int EP = KS * NX * 8 * 16 * CS, SZ = EP > 4 * CELLS ? EP : 4 * CELLS;
+  constexpr int NR = 8 * MT / (NE * NW), NG = 8 / NE, NX = MT / NR, THR = 64 * NW;
+  static_assert(NG * NX == NW && NX * NR == MT, "the waves' shares");
+  constexpr bool HEAD = OP == FO_M2L || OP == FO_M2P;
+  constexpr int NTERM = OP == 3 ? 256 : OP == 1 ? 8 * hterms(P) : hterms(P);
+  constexpr int ROW = FOLD_ROW, PLANE = FOLD_PLANE;
+  constexpr int NTE = m2lf_nte<NT>, CELLS = (2 * MT + 4) * PLANE, CS = 16 * NTE + 1, NPL = HEAD ? 5 : 4;
+  constexpr int EP = NX * 8 * 16 * CS, SZ = EP > NPL * CELLS ? EP : NPL * CELLS;
+  typedef H h2 __attribute__((ext_vector_type(2), aligned(sizeof(H))));
+  constexpr int RPP = (2 * MT + 4) * 12, RPT = THR / 6, FB = (4 * RPP + RPT - 1) / RPT;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
-  __shared__ int4 ktab[108];  // per K index of a chunk: plus image, and the distances to the minus ones
-  constexpr int NTERM = OP == 3 ? 256 : OP == 1 ? 8 * hterms(P) : hrow(P);
-  __shared__ float4 tsg[NTERM];  // per K term: the sign of a minus image along each axis
   __shared__ int scol[16 * NT];
   int grp = 0;
   while (grp + 1 < grid.ng && (int)blockIdx.x >= grid.first[grp + 1]) ++grp;
@@ -628,32 +765,20 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
   const int nsp = sg.n + 6, tb = lbk - sg.first_block;
   const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
   const long long ncellp = (long long)nsp * nsp * nsp;
-  const auto src = gmem(reinterpret_cast<const H*>(sg.a));
-  int vt[NT], off[NT];
+  // chunks and first fragment of each column tile
+  int nc[NT], off[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int2 e = tiles[T0 + t];
-    vt[t] = e.x;
+    nc[t] = e.x ? (e.x - (HEAD ? FOLD_HEAD : 0)) / 27 : 0;
     off[t] = e.y;
   }
-  for (int k = threadIdx.x; k < 108; k += 512) {
-    const int s = k % 27, jx = s / 9, jy = (s / 3) % 3, jz = s % 3;
-    ktab[k] = int4{(k / 27) * CELLS + jx * 144 + jy * 12 + jz, (2 * jx + 1) * 144, (2 * jy + 1) * 12, 2 * jz + 1};
-  }
-  for (int c = threadIdx.x; c < 16 * NT; c += 512) {
-    const int col = 16 * T0 + c;
-    scol[c] = fold_colmap<P, OP>(col);
-  }
-  for (int t = threadIdx.x; t < NTERM; t += 512) {
-    const int e = OP == 3 ? t >> 5 : OP == 1 ? c_ft<P>.col[t] >> 8 : t < hterms(P) ? c_ft<P>.par[t] : 0;
-    tsg[t] = float4{e & 4 ? -1.f : 1.f, e & 2 ? -1.f : 1.f, e & 1 ? -1.f : 1.f, 0.f};
-  }
+  for (int c = threadIdx.x; c < 16 * NT; c += THR) scol[c] = fold_colmap<P, OP>(16 * T0 + c);
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int e0 = (w % NG) * NE, ks = (w / NG) % KS, xg = w / (NG * KS);
-  const H sx = (e0 & 4) ? H(-1) : H(1), sy = (e0 & 2) ? H(-1) : H(1), sz = (e0 & 1) ? H(-1) : H(1);
-  // the lane's oct: image "plus 0" of the wave's first row tile
-  const H* ctr = lds + (2 * xg * NR + 3) * 144 + (2 * (i >> 2) + 3) * 12 + 2 * (i & 3) + 3;
+  const int e0 = (w % NG) * NE, xg = w / NG;
+  // the lane's oct: its first cell but two, in the wave's first row tile
+  const H* const oct = lds + 2 * xg * NR * PLANE + 2 * (i >> 2) * ROW + (i & 3);
   Acc acc[NR][NE][NT];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
@@ -661,149 +786,199 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
     for (int e = 0; e < NE; ++e)
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[r][e][t] = Acc{0, 0, 0, 0};
-  const H* we = W + e0 * 64 + lane;
-  // K steps [sa, sb) of chunk c (steps 27 c ..), column tiles 0 .. NA - 1
-  auto run = [&](auto nac, int c, int sa, int sb) {
-    constexpr int NA = decltype(nac)::value;
-    int s = sa + (ks - sa % KS + KS) % KS;
-    if (s >= sb) return;
-    auto aread = [&](int st, H (&r)[NR][8], float (&g)[3]) {
-      const int k = 4 * (st - 27 * c) + kq;  // < 108
-      const int4 q = ktab[k];
-      const float4 sg4 = tsg[4 * c + ((k * 38) >> 10)];  // k / 27
-      g[0] = sg4.x;
-      g[1] = sg4.y;
-      g[2] = sg4.z;
-      const H *p0 = ctr + q.x, *p1 = p0 - q.z, *p2 = p0 - q.y, *p3 = p1 - q.y;
+  // Planes of the tile's cells and two around from term t0 on (zero past the
+  // terms and the grid), to registers and then to slots at, at + 1, ...: CNT
+  // planes of RPP rows of 6 pairs along z.  The pairs are aligned to their
+  // element only; one that reaches past the grid is halo.
+  const int pz = threadIdx.x % 6, r0 = threadIdx.x / 6;
+  const auto src =
+      gmem(reinterpret_cast<const H*>(sg.a) + ((long long)(2 * ox0 + 1) * nsp + 2 * oy0 + 1) * nsp + 2 * oz0 + 1);
+  auto fetch = [&](auto cnt, int t0, h2* v) {
+    constexpr int ROWS = decltype(cnt)::value * RPP, N = (ROWS + RPT - 1) / RPT;
+    const bool zok = 2 * oz0 + 2 * pz + 2 < nsp && r0 < RPT;
+    const auto p = src + t0 * ncellp;
+    unsigned in = 0;
 #pragma unroll
-      for (int m = 0; m < NR; ++m) {
-        r[m][0] = p0[m * 288];
-        r[m][1] = p0[m * 288 - q.w];
-        r[m][2] = p1[m * 288];
-        r[m][3] = p1[m * 288 - q.w];
-        r[m][4] = p2[m * 288];
-        r[m][5] = p2[m * 288 - q.w];
-        r[m][6] = p3[m * 288];
-        r[m][7] = p3[m * 288 - q.w];
-      }
-    };
-    auto bread = [&](int st, H (&b)[NE][NA]) {
+    for (int u = 0; u < N; ++u) {
+      const int row = r0 + u * RPT, pn = row / RPP, q = row - pn * RPP, x = q / 12, y = q - 12 * x;
+      const bool ok = zok && row < ROWS && t0 + pn < NTERM && 2 * ox0 + 1 + x < nsp && 2 * oy0 + 1 + y < nsp;
+      v[u] = *(const __attribute__((address_space(1))) h2*)(p + (ok ? pn * ncellp + (unsigned)((x * nsp + y) * nsp + 2 * pz) : 0));
+      in |= (unsigned)ok << u;
+    }
+    return in;
+  };
+  auto place = [&](auto cnt, const h2* v, unsigned in, int at) {
+    constexpr int ROWS = decltype(cnt)::value * RPP, N = (ROWS + RPT - 1) / RPT;
 #pragma unroll
-      for (int t = 0; t < NA; ++t) {
-        const auto p = gmem(we + (size_t)(off[t] + st) * 512);
-#pragma unroll
-        for (int e = 0; e < NE; ++e) b[e][t] = p[e * 64];
-      }
-    };
-    H r[2][NR][8], b[2][NE][NA], a[NE];
-    float g[2][3];
-    aread(s, r[0], g[0]);
-    bread(s, b[0]);
-#pragma unroll 1
-    for (; s < sb; s += 2 * KS) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int st = s + u * KS, sn = st + KS < sb ? st + KS : s;
-        if (u == 0 || st < sb) {
-          bread(sn, b[u ^ 1]);
-          aread(sn, r[u ^ 1], g[u ^ 1]);
-          __builtin_amdgcn_sched_barrier(0);
-          const H gx = NE <= 4 ? sx * (H)g[u][0] : (H)g[u][0], gy = NE <= 2 ? sy * (H)g[u][1] : (H)g[u][1], gz = NE == 1 ? sz * (H)g[u][2] : (H)g[u][2];
-#pragma unroll
-          for (int m = 0; m < NR; ++m) {
-            fold8<NE>(r[u][m], gx, gy, gz, a);
-#pragma unroll
-            for (int e = 0; e < NE; ++e)
-#pragma unroll
-              for (int t = 0; t < NA; ++t) acc[m][e][t] = M::op(a[e], b[u][e][t], acc[m][e][t]);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
+    for (int u = 0; u < N; ++u) {
+      const int row = r0 + u * RPT, pn = row / RPP, q = row - pn * RPP;
+      if (row >= ROWS || r0 >= RPT) continue;
+      H* const to = lds + (at + pn) * CELLS + q * ROW + pz;
+      const bool ok = in >> u & 1;
+      to[0] = ok ? v[u][0] : H(0);
+      to[6] = ok ? v[u][1] : H(0);
     }
   };
-  // terms 4 c .. 4 c + 3 per chunk: 27 K steps
-  const int nch = (vt[0] + 26) / 27, c1 = (ip + 1) * nch / np;
-  for (int c = ip * nch / np; c < c1; ++c) {
-    __syncthreads();
-    constexpr int CNT = 4 * CELLS, FB = 7;
-#pragma unroll 1
-    for (int q0 = threadIdx.x; q0 < CNT; q0 += FB * 512) {
-      H v[FB];
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 4> four{};
+  constexpr bool AHEAD = FB <= 10;  // the next chunk is read beside a chunk's products
+  h2 nv[FB];
+  unsigned nin = 0;
+  auto bread = [&](auto nac, int st, H (&b)[NE][decltype(nac)::value]) {
 #pragma unroll
-      for (int u = 0; u < FB; ++u) {
-        const int q = q0 + u * 512, cell = q % CELLS, z = 2 * oz0 + 1 + cell % 12, y = 2 * oy0 + 1 + (cell / 12) % 12,
-                  x = 2 * ox0 + 1 + cell / 144;
-        v[u] = q < CNT && x < nsp && y < nsp && z < nsp
-                   ? src[(4 * c + q / CELLS) * ncellp + ((long long)x * nsp + y) * nsp + z]
-                   : H(0);
-      }
+    for (int t = 0; t < decltype(nac)::value; ++t) {
+      // (uniform base, the lane as a 32-bit offset)
+      const auto p = gmem(W + ((size_t)(off[t] + st) * 8 + e0) * 64);
 #pragma unroll
-      for (int u = 0; u < FB; ++u)
-        if (q0 + u * 512 < CNT) lds[q0 + u * 512] = v[u];
+      for (int e = 0; e < NE; ++e) b[e][t] = (p + e * 64)[(unsigned)lane];
     }
-    __syncthreads();
-    const int end = min(27 * c + 27, vt[0]);
-    int cur = 27 * c;
-    count_down<NT>([&](auto nac) {
-      constexpr int NA = decltype(nac)::value;
-      const int to = min(end, vt[NA - 1]);
-      if (to > cur) {
-        run(nac, c, cur, to);
-        cur = to;
-      }
+  };
+  auto products = [&](auto nac, const H (&a)[NR][NE], H (&b)[NE][decltype(nac)::value]) {
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int t = 0; t < decltype(nac)::value; ++t) acc[m][e][t] = M::op(a[m][e], b[e][t], acc[m][e][t]);
+  };
+  // chi of the axes the wave's patterns share
+  const H cx = NE <= 4 && (e0 & 4) ? H(-1) : H(1), cy = NE <= 2 && (e0 & 2) ? H(-1) : H(1),
+          cz = NE == 1 && (e0 & 1) ? H(-1) : H(1);
+  // the 27 sources of chunk c
+  auto run = [&](auto nac, int c, bool more) {
+    constexpr int NA = decltype(nac)::value;
+    const int t = (HEAD ? 1 : 0) + 4 * c + kq;  // the lane's term, and the signs of its minus images
+    const int par = t >= NTERM ? 0 : OP == 3 ? t >> 5 : OP == 1 ? c_ft<P>.col[t] >> 8 : c_ft<P>.par[t];
+    const H gx = par & 4 ? -cx : cx, gy = par & 2 ? -cy : cy, gz = par & 1 ? -cz : cz;
+    const int base = (HEAD ? FOLD_HEAD : 0) + 27 * c;
+    const H* const pl = oct + kq * CELLS;
+    const H* p[4];
+    auto images = [&](int q) {
+      const int jx = q / 3, jy = q - 3 * jx;
+      p[0] = pl + (3 + jx) * PLANE + (3 + jy) * ROW;
+      p[1] = pl + (3 + jx) * PLANE + (2 - jy) * ROW;
+      p[2] = pl + (2 - jx) * PLANE + (3 + jy) * ROW;
+      p[3] = pl + (2 - jx) * PLANE + (2 - jy) * ROW;
+    };
+    auto aread = [&](auto jc, H (&r)[NR][8]) {
+      constexpr int jz = decltype(jc)::value;
+#pragma unroll
+      for (int m = 0; m < NR; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          r[m][2 * q] = p[q][m * 2 * PLANE + fold_z(3 + jz)];
+          r[m][2 * q + 1] = p[q][m * 2 * PLANE + fold_z(2 - jz)];
+        }
+    };
+    // operands are read one step ahead: images as soon as the last are folded
+    H r[NR][8], b[3][NE][NA];
+    images(0);
+    bread(nac, base, b[0]);
+    aread(std::integral_constant<int, 0>{}, r);
+    if (AHEAD && more) {
+      nin = fetch(four, (HEAD ? 1 : 0) + 4 * (c + 1), nv);
+      asm volatile("" ::: "memory");  // (the loads stay up here)
+    }
+#pragma unroll 1
+    for (int q = 0; q < 9; ++q)
+      static_for<3>([&](auto jc) {
+        constexpr int jz = decltype(jc)::value, nx = (jz + 1) % 3;
+        H a[NR][NE];
+#pragma unroll
+        for (int m = 0; m < NR; ++m) fold8<NE>(r[m], gx, gy, gz, a[m]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (jz == 2) {
+          const int qn = q < 8 ? q + 1 : 0;  // (past the last: read, not used)
+          images(qn);
+          bread(nac, base + 3 * qn, b[nx]);
+        } else {
+          bread(nac, base + 3 * q + jz + 1, b[nx]);
+        }
+        aread(std::integral_constant<int, nx>{}, r);
+        __builtin_amdgcn_sched_barrier(0);
+        products(nac, a, b[jz]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+  };
+  const int c0 = ip * nc[0] / np, c1 = (ip + 1) * nc[0] / np;
+  const bool head = HEAD && ip == 0;
+  if (c0 < c1) nin = fetch(four, (HEAD ? 1 : 0) + 4 * c0, nv);
+  if (head) {
+    h2 hv[(RPP + RPT - 1) / RPT];
+    const unsigned hin = fetch(one, 0, hv);
+    place(one, hv, hin, 4);
+  }
+  if (c0 < c1) place(four, nv, nin, 0);
+  __syncthreads();
+  if (head) {
+    // term 0: 4 sources a step, at the lane's own places
+    const H* const pl = oct + 4 * CELLS;
+    H b[2][NE][NT];
+    bread(std::integral_constant<int, NT>{}, 0, b[0]);
+    static_for<FOLD_HEAD>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      H r[NR][8];
+      const int s = min(4 * u + kq, 26), jx = s / 9, jy = (s / 3) % 3, jz = s % 3;
+      const int xo[2] = {(3 + jx) * PLANE, (2 - jx) * PLANE}, yo[2] = {(3 + jy) * ROW, (2 - jy) * ROW},
+                zo[2] = {((1 + jz) & 1) * 6 + ((3 + jz) >> 1), (jz & 1) * 6 + ((2 - jz) >> 1)};
+#pragma unroll
+      for (int m = 0; m < NR; ++m)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[m][q] = pl[xo[q >> 2] + yo[(q >> 1) & 1] + zo[q & 1] + m * 2 * PLANE];
+      if constexpr (u + 1 < FOLD_HEAD) bread(std::integral_constant<int, NT>{}, u + 1, b[(u + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      H a[NR][NE];
+#pragma unroll
+      for (int m = 0; m < NR; ++m) fold8<NE>(r[m], cx, cy, cz, a[m]);
+      products(std::integral_constant<int, NT>{}, a, b[u & 1]);
+      __builtin_amdgcn_sched_barrier(0);
     });
   }
+  for (int c = c0; c < c1; ++c) {
+    // the tiles that have chunk c are a prefix of the group
+    int na = NT;
+    while (na > 1 && nc[na - 1] <= c) --na;
+    count_down<NT>([&](auto nac) {
+      if (na == decltype(nac)::value) run(nac, c, c + 1 < c1);
+    });
+    if (c + 1 < c1) {
+      __syncthreads();
+      if (!AHEAD) nin = fetch(four, (HEAD ? 1 : 0) + 4 * (c + 1), nv);
+      place(four, nv, nin, 0);
+      __syncthreads();
+    }
+  }
   // the 8 patterns' sums of result q of row tile r, through LDS (one row tile
-  // of each row group at a time), then from all parts of the K loop
-  constexpr int NQ = NX * 16 * 16 * NT;
-  double* const slot = part + (size_t)blockIdx.x * (NR * NQ * 8);
-  auto stage = [&](int r) {
+  // of each row group and NTE column tiles at a time), then from all parts of
+  // the K loop
+  constexpr int NQ = NX * 16 * 16 * NTE;
+  double* const slot = part + (size_t)blockIdx.x * (MT * 16 * 16 * NT * 8);
+  static_for<NR * (NT / NTE)>([&](auto rpc) {
+    constexpr int rp = decltype(rpc)::value, r = rp / (NT / NTE), t0 = rp % (NT / NTE) * NTE;
+    if (scol[16 * t0] < 0) return;  // (uniform: no columns there)
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+      for (int t = 0; t < NTE; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          lds[(((ks * NX + xg) * 8 + e0 + e) * 16 + M::row(v, kq)) * CS + 16 * t + i] = acc[r][e][t][v];
+          lds[((xg * 8 + e0 + e) * 16 + M::row(v, kq)) * CS + 16 * t + i] = acc[r][e][t0 + t][v];
     __syncthreads();
-  };
-  auto load = [&](int q, double (&y)[8]) {
-    const int col = m2lf_qcol<OP, NT>(q), row = m2lf_qrow<OP, NT>(q), xr = q / (256 * NT);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      double x = 0.0;
-#pragma unroll
-      for (int k = 0; k < KS; ++k) x += (double)lds[(((k * NX + xr) * 8 + e) * 16 + row) * CS + col];
-      y[e] = x;
-    }
-  };
-  if (np > 1) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      stage(r);
 #pragma unroll 1
-      for (int q = threadIdx.x; q < NQ; q += 512) {
-        double y[8];
-        load(q, y);
+    for (int q = threadIdx.x; q < NQ; q += THR) {
+      const int col = m2lf_qcol<OP, NTE>(q), row = m2lf_qrow<OP, NTE>(q), xr = q / (256 * NTE);
+      double y[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) slot[(size_t)(r * 8 + e) * NQ + q] = y[e];
+      for (int e = 0; e < 8; ++e) y[e] = (double)lds[((xr * 8 + e) * 16 + row) * CS + col];
+      if (np > 1) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) slot[(size_t)(rp * 8 + e) * NQ + q] = y[e];
+      } else {
+        m2lf_put<P, H, OP>(sg, scol[16 * t0 + col], ox0, oy0, oz0, xr * NR + r, row, y);
       }
     }
-    return;
-  }
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    stage(r);
-#pragma unroll 1
-    for (int q = threadIdx.x; q < NQ; q += 512) {
-      const int cb = scol[m2lf_qcol<OP, NT>(q)];
-      double y[8];
-      load(q, y);
-      m2lf_put<P, H, OP>(sg, cb, ox0 + (q / (256 * NT)) * NR + r, oy0, oz0, m2lf_qrow<OP, NT>(q), y);
-    }
-  }
+  });
 }
 
 // Adds the parts of the shared groups of a k_m2lf launch, in order.  Blocks:
@@ -811,25 +986,25 @@ __global__ __launch_bounds__(512, 2) void k_m2lf(const Seg* __restrict__ segs, i
 template <int P, typename H, int OP, int MT, int NT, int NR>
 __global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, int nseg, int T, const M2lGrid grid,
                                                   const double* __restrict__ part) {
-  constexpr int NQ = MT / NR * 256 * NT;
+  constexpr int NTE = m2lf_nte<NT>, NP = NT / NTE, NQ = MT / NR * 256 * NTE;
   int g = 0, left = (int)blockIdx.x / T;  // (a tile per T blocks of each shared group)
   while (grid.parts[g] == 1 || left-- > 0) ++g;
   const int lbk = (int)blockIdx.x % T, np = grid.parts[g];
   const Seg& sg = find_seg(segs, nseg, lbk);
   const int tb = lbk - sg.first_block;
   const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
-  const double* slot = part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NQ * 8);
-  for (int x = blockIdx.y * 256 + threadIdx.x; x < NR * NQ; x += gridDim.y * 256) {
-    const int r = x / NQ, q = x % NQ, col = 16 * NT * g + m2lf_qcol<OP, NT>(q);
+  const double* slot = part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NP * NQ * 8);
+  for (int x = blockIdx.y * 256 + threadIdx.x; x < NR * NP * NQ; x += gridDim.y * 256) {
+    const int rp = x / NQ, q = x % NQ, col = 16 * (NT * g + rp % NP * NTE) + m2lf_qcol<OP, NTE>(q);
     const int cb = fold_colmap<P, OP>(col);
     if (cb < 0) continue;
     double y[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = slot[(size_t)(r * 8 + e) * NQ + q];
+    for (int e = 0; e < 8; ++e) y[e] = slot[(size_t)(rp * 8 + e) * NQ + q];
     for (int k = 1; k < np; ++k)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] += slot[(size_t)k * (NR * NQ * 8) + (size_t)(r * 8 + e) * NQ + q];
-    m2lf_put<P, H, OP>(sg, cb, ox0 + (q / (256 * NT)) * NR + r, oy0, oz0, m2lf_qrow<OP, NT>(q), y);
+      for (int e = 0; e < 8; ++e) y[e] += slot[(size_t)k * (NR * NP * NQ * 8) + (size_t)(rp * 8 + e) * NQ + q];
+    m2lf_put<P, H, OP>(sg, cb, ox0, oy0, oz0, (q / (256 * NTE)) * NR + rp / NP, m2lf_qrow<OP, NTE>(q), y);
   }
 }
 
@@ -842,7 +1017,9 @@ __global__ void k_m2lf_adj_table(const double* __restrict__ Dtab, const int2* __
   const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
-  const int k = 4 * (f - tiles[t].y) + (lane >> 4), s = k % 27, cb = m2lf_col(P, k / 27), a = 16 * t + (lane & 15);
+  int kt, s;
+  fold_k(FO_M2LT, f - tiles[t].y, lane >> 4, &kt, &s);
+  const int cb = m2lf_col(P, kt), a = 16 * t + (lane & 15);
   const int kap = cb >> 8, b = cb & 255;
   double x = 0.0;
   if (cb >= 0 && a < hterms(nmax) && h_degree(a) + h_degree(b) <= P) {
@@ -877,7 +1054,9 @@ __global__ void k_m2pf_table(const double* __restrict__ Dtab2, const int2* __res
   const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
-  const int k = 4 * (f - tiles[t].y) + (lane >> 4), s = k % 27, kt = k / 27, col = 16 * t + (lane & 15);
+  const int col = 16 * t + (lane & 15);
+  int kt, s;
+  fold_k(adj ? FO_M2PT : FO_M2P, f - tiles[t].y, lane >> 4, &kt, &s);
   const int a = adj ? col : kt;
   double x = 0.0;
   if (a < hterms(nmax)) {
@@ -964,14 +1143,14 @@ __global__ __launch_bounds__(L2LF_THREADS) void k_l2lf(const Seg* __restrict__ s
   const long long Pc = P0 + r;
   if (Pc >= nps) return;
   const int p2 = (int)(Pc % ns), p1 = (int)((Pc / ns) % ns), p0 = (int)(Pc / ((long long)ns * ns));
-  const double* __restrict__ row = sg.c + Pc * 8 * HR;
+  const double* __restrict__ row = sg.c + Pc * frow(P);
   const double* src = s_src + r * SS;
   double* __restrict__ out = sg.b;
   for (int b = slot; b < HT; b += 32) {
     const int bt = c_ft<P>.full[b], pb = c_ft<P>.par[b];
     double y[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = row[k * HR + b];
+    for (int k = 0; k < 8; ++k) y[k] = row[fold_at(k, b)];
     double S[8];
 #pragma unroll
     for (int pat = 0; pat < 8; ++pat) {
@@ -995,10 +1174,10 @@ __global__ __launch_bounds__(L2LF_THREADS) void k_l2lf(const Seg* __restrict__ s
           S[e | bit] = a - c;
         }
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const long long c = ((long long)(2 * p0 + 1 - ((m >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((m >> 1) & 1))) * (2 * ns) +
-                          (2 * p2 + 1 - (m & 1));
-      out[c * HR + b] = fma(0.125 * chi(pb, m), y[m], S[m]);
+    for (int t = 0; t < 8; ++t) {
+      const long long c = ((long long)(2 * p0 + 1 - ((t >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((t >> 1) & 1))) * (2 * ns) +
+                          (2 * p2 + 1 - (t & 1));
+      out[c * HR + b] = fma(0.125 * chi(pb, t), y[t], S[t]);
     }
   }
 }

@@ -34,8 +34,8 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
   double x = 0.0;
   if (id < blka_off_p()) {
     // source sp of the positive octant, targets at y = the 8 images of u
-    const int e = (id >> 6) & 7, s = (id >> 9) % BLK_STEPS, o = (id >> 9) / BLK_STEPS, k = 4 * s + kq;
-    const int jj[3] = {k / 36, (k / 6) % 6, k % 6};
+    const int e = (id >> 6) & 7, st = (id >> 9) % BLK_STEPS, o = (id >> 9) / BLK_STEPS, pair = 4 * (st / 6) + kq;
+    const int jj[3] = {pair / 6, pair % 6, st % 6};
     if (j < 8)
       for (int minus = 0; minus < 8; ++minus) {
         int t = 0, v = 0, neg = 0;  // the target's place in its own block, the source seen from there, tau
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
                                                               const double* __restrict__ W,
                                                               const double* __restrict__ Mb, TO* __restrict__ drho,
                                                               int n, int tpa) {
-  constexpr int NE = 4, KS = 4 / NX, NPS = blk_psteps(P), CS = 9;
+  constexpr int NE = 4, KS = 2 / NX, NPS = blk_psteps(P), CS = 9;
   constexpr int EP = KS * 8 * NX * 16 * CS, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) double lds[SZ];
   const int nb = n >> 2, lb = blockIdx.x;
@@ -325,78 +325,53 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
   const long long N = (long long)n * n * n;
   const double dx = 1.0 / n;
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, ks = (w / NX) % KS, e0 = (w / 4) * NE;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, ks = (w / NX) % KS, e0 = (w >> 1) * NE;
   const double sx0 = e0 ? -1.0 : 1.0;
   constexpr int OFF_P = blka_off_p();
   d4 acc[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) acc[e] = d4{0, 0, 0, 0};
-  const double* ctr = lds + (4 * X + 6) * BLK_PLANE + (4 * (i >> 2) + 6) * BLK_ROW + 4 * (i & 3) + 6;
+  const double* ctr = lds + (4 * X + 6) * BLK_PLANE + blk_row(4 * (i >> 2) + 6) + 4 * (i & 3);
 #pragma unroll 1
   for (int o = 0; o < (dg ? 4 : 1); ++o) {
     __syncthreads();
-    {
-      constexpr int CNT = (4 * NX + 8) * 24 * 24, FB = 9;
-      const int x0 = 4 * bx0 - 4, y0 = 4 * by0 - 4, z0 = 4 * bz0 - 4;
-      const auto gs = gmem(o == 0 ? dphi : dg + (o - 1) * N);
-      // the accumulators' scale, with the Walsh sum's 1/8
-      const double sc = 0.125 * (o == 0 ? (DL == 1 ? 0.5 : 0.25) * dx * dx : (DL == 1 ? -0.25 : -0.0625) * dx);
-#pragma unroll 1
-      for (int q0 = threadIdx.x; q0 < CNT; q0 += FB * BLK_THREADS) {
-        TI v[FB];
-#pragma unroll
-        for (int u = 0; u < FB; ++u) {
-          const int e = q0 + u * BLK_THREADS, z = z0 + e % 24, y = y0 + (e / 24) % 24, x = x0 + e / 576;
-          const bool in = e < CNT && x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
-          v[u] = in ? gs[((long long)x * n + y) * n + z] : TI(0);
-        }
-#pragma unroll
-        for (int u = 0; u < FB; ++u) {
-          const int e = q0 + u * BLK_THREADS;
-          if (e < CNT) lds[(e / 576) * BLK_PLANE + ((e / 24) % 24) * BLK_ROW + e % 24] = sc * (double)v[u];
-        }
-      }
-    }
+    // the accumulators' scale, with the Walsh sum's 1/8
+    const double sc = 0.125 * (o == 0 ? (DL == 1 ? 0.5 : 0.25) * dx * dx : (DL == 1 ? -0.25 : -0.0625) * dx);
+    stage_cells<NX>(lds, o == 0 ? dphi : dg + (o - 1) * N, (TI*)nullptr, n, 4 * bx0 - 4, 4 * by0 - 4, 4 * bz0 - 4,
+                    [sc](TI v) { return sc * (double)v; });
     __syncthreads();
     // the sign of a minus image along the output's own axis
     const double sx = o == 1 ? -sx0 : sx0, sy = o == 2 ? -1.0 : 1.0, sz = o == 3 ? -1.0 : 1.0;
-    const auto wb = gmem(W + o * (BLK_STEPS * 512) + e0 * 64 + lane);
-    auto aread = [&](int s, double (&r)[8]) {
-      const int k = 4 * s + kq, jx = k / 36, jy = (k / 6) % 6, jz = k % 6;
-      const int px = jx * BLK_PLANE, mx = -BLK_PLANE - px, py = jy * BLK_ROW, my = -BLK_ROW - py;
-      const double *pp = ctr + px + py, *pm = ctr + px + my, *mp = ctr + mx + py, *mm = ctr + mx + my;
-      r[0] = pp[jz];
-      r[1] = pp[-1 - jz];
-      r[2] = pm[jz];
-      r[3] = pm[-1 - jz];
-      r[4] = mp[jz];
-      r[5] = mp[-1 - jz];
-      r[6] = mm[jz];
-      r[7] = mm[-1 - jz];
-    };
+    const auto wb = gmem(W + o * (BLK_STEPS * 512) + e0 * 64);
     auto bread = [&](int s, double (&b)[NE]) {
 #pragma unroll
-      for (int e = 0; e < NE; ++e) b[e] = wb[s * 512 + e * 64];
+      for (int e = 0; e < NE; ++e) b[e] = (wb + s * 512 + e * 64)[(unsigned)lane];
     };
+    // as in k_block
     double r[2][8], b[2][NE], a[NE];
-    aread(ks, r[0]);
-    bread(ks, b[0]);
+    const double* p[4];
+    blk_images(ctr, c_blk_place[4 * ks + kq], p);
+    bread(6 * ks, b[0]);
+    blk_read<0>(p, r[0]);
 #pragma unroll 1
-    for (int s = ks; s < BLK_STEPS; s += 2 * KS) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int st = s + u * KS, sn = st + KS < BLK_STEPS ? st + KS : ks;
-        if (u == 0 || st < BLK_STEPS) {
-          bread(sn, b[u ^ 1]);
-          aread(sn, r[u ^ 1]);
-          __builtin_amdgcn_sched_barrier(0);
-          fold8<NE>(r[u], sx, sy, sz, a);
-#pragma unroll
-          for (int e = 0; e < NE; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[u][e], acc[e], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
+    for (int grp = ks; grp < BLK_GROUPS; grp += KS)
+      static_for<6>([&](auto jc) {
+        constexpr int jz = decltype(jc)::value, u = jz & 1;
+        if constexpr (jz < 5) {
+          bread(6 * grp + jz + 1, b[u ^ 1]);
+          blk_read<jz + 1>(p, r[u ^ 1]);
+        } else {
+          const int nx = grp + KS < BLK_GROUPS ? grp + KS : ks;  // (past the last: read, not used)
+          bread(6 * nx, b[u ^ 1]);
+          blk_images(ctr, c_blk_place[4 * nx + kq], p);
+          blk_read<0>(p, r[u ^ 1]);
         }
-      }
-    }
+        __builtin_amdgcn_sched_barrier(0);
+        fold8<NE>(r[u], sx, sy, sz, a);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[u][e], acc[e], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
   }
   if (Mb && ks == 0) {
     const int cx = min(bx0 + X, nb - 1), cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1), nbp = nb + 6;
@@ -435,14 +410,15 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
     for (int e = 0; e < 8; ++e) x[e * ES] = y[e];
   }
   __syncthreads();
-#pragma unroll 1
-  for (int q = threadIdx.x; q < 4 * NX * 256; q += BLK_THREADS) {
-    const int z = q & 15, y = (q >> 4) & 15, x = q >> 8;
-    const int ux = 4 * bx0 + x, uy = 4 * by0 + y, uz = 4 * bz0 + z;
-    if (ux >= n || uy >= n || uz >= n) continue;
-    const int qx = x & 3, qy = y & 3, qz = z & 3;
-    const int minus = ((qx < 2) << 2) | ((qy < 2) << 1) | (qz < 2);
-    const int t = ((qx == 0 || qx == 3) << 2) | ((qy == 0 || qy == 3) << 1) | (qz == 0 || qz == 3);
-    drho[((long long)ux * n + uy) * n + uz] = (TO)lds[minus * ES + (16 * (x >> 2) + 4 * (y >> 2) + (z >> 2)) * CS + t];
-  }
+  const int z = threadIdx.x & 15, y = threadIdx.x >> 4, qy = y & 3, qz = z & 3;
+  const int uy = 4 * by0 + y, uz = 4 * bz0 + z;
+  const double* const res = lds + ((qy < 2) << 1 | (qz < 2)) * ES + (4 * (y >> 2) + (z >> 2)) * CS +
+                            ((qy == 0 || qy == 3) << 1 | (qz == 0 || qz == 3));
+  if (uy < n && uz < n)
+    static_for<4 * NX>([&](auto xc) {
+      constexpr int x = decltype(xc)::value, qx = x & 3;
+      constexpr int at = (qx < 2 ? 4 * ES : 0) + (qx == 0 || qx == 3 ? 4 : 0) + 16 * (x >> 2) * CS;
+      const int ux = 4 * bx0 + x;
+      if (ux < n) drho[((long long)ux * n + uy) * n + uz] = (TO)res[at];
+    });
 }

@@ -1575,29 +1575,25 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
 // Tile shapes of the folded M2L by variant (rows of octs, column tiles per
 // group, patterns per wave, K slices): forward, and transposes, whose few
 // column tiles are dominated by the first.
-template <int OP, int V>
+// X: FP32 products, which take half the time, so that folding an operand has to
+// serve more of them.
+template <int OP, int V, int X>
 struct M2lShape;
-template <> struct M2lShape<0, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
-template <> struct M2lShape<0, 1> { static constexpr int MT = 2, NT = 4, NE = 2, KS = 1; };
-template <> struct M2lShape<0, 2> { static constexpr int MT = 4, NT = 4, NE = 2, KS = 1; };
-template <> struct M2lShape<2, 0> : M2lShape<0, 0> {};
-template <> struct M2lShape<2, 1> : M2lShape<0, 1> {};
-template <> struct M2lShape<2, 2> : M2lShape<0, 2> {};
-template <> struct M2lShape<1, 0> { static constexpr int MT = 1, NT = 1, NE = 4, KS = 4; };
-template <> struct M2lShape<1, 1> { static constexpr int MT = 2, NT = 1, NE = 8, KS = 4; };
-template <> struct M2lShape<1, 2> { static constexpr int MT = 4, NT = 2, NE = 4, KS = 1; };
-
-template <> struct M2lShape<3, 0> : M2lShape<1, 0> {};
-template <> struct M2lShape<3, 1> : M2lShape<1, 1> {};
-template <> struct M2lShape<3, 2> : M2lShape<1, 2> {};
+template <int X> struct M2lShape<0, 0, X> { static constexpr int MT = 1, NT = 2, NE = 2, NW = 4; };
+template <> struct M2lShape<0, 1, 0> { static constexpr int MT = 2, NT = 2, NE = 4, NW = 4; };
+template <> struct M2lShape<0, 1, 1> { static constexpr int MT = 2, NT = 4, NE = 2, NW = 4; };
+template <int X> struct M2lShape<1, 0, X> { static constexpr int MT = 1, NT = 1, NE = 2, NW = 4; };
+template <int X> struct M2lShape<1, 1, X> { static constexpr int MT = 4, NT = 1, NE = 8, NW = 4; };
+template <int V, int X> struct M2lShape<2, V, X> : M2lShape<0, V, X> {};
+template <int V, int X> struct M2lShape<3, V, X> : M2lShape<1, V, X> {};
 
 // Grid of a launch over T tiles.  A block's K loop is cut where it would take
-// more than a quarter of what each compute unit has to do in the whole launch
+// more than half (small tiles: a quarter) of what each compute unit has to do in the whole launch
 // (the last blocks to start would otherwise set its length), down to one
 // chunk of 27 steps.
-template <int P, int OP, int V>
+template <int P, int OP, int V, int X>
 M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
-  using S = M2lShape<OP, V>;
+  using S = M2lShape<OP, V, X>;
   const int nt = fold_ntiles(OP, P);
   M2lGrid g;
   g.ng = (nt + S::NT - 1) / S::NT;
@@ -1608,7 +1604,7 @@ M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
     longest[t / S::NT] = std::max<long long>(longest[t / S::NT], st);
     total += st;
   }
-  const long long lim = std::max<long long>(27, total * T / pl->cus / 4);
+  const long long lim = std::max<long long>(27, total * T / pl->cus / (V ? 2 : 4));
   for (int i = 0; i < g.ng; ++i) {
     const long long chunks = (longest[i] + 26) / 27, want = (cost[i] + lim - 1) / lim;
     g.parts[i] = (int)std::max<long long>(1, std::min<long long>({want, chunks, 32}));
@@ -1619,23 +1615,28 @@ M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
   return g;
 }
 // doubles of partial sums of such a launch
-template <int P, int OP, int V>
-void m2lf_need(const fmm_plan* pl, int T, size_t* part) {
-  using S = M2lShape<OP, V>;
-  const M2lGrid g = m2lf_grid<P, OP, V>(pl, T);
+template <int P, int OP, int V, int X>
+void m2lf_need_x(const fmm_plan* pl, int T, size_t* part) {
+  using S = M2lShape<OP, V, X>;
+  const M2lGrid g = m2lf_grid<P, OP, V, X>(pl, T);
   if (!g.shared) return;
   *part = std::max(*part, (size_t)g.blocks * S::MT * 16 * 16 * S::NT * 8);
 }
+template <int P, int OP, int V>
+void m2lf_need(const fmm_plan* pl, int x, int T, size_t* part) {
+  if (x == 0) m2lf_need_x<P, OP, V, 0>(pl, T, part);
+  else m2lf_need_x<P, OP, V, 1>(pl, T, part);
+}
 template <int P, typename CT, int OP, int V>
 hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s) {
-  using S = M2lShape<OP, V>;
+  using S = M2lShape<OP, V, Mf<CT>::IDX>;
   using H = typename Mf<CT>::H;
-  const M2lGrid g = m2lf_grid<P, OP, V>(pl, st.blocks);
+  const M2lGrid g = m2lf_grid<P, OP, V, Mf<CT>::IDX>(pl, st.blocks);
   StageScope sc(pl, OP == FO_M2P ? ST_BOTTOM : ST_M2L, g.shared ? 2 : 1, s);
-  hipLaunchKernelGGL((k_m2lf<P, CT, OP, S::MT, S::NT, S::NE, S::KS>), dim3((unsigned)g.blocks), dim3(512), 0, s, st.dev,
+  hipLaunchKernelGGL((k_m2lf<P, CT, OP, S::MT, S::NT, S::NE, S::NW>), dim3((unsigned)g.blocks), dim3(64 * S::NW), 0, s, st.dev,
                      st.nseg, st.blocks, pl->fold_tiles[OP], (const H*)pl->fold_w[OP][x], g, pl->m2lf_part);
   if (g.shared)
-    hipLaunchKernelGGL((k_m2lf_sum<P, H, OP, S::MT, S::NT, S::MT * S::KS / S::NE>),
+    hipLaunchKernelGGL((k_m2lf_sum<P, H, OP, S::MT, S::NT, 8 * S::MT / (S::NE * S::NW)>),
                        dim3((unsigned)(g.shared * st.blocks), S::MT * S::NT), dim3(256), 0, s, st.dev, st.nseg, st.blocks,
                        g, pl->m2lf_part);
   return hipGetLastError();
@@ -1645,7 +1646,6 @@ hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s)
 template <int P, typename CT, int OP>
 hipError_t launch_fold(fmm_plan* pl, int x, int v, const SegTable& st, hipStream_t s) {
   if (!st.nseg) return hipSuccess;
-  if (v == 2) return launch_m2lf_v<P, CT, OP, 2>(pl, x, st, s);
   if (v == 1) return launch_m2lf_v<P, CT, OP, 1>(pl, x, st, s);
   return launch_m2lf_v<P, CT, OP, 0>(pl, x, st, s);
 }
@@ -1653,8 +1653,8 @@ hipError_t launch_fold(fmm_plan* pl, int x, int v, const SegTable& st, hipStream
 template <int P, typename CT, int OP>
 hipError_t launch_fold_site(fmm_plan* pl, int x, hipStream_t s) {
   const auto& st = OP == FO_M2P ? pl->s_m2pf[x] : pl->s_m2lf[x];
-  int v = m2lf_variant(pl, st[1].blocks, st[2].blocks);
-  if (pl->tune.grp == 1 && v > 0) --v;
+  int v = fold_variant(pl, OP, st[1].blocks);
+  if (pl->tune.grp == 1) v = 0;
   return launch_fold<P, CT, OP>(pl, x, v, st[v], s);
 }
 
@@ -1663,22 +1663,20 @@ hipError_t launch_fold_site(fmm_plan* pl, int x, hipStream_t s) {
 template <int P>
 hipError_t alloc_m2lf_part(fmm_plan* pl) {
   size_t part = 0;
-  auto need = [&](auto opc, auto adjc, const SegTable (&st)[3]) {
+  auto need = [&](auto opc, auto adjc, int x, const SegTable (&st)[3]) {
     constexpr int OP = decltype(opc)::value, ADJ = decltype(adjc)::value;
     if (!st[0].nseg) return;
-    const int v = m2lf_variant(pl, st[1].blocks, st[2].blocks);
-    // (a batch's autotuner may take the next smaller variant)
-    if (v == 2) m2lf_need<P, OP, 2>(pl, st[2].blocks, &part);
-    if (v >= 1) m2lf_need<P, OP, 1>(pl, st[1].blocks, &part);
-    if (v <= 1) m2lf_need<P, OP, 0>(pl, st[0].blocks, &part);
+    // (a batch's autotuner may take the smaller tiles)
+    const int v = fold_variant(pl, OP, st[1].blocks), va = fold_variant(pl, ADJ, st[2].blocks);
+    if (v) m2lf_need<P, OP, 1>(pl, x, st[1].blocks, &part);
+    if (!v || pl->batch) m2lf_need<P, OP, 0>(pl, x, st[0].blocks, &part);
     if (pl->batch) return;
-    if (v == 2) m2lf_need<P, ADJ, 2>(pl, st[2].blocks, &part);
-    if (v == 1) m2lf_need<P, ADJ, 1>(pl, st[1].blocks, &part);
-    if (v == 0) m2lf_need<P, ADJ, 0>(pl, st[0].blocks, &part);
+    if (va) m2lf_need<P, ADJ, 1>(pl, x, st[2].blocks, &part);
+    else m2lf_need<P, ADJ, 0>(pl, x, st[0].blocks, &part);
   };
   for (int x = 0; x < 2; ++x) {
-    need(std::integral_constant<int, FO_M2L>{}, std::integral_constant<int, FO_M2LT>{}, pl->s_m2lf[x]);
-    need(std::integral_constant<int, FO_M2P>{}, std::integral_constant<int, FO_M2PT>{}, pl->s_m2pf[x]);
+    need(std::integral_constant<int, FO_M2L>{}, std::integral_constant<int, FO_M2LT>{}, x, pl->s_m2lf[x]);
+    need(std::integral_constant<int, FO_M2P>{}, std::integral_constant<int, FO_M2PT>{}, x, pl->s_m2pf[x]);
   }
   if (!part) return hipSuccess;
   hipError_t e;
@@ -1687,16 +1685,16 @@ hipError_t alloc_m2lf_part(fmm_plan* pl) {
   return hipSuccess;
 }
 
-// Finest blocks (k_block) of site x (0 FP64, 1 low precision).  Tiles of 4
-// rows of blocks share each B fragment between 4 waves; fewer rows where they
-// would leave compute units idle.
+// Finest blocks (k_block) of site x (0 FP64, 1 low precision).  Tiles of two
+// rows of blocks read fewer densities twice; one row where two would leave
+// compute units idle.
 template <int P, typename CT, typename TI, typename TO>
 hipError_t launch_block(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   using H = typename Mf<CT>::H;
   if (!pl->s_blk[x][0].nseg) return hipSuccess;
   const long long rows = pl->blk_rows[x];
-  int v = rows >= 8LL * pl->cus ? 2 : rows >= 4LL * pl->cus ? 1 : 0;
-  if ((pl->force_bz ? pl->force_bz : pl->tune.bz) == 8 && v > 0) --v;
+  int v = rows >= 4LL * pl->cus ? 1 : 0;
+  if ((pl->force_bz ? pl->force_bz : pl->tune.bz) == 8) v = 0;
   unsigned int* cnt = pl->stamps ? pl->stamp_cnt : nullptr;
   unsigned long long* done = pl->stamps ? pl->stamp_time + 1 : nullptr;
   const SegTable& st = pl->s_blk[x][v];
@@ -1712,7 +1710,6 @@ hipError_t launch_block(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
                          cnt, done);
     return hipGetLastError();
   };
-  if (v == 2) return go(std::integral_constant<int, 4>{});
   if (v == 1) return go(std::integral_constant<int, 2>{});
   return go(std::integral_constant<int, 1>{});
 }
@@ -1914,7 +1911,6 @@ hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI*
                        dphi, dg, pl->wblk_adj, mb, drho, n, tpa);
     return hipGetLastError();
   };
-  if (rows >= 8LL * pl->cus) return go(std::integral_constant<int, 4>{});
   if (rows >= 4LL * pl->cus) return go(std::integral_constant<int, 2>{});
   return go(std::integral_constant<int, 1>{});
 }

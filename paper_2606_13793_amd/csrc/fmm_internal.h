@@ -180,8 +180,8 @@ struct Level {
   // operands to that type anyway.
   void* Lt = nullptr;
   // fields on the folded kernels (fmm_fold.h), in place of L: the M2L part of
-  // the locals of level k >= 3, Walsh-folded over the children, [parent][8]
-  // [hrow], FP64 (the finest level: the block kernel's compute type)
+  // the locals of level k >= 3, Walsh-folded over the children, [parent]
+  // [frow], FP64 (the finest level: the block kernel's compute type)
   void* Lw = nullptr;
   // levels 3 .. block_level: the complete locals' harmonic terms, [cell][hrow]
   double* Lc = nullptr;
@@ -469,10 +469,11 @@ inline int m2l_low_from(const fmm_plan* pl) {
 inline bool harmonic_float(const fmm_plan* pl, int F, int k) {
   return pl->precision == 1 && (k == F ? bottom_low(pl, F) : k + 1 >= m2l_low_from(pl));
 }
-// Tile of a folded M2L launch (0, 1, 2: 1, 2 or 4 rows of octs), from its
-// block counts: the largest that still gives every compute unit blocks.
-inline int m2lf_variant(const fmm_plan* pl, long long blocks2, long long blocks4) {
-  return blocks4 >= pl->cus ? 2 : blocks2 >= pl->cus / 4 ? 1 : 0;
+// Tiles of a folded operator's launch: 0 small (1 row of octs), 1 large (2
+// rows; transposes 4), from the number of large ones: large where they nearly
+// fill the compute units.
+inline int fold_variant(const fmm_plan* pl, int op, long long large) {
+  return large >= pl->cus / ((op & 1) ? 8 : 4) ? 1 : 0;
 }
 // whether the multipoles of level k (of a field with finest level F) get a
 // copy in the compute type: the low-precision bottom reads level F, the
