@@ -149,7 +149,9 @@ void release(fmm_plan* pl) {
   };
   free_st(pl->s_p2m);
   free_st(pl->s_p2m2);
+  free_st(pl->s_p2mf);
   for (auto& st : pl->s_m2m) free_st(st);
+  for (auto& st : pl->s_m2mf) free_st(st);
   for (auto& st : pl->s_conv) free_st(st);
   for (auto& st : pl->s_l2l) free_st(st);
   for (auto& a : pl->s_bot)
@@ -188,6 +190,7 @@ void release(fmm_plan* pl) {
   if (pl->dlists_p2p) (void)hipFree(pl->dlists_p2p);
   if (pl->adj_l2p) (void)hipFree(pl->adj_l2p);
   if (pl->adj_l2p2) (void)hipFree(pl->adj_l2p2);
+  if (pl->wshift) (void)hipFree(pl->wshift);
   if (pl->m2m_start) (void)hipFree(pl->m2m_start);
   if (pl->m2mt_start) (void)hipFree(pl->m2mt_start);
   if (pl->m2mt_a) (void)hipFree(pl->m2mt_a);
@@ -385,50 +388,66 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, m2m[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
+  SegList p2m, p2m2, p2mf, m2m[16], m2mf[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
-    Seg sg{};
-    sg.n = fd.n;
-    sg.field = f;
-    // the FP64 level-F multipoles are read only by an FP64 bottom kernel (the
-    // level below is formed from the unigrid), so a low-precision bottom
-    // gets its typed copy alone
-    sg.b = pl->dl == 1 && bottom_low(pl, F) ? nullptr : (double*)fd.lev[F].M;
-    sg.t = fd.lev[F].Mt;
-    if (pl->dl == 2) {
-      sg.u = fd.lev[F].Mh;
-      sg.split = harmonic_float(pl, F, F);
-    }
-    if (!block_field(pl, F) || pl->dl == 2) p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
-    // FMM-1: the multipoles of level F - 1 straight from the 4^3 unigrid
-    // cells of each cell (as FMM-2's P2M), which reads the density instead
-    // of the 8x larger level-F grid; M2M then starts at level F - 1
-    int top = F;
-    if (pl->dl == 1 && F >= 3) {
-      Seg s2{};
-      s2.n = fd.n;
-      s2.field = f;
-      s2.b = (double*)fd.lev[F - 1].M;
-      s2.t = fd.lev[F - 1].Mt;
-      s2.u = fd.lev[F - 1].Mh;
-      s2.split = harmonic_float(pl, F, F - 1);
-      const long long nc = 1LL << (3 * (F - 1));
-      p2m2.add(s2, cdiv(nc, 256));
-      top = F - 1;
-    }
-    for (int k = top; k >= 3; --k) {
-      Seg m{};
-      m.n = 1 << k;
-      m.field = f;
-      m.a = (const double*)fd.lev[k].M;
-      m.b = (double*)fd.lev[k - 1].M;
-      m.t = fd.lev[k - 1].Mt;
-      m.u = fd.lev[k - 1].Mh;
-      m.split = harmonic_float(pl, F, k - 1);
-      // parents per block of k_m2m: 16 up to 56 terms, else 8
-      m2m[k].add(m, cdiv(1LL << (3 * (k - 1)), pl->NM <= 56 ? 16 : 8));
+    if (block_field(pl, F)) {
+      // harmonic multipoles of the cells of 4^3 unigrid cells, and M2M up from
+      // there; FP64 planes, with a copy for a level whose M2L runs in FP32
+      const int top = block_level(pl, F);
+      auto copy = [&](int k) { return harmonic_float(pl, F, k) ? fd.lev[k].Mh : nullptr; };
+      if (top >= 2) {
+        Seg s2{};
+        s2.n = fd.n;
+        s2.field = f;
+        s2.b = (double*)fd.lev[top].M;
+        s2.u = copy(top);
+        p2mf.add(s2, cdiv(1LL << (3 * top), 256));
+      }
+      for (int k = top; k >= 3; --k) {
+        Seg m{};
+        m.n = 1 << (k - 1);
+        m.field = f;
+        m.a = (const double*)fd.lev[k].M;
+        m.b = (double*)fd.lev[k - 1].M;
+        m.u = copy(k - 1);
+        m2mf[k].add(m, cdiv(1LL << (3 * (k - 1)), 16));
+      }
+    } else {
+      Seg sg{};
+      sg.n = fd.n;
+      sg.field = f;
+      // the FP64 level-F multipoles are read only by an FP64 bottom kernel (the
+      // level below is formed from the unigrid), so a low-precision bottom
+      // gets its typed copy alone
+      sg.b = pl->dl == 1 && bottom_low(pl, F) ? nullptr : (double*)fd.lev[F].M;
+      sg.t = fd.lev[F].Mt;
+      p2m.add(sg, cdiv((long long)nF * nF * nF, 256));
+      // FMM-1: the multipoles of level F - 1 straight from the 4^3 unigrid
+      // cells of each cell (as FMM-2's P2M), which reads the density instead
+      // of the 8x larger level-F grid; M2M then starts at level F - 1
+      int top = F;
+      if (pl->dl == 1 && F >= 3) {
+        Seg s2{};
+        s2.n = fd.n;
+        s2.field = f;
+        s2.b = (double*)fd.lev[F - 1].M;
+        s2.t = fd.lev[F - 1].Mt;
+        const long long nc = 1LL << (3 * (F - 1));
+        p2m2.add(s2, cdiv(nc, 256));
+        top = F - 1;
+      }
+      for (int k = top; k >= 3; --k) {
+        Seg m{};
+        m.n = 1 << k;
+        m.field = f;
+        m.a = (const double*)fd.lev[k].M;
+        m.b = (double*)fd.lev[k - 1].M;
+        m.t = fd.lev[k - 1].Mt;
+        // parents per block of k_m2m: 16 up to 56 terms, else 8
+        m2m[k].add(m, cdiv(1LL << (3 * (k - 1)), pl->NM <= 56 ? 16 : 8));
+      }
     }
     if (block_field(pl, F)) {
       for (int k = F; k >= 3; --k) {  // the finest first: its blocks are the bulk of the launch
@@ -437,8 +456,8 @@ int build_schedule(fmm_plan* pl) {
         const int no = c.n >> 1;
         c.tpa = (int)cdiv(no, 4);
         c.field = f;
-        c.a = (const double*)fd.lev[k - 1].Mh;
         const bool low = harmonic_float(pl, F, k - 1), typed = low && k == F && pl->dl == 1;
+        c.a = (const double*)(low ? fd.lev[k - 1].Mh : fd.lev[k - 1].M);
         c.b = typed ? nullptr : (double*)fd.lev[k].Lw;
         c.u = typed ? fd.lev[k].Lw : nullptr;
         for (int v = 0; v < 3; ++v) {
@@ -451,7 +470,7 @@ int build_schedule(fmm_plan* pl) {
         c.n = nF;
         c.tpa = (int)cdiv(nF / 2, 4);
         c.field = f;
-        c.a = (const double*)fd.lev[F].Mh;
+        c.a = (const double*)(harmonic_float(pl, F, F) ? fd.lev[F].Mh : fd.lev[F].M);
         c.u = fd.m2p;
         for (int v = 0; v < 3; ++v) {
           c.tz = (int)cdiv(nF / 2, 1 << v);
@@ -597,8 +616,10 @@ int build_schedule(fmm_plan* pl) {
   int rc;
   if ((rc = upload_segs(pl, pl->s_p2m, p2m))) return rc;
   if ((rc = upload_segs(pl, pl->s_p2m2, p2m2))) return rc;
+  if ((rc = upload_segs(pl, pl->s_p2mf, p2mf))) return rc;
   for (int k = 0; k < 16; ++k) {
     if ((rc = upload_segs(pl, pl->s_m2m[k], m2m[k]))) return rc;
+    if ((rc = upload_segs(pl, pl->s_m2mf[k], m2mf[k]))) return rc;
     if ((rc = upload_segs(pl, pl->s_l2l[k], l2l[k]))) return rc;
     if ((rc = upload_segs(pl, pl->s_l2lf[k], l2lf[k]))) return rc;
   }
@@ -881,7 +902,9 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
   if (dev_alloc(pl, (void**)&pl->dtab, (size_t)343 * 8 * pl->ND * sizeof(double))) return bail();
   if (pl->dl == 2 && dev_alloc(pl, (void**)&pl->dtab2, (size_t)343 * 64 * pl->ND * sizeof(double))) return bail();
   if (dev_alloc(pl, (void**)&pl->dlists, 8 * fmm::NLIST_PAD * sizeof(int))) return bail();
-  {
+  bool listed = false;  // fields on the list-driven shifts
+  for (auto& fd : pl->fld) listed = listed || !fmm::block_field(pl, fd.F);
+  if (listed) {
     // L2L coefficient lists: for each local term b and parity pattern of g
     // (start index 8 b + pattern), the terms b + g with |b + g| <= p and
     // coefficient 2^-(|b|+1) 4^-|g| / g! (the sign for child q is
@@ -923,7 +946,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
       return bail();
     }
   }
-  {
+  if (listed) {
     // M2M coefficient lists: for each multipole term a, every b <= a with
     // g = a - b: LDS offset 8 b + parity pattern of g, coefficient
     // 2^-|b| 4^-|g| / g!
@@ -995,7 +1018,8 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
       lv.nkp = lv.nk + 6;
       lv.ncell = 1LL << (3 * k);
       lv.ncellp = (long long)lv.nkp * lv.nkp * lv.nkp;
-      const size_t mb = (size_t)pl->NC * lv.ncellp * 4 * sizeof(double);
+      // folded fields: planes of harmonic terms
+      const size_t mb = (fmm::block_field(pl, fd.F) ? (size_t)(p + 1) * (p + 1) : (size_t)pl->NC * 4) * lv.ncellp * sizeof(double);
       if (k <= fmm::block_level(pl, fd.F) || !fmm::block_field(pl, fd.F)) {  // (folded FMM-1 forms no finest multipoles)
         if (dev_alloc(pl, &lv.M, mb)) return bail();
         if (hipMemset(lv.M, 0, mb) != hipSuccess) {
@@ -1035,7 +1059,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     const size_t hr = (size_t)((p + 1) * (p + 1) + 3) / 4 * 4, fr = (size_t)((p + 1) * (p + 1) + 1) / 2 * 16;
     if (pl->dl == 2 && dev_alloc(pl, &fd.m2p, 4 * (size_t)fd.n * fd.n * fd.n * (low ? sizeof(float) : sizeof(double))))
       return bail();
-    if (!low && pl->dl == 1) {
+    if (&fd == &pl->fld[0]) {  // for the expansions' export
       const size_t b = (size_t)fd.n * fd.n * fd.n * (pl->precision == 0 ? sizeof(double) : sizeof(float));
       if (dev_alloc(pl, &fd.rho_copy, b)) return bail();
       if (hipMemset(fd.rho_copy, 0, b) != hipSuccess) {
@@ -1054,7 +1078,7 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
       if (k >= 3 && !zalloc(&lv.Lw, (size_t)(lv.ncell / 8) * fr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
       const bool upto = k <= fmm::block_level(pl, F);
       if (k >= 3 && upto && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
-      if (upto && !zalloc(&lv.Mh, (size_t)lv.ncellp * hr * (fmm::harmonic_float(pl, F, k) ? sizeof(float) : sizeof(double))))
+      if (upto && fmm::harmonic_float(pl, F, k) && !zalloc(&lv.Mh, (size_t)lv.ncellp * (p + 1) * (p + 1) * sizeof(float)))
         return bail();
     }
   }
@@ -1815,10 +1839,11 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   const int nch = (nt + 3) / 4;
   if (!out || count < (size_t)lv.ncell * nt) return fail(FMM_ERR_INVALID_ARG, "out must hold %lld doubles", lv.ncell * nt);
   const int nk = lv.nk;
-  if (which == 0 && level == plan->F && plan->dl == 1 && fmm::block_field(plan, plan->F)) {
-    // the block kernel forms no level-F multipoles: derive them from the
-    // copy of the density it left (P2M: sum_q rho_q (s_q / 4)^a / a!)
-    const int n = plan->n;
+  if (which == 0 && fmm::block_field(plan, plan->F)) {
+    // a folded field keeps harmonic terms only: derive the full ones from the
+    // copy of the density it left, sum_s rho_s w_s^a / a!, w the place of a
+    // unigrid cell in units of two cells, summed along z, y and x in turn
+    const int n = plan->n, m = n >> level, p = plan->p;
     const size_t N = (size_t)n * n * n;
     std::vector<double> rho(N);
     hipError_t e;
@@ -1830,24 +1855,32 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
       std::copy(r32.begin(), r32.end(), rho.begin());
     }
     if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
-    std::vector<int> mi(3 * fmm::nterms(plan->p));
-    fmm_multi_index(plan->p, mi.data(), mi.size());
-    auto fact = [](int k) { double f = 1; for (int i = 2; i <= k; ++i) f *= i; return f; };
+    std::vector<int> mi(3 * fmm::nterms(p));
+    fmm_multi_index(p, mi.data(), mi.size());
+    std::vector<double> pw((size_t)(p + 1) * m), zs(p + 1), yz((size_t)(p + 1) * (p + 1)), xyz((size_t)(p + 1) * (p + 1) * (p + 1));
+    for (int i = 0; i < m; ++i) {
+      double f = 1.0;
+      for (int k = 0; k <= p; ++k, f *= (m - 1 - 2 * i) / (2.0 * m * k)) pw[(size_t)k * m + i] = f;
+    }
     for (long long cidx = 0; cidx < lv.ncell; ++cidx) {
       const int c2 = (int)(cidx % nk), c1 = (int)((cidx / nk) % nk), c0 = (int)(cidx / ((long long)nk * nk));
-      double v[8];
-      for (int q = 0; q < 8; ++q)
-        v[q] = rho[((size_t)(2 * c0 + ((q >> 2) & 1)) * n + 2 * c1 + ((q >> 1) & 1)) * n + 2 * c2 + (q & 1)];
-      for (int t = 0; t < nt; ++t) {
-        const int *ex = &mi[3 * t], pat = ((ex[0] & 1) << 2) | ((ex[1] & 1) << 1) | (ex[2] & 1);
-        double s = 0.0;
-        for (int q = 0; q < 8; ++q) {
-          int b = q & pat;
-          b ^= b >> 2;
-          s += ((b ^ (b >> 1)) & 1) ? -v[q] : v[q];
+      std::fill(xyz.begin(), xyz.end(), 0.0);
+      for (int x = 0; x < m; ++x) {
+        std::fill(yz.begin(), yz.end(), 0.0);
+        for (int y = 0; y < m; ++y) {
+          std::fill(zs.begin(), zs.end(), 0.0);
+          const double* row = &rho[((size_t)(m * c0 + x) * n + m * c1 + y) * n + m * c2];
+          for (int z = 0; z < m; ++z)
+            for (int k = 0; k <= p; ++k) zs[k] += pw[(size_t)k * m + z] * row[z];
+          for (int j = 0; j <= p; ++j)
+            for (int k = 0; j + k <= p; ++k) yz[j * (p + 1) + k] += pw[(size_t)j * m + y] * zs[k];
         }
-        out[cidx * nt + t] = std::ldexp(s / (fact(ex[0]) * fact(ex[1]) * fact(ex[2])), -2 * (ex[0] + ex[1] + ex[2]));
+        for (int i = 0; i <= p; ++i)
+          for (int j = 0; i + j <= p; ++j)
+            for (int k = 0; i + j + k <= p; ++k)
+              xyz[(i * (p + 1) + j) * (p + 1) + k] += pw[(size_t)i * m + x] * yz[j * (p + 1) + k];
       }
+      for (int t = 0; t < nt; ++t) out[cidx * nt + t] = xyz[(mi[3 * t] * (p + 1) + mi[3 * t + 1]) * (p + 1) + mi[3 * t + 2]];
     }
     return ok();
   }

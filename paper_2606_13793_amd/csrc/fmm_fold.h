@@ -184,8 +184,10 @@ struct FoldTab {
   short col[8 * hterms(P)];             // m2lf_col
   unsigned char full[hterms(P)];        // full-term index of a reduced term
   unsigned char par[hterms(P)];         // its parity pattern
+  unsigned char deg[hterms(P)];         // its degree
+  unsigned char idx[hterms(P)];         // its place among the terms of that pattern
   signed char pt[8][4 * blk_psteps(P)];  // blk_pterm
-  constexpr FoldTab() : col(), full(), par(), pt() {
+  constexpr FoldTab() : col(), full(), par(), deg(), idx(), pt() {
     for (int i = 0; i < 8 * hterms(P); ++i) col[i] = (short)m2lf_col(P, i);
     int cnt[8] = {};
     for (auto& row : pt)
@@ -194,6 +196,8 @@ struct FoldTab {
       const int ex = h_exp(i), e = h_parity(i);
       full[i] = (unsigned char)mi_index(ex & 255, (ex >> 8) & 255, ex >> 16);
       par[i] = (unsigned char)e;
+      deg[i] = (unsigned char)h_degree(i);
+      idx[i] = (unsigned char)cnt[e];
       pt[e][cnt[e]++] = (signed char)i;
     }
   }
@@ -1093,91 +1097,4 @@ __global__ void k_m2pf_table(const double* __restrict__ Dtab2, const int2* __res
     x *= adj ? 1.0 / 64 : 1.0 / 8;
   }
   W[id] = static_cast<H>(x);
-}
-
-// L2L, eq. (L2L), in harmonic terms: the complete locals of the cells of one
-// level, [cell][hrow], from the M2L's rows (Walsh-folded over the children) and
-// the complete locals of the level above (null: the coarsest level).  With
-// S[b][pat] the shift's partial sum over the g of parity pattern pat
-// (coefficient lists of plan time, over the full terms b + g, which a block
-// expands once from the harmonic ones),
-//   L(child, b) = chi_b(sigma) sum_kappa chi_kappa(sigma) (Lw[kappa][b] / 8 + S[b][kappa ^ parity(b)]).
-// Thread (parent of 16, slot of 32): terms slot, slot + 32, ...
-// Segments: n = cells per axis of level k - 1, a = its complete locals (or
-// null), c = M2L rows of level k, b = the result.
-constexpr int L2LF_ROWS = 16, L2LF_THREADS = 512;
-template <int P>
-__global__ __launch_bounds__(L2LF_THREADS) void k_l2lf(const Seg* __restrict__ segs, int nseg,
-                                                       const int* __restrict__ cs, const int* __restrict__ cidx,
-                                                       const double* __restrict__ ccoef) {
-  constexpr int NL = nterms(P), HT = hterms(P), HR = hrow(P), E = l2l_entries(P), SS = NL + 1;
-  __shared__ int s_cs[8 * NL + 1];
-  __shared__ int s_idx[E];
-  __shared__ double s_coef[E];
-  __shared__ double s_src[L2LF_ROWS * SS];
-  __shared__ double s_h[L2LF_ROWS * HR];
-  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
-  const int ns = sg.n;
-  const long long nps = (long long)ns * ns * ns, P0 = (long long)(blockIdx.x - sg.first_block) * L2LF_ROWS;
-  const bool up = sg.a != nullptr;
-  if (up) {
-    for (int t = threadIdx.x; t <= 8 * NL; t += L2LF_THREADS) s_cs[t] = cs[t];
-    for (int t = threadIdx.x; t < E; t += L2LF_THREADS) {
-      s_idx[t] = cidx[t];
-      s_coef[t] = ccoef[t];
-    }
-    for (int t = threadIdx.x; t < L2LF_ROWS * HR; t += L2LF_THREADS)
-      s_h[t] = P0 + t / HR < nps ? sg.a[P0 * HR + t] : 0.0;
-    __syncthreads();
-    // full terms: (x, y, 2k + e) = (-1)^k sum_l C(k, l) (x + 2l, y + 2(k - l), e)
-    for (int t = threadIdx.x; t < L2LF_ROWS * NL; t += L2LF_THREADS) {
-      const int r = t / NL, f = t - r * NL, ex = c_mi_exp[f], z = mi_c(ex), k = z >> 1;
-      double v = 0.0;
-      for (int l = 0; l <= k; ++l)
-        v += (double)binom(k, l) * s_h[r * HR + h_index(mi_a(ex) + 2 * l, mi_b(ex) + 2 * (k - l), z & 1)];
-      s_src[r * SS + f] = (k & 1) ? -v : v;
-    }
-    __syncthreads();
-  }
-  const int slot = threadIdx.x & 31, r = threadIdx.x >> 5;
-  const long long Pc = P0 + r;
-  if (Pc >= nps) return;
-  const int p2 = (int)(Pc % ns), p1 = (int)((Pc / ns) % ns), p0 = (int)(Pc / ((long long)ns * ns));
-  const double* __restrict__ row = sg.c + Pc * frow(P);
-  const double* src = s_src + r * SS;
-  double* __restrict__ out = sg.b;
-  for (int b = slot; b < HT; b += 32) {
-    const int bt = c_ft<P>.full[b], pb = c_ft<P>.par[b];
-    double y[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = row[fold_at(k, b)];
-    double S[8];
-#pragma unroll
-    for (int pat = 0; pat < 8; ++pat) {
-      double x = 0.0;
-      if (up)
-#pragma unroll 2
-        for (int j = s_cs[8 * bt + pat]; j < s_cs[8 * bt + pat + 1]; ++j) x = fma(s_coef[j], src[s_idx[j]], x);
-      S[pat] = x;
-    }
-    // S over the patterns of the full shift; its Walsh index is kappa = pat ^ pb,
-    // so transform both sums apart and give S its sign chi_b
-#pragma unroll
-    for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (!(e & bit)) {
-          const double u = y[e], v = y[e | bit], a = S[e], c = S[e | bit];
-          y[e] = u + v;
-          y[e | bit] = u - v;
-          S[e] = a + c;
-          S[e | bit] = a - c;
-        }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const long long c = ((long long)(2 * p0 + 1 - ((t >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((t >> 1) & 1))) * (2 * ns) +
-                          (2 * p2 + 1 - (t & 1));
-      out[c * HR + b] = fma(0.125 * chi(pb, t), y[t], S[t]);
-    }
-  }
 }

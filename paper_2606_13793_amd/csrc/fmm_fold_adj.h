@@ -180,133 +180,6 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
   }
 }
 
-// L2L^T for one level k: from the complete locals' cotangents of its cells
-// ([cell][hrow]) to those of the M2L's rows (planes over the parents, Walsh
-// sums over the children / 8) and, unless k is the coarsest, to those of the
-// level above.  With W[b][pat] = sum_children sigma^pat Lc_bar(child, b), the
-// shift's transpose is the M2M's coefficient list at half weight over the
-// harmonic b, and the expansion to full terms transposes to h_reduce.
-template <int P>
-struct L2LAdj {
-  static constexpr int NL = nterms(P), HT = hterms(P), PAR = NL <= 56 ? 16 : 8;
-};
-template <int P, typename H>
-__global__ __launch_bounds__(256) void k_l2lf_adj(const double* __restrict__ lc, H* __restrict__ lb,
-                                                  double* __restrict__ lup, int ns, const int* __restrict__ cstart,
-                                                  const int* __restrict__ coff, const double* __restrict__ ccoef) {
-  constexpr int NL = L2LAdj<P>::NL, HT = L2LAdj<P>::HT, PAR = L2LAdj<P>::PAR, HR = hrow(P), WS = 8 * NL + 1;
-  __shared__ double W[PAR * WS];
-  __shared__ double full[PAR * NL];
-  const long long nps = (long long)ns * ns * ns, P0 = (long long)blockIdx.x * PAR;
-  const int nsp = ns + 6;
-  const long long ncp = (long long)nsp * nsp * nsp;
-  if (lup)
-    for (int q = threadIdx.x; q < PAR * WS; q += 256) W[q] = 0.0;
-  __syncthreads();
-  for (int q = threadIdx.x; q < PAR * HT; q += 256) {
-    const int b = q % HT, pl = q / HT;
-    const long long p = P0 + pl;
-    double y[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) y[m] = 0.0;
-    if (p < nps) {
-      const int p2 = (int)(p % ns), p1 = (int)((p / ns) % ns), p0 = (int)(p / ((long long)ns * ns));
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const long long c = ((long long)(2 * p0 + 1 - ((m >> 2) & 1)) * (2 * ns) + (2 * p1 + 1 - ((m >> 1) & 1))) * (2 * ns) +
-                            (2 * p2 + 1 - (m & 1));
-        y[m] = lc[c * HR + b];
-      }
-    }
-    walsh8(y);
-    const int bt = c_ft<P>.full[b];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) W[pl * WS + 8 * bt + k] = y[k];
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < PAR * 8 * HT; q += 256) {
-    const int pl = q % PAR, c = q / PAR;
-    const long long p = P0 + pl;
-    if (p >= nps) continue;
-    const int cb = c_ft<P>.col[c], b = cb & 255, bt = c_ft<P>.full[b];
-    const int p2 = (int)(p % ns), p1 = (int)((p / ns) % ns), p0 = (int)(p / ((long long)ns * ns));
-    lb[c * ncp + ((long long)(p0 + 3) * nsp + p1 + 3) * nsp + p2 + 3] =
-        static_cast<H>(0.125 * W[pl * WS + 8 * bt + ((cb >> 8) ^ c_ft<P>.par[b])]);
-  }
-  if (!lup) return;
-  for (int q = threadIdx.x; q < PAR * NL; q += 256) {
-    const int pl = q % PAR, e = q / PAR;
-    double acc = 0.0;
-#pragma unroll 4
-    for (int j = cstart[e]; j < cstart[e + 1]; ++j) acc = fma(ccoef[j], W[pl * WS + coff[j]], acc);
-    full[pl * NL + e] = 0.5 * acc;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < PAR * HT; q += 256) {
-    const int b = q % HT, pl = q / HT;
-    // transpose of the expansion to full terms: the same weights as h_reduce
-    if (P0 + pl < nps) lup[(P0 + pl) * HR + b] = h_reduce(b, [&](int t) { return full[pl * NL + t]; });
-  }
-}
-
-// M2M^T for one level k in harmonic terms: Mh_bar_k[child][b] += sum over the
-// full terms a = b + g of the parent, whose cotangents are those of its
-// harmonic terms expanded by Laplace's equation (the transpose of h_reduce).
-// Planes [term][(n + 6)^3]; np = cells per axis of level k - 1.
-constexpr int M2MA_PAR = 16;
-template <int P>
-__global__ __launch_bounds__(256) void k_m2mf_adj(const double* __restrict__ Mp, double* __restrict__ Mc, int np,
-                                                  const int* __restrict__ lstart, const int* __restrict__ la,
-                                                  const double* __restrict__ lcoef) {
-  constexpr int NM = nterms(P), HT = hterms(P), MS = NM | 1;
-  __shared__ double mh[M2MA_PAR * HT];
-  __shared__ double mrow[M2MA_PAR * MS];
-  const int npp = np + 6, nk = 2 * np, nkp = nk + 6;
-  const long long ncp = (long long)npp * npp * npp, nck = (long long)nkp * nkp * nkp, nps = (long long)np * np * np;
-  const long long P0 = (long long)blockIdx.x * M2MA_PAR;
-  for (int q = threadIdx.x; q < M2MA_PAR * HT; q += 256) {
-    const int pl = q % M2MA_PAR, t = q / M2MA_PAR;
-    const long long p = P0 + pl;
-    double v = 0.0;
-    if (p < nps) {
-      const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np));
-      v = Mp[t * ncp + ((long long)(p0 + 3) * npp + p1 + 3) * npp + p2 + 3];
-    }
-    mh[pl * HT + t] = v;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < M2MA_PAR * NM; q += 256) {
-    const int pl = q % M2MA_PAR, f = q / M2MA_PAR, ex = c_mi_exp[f], z = mi_c(ex), k = z >> 1;
-    double v = 0.0;
-    for (int l = 0; l <= k; ++l)
-      v += (double)binom(k, l) * mh[pl * HT + h_index(mi_a(ex) + 2 * l, mi_b(ex) + 2 * (k - l), z & 1)];
-    mrow[pl * MS + f] = (k & 1) ? -v : v;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < M2MA_PAR * HT; q += 256) {
-    const int pl = q % M2MA_PAR, b = q / M2MA_PAR;
-    const long long p = P0 + pl;
-    if (p >= nps) continue;
-    const int bt = c_ft<P>.full[b];
-    const double* mr = mrow + pl * MS;
-    double S[8];
-#pragma unroll
-    for (int pat = 0; pat < 8; ++pat) {
-      double x = 0.0;
-      for (int j = lstart[bt * 8 + pat]; j < lstart[bt * 8 + pat + 1]; ++j) x = fma(lcoef[j], mr[la[j]], x);
-      S[pat] = x;
-    }
-    walsh8(S);  // child c takes sum_pat (-1)^popc(c & pat) S[pat]
-    const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np));
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const long long cc = ((long long)(2 * p0 + ((c >> 2) & 1) + 3) * nkp + (2 * p1 + ((c >> 1) & 1) + 3)) * nkp +
-                           (2 * p2 + (c & 1) + 3);
-      Mc[b * nck + cc] += S[c];
-    }
-  }
-}
-
 // Transpose of the block stencil (P2P^T, M2P^T and the finest P2M^T), plus the
 // P2M^T of level F - 1: rho_bar of a 4^3 block from the cotangents of the 12^3
 // cells around, one output (phi, gx, gy, gz) in the LDS tile at a time, and

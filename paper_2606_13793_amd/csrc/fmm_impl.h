@@ -301,7 +301,8 @@ __global__ __launch_bounds__(256) void k_p2m(const Seg* __restrict__ segs, int n
 // 1/8)), and each term is then 8 products with the integer weights 3^k of
 // its slots, scaled by 8^-|a| / a!.  The term loop is unrolled (P fixed), so
 // the slots are register indices known at compile time.
-template <int P, typename TI, typename CT>
+// HARM: folded fields, harmonic planes only (b FP64, u a copy in FP32 or null).
+template <int P, typename TI, typename CT, bool HARM>
 __global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int nseg, IoArg io, int NM) {
   constexpr int NT = nterms(P), NC = (NT + 3) / 4;
   const Seg& sg = find_seg(segs, nseg, blockIdx.x);
@@ -357,20 +358,18 @@ __global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int 
       }
       d[decltype(ec)::value] = val;
       o[al % 4] = val;
-      if constexpr (al % 4 == 3 || al == NT - 1) {
+      if constexpr (!HARM && (al % 4 == 3 || al == NT - 1)) {
         *reinterpret_cast<d4*>(M + (c * ncellp + cp) * 4) = o;
         TypedChunk<CT>::template put<c, NC>(tv, o, sg.t, ncellp, cp);
         o = d4{0, 0, 0, 0};
       }
     });
-    if (sg.u)
+    if constexpr (HARM)
       static_for<2 * m + 1>([&](auto rc) {
         constexpr int i = m * m + decltype(rc)::value;
         const double v = h_reduce_deg<i>(d);
-        if (sg.split)
-          static_cast<float*>(sg.u)[i * ncellp + cp] = (float)v;
-        else
-          static_cast<double*>(sg.u)[i * ncellp + cp] = v;
+        M[i * ncellp + cp] = v;
+        if (sg.u) static_cast<float*>(sg.u)[i * ncellp + cp] = (float)v;
       });
     // (one degree at a time: the scheduler would otherwise form every term
     // before the first store and hold them all in registers)
@@ -613,6 +612,7 @@ __device__ __forceinline__ double p2p2_coef(int k, int grp, int q, int o) {
 
 #include "fmm_mfma.h"
 #include "fmm_fold.h"
+#include "fmm_shift.h"
 #include "fmm_fold_adj.h"
 
 // ---------------------------------------------------------------------------
@@ -1436,6 +1436,7 @@ hipError_t build_fold(fmm_plan* pl, int op, int x, hipStream_t s) {
 
 // every launch site's compute type: levels k < m2l_low_from and bottoms of
 // fields with F <= coarse_fp64_levels run in FP64
+template <int P>
 hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   hipLaunchKernelGGL(k_dtab, dim3(blocks_for(343 * 8, 64)), dim3(64), 0, s, pl->dtab, pl->p + 1, pl->ND);
   hipError_t e = hipGetLastError();
@@ -1450,6 +1451,13 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   {
     if (pl->s_m2lf[x][0].nseg && (e = build_fold(pl, FO_M2L, x, s)) != hipSuccess) return e;
     if (pl->s_m2pf[x][0].nseg && (e = build_fold(pl, FO_M2P, x, s)) != hipSuccess) return e;
+  }
+  if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
+    constexpr int cnt = ShiftShape<P>::GATHER + ShiftShape<P>::SCATTER;
+    if ((e = hipMalloc(&pl->wshift, cnt * sizeof(double))) != hipSuccess) return e;
+    pl->bytes += cnt * sizeof(double);
+    hipLaunchKernelGGL(k_shift_table<P>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->wshift);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
     double* G = nullptr;
@@ -1727,27 +1735,39 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   {
     StageScope sc(pl, ST_P2M, 1, s);
     // terms past nmax are written as zero
-    if (!pl->s_p2m.nseg)
-      ;
-    else if (pl->dl == 2)
-      hipLaunchKernelGGL((k_p2m2<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
-                         io, pl->NMX);
-    else if constexpr (Mf<CT>::IDX == 2)
-      hipLaunchKernelGGL((k_p2m<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
-                         io, pl->NMX);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (pl->s_p2m2.nseg) {
-      hipLaunchKernelGGL((k_p2m2<P, TI, CT>), dim3(pl->s_p2m2.blocks), dim3(256), 0, s, pl->s_p2m2.dev,
-                         pl->s_p2m2.nseg, io, pl->NMX);
+    if (pl->s_p2mf.nseg) {
+      hipLaunchKernelGGL((k_p2m2<P, TI, CT, true>), dim3(pl->s_p2mf.blocks), dim3(256), 0, s, pl->s_p2mf.dev,
+                         pl->s_p2mf.nseg, io, pl->NMX);
       if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if constexpr (Mf<CT>::IDX == 2) {
+      if (!pl->s_p2m.nseg)
+        ;
+      else if (pl->dl == 2)
+        hipLaunchKernelGGL((k_p2m2<P, TI, CT, false>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev,
+                           pl->s_p2m.nseg, io, pl->NMX);
+      else
+        hipLaunchKernelGGL((k_p2m<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
+                           io, pl->NMX);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if (pl->s_p2m2.nseg) {
+        hipLaunchKernelGGL((k_p2m2<P, TI, CT, false>), dim3(pl->s_p2m2.blocks), dim3(256), 0, s, pl->s_p2m2.dev,
+                           pl->s_p2m2.nseg, io, pl->NMX);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
     }
   }
   for (int k = pl->maxF; k >= 3; --k) {
-    const SegTable& st = pl->s_m2m[k];
-    if (!st.nseg) continue;
-    StageScope sc(pl, ST_M2M, 1, s);
-    hipLaunchKernelGGL((k_m2m<P, CT>), dim3(st.blocks), dim3(M2MShape<P>::THREADS), 0, s, st.dev, st.nseg,
-                       pl->m2m_start, pl->m2m_off, pl->m2m_coef, pl->NMX);
+    const SegTable &st = pl->s_m2m[k], &sf = pl->s_m2mf[k];
+    if (!st.nseg && !sf.nseg) continue;
+    StageScope sc(pl, ST_M2M, (st.nseg > 0) + (sf.nseg > 0), s);
+    if (sf.nseg)
+      hipLaunchKernelGGL((k_gather<P, false, double>), dim3(sf.blocks), dim3(256), 0, s, sf.dev, sf.nseg, Seg{},
+                         pl->wshift, hterms(pl->nmax));
+    if constexpr (Mf<CT>::IDX == 2)
+      if (st.nseg)
+        hipLaunchKernelGGL((k_m2m<P, CT>), dim3(st.blocks), dim3(M2MShape<P>::THREADS), 0, s, st.dev, st.nseg,
+                           pl->m2m_start, pl->m2m_off, pl->m2m_coef, pl->NMX);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_fold_site<P, double, FO_M2L>(pl, 0, s)) != hipSuccess) return e;
@@ -1768,8 +1788,8 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
     const SegTable& st = pl->s_l2lf[k];
     if (!st.nseg) continue;
     StageScope sc(pl, ST_L2L, 1, s);
-    hipLaunchKernelGGL(k_l2lf<P>, dim3(st.blocks), dim3(L2LF_THREADS), 0, s, st.dev, st.nseg, pl->l2l_start,
-                       pl->l2l_idx, pl->l2l_coef);
+    hipLaunchKernelGGL((k_scatter<P, true>), dim3(st.blocks), dim3(64 * ShiftShape<P>::NTB), 0, s, st.dev, st.nseg,
+                       Seg{}, pl->wshift);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   for (int k = 4; k <= pl->maxF - 1; ++k) {
@@ -1874,14 +1894,16 @@ hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI*
   }
   for (int k = B; k >= 3; --k) {
     const int ns = 1 << (k - 1);
-    const unsigned g = blocks_for((long long)ns * ns * ns, L2LAdj<P>::PAR);
-    double* up = k > 3 ? w.lc[k - 1] : nullptr;
+    Seg l{};
+    l.n = ns;
+    l.a = w.lc[k];
+    l.b = k > 3 ? w.lc[k - 1] : nullptr;
+    l.u = w.lb[k];
+    const dim3 g(blocks_for((long long)ns * ns * ns, 16));
     if (harmonic_float(pl, F, k - 1))
-      hipLaunchKernelGGL((k_l2lf_adj<P, float>), dim3(g), dim3(256), 0, s, w.lc[k], (float*)w.lb[k], up, ns,
-                         pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+      hipLaunchKernelGGL((k_gather<P, true, float>), g, dim3(256), 0, s, nullptr, 0, l, pl->wshift, hterms(P));
     else
-      hipLaunchKernelGGL((k_l2lf_adj<P, double>), dim3(g), dim3(256), 0, s, w.lc[k], (double*)w.lb[k], up, ns,
-                         pl->m2m_start, pl->m2m_off, pl->m2m_coef);
+      hipLaunchKernelGGL((k_gather<P, true, double>), g, dim3(256), 0, s, nullptr, 0, l, pl->wshift, hterms(P));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_fold<P, double, FO_M2LT>(pl, 0, w.m2ltf_v[0], w.m2ltf[0], s)) != hipSuccess) return e;
@@ -1897,9 +1919,12 @@ hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI*
   }
   for (int k = 3; k <= B; ++k) {
     const int np = 1 << (k - 1);
-    hipLaunchKernelGGL((k_m2mf_adj<P>), dim3(blocks_for((long long)np * np * np, M2MA_PAR)), dim3(256), 0, s,
-                       (const double*)pl->lev[k - 1].M, (double*)pl->lev[k].M, np, pl->m2mt_start, pl->m2mt_a,
-                       pl->m2mt_coef);
+    Seg m{};
+    m.n = np;
+    m.a = (const double*)pl->lev[k - 1].M;
+    m.b = (double*)pl->lev[k].M;
+    hipLaunchKernelGGL((k_scatter<P, false>), dim3(blocks_for((long long)np * np * np, 16)),
+                       dim3(64 * ShiftShape<P>::NTB), 0, s, nullptr, 0, m, pl->wshift);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const double* mb = B >= 2 ? (const double*)pl->lev[B].M : nullptr;
@@ -2013,7 +2038,7 @@ hipError_t Impl<P>::upload_constants() {
 template <int P>
 hipError_t Impl<P>::tables(fmm_plan* pl, hipStream_t s) {
   const hipError_t e = alloc_m2lf_part<P>(pl);
-  return e == hipSuccess ? tables_all(pl, s) : e;
+  return e == hipSuccess ? tables_all<P>(pl, s) : e;
 }
 
 template <int P>

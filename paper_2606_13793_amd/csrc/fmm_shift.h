@@ -1,0 +1,241 @@
+// Shifts between levels in harmonic terms, on the matrix cores.  Included by
+// fmm_impl.h.
+#pragma once
+
+// M2M, L2L and their transposes are one matrix.  With t = b + g over the full
+// terms and the harmonic ones D_a spanning them (D_t = sum_a w(a, t) D_a),
+//   C(a, b) = sum_g 2^-|b| 4^-|g| / g! w(a, b + g),  |g| = |a| - |b|,
+//   M2M      M(P, a) = sum_q sum_b chi_{a+b}(q) C(a, b) M(2P + q, b)
+//   L2L      L(2P + q, b) = own(q, b) + sum_a chi_{a+b}(q) C(a, b) / 2 L(P, a)
+// (chi: parities of the terms over the child's sign; w is h_reduce's, and keeps
+// degree and parity).  Sorting a into its 8 parity classes e makes the sign
+// chi_e(q) chi_b(q): a gather (M2M, transposed L2L) is a mirror folding of the
+// children about their parent, fold8, and 8 products over b; a scatter (L2L,
+// transposed M2M) is 8 products over the class's terms and an inverse Walsh sum,
+// which a lane holds whole.
+// Multipoles are planes [term][(n + 6)^3], so there a lane's column of a product
+// is the parent (stores run along z); locals are rows [cell][hrow], so there it
+// is the term.
+template <int P>
+struct ShiftShape {
+  static constexpr int HT = hterms(P), NS = (HT + 3) / 4, NPS = blk_psteps(P), NTC = (NPS + 3) / 4, NTB = (HT + 15) / 16;
+  static constexpr int SPW = (NS + 3) / 4;  // gather: K steps of each of the 4 waves
+  static constexpr int GATHER = NS * 8 * NTC * 64, SCATTER = 8 * NPS * NTB * 64;
+};
+
+__device__ inline double shift_coef(int a, int b) {
+  const int ea = h_exp(a), eb = h_exp(b), x = mi_a(ea), y = mi_b(ea), e = mi_c(ea);
+  double s = 0.0;
+  for (int l = 0; 2 * l <= x; ++l)
+    for (int m = 0; 2 * m <= y; ++m) {
+      const int g[3] = {x - 2 * l - mi_a(eb), y - 2 * m - mi_b(eb), 2 * (l + m) + e - mi_c(eb)};
+      if (g[0] < 0 || g[1] < 0 || g[2] < 0) continue;
+      double f = 1.0;
+      for (int i = 0; i < 3; ++i)
+        for (int k = 2; k <= g[i]; ++k) f *= k;
+      const double w = (double)(((l + m) & 1) ? -binom(l + m, l) : binom(l + m, l));
+      s += w * ldexp(1.0 / f, -h_degree(b) - 2 * (g[0] + g[1] + g[2]));
+    }
+  return s;
+}
+// Fragments of the gather [step][class][tile][64] (k-group kq: b = 4 s + kq;
+// lane: term 16 tile + i of the class), then of the scatter [class][step][tile]
+// [64] (k-group: term 4 s + kq of the class; lane: b = 16 tile + i).
+template <int P>
+__global__ void k_shift_table(double* __restrict__ W) {
+  using S = ShiftShape<P>;
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= S::GATHER + S::SCATTER) return;
+  const int i = id & 15, kq = (id >> 4) & 3;
+  int a, b;
+  if (id < S::GATHER) {
+    const int f = id >> 6, j = 16 * (f % S::NTC) + i;
+    a = j < 4 * S::NPS ? c_ft<P>.pt[(f / S::NTC) & 7][j] : -1;
+    b = 4 * (f / (8 * S::NTC)) + kq;
+  } else {
+    const int f = (id - S::GATHER) >> 6;
+    a = c_ft<P>.pt[f / (S::NTB * S::NPS)][4 * (f / S::NTB % S::NPS) + kq];
+    b = 16 * (f % S::NTB) + i;
+  }
+  W[id] = a >= 0 && b < S::HT ? shift_coef(a, b) : 0.0;
+}
+
+// Gather.  Segments: n = parents per axis, a = the children's values, b = the
+// parents' (ROWS: or null), u = M2M: copy of b in FP32, or null; ROWS: the
+// cotangents of the M2L's rows, planes [column][(n + 6)^3] over the parents in H,
+// the class sums over 8.  hm: terms written (the others are zero).
+// Block: 16 parents, 4 waves, each a quarter of the K steps: the loads of a wave
+// are all issued before its first product, and the quarters are added in LDS.
+// What bounds it: reading the children's values.
+template <int P, bool ROWS, typename H>
+__global__ __launch_bounds__(256, 2) void k_gather(const Seg* __restrict__ segs, int nseg, const Seg one,
+                                                   const double* __restrict__ W, int hm) {
+  using S = ShiftShape<P>;
+  constexpr int HT = S::HT, HR = hrow(P), NTC = S::NTC, SPW = S::SPW, RS = 17;
+  __shared__ double red[4 * 8 * NTC * 16 * RS];
+  const Seg& sg = nseg ? find_seg(segs, nseg, blockIdx.x) : one;
+  const int np = sg.n, npp = np + 6, nc = 2 * np + (ROWS ? 0 : 6);
+  const long long nps = (long long)np * np * np, ncpp = (long long)npp * npp * npp, ncc = (long long)nc * nc * nc;
+  const long long P0 = (long long)((int)blockIdx.x - sg.first_block) * 16;
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long pc = min(P0 + i, nps - 1);
+  const int p2 = (int)(pc % np), p1 = (int)((pc / np) % np), p0 = (int)(pc / ((long long)np * np));
+  const auto src = gmem(sg.a);
+  // v[u][m]: the child whose place in the parent has bits m (M2M: upper; ROWS:
+  // lower), the pair along z in one load
+  typedef double dz2 __attribute__((ext_vector_type(2), aligned(8)));
+  double v[SPW][8];
+#pragma unroll
+  for (int u = 0; u < SPW; ++u) {
+    const int b = min(4 * (w * SPW + u) + kq, HT - 1);  // (past the last: the table is zero)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int x = q >> 1, y = q & 1;
+      if constexpr (ROWS) {
+        const long long c = ((long long)(2 * p0 + 1 - x) * nc + 2 * p1 + 1 - y) * nc + 2 * p2;
+        v[u][2 * q] = src[(c + 1) * HR + b];
+        v[u][2 * q + 1] = src[c * HR + b];
+      } else {
+        const dz2 t = *(const __attribute__((address_space(1))) dz2*)(src + b * ncc +
+                                                                     ((long long)(2 * p0 + x + 3) * nc + 2 * p1 + y + 3) * nc + 2 * p2 + 3);
+        v[u][2 * q] = t[0];
+        v[u][2 * q + 1] = t[1];
+      }
+    }
+  }
+  d4 acc[8][NTC];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int t = 0; t < NTC; ++t) acc[e][t] = d4{0, 0, 0, 0};
+  const auto wt = gmem(W);
+#pragma unroll
+  for (int u = 0; u < SPW; ++u) {
+    const int s = w * SPW + u;
+    if (s >= S::NS) break;  // (uniform)
+    const int b = min(4 * s + kq, HT - 1), par = c_ft<P>.par[b];
+    double tb[8][NTC], a[8];
+    if (!ROWS || sg.b)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int t = 0; t < NTC; ++t) tb[e][t] = (wt + ((s * 8 + e) * NTC + t) * 64)[(unsigned)lane];
+    fold8<8>(v[u], par & 4 ? -1.0 : 1.0, par & 2 ? -1.0 : 1.0, par & 1 ? -1.0 : 1.0, a);
+    if constexpr (ROWS) {
+      if (4 * s + kq < HT && P0 + i < nps) {
+        const int m = c_ft<P>.deg[b];
+        H* const to = static_cast<H*>(sg.u) + (7 * m * m + b) * ncpp + ((long long)(p0 + 3) * npp + p1 + 3) * npp + p2 + 3;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) to[e * (2 * m + 1) * ncpp] = static_cast<H>(0.125 * a[e]);
+      }
+      if (!sg.b) continue;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int t = 0; t < NTC; ++t)
+        acc[e][t] = ROWS ? __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], tb[e][t], acc[e][t], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f64_16x16x4f64(tb[e][t], a[e], acc[e][t], 0, 0, 0);
+  }
+  if (ROWS && !sg.b) return;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int t = 0; t < NTC; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[(((w * 8 + e) * NTC + t) * 16 + Mf<double>::row(r, kq)) * RS + i] = acc[e][t][r];
+  __syncthreads();
+  for (int q = threadIdx.x; q < 16 * HT; q += 256) {
+    // (rows: the terms of a parent; planes: the parents of a term)
+    const int a = ROWS ? q % HT : q >> 4, pl = ROWS ? q / HT : q & 15;
+    const long long p = P0 + pl;
+    if (p >= nps) continue;
+    const int e = c_ft<P>.par[a], j = c_ft<P>.idx[a];
+    const int at = ((e * NTC + (j >> 4)) * 16 + (ROWS ? pl : j & 15)) * RS + (ROWS ? j & 15 : pl);
+    double x = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x += red[k * 8 * NTC * 16 * RS + at];
+    if constexpr (ROWS) {
+      sg.b[p * HR + a] = 0.5 * x;
+    } else {
+      const int q2 = (int)(p % np), q1 = (int)((p / np) % np), q0 = (int)(p / ((long long)np * np));
+      const long long to = a * ncpp + ((long long)(q0 + 3) * npp + q1 + 3) * npp + q2 + 3;
+      if (a >= hm) x = 0.0;
+      sg.b[to] = x;
+      if (sg.u) static_cast<float*>(sg.u)[to] = (float)x;
+    }
+  }
+}
+
+// Scatter.  Segments: n = parents per axis, a = the parents' values (ROWS: null
+// where there are none), b = the children's (planes: added to), ROWS: c = the
+// M2L's rows [parent][frow], sums over the children's signs times 8.
+// Block: 16 parents, one wave for each 16 terms b: it holds the 8 classes of a
+// (parent, term) in one lane, so the inverse Walsh sum needs no exchange.
+// What bounds it: the children's values.
+template <int P, bool ROWS>
+__global__ __launch_bounds__(64 * ShiftShape<P>::NTB) void k_scatter(const Seg* __restrict__ segs, int nseg, const Seg one,
+                                                                    const double* __restrict__ W) {
+  using S = ShiftShape<P>;
+  constexpr int HT = S::HT, HR = hrow(P), FR = frow(P), NPS = S::NPS, NTB = S::NTB;
+  const Seg& sg = nseg ? find_seg(segs, nseg, blockIdx.x) : one;
+  const int np = sg.n, npp = np + 6, nc = 2 * np + (ROWS ? 0 : 6);
+  const long long nps = (long long)np * np * np, ncpp = (long long)npp * npp * npp, ncc = (long long)nc * nc * nc;
+  const long long P0 = (long long)((int)blockIdx.x - sg.first_block) * 16;
+  const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  d4 acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = d4{0, 0, 0, 0};
+  if (sg.a) {
+    const long long pc = min(P0 + i, nps - 1);
+    const int p2 = (int)(pc % np), p1 = (int)((pc / np) % np), p0 = (int)(pc / ((long long)np * np));
+    const auto src = gmem(sg.a + (ROWS ? pc * HR : ((long long)(p0 + 3) * npp + p1 + 3) * npp + p2 + 3));
+    const auto wt = gmem(W + S::GATHER + t * 64);
+    double v[8][NPS];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int s = 0; s < NPS; ++s) v[e][s] = src[max((int)c_ft<P>.pt[e][4 * s + kq], 0) * (ROWS ? 1LL : ncpp)];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int s = 0; s < NPS; ++s) {
+        // (a class's places past its last term: the table is zero)
+        const double tb = (wt + (e * NPS + s) * NTB * 64)[(unsigned)lane];
+        acc[e] = ROWS ? __builtin_amdgcn_mfma_f64_16x16x4f64(v[e][s], tb, acc[e], 0, 0, 0)
+                      : __builtin_amdgcn_mfma_f64_16x16x4f64(tb, v[e][s], acc[e], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = Mf<double>::row(r, kq), b = 16 * t + (ROWS ? i : row);
+    const long long p = P0 + (ROWS ? row : i);
+    if (b >= HT || p >= nps) continue;
+    const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np)), pb = c_ft<P>.par[b];
+    double y[8];
+    if constexpr (ROWS) {
+      const auto own = gmem(sg.c + p * FR + fold_at(0, b));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = fma(0.125, own[2 * e], 0.5 * acc[e][r]);
+      walsh8(y);
+      double* const to = sg.b + (((long long)(2 * p0) * nc + 2 * p1) * nc + 2 * p2) * HR + b;
+#pragma unroll
+      for (int m = 0; m < 8; ++m)  // minus bits
+        to[((long long)((m & 4 ? 0 : 1) * nc + (m & 2 ? 0 : 1)) * nc + (m & 1 ? 0 : 1)) * HR] = chi(pb, m) * y[m];
+    } else {
+      typedef double dz2 __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = acc[e][r];
+      walsh8(y);
+      double* const to = sg.b + b * ncc + ((long long)(2 * p0 + 3) * nc + 2 * p1 + 3) * nc + 2 * p2 + 3;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {  // upper bits
+        dz2* const z = reinterpret_cast<dz2*>(to + ((long long)(q >> 1) * nc + (q & 1)) * nc);
+        *z += dz2{chi(pb, 2 * q) * y[2 * q], chi(pb, 2 * q + 1) * y[2 * q + 1]};
+      }
+    }
+  }
+}
