@@ -92,8 +92,8 @@ constexpr __host__ __device__ int blk_pterm(int P, int e, int k) {
     if (h_parity(i) == e && k-- == 0) return i;
   return -1;
 }
-// table layout (elements): the folded stencil [54][8][2][64], the own locals
-// [steps][2][64], the level F-1 locals [8][steps][2][64]
+// table layout (elements): the folded stencil [54][8][64][2 column tiles], the
+// own locals [steps][64][2], the level F-1 locals [8][steps][64][2]
 constexpr __host__ __device__ int blk_off_l() { return BLK_STEPS * 8 * 2 * 64; }
 constexpr __host__ __device__ int blk_off_p(int P) { return blk_off_l() + 2 * blk_lpairs(P) * 2 * 64; }
 constexpr __host__ __device__ int blk_table(int P) { return blk_off_p(P) + 8 * blk_psteps(P) * 2 * 64; }
@@ -148,7 +148,7 @@ template <typename H>
 __global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int P, int dl) {
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= blk_table(P)) return;
-  const int lane = id & 63, tile = (id >> 6) & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
+  const int lane = (id >> 1) & 63, tile = id & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
   const int t = col >> 2, o = col & 3;
   double x = 0.0;
   if (id < blk_off_l()) {
@@ -338,19 +338,20 @@ __device__ __forceinline__ void blk_read(const H* const (&p)[4], H (&r)[8]) {
 // blocks (of 4 waves) per compute unit
 template <typename CT, int NX>
 constexpr int blk_occ = Mf<CT>::IDX == 0 ? 2 : NX == 2 ? 3 : 4;
-template <int P, typename CT, typename TI, typename TO, int NX, int DL>
+template <int P, typename CT, typename TI, typename TO, int NX, int NT, int DL>
 __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     const Seg* __restrict__ segs, int nseg, IoArg io, const typename Mf<CT>::H* __restrict__ W,
     unsigned int* __restrict__ stamp_cnt, unsigned long long* __restrict__ stamp_done) {
   using M = Mf<CT>;
   using H = typename M::H;
   using Acc = typename M::Acc;
+  typedef H h2 __attribute__((ext_vector_type(2)));
   constexpr int NE = 4, KS = Mf<CT>::IDX == 0 ? 2 / NX : 2, NR = NX * KS / 2, HR = hrow(P), FR = frow(P);
   constexpr int NLP = blk_lpairs(P), NPS = blk_psteps(P), OFF_L = blk_off_l(), OFF_P = blk_off_p(P);
   // own-local pairs of steps of the last K slice, which has one group less
   constexpr int LSPLIT = KS == 1 ? NLP : NLP < (8 + NPS + 2 * NLP) / 4 ? NLP : (8 + NPS + 2 * NLP) / 4;
-  // epilogue image of the results of NXR row tiles, [slice][half][4][NXR * 16][33]
-  constexpr int NXR = NX / NR, ES = NXR * 16 * 33;
+  // epilogue image of the results of NXR row tiles, [slice][half][4][NXR * 16][CS]
+  constexpr int NXR = NX / NR, CS = 16 * NT + 1, ES = NXR * 16 * CS;
   constexpr int EP = KS * 8 * ES, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
   __shared__ int spt[8 * NPS * 4];
@@ -361,40 +362,46 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
   const int lb = blockIdx.x - sg.first_block;
   const int bx0 = (lb / (sg.tpa * sg.tpa)) * NX, by0 = ((lb / sg.tpa) % sg.tpa) * 4, bz0 = (lb % sg.tpa) * 4;
   for (int t = threadIdx.x; t < 8 * NPS * 4; t += BLK_THREADS) spt[t] = c_ft<P>.pt[t / (NPS * 4)][t % (NPS * 4)];
-  stage_cells<NX>(lds, io_rho<TI>(io, sg.field), static_cast<TI*>(sg.t), n, 4 * bx0 - 4, 4 * by0 - 4, 4 * bz0 - 4,
+  const int t0 = NT == 1 ? blockIdx.y : 0;  // column tile
+  stage_cells<NX>(lds, io_rho<TI>(io, sg.field), t0 ? nullptr : static_cast<TI*>(sg.t), n, 4 * bx0 - 4, 4 * by0 - 4, 4 * bz0 - 4,
                   [](TI v) { return static_cast<H>(v); });
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   // the wave's first row tile, K slice and half of the patterns
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = KS == 1 ? w & 1 : 0, ks = KS == 1 ? 0 : w & 1,
             half = w >> 1, e0 = half * NE;
   const H sx = half ? H(-1) : H(1);
-  Acc acc[NR][NE][2];
+  Acc acc[NR][NE][NT];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) acc[r][e][0] = acc[r][e][1] = Acc{0, 0, 0, 0};
-  auto products = [&](const H (&a)[NR][NE], const H (&b)[NE][2]) {
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[r][e][t] = Acc{0, 0, 0, 0};
+  auto products = [&](const H (&a)[NR][NE], const H (&b)[NE][NT]) {
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        acc[r][e][0] = M::op(a[r][e], b[e][0], acc[r][e][0]);
-        acc[r][e][1] = M::op(a[r][e], b[e][1], acc[r][e][1]);
-      }
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[r][e][t] = M::op(a[r][e], b[e][t], acc[r][e][t]);
   };
   __syncthreads();
   // ---- the 12^3 densities
   {
     const H* ctr = lds + (4 * X + 6) * BLK_PLANE + blk_row(4 * (i >> 2) + 6) + 4 * (i & 3);
-    const auto wb = gmem(W + e0 * 128);  // (uniform base, the lane as a 32-bit offset)
-    auto bread = [&](int s, H (&b)[NE][2]) {
+    const auto wb = gmem(W + e0 * 128 + t0);  // (uniform base, the lane as a 32-bit offset)
+    auto bread = [&](int s, H (&b)[NE][NT]) {
 #pragma unroll
       for (int e = 0; e < NE; ++e)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) b[e][t] = (wb + s * 1024 + e * 128 + t * 64)[(unsigned)lane];
+        if constexpr (NT == 2) {
+          const h2 v = *(const __attribute__((address_space(1))) h2*)(wb + s * 1024 + e * 128 + 2u * lane);
+          b[e][0] = v[0], b[e][1] = v[1];
+        } else {
+          b[e][0] = (wb + s * 1024 + e * 128)[2u * lane];
+        }
     };
     const H* p[4];
-    H r[NR][8], b[2][NE][2], a[NR][NE];
+    H r[NR][8], b[2][NE][NT], a[NR][NE];
     auto aread = [&](auto jc) {
 #pragma unroll
       for (int m = 0; m < NR; ++m)
@@ -437,22 +444,22 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     cell[r] = ((long long)min(bx0 + X + r, nb - 1) * nb + min(by0 + (i >> 2), nb - 1)) * nb + min(bz0 + (i & 3), nb - 1);
   if (DL == 1 && sg.u) {
     typedef H h8 __attribute__((ext_vector_type(8), aligned(16)));
-    const auto wl = gmem(W + OFF_L);
+    const auto wl = gmem(W + OFF_L + t0);
     const auto own = gmem(static_cast<const H*>(sg.u) + 2 * e0);
     h8 x[2][NR];
-    H y[2][2][2];
+    H y[2][2][NT];
     // pair of steps s: 4 patterns of 2 terms are one run
-    auto read = [&](int s, h8 (&x)[NR], H (&y)[2][2]) {
+    auto read = [&](int s, h8 (&x)[NR], H (&y)[2][NT]) {
       const int q = min(4 * s + kq, FR / 16 - 1);  // (past the last: the table is zero)
 #pragma unroll
       for (int r = 0; r < NR; ++r) x[r] = *(const __attribute__((address_space(1))) h8*)(own + cell[r] * FR + 16 * q);
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) y[v][t] = (wl + s * 256 + v * 128 + t * 64)[(unsigned)lane];
+        for (int t = 0; t < NT; ++t) y[v][t] = (wl + s * 256 + v * 128 + t)[2u * lane];
     };
     const int s0 = KS == 1 || ks ? 0 : LSPLIT, s1 = KS == 1 || !ks ? NLP : LSPLIT;
-    auto step = [&](const h8 (&x)[NR], const H (&y)[2][2]) {
+    auto step = [&](const h8 (&x)[NR], const H (&y)[2][NT]) {
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
@@ -460,7 +467,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
           for (int e = 0; e < NE; ++e)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) acc[r][e][t] = M::op(x[r][2 * e + v], y[v][t], acc[r][e][t]);
+            for (int t = 0; t < NT; ++t) acc[r][e][t] = M::op(x[r][2 * e + v], y[v][t], acc[r][e][t]);
     };
     if (s0 < s1) {
       read(s0, x[0], y[0]);
@@ -478,7 +485,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     }
   }
   if (sg.d && ks == 0) {
-    const auto wp = gmem(W + OFF_P + e0 * (NPS * 128));
+    const auto wp = gmem(W + OFF_P + e0 * (NPS * 128) + t0);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const auto par = gmem(sg.d + cell[r] * HR);
@@ -496,8 +503,9 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
         for (int s = 0; s < NPS; ++s) {
           const H a = static_cast<H>(v[e][s]);
-          acc[r][e][0] = M::op(a, (wp + (e * NPS + s) * 128)[(unsigned)lane], acc[r][e][0]);
-          acc[r][e][1] = M::op(a, (wp + (e * NPS + s) * 128 + 64)[(unsigned)lane], acc[r][e][1]);
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            acc[r][e][t] = M::op(a, (wp + (e * NPS + s) * 128 + t)[2u * lane], acc[r][e][t]);
         }
     }
   }
@@ -510,7 +518,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
   const int z = threadIdx.x & 15, y = threadIdx.x >> 4, qy = y & 3, qz = z & 3;
   const int uy = 4 * by0 + y, uz = 4 * bz0 + z, myz = (qy < 2) << 1 | (qz < 2);
   const int tyz = (qy == 0 || qy == 3) << 1 | (qz == 0 || qz == 3);
-  const H* const res = lds + myz * ES + (4 * (y >> 2) + (z >> 2)) * 33 + 4 * tyz;
+  const H* const res = lds + myz * ES + (4 * (y >> 2) + (z >> 2)) * CS + 4 * tyz;
   const double sc[4] = {0.125 * sphi, 0.125 * sgr, (qy < 2 ? -0.125 : 0.125) * sgr, (qz < 2 ? -0.125 : 0.125) * sgr};
   const long long blk0 = ((long long)bx0 * nb + (uy >> 2)) * nb + (uz >> 2), pyz = qy * 4 + qz;
   const unsigned at = (unsigned)(y * n + z);
@@ -520,12 +528,12 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     // patterns) when the results are read back as z runs
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const H p0 = acc[R][0][t][v] + acc[R][1][t][v], m0 = acc[R][0][t][v] - acc[R][1][t][v],
                 p1 = acc[R][2][t][v] + acc[R][3][t][v], m1 = acc[R][2][t][v] - acc[R][3][t][v];
-        H* const to = lds + (ks * 2 + half) * 4 * ES + (16 * X + M::row(v, kq)) * 33 + 16 * t + i;
+        H* const to = lds + (ks * 2 + half) * 4 * ES + (16 * X + M::row(v, kq)) * CS + 16 * t + i;
         to[0] = p0 + p1;
         to[ES] = m0 + m1;
         to[2 * ES] = p0 - p1;
@@ -535,7 +543,9 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     if (uy < n && uz < n)
       static_for<4 * NXR>([&](auto xc) {
         constexpr int x = decltype(xc)::value, qx = x & 3, XT = x >> 2, XB = R + XT;
-        constexpr int ro = (qx == 0 || qx == 3 ? 16 : 0) + 16 * XT * 33;
+        // (column tile 1: the outer two cells along x)
+        constexpr int outer = qx == 0 || qx == 3, ro = (NT == 2 ? 16 * outer : 0) + 16 * XT * CS;
+        if (NT == 1 && outer != t0) return;
         const int ux = 4 * (bx0 + XB) + qx;
         if (ux >= n) return;
         const long long row = ((long long)ux * n + 4 * by0) * n + 4 * bz0;  // (uniform)
@@ -562,7 +572,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     __syncthreads();
     if (threadIdx.x == 0) {
       __threadfence();
-      if (atomicAdd(stamp_cnt + sg.field, 1u) == (unsigned int)(sg.tpa * sg.tpa * sg.tz) - 1)
+      if (atomicAdd(stamp_cnt + sg.field, 1u) == (unsigned int)(sg.tpa * sg.tpa * sg.tz * (NT == 1 ? 2 : 1)) - 1)
         stamp_done[sg.field] = wall_clock64();
     }
   }
@@ -609,14 +619,15 @@ __host__ __device__ inline void fold_k(int op, int st, int kq, int* term, int* s
   *src = c % 27;
 }
 
-// B fragments in the compute type, [fragment (tile, step)][8 patterns][64];
+// B fragments in the compute type, [fragment (tile, step)][4 pairs of
+// patterns][64][2];
 // tiles[t] = (steps, first fragment).
 template <typename H>
 __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __restrict__ tiles, H* __restrict__ W, int P,
                              int nmax, int ND, long long cnt) {
   const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (id >= cnt) return;
-  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  const int lane = (int)(id >> 1) & 63, e = ((int)(id >> 7) & 3) * 2 + (int)(id & 1), f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
   const int kap = (lane >> 1) & 7, b = 2 * t + (lane & 1);  // fold_at
@@ -752,12 +763,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ seg
   using H = typename M::H;
   using Acc = typename M::Acc;
   constexpr int NR = 8 * MT / (NE * NW), NG = 8 / NE, NX = MT / NR, THR = 64 * NW;
-  static_assert(NG * NX == NW && NX * NR == MT, "the waves' shares");
+  static_assert(NG * NX == NW && NX * NR == MT && NE % 2 == 0, "the waves' shares");
   constexpr bool HEAD = OP == FO_M2L || OP == FO_M2P;
   constexpr int NTERM = OP == 3 ? 256 : OP == 1 ? 8 * hterms(P) : hterms(P);
   constexpr int ROW = FOLD_ROW, PLANE = FOLD_PLANE;
   constexpr int NTE = m2lf_nte<NT>, CELLS = (2 * MT + 4) * PLANE, CS = 16 * NTE + 1, NPL = HEAD ? 5 : 4;
   constexpr int EP = NX * 8 * 16 * CS, SZ = EP > NPL * CELLS ? EP : NPL * CELLS;
+  typedef H hp __attribute__((ext_vector_type(2)));  // two patterns of a fragment
   typedef H h2 __attribute__((ext_vector_type(2), aligned(sizeof(H))));
   constexpr int RPP = (2 * MT + 4) * 12, RPT = THR / 6, FB = (4 * RPP + RPT - 1) / RPT;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
@@ -834,7 +846,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ seg
       // (uniform base, the lane as a 32-bit offset)
       const auto p = gmem(W + ((size_t)(off[t] + st) * 8 + e0) * 64);
 #pragma unroll
-      for (int e = 0; e < NE; ++e) b[e][t] = (p + e * 64)[(unsigned)lane];
+      for (int e = 0; e < NE; e += 2) {
+        const hp v = *(const __attribute__((address_space(1))) hp*)(p + e * 64 + 2u * lane);
+        b[e][t] = v[0], b[e + 1][t] = v[1];
+      }
     }
   };
   auto products = [&](auto nac, const H (&a)[NR][NE], H (&b)[NE][decltype(nac)::value]) {
@@ -1005,6 +1020,8 @@ __global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, 
     double y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = slot[(size_t)(rp * 8 + e) * NQ + q];
+    // (several parts' loads in flight; the sum keeps its order)
+#pragma unroll 4
     for (int k = 1; k < np; ++k)
 #pragma unroll
       for (int e = 0; e < 8; ++e) y[e] += slot[(size_t)k * (NR * NP * NQ * 8) + (size_t)(rp * 8 + e) * NQ + q];
@@ -1018,7 +1035,7 @@ __global__ void k_m2lf_adj_table(const double* __restrict__ Dtab, const int2* __
                                  int P, int nmax, int ND, long long cnt) {
   const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (id >= cnt) return;
-  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  const int lane = (int)(id >> 1) & 63, e = ((int)(id >> 7) & 3) * 2 + (int)(id & 1), f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
   int kt, s;
@@ -1055,7 +1072,7 @@ __global__ void k_m2pf_table(const double* __restrict__ Dtab2, const int2* __res
                              int nmax, int ND, long long cnt, int adj) {
   const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (id >= cnt) return;
-  const int lane = (int)(id & 63), e = (int)(id >> 6) & 7, f = (int)(id >> 9);
+  const int lane = (int)(id >> 1) & 63, e = ((int)(id >> 7) & 3) * 2 + (int)(id & 1), f = (int)(id >> 9);
   int t = 0;
   while (tiles[t].y + tiles[t].x <= f) ++t;
   const int col = 16 * t + (lane & 15);

@@ -17,11 +17,12 @@
 // plan, M2L^T runs in the compute type of the forward M2L of its level.
 #pragma once
 
-// column tiles of the stencil transpose: [4 outputs][54 steps][8 patterns][64],
-// 8 live columns (the sources of the positive octant); then P2M^T,
-// [8][blk_psteps][64]
-constexpr __host__ __device__ int blka_off_p() { return 4 * BLK_STEPS * 8 * 64; }
-constexpr __host__ __device__ int blka_off_l(int P) { return blka_off_p() + 8 * blk_psteps(P) * 64; }
+// The stencil transpose has 8 columns, the sources of the positive octant:
+// products of 16 x 4 x 4, fragments of 4 columns and 4 k-groups.
+// [4 outputs][54 steps][8 patterns][4 kq][4][2]; then P2M^T,
+// [8][blk_psteps][4 kq][4][2]
+constexpr __host__ __device__ int blka_off_p() { return 4 * BLK_STEPS * 8 * 32; }
+constexpr __host__ __device__ int blka_off_l(int P) { return blka_off_p() + 8 * blk_psteps(P) * 32; }
 // L2P^T: own locals [8 steps][tiles][64], level F-1 [8 patterns][8 steps][64]
 constexpr __host__ __device__ int blka_ltiles(int P) { return (hterms(P) + 15) / 16; }
 constexpr __host__ __device__ int blka_off_lp(int P) { return blka_off_l(P) + 8 * blka_ltiles(P) * 64; }
@@ -30,31 +31,31 @@ constexpr __host__ __device__ int blka_table(int P) { return blka_off_lp(P) + 64
 __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int P, int nmax, int dl) {
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= blka_table(P)) return;
-  const int lane = id & 63, j = lane & 15, kq = lane >> 4;
+  const bool quads = id < blka_off_l(P);
+  const int lane = id & 63, j = quads ? ((id >> 1) & 3) + 4 * (id & 1) : lane & 15, kq = quads ? (id >> 3) & 3 : lane >> 4;
   double x = 0.0;
   if (id < blka_off_p()) {
     // source sp of the positive octant, targets at y = the 8 images of u
-    const int e = (id >> 6) & 7, st = (id >> 9) % BLK_STEPS, o = (id >> 9) / BLK_STEPS, pair = 4 * (st / 6) + kq;
+    const int e = (id >> 5) & 7, st = (id >> 8) % BLK_STEPS, o = (id >> 8) / BLK_STEPS, pair = 4 * (st / 6) + kq;
     const int jj[3] = {pair / 6, pair % 6, st % 6};
-    if (j < 8)
-      for (int minus = 0; minus < 8; ++minus) {
-        int t = 0, v = 0, neg = 0;  // the target's place in its own block, the source seen from there, tau
-        for (int a = 0; a < 3; ++a) {
-          const int u2 = (minus >> (2 - a)) & 1 ? -(2 * jj[a] + 1) : 2 * jj[a] + 1;  // 2 y
-          const int B = (u2 + 4 + 16) / 8 - 2, r2 = u2 - 8 * B;                      // block offset, 2 (y - 4 B)
-          const int sp2 = 2 * ((j >> (2 - a)) & 1) + 1;
-          const int v2 = r2 < 0 ? 8 * B - sp2 : sp2 - 8 * B;
-          neg = neg << 1 | (r2 < 0);
-          t = t << 1 | (r2 > 2 || r2 < -2);
-          v = v * 12 + (v2 + 11) / 2;
-        }
-        const int eo = o ? 8 >> o : 0;  // the axis of output o
-        x += chi(e, minus) * chi(eo, minus) * chi(eo, neg) * G[((size_t)t * 1728 + v) * 4 + o];
+    for (int minus = 0; minus < 8; ++minus) {
+      int t = 0, v = 0, neg = 0;  // the target's place in its own block, the source seen from there, tau
+      for (int a = 0; a < 3; ++a) {
+        const int u2 = (minus >> (2 - a)) & 1 ? -(2 * jj[a] + 1) : 2 * jj[a] + 1;  // 2 y
+        const int B = (u2 + 4 + 16) / 8 - 2, r2 = u2 - 8 * B;                      // block offset, 2 (y - 4 B)
+        const int sp2 = 2 * ((j >> (2 - a)) & 1) + 1;
+        const int v2 = r2 < 0 ? 8 * B - sp2 : sp2 - 8 * B;
+        neg = neg << 1 | (r2 < 0);
+        t = t << 1 | (r2 > 2 || r2 < -2);
+        v = v * 12 + (v2 + 11) / 2;
       }
+      const int eo = o ? 8 >> o : 0;  // the axis of output o
+      x += chi(e, minus) * chi(eo, minus) * chi(eo, neg) * G[((size_t)t * 1728 + v) * 4 + o];
+    }
   } else if (id < blka_off_l(P)) {
-    const int s = (id - blka_off_p()) >> 6, np = blk_psteps(P), e = s / np;
+    const int s = (id - blka_off_p()) >> 5, np = blk_psteps(P), e = s / np;
     const int b = blk_pterm(P, e, 4 * (s % np) + kq);
-    if (j < 8 && b >= 0 && h_degree(b) <= nmax) {
+    if (b >= 0 && h_degree(b) <= nmax) {
       // P2M weights w^a / a!, w = -(1/8 or 3/8)
       const double w[3] = {(j & 4) ? -0.375 : -0.125, (j & 2) ? -0.375 : -0.125, (j & 1) ? -0.375 : -0.125};
       x = 8.0 * h_reduce(b, [&](int bt) {
@@ -184,13 +185,16 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
 // P2M^T of level F - 1: rho_bar of a 4^3 block from the cotangents of the 12^3
 // cells around, one output (phi, gx, gy, gz) in the LDS tile at a time, and
 // the adjoint harmonic multipoles of its own level F-1 cell (planes; or null).
-// Tiles and folding as in k_block; 8 of the 16 columns of a product are live.
+// Tiles and folding as in k_block.  Products of 16 x 4 x 4 (17 cycles; lane =
+// column + 4 (row / 4) + 16 (row % 4) of the result), as one of 16 x 16 x 4 (64
+// cycles) would have 8 dead columns.
 template <int P, typename TI, typename TO, int NX, int DL>
 __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restrict__ dphi, const TI* __restrict__ dg,
                                                               const double* __restrict__ W,
                                                               const double* __restrict__ Mb, TO* __restrict__ drho,
                                                               int n, int tpa) {
-  constexpr int NE = 4, KS = 2 / NX, NPS = blk_psteps(P), CS = 9;
+  typedef double d2v __attribute__((ext_vector_type(2)));
+  constexpr int NE = 4, KS = 2, NR = NX, NPS = blk_psteps(P), CS = 9;
   constexpr int EP = KS * 8 * NX * 16 * CS, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) double lds[SZ];
   const int nb = n >> 2, lb = blockIdx.x;
@@ -198,13 +202,12 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
   const long long N = (long long)n * n * n;
   const double dx = 1.0 / n;
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), X = w % NX, ks = (w / NX) % KS, e0 = (w >> 1) * NE;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ks = w & 1, e0 = (w >> 1) * NE;
   const double sx0 = e0 ? -1.0 : 1.0;
   constexpr int OFF_P = blka_off_p();
-  d4 acc[NE];
-#pragma unroll
-  for (int e = 0; e < NE; ++e) acc[e] = d4{0, 0, 0, 0};
-  const double* ctr = lds + (4 * X + 6) * BLK_PLANE + blk_row(4 * (i >> 2) + 6) + 4 * (i & 3);
+  double acc[NR][NE][2] = {};
+  const unsigned quad = (lane >> 4) * 4 + (lane & 3);
+  const double* ctr = lds + 6 * BLK_PLANE + blk_row(4 * (i >> 2) + 6) + 4 * (i & 3);
 #pragma unroll 1
   for (int o = 0; o < (dg ? 4 : 1); ++o) {
     __syncthreads();
@@ -215,61 +218,88 @@ __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restri
     __syncthreads();
     // the sign of a minus image along the output's own axis
     const double sx = o == 1 ? -sx0 : sx0, sy = o == 2 ? -1.0 : 1.0, sz = o == 3 ? -1.0 : 1.0;
-    const auto wb = gmem(W + o * (BLK_STEPS * 512) + e0 * 64);
-    auto bread = [&](int s, double (&b)[NE]) {
+    const auto wb = gmem(W + o * (BLK_STEPS * 256) + e0 * 32);
+    auto bread = [&](int s, d2v (&b)[NE]) {
 #pragma unroll
-      for (int e = 0; e < NE; ++e) b[e] = (wb + s * 512 + e * 64)[(unsigned)lane];
+      for (int e = 0; e < NE; ++e) b[e] = *(const __attribute__((address_space(1))) d2v*)(wb + s * 256 + e * 32 + 2 * quad);
     };
     // as in k_block
-    double r[2][8], b[2][NE], a[NE];
+    double r[NR][8], a[NR][NE];
+    d2v b[2][NE];
     const double* p[4];
+    auto aread = [&](auto jc) {
+#pragma unroll
+      for (int m = 0; m < NR; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          r[m][2 * q] = p[q][m * 4 * BLK_PLANE + 6 + decltype(jc)::value];
+          r[m][2 * q + 1] = p[q][m * 4 * BLK_PLANE + 5 - decltype(jc)::value];
+        }
+    };
     blk_images(ctr, c_blk_place[4 * ks + kq], p);
     bread(6 * ks, b[0]);
-    blk_read<0>(p, r[0]);
+    aread(std::integral_constant<int, 0>{});
 #pragma unroll 1
-    for (int grp = ks; grp < BLK_GROUPS; grp += KS)
+    for (int grp = ks; grp < BLK_GROUPS; grp += KS) {
+      const int gn = grp + KS < BLK_GROUPS ? grp + KS : ks;  // (past the last: read, not used)
+      const int pn = c_blk_place[4 * gn + kq];
       static_for<6>([&](auto jc) {
         constexpr int jz = decltype(jc)::value, u = jz & 1;
+#pragma unroll
+        for (int m = 0; m < NR; ++m) fold8<NE>(r[m], sx, sy, sz, a[m]);
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (jz < 5) {
           bread(6 * grp + jz + 1, b[u ^ 1]);
-          blk_read<jz + 1>(p, r[u ^ 1]);
         } else {
-          const int nx = grp + KS < BLK_GROUPS ? grp + KS : ks;  // (past the last: read, not used)
-          bread(6 * nx, b[u ^ 1]);
-          blk_images(ctr, c_blk_place[4 * nx + kq], p);
-          blk_read<0>(p, r[u ^ 1]);
+          bread(6 * gn, b[u ^ 1]);
+          blk_images(ctr, pn, p);
         }
+        aread(std::integral_constant<int, (jz + 1) % 6>{});
         __builtin_amdgcn_sched_barrier(0);
-        fold8<NE>(r[u], sx, sy, sz, a);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[u][e], acc[e], 0, 0, 0);
+        for (int m = 0; m < NR; ++m)
+#pragma unroll
+          for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+              acc[m][e][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[m][e], b[u][e][g], acc[m][e][g], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       });
+    }
   }
-  if (Mb && ks == 0) {
-    const int cx = min(bx0 + X, nb - 1), cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1), nbp = nb + 6;
-    const long long ncp = (long long)nbp * nbp * nbp, cell = ((long long)(cx + 3) * nbp + cy + 3) * nbp + cz + 3;
-    const double* wp = W + OFF_P + e0 * (NPS * 64) + lane;
+  // (the shorter K slice takes the multipoles)
+  if (Mb && ks == 1) {
+    const int cy = min(by0 + (i >> 2), nb - 1), cz = min(bz0 + (i & 3), nb - 1), nbp = nb + 6;
+    const long long ncp = (long long)nbp * nbp * nbp;
+    const double* wp = W + OFF_P + e0 * (NPS * 32) + 2 * quad;
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const long long cell = ((long long)(min(bx0 + m, nb - 1) + 3) * nbp + cy + 3) * nbp + cz + 3;
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+#pragma unroll
+        for (int s = 0; s < NPS; ++s) {
+          const int bt = c_ft<P>.pt[e0 + e][4 * s + kq];
+          // (the stencil's accumulators carry the Walsh sum's 1/8)
+          const double v = Mb[(bt >= 0 ? bt : 0) * ncp + cell];
+          const d2v b = *reinterpret_cast<const d2v*>(wp + (e * NPS + s) * 32);
+#pragma unroll
+          for (int g = 0; g < 2; ++g)
+            acc[m][e][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(bt >= 0 ? 0.125 * v : 0.0, b[g], acc[m][e][g], 0, 0, 0);
+        }
+    }
+  }
+  __syncthreads();
+  constexpr int ROWS = NX * 16, ES = ROWS * CS;
+#pragma unroll
+  for (int m = 0; m < NR; ++m)
 #pragma unroll
     for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int s = 0; s < NPS; ++s) {
-        const int bt = c_ft<P>.pt[e0 + e][4 * s + kq];
-        // (the stencil's accumulators carry the Walsh sum's 1/8)
-        const double v = Mb[(bt >= 0 ? bt : 0) * ncp + cell];
-        acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(bt >= 0 ? 0.125 * v : 0.0, wp[(e * NPS + s) * 64], acc[e], 0, 0, 0);
-      }
-  }
+      for (int g = 0; g < 2; ++g)
+        lds[(ks * 8 + e0 + e) * ES + (16 * m + kq + 4 * ((lane >> 2) & 3)) * CS + 4 * g + (lane & 3)] = acc[m][e][g];
   __syncthreads();
-  constexpr int NR = NX * 16, ES = NR * CS;
-  if (i < 8) {
-#pragma unroll
-    for (int e = 0; e < NE; ++e)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) lds[(ks * 8 + e0 + e) * ES + (16 * X + 4 * v + kq) * CS + i] = acc[e][v];
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < NR * 8; q += BLK_THREADS) {
+  for (int q = threadIdx.x; q < ROWS * 8; q += BLK_THREADS) {
     double* x = lds + (q >> 3) * CS + (q & 7);
     double y[8];
 #pragma unroll
