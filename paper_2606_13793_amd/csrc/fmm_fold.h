@@ -754,30 +754,56 @@ __device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox0, int oy0
 // column tiles per pass of the epilogue
 template <int NT>
 constexpr int m2lf_nte = NT % 2 ? NT : NT / 2;
-template <int P, typename CT, int OP, int MT, int NT, int NE, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ segs, int nseg, int T,
-                                                     const int2* __restrict__ tiles,
-                                                     const typename Mf<CT>::H* __restrict__ W, const M2lGrid grid,
-                                                     double* __restrict__ part) {
+// Tile shapes of the folded M2L by variant (rows of octs, column tiles per
+// group, patterns per wave, K slices): forward, and transposes, whose few
+// column tiles are dominated by the first.
+// X: FP32 products, which take half the time, so that folding an operand has to
+// serve more of them.
+template <int OP, int V, int X>
+struct M2lShape {  // V = -1: none
+  static constexpr int MT = 1, NT = 1, NE = 2, NW = 0;
+};
+template <int X> struct M2lShape<0, 0, X> { static constexpr int MT = 1, NT = 2, NE = 2, NW = 4; };
+template <> struct M2lShape<0, 1, 0> { static constexpr int MT = 2, NT = 2, NE = 4, NW = 4; };
+template <> struct M2lShape<0, 1, 1> { static constexpr int MT = 2, NT = 4, NE = 2, NW = 4; };
+template <int X> struct M2lShape<1, 0, X> { static constexpr int MT = 1, NT = 1, NE = 2, NW = 4; };
+template <int X> struct M2lShape<1, 1, X> { static constexpr int MT = 4, NT = 1, NE = 8, NW = 4; };
+template <int V, int X> struct M2lShape<2, V, X> : M2lShape<0, V, X> {};
+template <int V, int X> struct M2lShape<3, V, X> : M2lShape<1, V, X> {};
+
+template <typename CT, int OP, typename S>
+struct M2lLds {
+  using H = typename Mf<CT>::H;
+  static constexpr int NR = S::NW ? 8 * S::MT / (S::NE * S::NW) : 1, NX = S::MT / NR, CS = 16 * m2lf_nte<S::NT> + 1;
+  static constexpr int CELLS = (2 * S::MT + 4) * FOLD_PLANE, NPL = OP == FO_M2L || OP == FO_M2P ? 5 : 4;
+  static constexpr int EP = NX * 8 * 16 * CS, SZ = EP > NPL * CELLS ? EP : NPL * CELLS;
+  static constexpr int BYTES = S::NW ? (int)(SZ * sizeof(H)) + 64 * S::NT : 0;
+};
+template <int P, typename CT, int OP, typename S>
+__device__ __forceinline__ void m2lf_run(const M2lArgs& args, int block, char* smem) {
   using M = Mf<CT>;
   using H = typename M::H;
   using Acc = typename M::Acc;
-  constexpr int NR = 8 * MT / (NE * NW), NG = 8 / NE, NX = MT / NR, THR = 64 * NW;
+  using L = M2lLds<CT, OP, S>;
+  constexpr int MT = S::MT, NT = S::NT, NE = S::NE, NW = S::NW;
+  constexpr int NR = L::NR, NG = 8 / NE, NX = L::NX, THR = 64 * NW;
   static_assert(NG * NX == NW && NX * NR == MT && NE % 2 == 0, "the waves' shares");
   constexpr bool HEAD = OP == FO_M2L || OP == FO_M2P;
   constexpr int NTERM = OP == 3 ? 256 : OP == 1 ? 8 * hterms(P) : hterms(P);
   constexpr int ROW = FOLD_ROW, PLANE = FOLD_PLANE;
-  constexpr int NTE = m2lf_nte<NT>, CELLS = (2 * MT + 4) * PLANE, CS = 16 * NTE + 1, NPL = HEAD ? 5 : 4;
-  constexpr int EP = NX * 8 * 16 * CS, SZ = EP > NPL * CELLS ? EP : NPL * CELLS;
+  constexpr int NTE = m2lf_nte<NT>, CELLS = L::CELLS, CS = L::CS;
   typedef H hp __attribute__((ext_vector_type(2)));  // two patterns of a fragment
   typedef H h2 __attribute__((ext_vector_type(2), aligned(sizeof(H))));
   constexpr int RPP = (2 * MT + 4) * 12, RPT = THR / 6, FB = (4 * RPP + RPT - 1) / RPT;
-  __shared__ __attribute__((aligned(16))) H lds[SZ];
-  __shared__ int scol[16 * NT];
+  H* const lds = reinterpret_cast<H*>(smem);
+  int* const scol = reinterpret_cast<int*>(smem + L::SZ * sizeof(H));
+  const M2lGrid& grid = args.grid;
+  const int2* __restrict__ tiles = args.tiles;
+  const H* __restrict__ W = static_cast<const H*>(args.W);
   int grp = 0;
-  while (grp + 1 < grid.ng && (int)blockIdx.x >= grid.first[grp + 1]) ++grp;
-  const int T0 = grp * NT, np = grid.parts[grp], rb = (int)blockIdx.x - grid.first[grp], lbk = rb / np, ip = rb % np;
-  const Seg& sg = find_seg(segs, nseg, lbk);
+  while (grp + 1 < grid.ng && block >= grid.first[grp + 1]) ++grp;
+  const int T0 = grp * NT, np = grid.parts[grp], rb = block - grid.first[grp], lbk = rb / np, ip = rb % np;
+  const Seg& sg = find_seg(args.segs, args.nseg, lbk);
   const int nsp = sg.n + 6, tb = lbk - sg.first_block;
   const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
   const long long ncellp = (long long)nsp * nsp * nsp;
@@ -971,7 +997,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ seg
   // of each row group and NTE column tiles at a time), then from all parts of
   // the K loop
   constexpr int NQ = NX * 16 * 16 * NTE;
-  double* const slot = part + (size_t)blockIdx.x * (MT * 16 * 16 * NT * 8);
+  double* const slot = args.part + (size_t)block * (MT * 16 * 16 * NT * 8);
   static_for<NR * (NT / NTE)>([&](auto rpc) {
     constexpr int rp = decltype(rpc)::value, r = rp / (NT / NTE), t0 = rp % (NT / NTE) * NTE;
     if (scol[16 * t0] < 0) return;  // (uniform: no columns there)
@@ -1000,20 +1026,41 @@ __global__ __launch_bounds__(64 * NW, 2) void k_m2lf(const Seg* __restrict__ seg
   });
 }
 
-// Adds the parts of the shared groups of a k_m2lf launch, in order.  Blocks:
-// (group, tile), the groups with several parts only (sum_first: first block).
-template <int P, typename H, int OP, int MT, int NT, int NR>
-__global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, int nseg, int T, const M2lGrid grid,
-                                                  const double* __restrict__ part) {
+// a: the FP64 share of a launch (its blocks first), b: the FP32 share
+template <int P, int OP, typename SA, typename SB>
+__global__ __launch_bounds__(256, 2) void k_m2lf(const M2lArgs a, const M2lArgs b) {
+  constexpr int LA = M2lLds<double, OP, SA>::BYTES, LB = M2lLds<float, OP, SB>::BYTES;
+  static_assert(SA::NW % 4 == 0 && SB::NW % 4 == 0 && SA::NW <= 4 && SB::NW <= 4, "4 waves");
+  __shared__ __attribute__((aligned(16))) char smem[LA > LB ? LA : LB];
+  if constexpr (!SB::NW) {
+    m2lf_run<P, double, OP, SA>(a, blockIdx.x, smem);
+  } else if constexpr (!SA::NW) {
+    m2lf_run<P, float, OP, SB>(b, blockIdx.x, smem);
+  } else {
+    const int first = (int)a.grid.blocks;
+    if ((int)blockIdx.x < first)
+      m2lf_run<P, double, OP, SA>(a, blockIdx.x, smem);
+    else
+      m2lf_run<P, float, OP, SB>(b, (int)blockIdx.x - first, smem);
+  }
+}
+
+// Adds the parts of the shared groups of a k_m2lf launch, in order: MT x NT
+// blocks for each tile of each such group (the FP64 share's na first).
+template <int P, typename H, int OP, typename S>
+__device__ __forceinline__ void m2lf_add(const M2lArgs& args, int block) {
+  constexpr int MT = S::MT, NT = S::NT, NR = 8 * MT / (S::NE * S::NW), SUB = MT * NT;
   constexpr int NTE = m2lf_nte<NT>, NP = NT / NTE, NQ = MT / NR * 256 * NTE;
-  int g = 0, left = (int)blockIdx.x / T;  // (a tile per T blocks of each shared group)
+  const M2lGrid& grid = args.grid;
+  const int sub = block % SUB, tile = block / SUB, T = args.T;
+  int g = 0, left = tile / T;  // (a tile per T blocks of each shared group)
   while (grid.parts[g] == 1 || left-- > 0) ++g;
-  const int lbk = (int)blockIdx.x % T, np = grid.parts[g];
-  const Seg& sg = find_seg(segs, nseg, lbk);
+  const int lbk = tile % T, np = grid.parts[g];
+  const Seg& sg = find_seg(args.segs, args.nseg, lbk);
   const int tb = lbk - sg.first_block;
   const int ox0 = (tb / (sg.tpa * sg.tpa)) * MT, oy0 = ((tb / sg.tpa) % sg.tpa) * 4, oz0 = (tb % sg.tpa) * 4;
-  const double* slot = part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NP * NQ * 8);
-  for (int x = blockIdx.y * 256 + threadIdx.x; x < NR * NP * NQ; x += gridDim.y * 256) {
+  const double* slot = args.part + ((size_t)grid.first[g] + (size_t)lbk * np) * (NR * NP * NQ * 8);
+  for (int x = sub * 256 + threadIdx.x; x < NR * NP * NQ; x += SUB * 256) {
     const int rp = x / NQ, q = x % NQ, col = 16 * (NT * g + rp % NP * NTE) + m2lf_qcol<OP, NTE>(q);
     const int cb = fold_colmap<P, OP>(col);
     if (cb < 0) continue;
@@ -1027,6 +1074,13 @@ __global__ __launch_bounds__(256) void k_m2lf_sum(const Seg* __restrict__ segs, 
       for (int e = 0; e < 8; ++e) y[e] += slot[(size_t)k * (NR * NP * NQ * 8) + (size_t)(rp * 8 + e) * NQ + q];
     m2lf_put<P, H, OP>(sg, cb, ox0, oy0, oz0, (q / (256 * NTE)) * NR + rp / NP, m2lf_qrow<OP, NTE>(q), y);
   }
+}
+template <int P, int OP, typename SA, typename SB>
+__global__ __launch_bounds__(256) void k_m2lf_sum(const M2lArgs a, const M2lArgs b, int na) {
+  if constexpr (SA::NW > 0)
+    if ((int)blockIdx.x < na) m2lf_add<P, double, OP, SA>(a, blockIdx.x);
+  if constexpr (SB::NW > 0)
+    if ((int)blockIdx.x >= na) m2lf_add<P, float, OP, SB>(b, (int)blockIdx.x - na);
 }
 
 // The other operators' B fragments, as k_m2lf_table.

@@ -1580,21 +1580,6 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tile shapes of the folded M2L by variant (rows of octs, column tiles per
-// group, patterns per wave, K slices): forward, and transposes, whose few
-// column tiles are dominated by the first.
-// X: FP32 products, which take half the time, so that folding an operand has to
-// serve more of them.
-template <int OP, int V, int X>
-struct M2lShape;
-template <int X> struct M2lShape<0, 0, X> { static constexpr int MT = 1, NT = 2, NE = 2, NW = 4; };
-template <> struct M2lShape<0, 1, 0> { static constexpr int MT = 2, NT = 2, NE = 4, NW = 4; };
-template <> struct M2lShape<0, 1, 1> { static constexpr int MT = 2, NT = 4, NE = 2, NW = 4; };
-template <int X> struct M2lShape<1, 0, X> { static constexpr int MT = 1, NT = 1, NE = 2, NW = 4; };
-template <int X> struct M2lShape<1, 1, X> { static constexpr int MT = 4, NT = 1, NE = 8, NW = 4; };
-template <int V, int X> struct M2lShape<2, V, X> : M2lShape<0, V, X> {};
-template <int V, int X> struct M2lShape<3, V, X> : M2lShape<1, V, X> {};
-
 // Grid of a launch over T tiles.  A block's K loop is cut where it would take
 // more than half (small tiles: a quarter) of what each compute unit has to do in the whole launch
 // (the last blocks to start would otherwise set its length), down to one
@@ -1635,57 +1620,88 @@ void m2lf_need(const fmm_plan* pl, int x, int T, size_t* part) {
   if (x == 0) m2lf_need_x<P, OP, V, 0>(pl, T, part);
   else m2lf_need_x<P, OP, V, 1>(pl, T, part);
 }
-template <int P, typename CT, int OP, int V>
-hipError_t launch_m2lf_v(fmm_plan* pl, int x, const SegTable& st, hipStream_t s) {
-  using S = M2lShape<OP, V, Mf<CT>::IDX>;
-  using H = typename Mf<CT>::H;
-  const M2lGrid g = m2lf_grid<P, OP, V, Mf<CT>::IDX>(pl, st.blocks);
-  StageScope sc(pl, OP == FO_M2P ? ST_BOTTOM : ST_M2L, g.shared ? 2 : 1, s);
-  hipLaunchKernelGGL((k_m2lf<P, CT, OP, S::MT, S::NT, S::NE, S::NW>), dim3((unsigned)g.blocks), dim3(64 * S::NW), 0, s, st.dev,
-                     st.nseg, st.blocks, pl->fold_tiles[OP], (const H*)pl->fold_w[OP][x], g, pl->m2lf_part);
-  if (g.shared)
-    hipLaunchKernelGGL((k_m2lf_sum<P, H, OP, S::MT, S::NT, 8 * S::MT / (S::NE * S::NW)>),
-                       dim3((unsigned)(g.shared * st.blocks), S::MT * S::NT), dim3(256), 0, s, st.dev, st.nseg, st.blocks,
-                       g, pl->m2lf_part);
+template <int P, int OP, int V, int X>
+M2lArgs m2lf_args(const fmm_plan* pl, const SegTable& st, double* part) {
+  M2lArgs a;
+  a.segs = st.dev;
+  a.nseg = st.nseg;
+  a.T = st.blocks;
+  a.tiles = pl->fold_tiles[OP];
+  a.W = pl->fold_w[OP][X];
+  a.part = part;
+  a.grid = m2lf_grid<P, OP, V, X>(pl, st.blocks);
+  return a;
+}
+// VA, VB: variants of the FP64 and FP32 shares, -1 for none.
+template <int P, int OP, int VA, int VB>
+hipError_t launch_m2lf_v(fmm_plan* pl, const SegTable& sa, const SegTable& sb, hipStream_t s) {
+  using SA = M2lShape<OP, VA, 0>;
+  using SB = M2lShape<OP, VB, 1>;
+  M2lArgs a, b;
+  size_t used = 0;
+  if constexpr (VA >= 0) {
+    a = m2lf_args<P, OP, VA, 0>(pl, sa, pl->m2lf_part);
+    m2lf_need_x<P, OP, VA, 0>(pl, sa.blocks, &used);
+  }
+  if constexpr (VB >= 0) b = m2lf_args<P, OP, VB, 1>(pl, sb, pl->m2lf_part + used);
+  StageScope sc(pl, OP == FO_M2P ? ST_BOTTOM : ST_M2L, a.grid.shared + b.grid.shared ? 2 : 1, s);
+  hipLaunchKernelGGL((k_m2lf<P, OP, SA, SB>), dim3((unsigned)(a.grid.blocks + b.grid.blocks)), dim3(256), 0, s, a, b);
+  const int na = a.grid.shared * a.T * SA::MT * SA::NT, nb = b.grid.shared * b.T * SB::MT * SB::NT;
+  if (na + nb) hipLaunchKernelGGL((k_m2lf_sum<P, OP, SA, SB>), dim3(na + nb), dim3(256), 0, s, a, b, na);
   return hipGetLastError();
 }
 
-// A folded operator over the tiles of variant v.
-template <int P, typename CT, int OP>
-hipError_t launch_fold(fmm_plan* pl, int x, int v, const SegTable& st, hipStream_t s) {
-  if (!st.nseg) return hipSuccess;
-  if (v == 1) return launch_m2lf_v<P, CT, OP, 1>(pl, x, st, s);
-  return launch_m2lf_v<P, CT, OP, 0>(pl, x, st, s);
+// A folded operator: the FP64 segments sa over the tiles of variant va, the FP32
+// ones sb over those of vb.  Both types in one launch where the FP64 levels are
+// few and coarse (variant 0): their blocks then run beside the others instead
+// of before them (64^3, p = 5: 14 + 7 us of 99).
+template <int P, int OP>
+hipError_t launch_fold(fmm_plan* pl, int va, const SegTable& sa, int vb, const SegTable& sb, hipStream_t s) {
+  constexpr bool BOTH = OP == FO_M2L || OP == FO_M2LT;
+  hipError_t e = hipSuccess;
+  if constexpr (BOTH) {
+    if (sa.nseg && sb.nseg && va == 0)
+      return vb == 1 ? launch_m2lf_v<P, OP, 0, 1>(pl, sa, sb, s) : launch_m2lf_v<P, OP, 0, 0>(pl, sa, sb, s);
+  }
+  if (sa.nseg)
+    e = va == 1 ? launch_m2lf_v<P, OP, 1, -1>(pl, sa, sb, s) : launch_m2lf_v<P, OP, 0, -1>(pl, sa, sb, s);
+  if (sb.nseg && e == hipSuccess)
+    e = vb == 1 ? launch_m2lf_v<P, OP, -1, 1>(pl, sa, sb, s) : launch_m2lf_v<P, OP, -1, 0>(pl, sa, sb, s);
+  return e;
 }
-// Forward operators of site x (0 FP64, 1 FP32).
-template <int P, typename CT, int OP>
-hipError_t launch_fold_site(fmm_plan* pl, int x, hipStream_t s) {
-  const auto& st = OP == FO_M2P ? pl->s_m2pf[x] : pl->s_m2lf[x];
-  int v = fold_variant(pl, OP, st[1].blocks);
-  if (pl->tune.grp == 1) v = 0;
-  return launch_fold<P, CT, OP>(pl, x, v, st[v], s);
+// Forward operators.
+template <int P, int OP>
+hipError_t launch_fold_site(fmm_plan* pl, hipStream_t s) {
+  const auto& st = OP == FO_M2P ? pl->s_m2pf : pl->s_m2lf;
+  int v[2];
+  for (int x = 0; x < 2; ++x) v[x] = pl->tune.grp == 1 ? 0 : fold_variant(pl, OP, st[x][1].blocks);
+  return launch_fold<P, OP>(pl, v[0], st[0][v[0]], v[1], st[1][v[1]], s);
 }
 
 // The workspace those launches share.  The transpose's launches have the
 // forward ones' tiles (one field).
 template <int P>
 hipError_t alloc_m2lf_part(fmm_plan* pl) {
-  size_t part = 0;
-  auto need = [&](auto opc, auto adjc, int x, const SegTable (&st)[3]) {
-    constexpr int OP = decltype(opc)::value, ADJ = decltype(adjc)::value;
-    if (!st[0].nseg) return;
-    // (a batch's autotuner may take the smaller tiles)
-    const int v = fold_variant(pl, OP, st[1].blocks), va = fold_variant(pl, ADJ, st[2].blocks);
-    if (v) m2lf_need<P, OP, 1>(pl, x, st[1].blocks, &part);
-    if (!v || pl->batch) m2lf_need<P, OP, 0>(pl, x, st[0].blocks, &part);
-    if (pl->batch) return;
-    if (va) m2lf_need<P, ADJ, 1>(pl, x, st[2].blocks, &part);
-    else m2lf_need<P, ADJ, 0>(pl, x, st[0].blocks, &part);
+  // one operator's launch: the two types side by side, each at its largest
+  auto both = [&](auto opc, const SegTable (&st)[2][3]) {
+    constexpr int OP = decltype(opc)::value;
+    size_t sum = 0;
+    for (int x = 0; x < 2; ++x) {
+      if (!st[x][0].nseg) continue;
+      const int large = OP & 1 ? 2 : 1, v = fold_variant(pl, OP, st[x][large].blocks);
+      size_t most = 0;
+      // (a batch's autotuner may take the smaller tiles)
+      if (v) m2lf_need<P, OP, 1>(pl, x, st[x][large].blocks, &most);
+      if (!v || pl->batch) m2lf_need<P, OP, 0>(pl, x, st[x][0].blocks, &most);
+      sum += most;
+    }
+    return sum;
   };
-  for (int x = 0; x < 2; ++x) {
-    need(std::integral_constant<int, FO_M2L>{}, std::integral_constant<int, FO_M2LT>{}, x, pl->s_m2lf[x]);
-    need(std::integral_constant<int, FO_M2P>{}, std::integral_constant<int, FO_M2PT>{}, x, pl->s_m2pf[x]);
-  }
+  size_t part = std::max(both(std::integral_constant<int, FO_M2L>{}, pl->s_m2lf),
+                         both(std::integral_constant<int, FO_M2P>{}, pl->s_m2pf));
+  if (!pl->batch)
+    part = std::max({part, both(std::integral_constant<int, FO_M2LT>{}, pl->s_m2lf),
+                     both(std::integral_constant<int, FO_M2PT>{}, pl->s_m2pf)});
   if (!part) return hipSuccess;
   hipError_t e;
   if ((e = hipMalloc(&pl->m2lf_part, part * sizeof(double))) != hipSuccess) return e;
@@ -1773,12 +1789,8 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
                            pl->m2m_start, pl->m2m_off, pl->m2m_coef, pl->NMX);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_fold_site<P, double, FO_M2L>(pl, 0, s)) != hipSuccess) return e;
-  if ((e = launch_fold_site<P, double, FO_M2P>(pl, 0, s)) != hipSuccess) return e;
-  if constexpr (std::is_same<CT, float>::value) {
-    if ((e = launch_fold_site<P, float, FO_M2L>(pl, 1, s)) != hipSuccess) return e;
-    if ((e = launch_fold_site<P, float, FO_M2P>(pl, 1, s)) != hipSuccess) return e;
-  }
+  if ((e = launch_fold_site<P, FO_M2L>(pl, s)) != hipSuccess) return e;
+  if ((e = launch_fold_site<P, FO_M2P>(pl, s)) != hipSuccess) return e;
   if ((e = launch_conv<P, double, CV_M2L>(pl, pl->s_conv[0], pl->wm2l[0], s)) != hipSuccess) return e;
   if ((e = launch_split_reduce(pl, pl->s_red[0], s)) != hipSuccess) return e;
   if constexpr (Mf<CT>::IDX == 2) {
@@ -1909,16 +1921,12 @@ hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI*
       hipLaunchKernelGGL((k_gather<P, true, double>), g, dim3(256), 0, s, nullptr, 0, l, pl->wshift, hterms(P));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_fold<P, double, FO_M2LT>(pl, 0, w.m2ltf_v[0], w.m2ltf[0], s)) != hipSuccess) return e;
-  if constexpr (std::is_same<CT, float>::value)
-    if ((e = launch_fold<P, float, FO_M2LT>(pl, 1, w.m2ltf_v[1], w.m2ltf[1], s)) != hipSuccess) return e;
+  if ((e = launch_fold<P, FO_M2LT>(pl, w.m2ltf_v[0], w.m2ltf[0], w.m2ltf_v[1], w.m2ltf[1], s)) != hipSuccess) return e;
   if constexpr (DL == 2) {
-    bool low = false;
-    if constexpr (std::is_same<CT, float>::value) {
-      low = bottom_low(pl, F);
-      if (low && (e = launch_fold<P, float, FO_M2PT>(pl, 1, w.m2ptf_v, w.m2ptf, s)) != hipSuccess) return e;
-    }
-    if (!low && (e = launch_fold<P, double, FO_M2PT>(pl, 0, w.m2ptf_v, w.m2ptf, s)) != hipSuccess) return e;
+    const SegTable none;
+    const bool low = pl->precision == 1 && bottom_low(pl, F);
+    if ((e = launch_fold<P, FO_M2PT>(pl, w.m2ptf_v, low ? none : w.m2ptf, w.m2ptf_v, low ? w.m2ptf : none, s)) != hipSuccess)
+      return e;
   }
   for (int k = 3; k <= B; ++k) {
     const int np = 1 << (k - 1);

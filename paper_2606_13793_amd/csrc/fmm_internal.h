@@ -287,6 +287,15 @@ struct M2lGrid {
   long long blocks = 0;
   int shared = 0;  // groups with more than one part
 };
+// One compute type's share of such a launch.
+struct M2lArgs {
+  const Seg* segs = nullptr;
+  int nseg = 0, T = 0;
+  const int2* tiles = nullptr;
+  const void* W = nullptr;
+  double* part = nullptr;  // partial sums of the shared groups
+  M2lGrid grid;
+};
 
 // launch-shape choices picked by the batch autotuner
 struct Tuning {
