@@ -149,7 +149,8 @@ void release(fmm_plan* pl) {
   };
   free_st(pl->s_p2m);
   free_st(pl->s_p2m2);
-  free_st(pl->s_p2mf);
+  free_st(pl->s_p2mh);
+  free_st(pl->s_up);
   for (auto& st : pl->s_m2m) free_st(st);
   for (auto& st : pl->s_m2mf) free_st(st);
   for (auto& st : pl->s_conv) free_st(st);
@@ -388,7 +389,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, p2mf, m2m[16], m2mf[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
+  SegList p2m, p2m2, p2mh, up, m2m[16], m2mf[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -397,15 +398,30 @@ int build_schedule(fmm_plan* pl) {
       // there; FP64 planes, with a copy for a level whose M2L runs in FP32
       const int top = block_level(pl, F);
       auto copy = [&](int k) { return harmonic_float(pl, F, k) ? fd.lev[k].Mh : nullptr; };
-      if (top >= 2) {
+      // Small fields form three levels at once (k_up): its 4 x 4 x 4 cells write
+      // quarter lines, which costs large ones more than the launches it saves
+      // (64^3, p = 5: 8 + 6 + 6 us -> 11; the whole call at 256^3, p = 6: + 130 us)
+      const bool fused = (1LL << (3 * (top - 2))) <= pl->cus;
+      const int ups = top < 2 ? 0 : fused ? std::min(3, top - 1) : 1;
+      if (ups && !fused) {
         Seg s2{};
         s2.n = fd.n;
         s2.field = f;
         s2.b = (double*)fd.lev[top].M;
         s2.u = copy(top);
-        p2mf.add(s2, cdiv(1LL << (3 * top), 256));
+        p2mh.add(s2, cdiv(1LL << (3 * top), 256));
+      } else if (ups) {
+        Seg u{};
+        u.n = fd.n;
+        u.field = f;
+        u.split = ups;
+        u.a = (const double*)fd.lev[top].M;
+        u.b = (double*)copy(top);
+        if (ups > 1) u.c = (const double*)fd.lev[top - 1].M, u.t = copy(top - 1);
+        if (ups > 2) u.d = (const double*)fd.lev[top - 2].M, u.u = copy(top - 2);
+        up.add(u, 1LL << (3 * (top - 2)));
       }
-      for (int k = top; k >= 3; --k) {
+      for (int k = top - ups + 1; k >= 3; --k) {
         Seg m{};
         m.n = 1 << (k - 1);
         m.field = f;
@@ -460,6 +476,7 @@ int build_schedule(fmm_plan* pl) {
         c.a = (const double*)(low ? fd.lev[k - 1].Mh : fd.lev[k - 1].M);
         c.b = typed ? nullptr : (double*)fd.lev[k].Lw;
         c.u = typed ? fd.lev[k].Lw : nullptr;
+        c.t = k == 3 ? fd.lev[k].Lc : nullptr;  // (null where it is the finest)
         for (int v = 0; v < 3; ++v) {
           c.tz = (int)cdiv(no, 1 << v);
           m2lf[low ? 1 : 0][v].add(c, (long long)c.tpa * c.tpa * c.tz);
@@ -477,11 +494,11 @@ int build_schedule(fmm_plan* pl) {
           m2pf[bottom_low(pl, F) ? 1 : 0][v].add(c, (long long)c.tpa * c.tpa * c.tz);
         }
       }
-      for (int k = 3; k <= block_level(pl, F); ++k) {
+      for (int k = 4; k <= block_level(pl, F); ++k) {
         Seg l{};
         l.n = 1 << (k - 1);
         l.field = f;
-        l.a = k > 3 ? fd.lev[k - 1].Lc : nullptr;
+        l.a = fd.lev[k - 1].Lc;
         l.c = (const double*)fd.lev[k].Lw;
         l.b = fd.lev[k].Lc;
         l2lf[k].add(l, cdiv((long long)l.n * l.n * l.n, 16));
@@ -616,7 +633,8 @@ int build_schedule(fmm_plan* pl) {
   int rc;
   if ((rc = upload_segs(pl, pl->s_p2m, p2m))) return rc;
   if ((rc = upload_segs(pl, pl->s_p2m2, p2m2))) return rc;
-  if ((rc = upload_segs(pl, pl->s_p2mf, p2mf))) return rc;
+  if ((rc = upload_segs(pl, pl->s_p2mh, p2mh))) return rc;
+  if ((rc = upload_segs(pl, pl->s_up, up))) return rc;
   for (int k = 0; k < 16; ++k) {
     if ((rc = upload_segs(pl, pl->s_m2m[k], m2m[k]))) return rc;
     if ((rc = upload_segs(pl, pl->s_m2mf[k], m2mf[k]))) return rc;
@@ -1075,7 +1093,8 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
     };
     for (int k = 2; k <= F; ++k) {
       fmm::Level& lv = fd.lev[k];
-      if (k >= 3 && !zalloc(&lv.Lw, (size_t)(lv.ncell / 8) * fr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
+      // (level 3's M2L forms its complete locals itself)
+      if ((k > 3 || (k == 3 && fmm::block_level(pl, F) < 3)) && !zalloc(&lv.Lw, (size_t)(lv.ncell / 8) * fr * (k == F && low && pl->dl == 1 ? sizeof(float) : sizeof(double)))) return bail();
       const bool upto = k <= fmm::block_level(pl, F);
       if (k >= 3 && upto && !zalloc((void**)&lv.Lc, (size_t)lv.ncell * hr * sizeof(double))) return bail();
       if (upto && fmm::harmonic_float(pl, F, k) && !zalloc(&lv.Mh, (size_t)lv.ncellp * (p + 1) * (p + 1) * sizeof(float)))

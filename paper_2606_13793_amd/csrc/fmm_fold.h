@@ -668,7 +668,8 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
 // Segments: n = source grid cells per axis, tpa = tiles along y and z, tz =
 // tiles along x; OP 0: a = harmonic multipoles of the source grid in the compute
 // type, [term][(n + 6)^3] (terms padded to a multiple of 4), u = result in the
-// compute type or b = result in FP64, [n^3][frow]; OP 2: the same, u =
+// compute type or b = result in FP64, [n^3][frow], or t = complete locals of the
+// children, [(2 n)^3][hrow] (the coarsest level); OP 2: the same, u =
 // [n^3][4][4^3]; OP 1, 3: a = cotangent planes [K term][(n + 6)^3] in the compute
 // type, b = result, planes [term][(n + 6)^3].
 // Tile: MT x 4 x 4 octs.  NW waves: 8 / NE groups of NE patterns, MT / NR
@@ -738,6 +739,28 @@ __device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox0, int oy0
   } else {
     const int kap = cb >> 16;
     const unsigned off = (unsigned)((2 * (dx * ns + dy) * ns + 2 * dz) * FR + (cb & 0xffff));
+    if (sg.t) {
+      // coarsest level: nothing comes from above, so the locals of the children
+      // c are complete, L(2P + c, b) = chi_b(c) / 8 sum_kappa chi_kappa(c) Lw; the 8
+      // patterns of a term are 8 lanes two apart
+      const int b = 2 * ((cb & 0xffff) >> 4) + (cb & 1), nc = 2 * ns;
+      const double sc = 0.125 * chi(c_ft<P>.par[b], kap);
+      double* const out = static_cast<double*>(sg.t);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        double v = chi(kap, m) * y[m];
+#pragma unroll
+        for (int bit = 1; bit < 8; bit <<= 1) {
+          const double o = __shfl_xor(v, 2 * bit);
+          v = kap & bit ? o - v : v + o;
+        }
+        const int x0 = 2 * (2 * (ox0 + dx) + (m & 4 ? 0 : 1)) + (kap & 4 ? 0 : 1),
+                  x1 = 2 * (2 * (oy0 + dy) + (m & 2 ? 0 : 1)) + (kap & 2 ? 0 : 1),
+                  x2 = 2 * (2 * (oz0 + dz) + (m & 1 ? 0 : 1)) + (kap & 1 ? 0 : 1);
+        out[(((long long)x0 * nc + x1) * nc + x2) * hrow(P) + b] = sc * v;
+      }
+      return;
+    }
     const long long p0 = ((long long)2 * ox0 * ns + 2 * oy0) * ns + 2 * oz0;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {

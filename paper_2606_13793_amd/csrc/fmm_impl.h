@@ -301,23 +301,10 @@ __global__ __launch_bounds__(256) void k_p2m(const Seg* __restrict__ segs, int n
 // 1/8)), and each term is then 8 products with the integer weights 3^k of
 // its slots, scaled by 8^-|a| / a!.  The term loop is unrolled (P fixed), so
 // the slots are register indices known at compile time.
-// HARM: folded fields, harmonic planes only (b FP64, u a copy in FP32 or null).
-template <int P, typename TI, typename CT, bool HARM>
-__global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int nseg, IoArg io, int NM) {
-  constexpr int NT = nterms(P), NC = (NT + 3) / 4;
-  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
-  const int n = sg.n;
-  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
-  double* __restrict__ M = sg.b;
-  const int nF = n >> 2, nFp = nF + 6;
-  const long long nT = (long long)nF * nF * nF;
-  const long long T = (long long)(blockIdx.x - sg.first_block) * 256 + threadIdx.x;
-  if (T >= nT) return;
-  const int t2 = (int)(T % nF), t1 = (int)((T / nF) % nF), t0 = (int)(T / ((long long)nF * nF));
-  double v[64];
+template <typename TI>
+__device__ __forceinline__ void p2m2_slots(const TI* __restrict__ rho, int n, double (&v)[64]) {
 #pragma unroll
-  for (int sb = 0; sb < 64; ++sb)
-    v[sb] = (double)rho[((long long)(4 * t0 + (sb >> 4)) * n + (4 * t1 + ((sb >> 2) & 3))) * n + (4 * t2 + (sb & 3))];
+  for (int sb = 0; sb < 64; ++sb) v[sb] = (double)rho[((long long)(sb >> 4) * n + ((sb >> 2) & 3)) * n + (sb & 3)];
   // butterflies along z (stride 1), y (4), x (16)
 #pragma unroll
   for (int st = 1; st <= 16; st *= 4) {
@@ -331,49 +318,50 @@ __global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int 
         v[l + 3 * st] = r1 - r2;
       }
   }
+}
+template <int AL>
+__device__ __forceinline__ double p2m2_term(const double (&v)[64]) {
+  constexpr int ex = mi_exp_of(AL);
+  constexpr int ax = ex & 255, ay = (ex >> 8) & 255, az = ex >> 16;
+  constexpr int base = 16 * 2 * (ax & 1) + 4 * 2 * (ay & 1) + 2 * (az & 1);
+  double x = 0.0;
+  static_for<8>([&](auto mc) {
+    constexpr int m = decltype(mc)::value, mx = m >> 2, my = (m >> 1) & 1, mz = m & 1;
+    constexpr double wt = pow3(mx ? 0 : ax) * pow3(my ? 0 : ay) * pow3(mz ? 0 : az);
+    x = fma(wt, v[base + 16 * mx + 4 * my + mz], x);
+  });
+  constexpr double sc = 1.0 / (fact_d(ax) * fact_d(ay) * fact_d(az) * (double)(1LL << (3 * (ax + ay + az))));
+  return sc * x;
+}
+template <int P, typename TI, typename CT>
+__global__ __launch_bounds__(256) void k_p2m2(const Seg* __restrict__ segs, int nseg, IoArg io, int NM) {
+  constexpr int NT = nterms(P), NC = (NT + 3) / 4;
+  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
+  const int n = sg.n;
+  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
+  double* __restrict__ M = sg.b;
+  const int nF = n >> 2, nFp = nF + 6;
+  const long long nT = (long long)nF * nF * nF;
+  const long long T = (long long)(blockIdx.x - sg.first_block) * 256 + threadIdx.x;
+  if (T >= nT) return;
+  const int t2 = (int)(T % nF), t1 = (int)((T / nF) % nF), t0 = (int)(T / ((long long)nF * nF));
+  double v[64];
+  p2m2_slots(rho + (((long long)4 * t0) * n + 4 * t1) * n + 4 * t2, n, v);
   const long long ncellp = (long long)nFp * nFp * nFp;
   const long long cp = ((long long)(t0 + 3) * nFp + (t1 + 3)) * nFp + (t2 + 3);
   double tv[TypedChunk<CT>::KC];  // the typed chunk being filled
   d4 o = d4{0, 0, 0, 0};
-  // degree by degree: the full terms, written in chunks of 4, and from those
-  // of one degree its harmonic terms
-  static_for<P + 1>([&](auto dc) {
-    constexpr int m = decltype(dc)::value;
-    double d[ndeg(m)];
-    static_for<ndeg(m)>([&](auto ec) {
-      constexpr int al = nterms(m - 1) + decltype(ec)::value, c = al / 4;
-      double val = 0.0;
-      {
-        constexpr int ex = mi_exp_of(al);
-        constexpr int ax = ex & 255, ay = (ex >> 8) & 255, az = ex >> 16;
-        constexpr int base = 16 * 2 * (ax & 1) + 4 * 2 * (ay & 1) + 2 * (az & 1);
-        double x = 0.0;
-        static_for<8>([&](auto mc) {
-          constexpr int m = decltype(mc)::value, mx = m >> 2, my = (m >> 1) & 1, mz = m & 1;
-          constexpr double wt = pow3(mx ? 0 : ax) * pow3(my ? 0 : ay) * pow3(mz ? 0 : az);
-          x = fma(wt, v[base + 16 * mx + 4 * my + mz], x);
-        });
-        constexpr double sc = 1.0 / (fact_d(ax) * fact_d(ay) * fact_d(az) * (double)(1LL << (3 * (ax + ay + az))));
-        if (al < NM) val = sc * x;
-      }
-      d[decltype(ec)::value] = val;
-      o[al % 4] = val;
-      if constexpr (!HARM && (al % 4 == 3 || al == NT - 1)) {
-        *reinterpret_cast<d4*>(M + (c * ncellp + cp) * 4) = o;
-        TypedChunk<CT>::template put<c, NC>(tv, o, sg.t, ncellp, cp);
-        o = d4{0, 0, 0, 0};
-      }
-    });
-    if constexpr (HARM)
-      static_for<2 * m + 1>([&](auto rc) {
-        constexpr int i = m * m + decltype(rc)::value;
-        const double v = h_reduce_deg<i>(d);
-        M[i * ncellp + cp] = v;
-        if (sg.u) static_cast<float*>(sg.u)[i * ncellp + cp] = (float)v;
-      });
-    // (one degree at a time: the scheduler would otherwise form every term
-    // before the first store and hold them all in registers)
-    __builtin_amdgcn_sched_barrier(0);
+  static_for<NT>([&](auto ac) {
+    constexpr int al = decltype(ac)::value, c = al / 4;
+    o[al % 4] = al < NM ? p2m2_term<al>(v) : 0.0;
+    if constexpr (al % 4 == 3 || al == NT - 1) {
+      *reinterpret_cast<d4*>(M + (c * ncellp + cp) * 4) = o;
+      TypedChunk<CT>::template put<c, NC>(tv, o, sg.t, ncellp, cp);
+      o = d4{0, 0, 0, 0};
+      // (a chunk at a time: the scheduler would otherwise form every term before
+      // the first store and hold them all in registers)
+      __builtin_amdgcn_sched_barrier(0);
+    }
   });
 }
 
@@ -1453,7 +1441,7 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
     if (pl->s_m2pf[x][0].nseg && (e = build_fold(pl, FO_M2P, x, s)) != hipSuccess) return e;
   }
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
-    constexpr int cnt = ShiftShape<P>::GATHER + ShiftShape<P>::SCATTER;
+    constexpr int cnt = ShiftShape<P>::TABLE;
     if ((e = hipMalloc(&pl->wshift, cnt * sizeof(double))) != hipSuccess) return e;
     pl->bytes += cnt * sizeof(double);
     hipLaunchKernelGGL(k_shift_table<P>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->wshift);
@@ -1754,23 +1742,28 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   {
     StageScope sc(pl, ST_P2M, 1, s);
     // terms past nmax are written as zero
-    if (pl->s_p2mf.nseg) {
-      hipLaunchKernelGGL((k_p2m2<P, TI, CT, true>), dim3(pl->s_p2mf.blocks), dim3(256), 0, s, pl->s_p2mf.dev,
-                         pl->s_p2mf.nseg, io, pl->NMX);
+    if (pl->s_p2mh.nseg) {
+      hipLaunchKernelGGL((k_p2mh<P, TI>), dim3(pl->s_p2mh.blocks), dim3(256), 0, s, pl->s_p2mh.dev, pl->s_p2mh.nseg,
+                         io, hterms(pl->nmax));
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (pl->s_up.nseg) {
+      hipLaunchKernelGGL((k_up<P, TI>), dim3(pl->s_up.blocks), dim3(256), 0, s, pl->s_up.dev, pl->s_up.nseg, io,
+                         pl->wshift + ShiftShape<P>::GATHER + ShiftShape<P>::SCATTER, hterms(pl->nmax));
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if constexpr (Mf<CT>::IDX == 2) {
       if (!pl->s_p2m.nseg)
         ;
       else if (pl->dl == 2)
-        hipLaunchKernelGGL((k_p2m2<P, TI, CT, false>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev,
+        hipLaunchKernelGGL((k_p2m2<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev,
                            pl->s_p2m.nseg, io, pl->NMX);
       else
         hipLaunchKernelGGL((k_p2m<P, TI, CT>), dim3(pl->s_p2m.blocks), dim3(256), 0, s, pl->s_p2m.dev, pl->s_p2m.nseg,
                            io, pl->NMX);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       if (pl->s_p2m2.nseg) {
-        hipLaunchKernelGGL((k_p2m2<P, TI, CT, false>), dim3(pl->s_p2m2.blocks), dim3(256), 0, s, pl->s_p2m2.dev,
+        hipLaunchKernelGGL((k_p2m2<P, TI, CT>), dim3(pl->s_p2m2.blocks), dim3(256), 0, s, pl->s_p2m2.dev,
                            pl->s_p2m2.nseg, io, pl->NMX);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }

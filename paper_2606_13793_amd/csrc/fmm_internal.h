@@ -365,7 +365,8 @@ struct fmm_plan {
   fmm::SegTable s_p2m;
   fmm::SegTable s_p2m2;             // FMM-1: level F - 1 formed from the unigrid (64 cells each)
   bool lt_live = false;             // the M2L writes the finest locals in the compute type (Level::Lt)
-  fmm::SegTable s_p2mf;             // folded fields: harmonic multipoles of the 4^3 unigrid cells
+  fmm::SegTable s_p2mh;             // folded fields: harmonic multipoles of the 4^3 unigrid cells
+  fmm::SegTable s_up;               // small folded fields: those and the two levels above
   fmm::SegTable s_m2m[16];          // M2M into level k - 1 (index k)
   fmm::SegTable s_m2mf[16];         // the same of folded fields
   double* wshift = nullptr;         // folded fields: fragments of the shifts between levels

@@ -20,7 +20,8 @@ template <int P>
 struct ShiftShape {
   static constexpr int HT = hterms(P), NS = (HT + 3) / 4, NPS = blk_psteps(P), NTC = (NPS + 3) / 4, NTB = (HT + 15) / 16;
   static constexpr int SPW = (NS + 3) / 4;  // gather: K steps of each of the 4 waves
-  static constexpr int GATHER = NS * 8 * NTC * 64, SCATTER = 8 * NPS * NTB * 64;
+  static constexpr int GATHER = NS * 8 * NTC * 64, SCATTER = 8 * NPS * NTB * 64, PLAIN = HT * HT;
+  static constexpr int TABLE = GATHER + SCATTER + PLAIN;
 };
 
 __device__ inline double shift_coef(int a, int b) {
@@ -40,22 +41,25 @@ __device__ inline double shift_coef(int a, int b) {
 }
 // Fragments of the gather [step][class][tile][64] (k-group kq: b = 4 s + kq;
 // lane: term 16 tile + i of the class), then of the scatter [class][step][tile]
-// [64] (k-group: term 4 s + kq of the class; lane: b = 16 tile + i).
+// [64] (k-group: term 4 s + kq of the class; lane: b = 16 tile + i), then C[b][a].
 template <int P>
 __global__ void k_shift_table(double* __restrict__ W) {
   using S = ShiftShape<P>;
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= S::GATHER + S::SCATTER) return;
+  if (id >= S::TABLE) return;
   const int i = id & 15, kq = (id >> 4) & 3;
   int a, b;
   if (id < S::GATHER) {
     const int f = id >> 6, j = 16 * (f % S::NTC) + i;
     a = j < 4 * S::NPS ? c_ft<P>.pt[(f / S::NTC) & 7][j] : -1;
     b = 4 * (f / (8 * S::NTC)) + kq;
-  } else {
+  } else if (id < S::GATHER + S::SCATTER) {
     const int f = (id - S::GATHER) >> 6;
     a = c_ft<P>.pt[f / (S::NTB * S::NPS)][4 * (f / S::NTB % S::NPS) + kq];
     b = 16 * (f % S::NTB) + i;
+  } else {
+    a = (id - S::GATHER - S::SCATTER) % S::HT;
+    b = (id - S::GATHER - S::SCATTER) / S::HT;
   }
   W[id] = a >= 0 && b < S::HT ? shift_coef(a, b) : 0.0;
 }
@@ -169,8 +173,7 @@ __global__ __launch_bounds__(256, 2) void k_gather(const Seg* __restrict__ segs,
   }
 }
 
-// Scatter.  Segments: n = parents per axis, a = the parents' values (ROWS: null
-// where there are none), b = the children's (planes: added to), ROWS: c = the
+// Scatter.  Segments: n = parents per axis, a = the parents' values, b = the children's (planes: added to), ROWS: c = the
 // M2L's rows [parent][frow], sums over the children's signs times 8.
 // Block: 16 parents, one wave for each 16 terms b: it holds the 8 classes of a
 // (parent, term) in one lane, so the inverse Walsh sum needs no exchange.
@@ -237,5 +240,143 @@ __global__ __launch_bounds__(64 * ShiftShape<P>::NTB) void k_scatter(const Seg* 
         *z += dz2{chi(pb, 2 * q) * y[2 * q], chi(pb, 2 * q + 1) * y[2 * q + 1]};
       }
     }
+  }
+}
+
+// Harmonic multipoles of the cells of 4^3 unigrid cells, one thread each.
+// Segments: n = unigrid cells per axis, field, b = planes, u = copy in FP32 or
+// null.  hm: terms written (the others are zero).
+// What bounds it: reading the densities and writing the planes (whole lines, as
+// the lanes of a wave run along z).
+template <int P, typename TI>
+__global__ __launch_bounds__(256) void k_p2mh(const Seg* __restrict__ segs, int nseg, IoArg io, int hm) {
+  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
+  const int n = sg.n, nk = n >> 2, gp = nk + 6;
+  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
+  const long long T = (long long)((int)blockIdx.x - sg.first_block) * 256 + threadIdx.x;
+  if (T >= (long long)nk * nk * nk) return;
+  const int t2 = (int)(T % nk), t1 = (int)((T / nk) % nk), t0 = (int)(T / ((long long)nk * nk));
+  double v[64];
+  p2m2_slots(rho + (((long long)4 * t0) * n + 4 * t1) * n + 4 * t2, n, v);
+  const long long ncp = (long long)gp * gp * gp, cp = ((long long)(t0 + 3) * gp + t1 + 3) * gp + t2 + 3;
+  static_for<P + 1>([&](auto dc) {
+    constexpr int m = decltype(dc)::value;
+    double d[ndeg(m)];
+    static_for<ndeg(m)>([&](auto ec) { d[decltype(ec)::value] = p2m2_term<nterms(m - 1) + decltype(ec)::value>(v); });
+    static_for<2 * m + 1>([&](auto rc) {
+      constexpr int i = m * m + decltype(rc)::value;
+      const double x = i < hm ? h_reduce_deg<i>(d) : 0.0;
+      sg.b[i * ncp + cp] = x;
+      if (sg.u) static_cast<float*>(sg.u)[i * ncp + cp] = (float)x;
+    });
+    // (one degree at a time: the scheduler would otherwise form every term
+    // before the first store and hold them all in registers)
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+// Upward pass of a folded field from its unigrid: harmonic multipoles of the
+// cells of 4^3 unigrid cells (level k) and of the two levels above.
+// Segments: n = unigrid cells per axis, field, split = levels (1 to 3),
+// a, c, d = planes of levels k, k - 1, k - 2 (FP64, written), b, t, u = their
+// copies in FP32, or null.
+// Block: 16^3 unigrid cells, 64 cells of level k, 8 and 1 above.  The lane's cell
+// is P2M's (one wave would do; the 4 waves share the terms by degree), its values
+// stay in LDS, and the shifts are plain sums of the matrix C over the 8 children's
+// sums of a parity: 8 parents would leave half of a matrix product empty.
+// What bounds it: on small grids the latency of one pass from the densities to
+// the planes, of which separate launches had one each.
+constexpr int up_owner(int P, int m) {  // the wave that forms degree m
+  int load[4] = {}, own = 0;
+  for (int d = P; d >= m; --d) {
+    own = 0;
+    for (int w = 1; w < 4; ++w)
+      if (load[w] < load[own]) own = w;
+    load[own] += ndeg(d);
+  }
+  return own;
+}
+template <int P, typename TI>
+__global__ __launch_bounds__(256) void k_up(const Seg* __restrict__ segs, int nseg, IoArg io,
+                                            const double* __restrict__ C, int hm) {
+  constexpr int HT = hterms(P), CS = 65;
+  __shared__ double cell[HT * CS];         // [term][cell]
+  __shared__ double sums[8 * HT * 8];      // [class][term][parent]
+  __shared__ double mid[HT * 9];           // [term][level k - 1]
+  const Seg& sg = find_seg(segs, nseg, blockIdx.x);
+  const int n = sg.n, nk = n >> 2, lb = (int)blockIdx.x - sg.first_block, nr = n >> 4;
+  const int b0 = lb / (nr * nr), b1 = (lb / nr) % nr, b2 = lb % nr;
+  const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto put = [&](const double* planes, void* copy, int g, int x, int y, int z, int term, double v) {
+    const int gp = g + 6;
+    const long long at = term * ((long long)gp * gp * gp) + ((long long)(x + 3) * gp + y + 3) * gp + z + 3;
+    const_cast<double*>(planes)[at] = v;
+    if (copy) static_cast<float*>(copy)[at] = (float)v;
+  };
+  {
+    const int t0 = 4 * b0 + (lane >> 4), t1 = 4 * b1 + ((lane >> 2) & 3), t2 = 4 * b2 + (lane & 3);
+    double v[64];
+    p2m2_slots(rho + (((long long)4 * t0) * n + 4 * t1) * n + 4 * t2, n, v);
+    static_for<P + 1>([&](auto dc) {
+      constexpr int m = decltype(dc)::value;
+      if (w != up_owner(P, m)) return;
+      double d[ndeg(m)];
+      static_for<ndeg(m)>([&](auto ec) { d[decltype(ec)::value] = p2m2_term<nterms(m - 1) + decltype(ec)::value>(v); });
+      static_for<2 * m + 1>([&](auto rc) {
+        constexpr int i = m * m + decltype(rc)::value;
+        const double x = i < hm ? h_reduce_deg<i>(d) : 0.0;
+        cell[i * CS + lane] = x;
+        put(sg.a, sg.b, nk, t0, t1, t2, i, x);
+      });
+      // (one degree at a time: the scheduler would otherwise form every term
+      // before the first store and hold them all in registers)
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  // sums over the children's signs: chi_{e + parity(b)}; bits of a child: upper
+  auto fold = [&](const double* from, int stride, int np, auto child) {
+    for (int q = threadIdx.x; q < np * HT; q += 256) {
+      const int p = q % np, b = q / np, par = c_ft<P>.par[b];
+      double r[8], a[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) r[m] = from[b * stride + child(p, m)];
+      fold8<8>(r, par & 4 ? -1.0 : 1.0, par & 2 ? -1.0 : 1.0, par & 1 ? -1.0 : 1.0, a);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sums[(e * HT + b) * np + p] = a[e];
+    }
+  };
+  if (sg.split < 2) return;
+  __syncthreads();
+  fold(cell, CS, 8, [](int p, int m) {
+    return 16 * (2 * (p >> 2) + (m >> 2)) + 4 * (2 * ((p >> 1) & 1) + ((m >> 1) & 1)) + 2 * (p & 1) + (m & 1);
+  });
+  __syncthreads();
+  for (int q = threadIdx.x; q < 8 * HT; q += 256) {
+    const int p = q & 7, a = q >> 3, nb = hterms(c_ft<P>.deg[a]);
+    const double* x = sums + c_ft<P>.par[a] * (HT * 8) + p;
+    double v = 0.0;
+#pragma unroll 4
+    for (int b = 0; b < nb; ++b) v = fma(C[b * HT + a], x[b * 8], v);
+    if (a >= hm) v = 0.0;
+    mid[a * 9 + p] = v;
+    put(sg.c, sg.t, nk >> 1, 2 * b0 + (p >> 2), 2 * b1 + ((p >> 1) & 1), 2 * b2 + (p & 1), a, v);
+  }
+  if (sg.split < 3) return;
+  __syncthreads();
+  fold(mid, 9, 1, [](int, int m) { return m; });
+  __syncthreads();
+  // (4 lanes share a sum)
+  for (int q = threadIdx.x; q < 4 * HT; q += 256) {
+    const int a = q >> 2, nb = hterms(c_ft<P>.deg[a]);
+    const double* x = sums + c_ft<P>.par[a] * HT;
+    double v = 0.0;
+#pragma unroll 4
+    for (int b = q & 3; b < nb; b += 4) v = fma(C[b * HT + a], x[b], v);
+    v += __shfl_xor(v, 1);
+    v += __shfl_xor(v, 2);
+    if (a >= hm) v = 0.0;
+    if ((q & 3) == 0) put(sg.d, sg.u, nk >> 2, b0, b1, b2, a, v);
   }
 }
