@@ -83,8 +83,9 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
 // transposed tables: Lw_bar_F columns (e, b) to padded planes
 // [column][(nb + 6)^3] in the compute type of the transposed M2L, and the
 // terms of parity e of Lc_bar_{F-1}, [block][hrow].  Bound by its traffic
-// (reads 4 values a cell, writes 8 (p + 1)^2 a block); rows consecutive along
-// z make every plane's store a run of 16.
+// (reads 4 values a cell, writes 8 (p + 1)^2 a block); the blocks are the columns
+// of the products, so that a wave's store to a plane is a run of 16 along z
+// straight from its registers (128^3, p = 6: 63 us, through LDS 78).
 // FMM-2: no own part; lb takes Y itself, planes [32 e + 4 t + o][(nb + 6)^3].
 template <int P, typename TI, typename H, int DL>
 __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, const TI* __restrict__ dg, int n,
@@ -92,9 +93,8 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
                                                    double* __restrict__ lc) {
   constexpr int HR = hrow(P), NT = blka_ltiles(P), HT = hterms(P), NPT = 4 * blk_psteps(P);
   constexpr int OFF_L = blka_off_l(P), OFF_P = blka_off_lp(P);
-  constexpr int YS = 33, RS = 17;  // LDS row strides
-  constexpr int SZ = 8 * 16 * YS > 8 * (HT + 16) * RS ? 8 * 16 * YS : 8 * (HT + 16) * RS;
-  __shared__ double lds[SZ];
+  constexpr int YS = 33;  // LDS row stride
+  __shared__ double lds[8 * 16 * YS];
   const int nb = n >> 2, nbp = nb + 6;
   const long long nblk = (long long)nb * nb * nb, N = (long long)n * n * n, ncp = (long long)nbp * nbp * nbp;
   const long long B0 = (long long)blockIdx.x * 16;
@@ -147,38 +147,31 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
     const double a = lds[(e * 16 + i) * YS + 4 * s + kq];
 #pragma unroll
     for (int t = 0; t < NT && DL == 1; ++t)
-      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_L + (s * NT + t) * 64 + lane], acc[t], 0, 0, 0);
-    if (lc) ap = __builtin_amdgcn_mfma_f64_16x16x4f64(a, W[OFF_P + (e * 8 + s) * 64 + lane], ap, 0, 0, 0);
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(W[OFF_L + (s * NT + t) * 64 + lane], a, acc[t], 0, 0, 0);
+    if (lc) ap = __builtin_amdgcn_mfma_f64_16x16x4f64(W[OFF_P + (e * 8 + s) * 64 + lane], a, ap, 0, 0, 0);
   }
-  __syncthreads();
-  // results by column, blocks along a row
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  // rows of the results: columns b of pattern e, places in class e
+  const long long B = B0 + i;
+  if (B >= nblk) return;
+  if constexpr (DL == 1) {
+    const int b2 = (int)(B % nb), b1 = (int)((B / nb) % nb), b0 = (int)(B / ((long long)nb * nb));
+    H* const to = lb + ((long long)(b0 + 3) * nbp + b1 + 3) * nbp + b2 + 3;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      if (16 * t + i < HT) lds[(e * (HT + 16) + 16 * t + i) * RS + 4 * v + kq] = acc[t][v];
-    lds[(e * (HT + 16) + HT + i) * RS + 4 * v + kq] = ap[v];
-  }
-  __syncthreads();
-  if constexpr (DL == 1) {
-    const int bl = threadIdx.x & 15;
-    const long long B = B0 + bl;
-    if (B < nblk) {
-      const int b2 = (int)(B % nb), b1 = (int)((B / nb) % nb), b0 = (int)(B / ((long long)nb * nb));
-      const long long cp = ((long long)(b0 + 3) * nbp + b1 + 3) * nbp + b2 + 3;
-      for (int c = threadIdx.x >> 4; c < 8 * HT; c += 32) {
-        const int q = c_ft<P>.col[c], k = q >> 8, b = q & 255;
-        lb[c * ncp + cp] = static_cast<H>(lds[(k * (HT + 16) + b) * RS + bl]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int b = 16 * t + 4 * v + kq;
+        if (b >= HT) continue;
+        const int m = c_ft<P>.deg[b];
+        to[(7 * m * m + b + e * (2 * m + 1)) * ncp] = static_cast<H>(acc[t][v]);
       }
-    }
   }
-  if (lc) {
-    for (int q = threadIdx.x; q < 16 * 128; q += 512) {
-      const int j = q & 15, pe = (q >> 4) & 7, bl = q >> 7;
-      const int b = j < NPT ? c_ft<P>.pt[pe][j] : -1;
-      if (b >= 0 && B0 + bl < nblk) lc[(B0 + bl) * HR + b] = lds[(pe * (HT + 16) + HT + j) * RS + bl];
+  if (lc)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int j = 4 * v + kq, b = j < NPT ? c_ft<P>.pt[e][j] : -1;
+      if (b >= 0) lc[B * HR + b] = ap[v];
     }
-  }
 }
 
 // Transpose of the block stencil (P2P^T, M2P^T and the finest P2M^T), plus the

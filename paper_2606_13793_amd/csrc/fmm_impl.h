@@ -1569,9 +1569,12 @@ hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
 }
 
 // Grid of a launch over T tiles.  A block's K loop is cut where it would take
-// more than half (small tiles: a quarter) of what each compute unit has to do in the whole launch
-// (the last blocks to start would otherwise set its length), down to one
-// chunk of 27 steps.
+// more than half (large tiles of a transpose: all) of what each compute unit has
+// to do in the whole launch, as the last blocks to start would otherwise set its
+// length, down to one chunk of 27 steps.  M2L and the sum of its parts, us, at a
+// quarter / half / all: 64^3, p = 5, FP32 29 + 10 / 25 + 9 / 28 + 8; transposed,
+// 64^3, p = 4, FP32 33 + 13 / 31 + 12 / 40 + 12; 128^3, p = 6, FP64 - / 538 + 12 /
+// 516 + 9.
 template <int P, int OP, int V, int X>
 M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
   using S = M2lShape<OP, V, X>;
@@ -1585,7 +1588,7 @@ M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
     longest[t / S::NT] = std::max<long long>(longest[t / S::NT], st);
     total += st;
   }
-  const long long lim = std::max<long long>(27, total * T / pl->cus / (V ? 2 : 4));
+  const long long lim = std::max<long long>(27, total * T / pl->cus / ((OP & 1) && V ? 1 : 2));
   for (int i = 0; i < g.ng; ++i) {
     const long long chunks = (longest[i] + 26) / 27, want = (cost[i] + lim - 1) / lim;
     g.parts[i] = (int)std::max<long long>(1, std::min<long long>({want, chunks, 32}));

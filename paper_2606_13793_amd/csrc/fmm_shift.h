@@ -189,56 +189,81 @@ __global__ __launch_bounds__(64 * ShiftShape<P>::NTB) void k_scatter(const Seg* 
   const long long P0 = (long long)((int)blockIdx.x - sg.first_block) * 16;
   const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the lane's 4 results (parent, term), clamped into the grid; what they add to
+  // is read before anything else
+  typedef double dz2 __attribute__((ext_vector_type(2), aligned(8)));
+  const int tb0 = 16 * t;
+  double own[4][8];
+  long long at[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = Mf<double>::row(r, kq), b = min(tb0 + (ROWS ? i : row), HT - 1);
+    const long long p = min(P0 + (ROWS ? row : i), nps - 1);
+    const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np));
+    if constexpr (ROWS) {
+      at[r] = (((long long)(2 * p0) * nc + 2 * p1) * nc + 2 * p2) * HR + b;
+      const auto from = gmem(sg.c + p * FR + fold_at(0, b));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) own[r][e] = from[2 * e];
+    } else {
+      at[r] = b * ncc + ((long long)(2 * p0 + 3) * nc + 2 * p1 + 3) * nc + 2 * p2 + 3;
+      const auto from = gmem(sg.b + at[r]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const dz2 z = *(const __attribute__((address_space(1))) dz2*)(from + ((long long)(q >> 1) * nc + (q & 1)) * nc);
+        own[r][2 * q] = z[0];
+        own[r][2 * q + 1] = z[1];
+      }
+    }
+  }
   d4 acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = d4{0, 0, 0, 0};
-  if (sg.a) {
+  {
     const long long pc = min(P0 + i, nps - 1);
     const int p2 = (int)(pc % np), p1 = (int)((pc / np) % np), p0 = (int)(pc / ((long long)np * np));
     const auto src = gmem(sg.a + (ROWS ? pc * HR : ((long long)(p0 + 3) * npp + p1 + 3) * npp + p2 + 3));
     const auto wt = gmem(W + S::GATHER + t * 64);
-    double v[8][NPS];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int s = 0; s < NPS; ++s) v[e][s] = src[max((int)c_ft<P>.pt[e][4 * s + kq], 0) * (ROWS ? 1LL : ncpp)];
+    double v[8][NPS], tb[8][NPS];
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int s = 0; s < NPS; ++s) {
         // (a class's places past its last term: the table is zero)
-        const double tb = (wt + (e * NPS + s) * NTB * 64)[(unsigned)lane];
-        acc[e] = ROWS ? __builtin_amdgcn_mfma_f64_16x16x4f64(v[e][s], tb, acc[e], 0, 0, 0)
-                      : __builtin_amdgcn_mfma_f64_16x16x4f64(tb, v[e][s], acc[e], 0, 0, 0);
+        v[e][s] = src[max((int)c_ft<P>.pt[e][4 * s + kq], 0) * (ROWS ? 1LL : ncpp)];
+        tb[e][s] = (wt + (e * NPS + s) * NTB * 64)[(unsigned)lane];
       }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int s = 0; s < NPS; ++s)
+        acc[e] = ROWS ? __builtin_amdgcn_mfma_f64_16x16x4f64(v[e][s], tb[e][s], acc[e], 0, 0, 0)
+                      : __builtin_amdgcn_mfma_f64_16x16x4f64(tb[e][s], v[e][s], acc[e], 0, 0, 0);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int row = Mf<double>::row(r, kq), b = 16 * t + (ROWS ? i : row);
-    const long long p = P0 + (ROWS ? row : i);
-    if (b >= HT || p >= nps) continue;
-    const int p2 = (int)(p % np), p1 = (int)((p / np) % np), p0 = (int)(p / ((long long)np * np)), pb = c_ft<P>.par[b];
+    const int row = Mf<double>::row(r, kq), b = tb0 + (ROWS ? i : row);
+    if (b >= HT || P0 + (ROWS ? row : i) >= nps) continue;
+    const int pb = c_ft<P>.par[b];
     double y[8];
     if constexpr (ROWS) {
-      const auto own = gmem(sg.c + p * FR + fold_at(0, b));
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = fma(0.125, own[2 * e], 0.5 * acc[e][r]);
+      for (int e = 0; e < 8; ++e) y[e] = fma(0.125, own[r][e], 0.5 * acc[e][r]);
       walsh8(y);
-      double* const to = sg.b + (((long long)(2 * p0) * nc + 2 * p1) * nc + 2 * p2) * HR + b;
+      double* const to = sg.b + at[r];
 #pragma unroll
       for (int m = 0; m < 8; ++m)  // minus bits
         to[((long long)((m & 4 ? 0 : 1) * nc + (m & 2 ? 0 : 1)) * nc + (m & 1 ? 0 : 1)) * HR] = chi(pb, m) * y[m];
     } else {
-      typedef double dz2 __attribute__((ext_vector_type(2), aligned(8)));
 #pragma unroll
       for (int e = 0; e < 8; ++e) y[e] = acc[e][r];
       walsh8(y);
-      double* const to = sg.b + b * ncc + ((long long)(2 * p0 + 3) * nc + 2 * p1 + 3) * nc + 2 * p2 + 3;
+      double* const to = sg.b + at[r];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {  // upper bits
-        dz2* const z = reinterpret_cast<dz2*>(to + ((long long)(q >> 1) * nc + (q & 1)) * nc);
-        *z += dz2{chi(pb, 2 * q) * y[2 * q], chi(pb, 2 * q + 1) * y[2 * q + 1]};
-      }
+      for (int q = 0; q < 4; ++q)  // upper bits
+        *reinterpret_cast<dz2*>(to + ((long long)(q >> 1) * nc + (q & 1)) * nc) =
+            dz2{own[r][2 * q] + chi(pb, 2 * q) * y[2 * q], own[r][2 * q + 1] + chi(pb, 2 * q + 1) * y[2 * q + 1]};
     }
   }
 }
