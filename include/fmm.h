@@ -78,10 +78,11 @@ typedef struct {
                                (FMM-2, App. A; n >= 16) */
   int check_finite;         /* nonzero: fmm_solve scans rho for NaN/Inf first (single-field plans) */
   int autotune;             /* batch plans: time the launch-shape candidates at creation; default 1 */
-  int bottom_tile;          /* depth (level-F cells along z) of the bottom kernel's tiles: 0 = chosen
-                               by the plan (default: 16, or 8 where 16-deep tiles would leave
-                               compute units idle, or the autotuner's choice), 8 or 16 to force one
-                               (delta_l = 2 plans take 16 only).  Results do not depend on it
+  int bottom_tile;          /* tiles of the finest-level kernel: 0 = chosen by the plan (default: 16,
+                               or 8 where those would leave compute units idle, or the autotuner's
+                               choice), 8 or 16 to force small or large ones (one or two rows of 4^3
+                               unigrid cells; BF16 levels: 8 or 16 cells deep; delta_l = 2 plans take
+                               16 only).  Results do not depend on it
                                beyond rounding order. */
   const char* autotune_cache; /* batch plans with autotune: path of a text file that remembers the
                                autotuner's choice per (GPU architecture, compute units, field sizes,
@@ -165,7 +166,7 @@ int fmm_solve_backward_noalloc(fmm_plan* plan, const void* dphi, const void* dg,
  * fmm_batch_plan_create: count fields, n[i] as for fmm_plan_create, one order
  *   p and one set of options (check_finite is not provided).  With
  *   opt->autotune (the default) the plan times each launch-shape candidate
- *   (bottom-kernel tile depth 16 or 8, wide or narrow M2L column groups) on
+ *   (large or small finest-level tiles, wide or narrow M2L column groups) on
  *   zero densities of the batch and keeps the fastest; this allocates
  *   temporary I/O buffers for every field.  Synchronous.  NULL on error.
  * fmm_batch_solve: rho[i], phi[i] (and g[i], if g is not NULL and g[i] is not
@@ -224,7 +225,9 @@ int fmm_last_status(void);
  * it may finish pending work on the plan's buffers (the finest level keeps
  * only its M2L part during a solve), so call it only between solves on the
  * null stream's device.  Copies to HOST
- * memory `out`, as double, the scaled expansions the kernels keep:
+ * memory `out`, as double, the scaled expansions (FP64 and FP32 levels keep
+ * them in harmonic terms only: full multipoles are then formed on the host from
+ * the plan's copy of the density, full locals by Laplace's equation):
  *   which = 0: multipoles of level `level` (2 <= level <= F), nterms(nmax) per cell,
  *              Mhat[a] = (-1)^|a| M[a] / (a! h^|a| dx^3), M[a] = sum m (x - c)^a
  *   which = 1: locals of level `level` (3 <= level <= F),

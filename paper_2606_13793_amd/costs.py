@@ -83,6 +83,48 @@ def m2p_pairs(n: int, delta_l: int = 1) -> int:
     return 8 ** delta_l * list_pairs(n >> delta_l)
 
 
+def folded_flops(n: int, p: int, nmax: int | None = None, delta_l: int = 1) -> dict:
+    """Flops that the folded kernels of FP64 and FP32 fields execute per stage
+    of one solve (phi and g): the matrix products as issued, 16 x 16 x 4
+    multiply-adds each, with the rows, columns and K steps that only fill them
+    up.  This is what a rate is measured against; solve_flops counts the same
+    solve by the operators as the paper writes them, which mirror images and
+    Laplace's equation make about 20 times fewer."""
+    nmax = p if nmax is None else nmax
+    F = n.bit_length() - 1 - delta_l
+    B = F + delta_l - 2  # the level of the cells of 4^3 unigrid cells
+    H = lambda m: (m + 1) ** 2 if m >= 0 else 0
+    cdiv = lambda a, b: -(-a // b)
+    tile = 2 * 16 * 16 * 4
+    chunks = lambda q: 7 + 27 * cdiv(H(q) - 1, 4)
+    degree = lambda i: next(m for m in range(p + 1) if H(m) > i)
+    classes = [0] * 8  # harmonic terms by parity
+    for m in range(p + 1):
+        for x in range(m + 1):
+            classes[(x & 1) << 2 | ((m - x) & 1) << 1] += 1
+        for x in range(m):
+            classes[(x & 1) << 2 | ((m - 1 - x) & 1) << 1 | 1] += 1
+    nps = cdiv(max(classes), 4)
+    rows = lambda cells: cells // 2 * cdiv(cells // 2, 4) ** 2  # row tiles of 16 octs
+    m2l_steps = sum(chunks(min(nmax, p - degree(2 * t))) for t in range(cdiv(H(p), 2)))
+    out = {}
+    out["p2m"] = 8 ** B * (2 * 8 * nterms(nmax) + 3 * 64) if B >= 2 else 0
+    out["m2m"] = sum(cdiv(8 ** (k - 1), 16) * cdiv(H(p), 4) * 8 * cdiv(nps, 4) * tile for k in range(3, B + 1))
+    out["m2l"] = sum(rows(2 ** (k - 1)) * m2l_steps * 8 * tile for k in range(3, F + 1))
+    out["l2l"] = sum(cdiv(8 ** (k - 1), 16) * 8 * nps * cdiv(H(p), 16) * tile for k in range(4, B + 1))
+    steps = 54 * 8
+    if delta_l == 1 and F >= 3:
+        steps += 2 * cdiv(H(p), 8) * 8
+    if B >= 3:
+        steps += 8 * nps
+    nb = n // 4
+    out["bottom"] = nb * cdiv(nb, 4) ** 2 * steps * 2 * tile
+    if delta_l == 2:
+        out["bottom"] += rows(2 ** F) * 16 * chunks(nmax) * 8 * tile
+    out["total"] = sum(out.values())
+    return out
+
+
 # The paper's per-operator counts at its own orders (Sec. 4: locals p = 3,
 # multipoles nmax = 2, only the potential at the finest level), per cell and
 # interaction, as printed there.

@@ -155,8 +155,7 @@ void release(fmm_plan* pl) {
   for (auto& st : pl->s_m2mf) free_st(st);
   for (auto& st : pl->s_conv) free_st(st);
   for (auto& st : pl->s_l2l) free_st(st);
-  for (auto& a : pl->s_bot)
-    for (auto& st : a) free_st(st);
+  for (auto& st : pl->s_bot) free_st(st);
   for (auto& a : pl->s_blk)
     for (auto& st : a) free_st(st);
   for (auto& a : pl->s_m2lf)
@@ -389,7 +388,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, p2mh, up, m2m[16], m2mf[16], conv[2], l2l[16], bot[2][2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
+  SegList p2m, p2m2, p2mh, up, m2m[16], m2mf[16], conv[2], l2l[16], bot[2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -553,7 +552,7 @@ int build_schedule(fmm_plan* pl) {
       b.c = F >= 3 ? (const double*)fd.lev[F].L : nullptr;
       b.d = F >= 4 ? (const double*)fd.lev[F - 1].L : nullptr;
       b.t = fd.lev[F].Mt;
-      bot[bottom_low(pl, F) ? 1 : 0][z].add(b, (long long)b.tpa * b.tpa * b.tz);
+      bot[z].add(b, (long long)b.tpa * b.tpa * b.tz);
     }
   }
   // A site whose row grids are all at most 8 cells deep (the coarse FP64
@@ -623,12 +622,11 @@ int build_schedule(fmm_plan* pl) {
         if (c.u) lt[c.field] = c.u;
     pl->lt_live = false;
     for (auto p : lt) pl->lt_live = pl->lt_live || p;
-    for (auto& bs : bot)
-      for (auto& bl : bs)
-        for (auto& b : bl.v) {
-          b.u = lt[b.field];
-          pl->lt_live = pl->lt_live || b.u;
-        }
+    for (auto& bl : bot)
+      for (auto& b : bl.v) {
+        b.u = lt[b.field];
+        pl->lt_live = pl->lt_live || b.u;
+      }
   }
   int rc;
   if ((rc = upload_segs(pl, pl->s_p2m, p2m))) return rc;
@@ -645,8 +643,7 @@ int build_schedule(fmm_plan* pl) {
     if ((rc = upload_segs(pl, pl->s_conv[x], conv[x]))) return rc;
     pl->s_conv[x].cz = cz[x];
     if ((rc = upload_segs(pl, pl->s_red[x], red[x]))) return rc;
-    for (int z = 0; z < 2; ++z)
-      if ((rc = upload_segs(pl, pl->s_bot[x][z], bot[x][z]))) return rc;
+    if ((rc = upload_segs(pl, pl->s_bot[x], bot[x]))) return rc;
     for (int v = 0; v < 3; ++v)
       if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v])) || (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])) ||
           (rc = upload_segs(pl, pl->s_m2pf[x][v], m2pf[x][v])))

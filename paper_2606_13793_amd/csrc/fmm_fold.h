@@ -312,29 +312,28 @@ __device__ __forceinline__ void blk_images(const H* ctr, int q, const H* (&p)[4]
   p[2] = p[0] - dx;
   p[3] = p[1] - dx;
 }
-template <int JZ, typename H>
-__device__ __forceinline__ void blk_read(const H* const (&p)[4], H (&r)[8]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    r[2 * q] = p[q][6 + JZ];
-    r[2 * q + 1] = p[q][5 - JZ];
-  }
-}
 
 // Segments: n = unigrid cells per axis, tpa = tiles along y and z, tz = tiles
 // along x, field, t = copy of the density to leave in the plan (or null),
 // u = own locals [block][frow] in the compute type (or null: F = 2),
 // d = complete locals of the blocks' cells [block][hrow] (or null), c = FMM-2:
 // M2P, [block][4][4^3] in the compute type.
-// Tile: NX x 4 x 4 blocks; 4 waves: row tile X (the 4 x 4 blocks of plane X),
-// one half of the patterns, and for NX = 1 one of two slices of the K steps.
-// What bounds it: the matrix cores (54 + 13 + 3 K steps of 16 products per row
+// Tile: NX x 4 x 4 blocks, NT of the 2 column tiles (one: t = 0 the inner, 1 the
+// outer cells along x; blockIdx.y).  4 waves, each with one half of the patterns
+// and NR row tiles (the 4 x 4 blocks of a plane) of one of KS slices of the K steps.
+// What bounds it: the matrix cores (54 + 14 + 3 K steps of 16 products per row
 // tile at p = 6), and, as vector operations do not run beside FP64 products,
 // everything else a wave executes.  So a lane folds the 8 mirror images of its
 // operand from the LDS tile itself (12 adds for 8 products) at addresses formed
-// once for 6 steps, B comes through the caches at a uniform base, and the
-// epilogue forms addresses once per thread.  Blocks are small so that a CU holds
-// two (FP32: four): one's staging and stores run beside the other's products.
+// once for 6 steps, B comes through the caches at a uniform base, both column
+// tiles in one load, and the epilogue forms addresses once per thread.  FP32
+// products take half as long, and there B's loads bound a wave: each fragment
+// serves two row tiles (256^3, p = 6, FP32: 666 us -> 515; FP64, where that is no
+// gain, 875 against 862; 1146 before the addresses were formed per group and the
+// own locals read as runs).  FP64 at 256^3: 370 us of products for the stencil and
+// 115 for L2P at 2.4 GHz, and 949 MB of locals, 200 us of copy rate.  Blocks are
+// small so that a CU holds two (FP32: three or four): one's staging and stores
+// run beside the other's products.
 // blocks (of 4 waves) per compute unit
 template <typename CT, int NX>
 constexpr int blk_occ = Mf<CT>::IDX == 0 ? 2 : NX == 2 ? 3 : 4;

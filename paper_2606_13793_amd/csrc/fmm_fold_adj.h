@@ -180,7 +180,10 @@ __global__ __launch_bounds__(512) void k_blk_adj_l(const TI* __restrict__ dphi, 
 // the adjoint harmonic multipoles of its own level F-1 cell (planes; or null).
 // Tiles and folding as in k_block.  Products of 16 x 4 x 4 (17 cycles; lane =
 // column + 4 (row / 4) + 16 (row % 4) of the result), as one of 16 x 16 x 4 (64
-// cycles) would have 8 dead columns.
+// cycles) would have 8 dead columns.  Then table loads bound a wave, so a
+// fragment of 8 columns is one load and serves the NX row tiles (128^3, p = 6: 210
+// us with 16 columns, 237 with narrow products for one row tile, 133 now; one row
+// tile per block, which small grids take to fill the device, 163).
 template <int P, typename TI, typename TO, int NX, int DL>
 __global__ __launch_bounds__(BLK_THREADS, 2) void k_block_adj(const TI* __restrict__ dphi, const TI* __restrict__ dg,
                                                               const double* __restrict__ W,

@@ -3,24 +3,29 @@
 // everything but Impl<P> has internal linkage there (each translation unit
 // carries its own constant tables and kernels).
 //
-// Pass order of one solve (Sec. 2 of the paper):
-//   k_p2m            rho -> Mhat_F                       eq. (multipole)
-//   k_m2m            Mhat_k -> Mhat_{k-1}, k = F..3      eq. (M2M)
-//   k_conv (CV_M2L)  Mhat_{k-1} -> Lam_k, k = 3..F       eq. (M2L) over the oct-shared lists
-//                                                        (Sec. 2.2), all levels per launch
-//   k_l2l            Lhat_{k-1} -> Lhat_k (+=), 4..F-1   eq. (L2L)
-//   k_bottom         Mhat_F, Lhat, rho -> phi, g         M2P at the unigrid centres (Sec. 4),
-//                                                        L2P and the near field, eq. (direct)
+// Pass order of one solve (Sec. 2 of the paper), FP64 and FP32 fields and BF16
+// ones whose finest level is coarse ("folded" fields):
+//   k_p2mh, k_gather  rho -> M_B, M_k -> M_{k-1}, k = B..3   eq. (multipole), (M2M)
+//   (k_up             both, three levels at once, small fields)
+//   k_m2lf (+ _sum)   M_{k-1} -> Lw_k, k = 3..F, all levels per launch   eq. (M2L)
+//                     over the oct-shared lists (Sec. 2.2); FMM-2 also M2P (Sec. 4)
+//   k_scatter         L_{k-1}, Lw_k -> L_k, 4..B             eq. (L2L)
+//   k_block           rho, Lw_F, L_B -> phi, g               L2P, near field eq. (direct),
+//                                                            FMM-1: M2P of the adjacent cells
+// B is the level of the cells of 4^3 unigrid cells.  Everything is in harmonic
+// terms (fmm_harmonic.h) and folded about mirror planes (fmm_fold.h, fmm_shift.h;
+// the backward pass, the same operators transposed: fmm_fold_adj.h).
+// BF16 fields round full Cartesian terms to BF16, so they keep those:
+//   k_p2m, k_p2m2, k_m2m, k_conv (fmm_mfma.h; coarse levels in FP64), k_l2l, k_bottom
 // Every launch spans a table of segments (grids of several levels and/or
 // fields); a block finds its segment by binary search over the first blocks.
-// The matrix-core kernels (fmm_mfma.h) are generic over FP64 / FP32 / BF16
-// operands; the upward pass and the L2L chain are FP64.
+// The upward pass and the L2L chain are FP64.
 //
-// Layouts: multipoles and locals are "chunked", [ceil(terms/4)][cells][4], so
-// that a matrix-core operand fragment (4 consecutive terms of one cell) is one
-// 32-byte load and cells of a z line are contiguous.  Multipole grids carry a
-// zero halo of 3 cells per side: the clipped interaction lists of the isolated
-// boundary then need no bounds checks.
+// Layouts: multipoles and cotangents of folded fields are planes [term][cells];
+// those of BF16 fields, and their locals, are "chunked", [ceil(terms/4)][cells][4],
+// so that a matrix-core operand fragment (4 consecutive terms of one cell) is one
+// 32-byte load.  Multipole grids carry a zero halo of 3 cells per side: the
+// clipped interaction lists of the isolated boundary then need no bounds checks.
 #pragma once
 #include "fmm_internal.h"
 
@@ -1323,13 +1328,12 @@ hipError_t build_tile_table(fmm_plan* pl, int op, hipStream_t s) {
     // the kernel takes the tiles that have a chunk to be a prefix of the group
     if (t > 0 && h[2 * t] > h[2 * t - 2]) return hipErrorInvalidValue;
     h[nb + t] = h[2 * t];
-    if (X == 0 && (op == CV_M2LT || op == CV_M2PT || op == CV_M2PT2))
+    if (X == 0 && op == CV_M2LT)
       for (int c = 0; c < h[2 * t]; ++c) {
         // the tile's columns are multipole terms a, sorted by degree; in the
         // transposed M2L, K chunk c holds local columns of degree >= d, where
-        // term a has non-zero entries only if |a| + d <= p; the transposed
-        // M2Ps use every term (columns past the last term are padding)
-        const int d = op == CV_M2LT ? m2l_col_degree(KC * c) : 0;
+        // term a has non-zero entries only if |a| + d <= p
+        const int d = m2l_col_degree(KC * c);
         int ncol = 0;
         for (int a = 16 * t; a < 16 * t + 16 && a < nterms(pl->p); ++a) ncol += mi_degree(a) + d <= pl->p;
         if (ncol <= 4) {
@@ -1346,44 +1350,42 @@ hipError_t build_tile_table(fmm_plan* pl, int op, hipStream_t s) {
              : hipGetLastError();
 }
 
-template <typename CT>
-hipError_t build_tables_t(fmm_plan* pl, bool bottom, bool m2l, hipStream_t s) {
-  using M = Mf<CT>;
-  using H = typename M::H;
+// B fragments of BF16 plans: the bottom's and the M2L's, and in FP64 the M2L's of
+// their coarse levels.
+hipError_t build_tables_bf16(fmm_plan* pl, hipStream_t s) {
+  using M = Mf<bf16_tag>;
+  using H = M::H;
   constexpr int KC = M::KC, OPM = M::OPM, VPL = M::VPL, EL = 64 / OPM, KT = 4 * VPL, X = M::IDX;
   const int NM = pl->NM, NL = pl->NL;
-  const long long NCK = (NM + KC - 1) / KC, NLT = (NL + KT - 1) / KT, NPT = kNearK1 / KT;
+  const long long NCK = (NM + KC - 1) / KC, NLT = (NL + KT - 1) / KT;
   hipError_t e;
-  if (bottom && !pl->wm2p[X] && pl->dl == 2) {
+  if (pl->s_conv[0].nseg) {
+    if ((e = build_conv_table<double>(pl, CV_M2L, &pl->wm2l[0], s)) != hipSuccess) return e;
+    if ((e = build_tile_table<double>(pl, CV_M2L, s)) != hipSuccess) return e;
+  }
+  if (pl->s_bot[0].nseg) {
     // FMM-2: 8 groups of each table, near field over the 12^3 block
-    const long long NPT2 = (1728 + KT - 1) / KT;
-    const long long n_m2p = 8 * NCK * NSLOT * 2 * EL * VPL, n_l2p = 8 * NLT * 2 * 64 * VPL,
-                    n_p2p = 8 * NPT2 * 2 * 64 * VPL;
+    const int groups = pl->dl == 2 ? 8 : 1;
+    const long long NPT = pl->dl == 2 ? (1728 + KT - 1) / KT : kNearK1 / KT;
+    const long long n_m2p = groups * NCK * NSLOT * 2 * EL * VPL, n_l2p = groups * NLT * 2 * 64 * VPL,
+                    n_p2p = groups * NPT * 2 * 64 * VPL;
     if ((e = hipMalloc(&pl->wm2p[X], n_m2p * sizeof(H))) != hipSuccess) return e;
     if ((e = hipMalloc(&pl->wl2p[X], n_l2p * sizeof(H))) != hipSuccess) return e;
     if ((e = hipMalloc(&pl->wl2p2[X], 8 * n_l2p * sizeof(H))) != hipSuccess) return e;
     if ((e = hipMalloc(&pl->wp2p[X], n_p2p * sizeof(H))) != hipSuccess) return e;
-    pl->bytes += (n_m2p + 9 * n_l2p + n_p2p) * sizeof(H);
     const long long cnt = n_m2p + 9 * n_l2p + n_p2p;
-    hipLaunchKernelGGL((k_expand_bottom2<CT>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab2,
-                       (H*)pl->wm2p[X], (H*)pl->wl2p[X], (H*)pl->wl2p2[X], (H*)pl->wp2p[X], NM, NL, pl->ND);
+    pl->bytes += cnt * sizeof(H);
+    if (pl->dl == 2)
+      hipLaunchKernelGGL((k_expand_bottom2<bf16_tag>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab2,
+                         (H*)pl->wm2p[X], (H*)pl->wl2p[X], (H*)pl->wl2p2[X], (H*)pl->wp2p[X], NM, NL, pl->ND);
+    else
+      hipLaunchKernelGGL((k_expand_bottom<bf16_tag>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab,
+                         (H*)pl->wm2p[X], (H*)pl->wl2p[X], (H*)pl->wl2p2[X], (H*)pl->wp2p[X], NM, NL, pl->ND);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (bottom && !pl->wm2p[X]) {
-    const long long n_m2p = NCK * NSLOT * 2 * EL * VPL, n_l2p = NLT * 2 * 64 * VPL, n_p2p = NPT * 2 * 64 * VPL;
-    if ((e = hipMalloc(&pl->wm2p[X], n_m2p * sizeof(H))) != hipSuccess) return e;
-    if ((e = hipMalloc(&pl->wl2p[X], n_l2p * sizeof(H))) != hipSuccess) return e;
-    if ((e = hipMalloc(&pl->wl2p2[X], 8 * n_l2p * sizeof(H))) != hipSuccess) return e;
-    if ((e = hipMalloc(&pl->wp2p[X], n_p2p * sizeof(H))) != hipSuccess) return e;
-    pl->bytes += (n_m2p + 9 * n_l2p + n_p2p) * sizeof(H);
-    const long long cnt = n_m2p + 9 * n_l2p + n_p2p;
-    hipLaunchKernelGGL((k_expand_bottom<CT>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->dtab,
-                       (H*)pl->wm2p[X], (H*)pl->wl2p[X], (H*)pl->wl2p2[X], (H*)pl->wp2p[X], NM, NL, pl->ND);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (m2l && !pl->wm2l[X]) {
-    if ((e = build_conv_table<CT>(pl, CV_M2L, &pl->wm2l[X], s)) != hipSuccess) return e;
-    if ((e = build_tile_table<CT>(pl, CV_M2L, s)) != hipSuccess) return e;
+  if (pl->s_conv[1].nseg) {
+    if ((e = build_conv_table<bf16_tag>(pl, CV_M2L, &pl->wm2l[X], s)) != hipSuccess) return e;
+    if ((e = build_tile_table<bf16_tag>(pl, CV_M2L, s)) != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -1422,8 +1424,6 @@ hipError_t build_fold(fmm_plan* pl, int op, int x, hipStream_t s) {
   return x ? go((float*)pl->fold_w[op][x]) : go((double*)pl->fold_w[op][x]);
 }
 
-// every launch site's compute type: levels k < m2l_low_from and bottoms of
-// fields with F <= coarse_fp64_levels run in FP64
 template <int P>
 hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
   hipLaunchKernelGGL(k_dtab, dim3(blocks_for(343 * 8, 64)), dim3(64), 0, s, pl->dtab, pl->p + 1, pl->ND);
@@ -1433,21 +1433,16 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
     hipLaunchKernelGGL(k_dtab2, dim3(blocks_for(343 * 64, 64)), dim3(64), 0, s, pl->dtab2, pl->p + 1, pl->ND);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const bool m2l64 = pl->s_conv[0].nseg > 0, m2llow = pl->s_conv[1].nseg > 0;
-  const bool bot64 = pl->s_bot[0][0].nseg > 0, botlow = pl->s_bot[1][0].nseg > 0;
-  for (int x = 0; x < 2; ++x)
-  {
+  for (int x = 0; x < 2; ++x) {
     if (pl->s_m2lf[x][0].nseg && (e = build_fold(pl, FO_M2L, x, s)) != hipSuccess) return e;
     if (pl->s_m2pf[x][0].nseg && (e = build_fold(pl, FO_M2P, x, s)) != hipSuccess) return e;
   }
   if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
-    constexpr int cnt = ShiftShape<P>::TABLE;
-    if ((e = hipMalloc(&pl->wshift, cnt * sizeof(double))) != hipSuccess) return e;
-    pl->bytes += cnt * sizeof(double);
-    hipLaunchKernelGGL(k_shift_table<P>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, pl->wshift);
+    constexpr int nshift = ShiftShape<P>::TABLE;
+    if ((e = hipMalloc(&pl->wshift, nshift * sizeof(double))) != hipSuccess) return e;
+    pl->bytes += nshift * sizeof(double);
+    hipLaunchKernelGGL(k_shift_table<P>, dim3(blocks_for(nshift, 256)), dim3(256), 0, s, pl->wshift);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (pl->s_blk[0][0].nseg || pl->s_blk[1][0].nseg) {
     double* G = nullptr;
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
     hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND,
@@ -1471,10 +1466,7 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
     (void)hipFree(G);
     if (e != hipSuccess) return e;
   }
-  if ((e = build_tables_t<double>(pl, bot64, m2l64, s)) != hipSuccess) return e;
-  if (pl->precision == 1) e = build_tables_t<float>(pl, botlow, m2llow, s);
-  if (pl->precision == 2) e = build_tables_t<bf16_tag>(pl, botlow, m2llow, s);
-  return e;
+  return pl->precision == 2 ? build_tables_bf16(pl, s) : hipSuccess;
 }
 
 // Sums the split partial results of each segment of a convolution.
@@ -1533,39 +1525,31 @@ hipError_t launch_l2l_site(fmm_plan* pl, const SegTable& st, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int P, typename CT, typename TI, typename TO>
-hipError_t launch_bottom(fmm_plan* pl, int x, IoArg io, hipStream_t s) {
+template <int P, typename TI, typename TO>
+hipError_t launch_bottom(fmm_plan* pl, IoArg io, hipStream_t s) {
+  using CT = bf16_tag;
   using H = typename Mf<CT>::H;
   constexpr int X = Mf<CT>::IDX;
   // the tuned tile depth, or 8 when 16-deep tiles would leave compute units
-  // idle (few or small fields at this site, e.g. the FP64 bottoms of the
-  // coarse fields of a mixed-precision batch)
+  // idle (few or small fields at this site)
   int z = pl->tune.bz == 8 ? 1 : 0;
-  if (z == 0 && pl->s_bot[x][0].blocks < pl->cus) z = 1;
+  if (z == 0 && pl->s_bot[0].blocks < pl->cus) z = 1;
   if (pl->force_bz) z = pl->force_bz == 8 ? 1 : 0;  // the caller's choice
   if (pl->dl == 2) z = 0;  // FMM-2 launches 8 blocks per tile
-  const SegTable& st = pl->s_bot[x][z];
+  const SegTable& st = pl->s_bot[z];
   if (!st.nseg) return hipSuccess;
   // M2P K chunks: those of the multipole terms kept (nmax)
   const int nck = (pl->NMX + Mf<CT>::KC - 1) / Mf<CT>::KC;
   unsigned int* cnt = pl->stamps ? pl->stamp_cnt : nullptr;
   unsigned long long* done = pl->stamps ? pl->stamp_time + 1 : nullptr;
   StageScope sc(pl, ST_BOTTOM, 1, s);
-  if (pl->dl == 2) {
-    hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 16, 2>), dim3(st.blocks, 8), dim3(bottom_threads<CT>()), 0, s, st.dev,
-                       st.nseg, io, (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X],
-                       (const H*)pl->wp2p[X], pl->dlists, nck, cnt, done);
+  auto go = [&](auto* kernel, dim3 g) {
+    hipLaunchKernelGGL(kernel, g, dim3(BOT_THREADS), 0, s, st.dev, st.nseg, io, (const H*)pl->wm2p[X],
+                       (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X], pl->dlists, nck, cnt, done);
     return hipGetLastError();
-  }
-  if (z == 0)
-    hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 16, 1>), dim3(st.blocks), dim3(bottom_threads<CT>()), 0, s, st.dev, st.nseg, io,
-                       (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X],
-                       pl->dlists, nck, cnt, done);
-  else
-    hipLaunchKernelGGL((k_bottom<P, CT, TI, TO, 8, 1>), dim3(st.blocks), dim3(bottom_threads<CT>()), 0, s, st.dev, st.nseg, io,
-                       (const H*)pl->wm2p[X], (const H*)pl->wl2p[X], (const H*)pl->wl2p2[X], (const H*)pl->wp2p[X],
-                       pl->dlists, nck, cnt, done);
-  return hipGetLastError();
+  };
+  if (pl->dl == 2) return go(k_bottom<P, CT, TI, TO, 16, 2>, dim3(st.blocks, 8));
+  return z == 0 ? go(k_bottom<P, CT, TI, TO, 16, 1>, dim3(st.blocks)) : go(k_bottom<P, CT, TI, TO, 8, 1>, dim3(st.blocks));
 }
 
 // Grid of a launch over T tiles.  A block's K loop is cut where it would take
@@ -1787,9 +1771,9 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   }
   if ((e = launch_fold_site<P, FO_M2L>(pl, s)) != hipSuccess) return e;
   if ((e = launch_fold_site<P, FO_M2P>(pl, s)) != hipSuccess) return e;
-  if ((e = launch_conv<P, double, CV_M2L>(pl, pl->s_conv[0], pl->wm2l[0], s)) != hipSuccess) return e;
-  if ((e = launch_split_reduce(pl, pl->s_red[0], s)) != hipSuccess) return e;
   if constexpr (Mf<CT>::IDX == 2) {
+    if ((e = launch_conv<P, double, CV_M2L>(pl, pl->s_conv[0], pl->wm2l[0], s)) != hipSuccess) return e;
+    if ((e = launch_split_reduce(pl, pl->s_red[0], s)) != hipSuccess) return e;
     if ((e = launch_conv<P, CT, CV_M2L>(pl, pl->s_conv[1], pl->wm2l[Mf<CT>::IDX], s)) != hipSuccess) return e;
     if ((e = launch_split_reduce(pl, pl->s_red[1], s)) != hipSuccess) return e;
   }
@@ -1812,29 +1796,13 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
   if constexpr (std::is_same<CT, float>::value)
     if ((e = launch_block<P, float, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;
   if constexpr (Mf<CT>::IDX == 2)
-    if ((e = launch_bottom<P, CT, TI, TO>(pl, 1, io, s)) != hipSuccess) return e;
+    if ((e = launch_bottom<P, TI, TO>(pl, io, s)) != hipSuccess) return e;
   return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
 // adjoint solve (field 0)
 // ---------------------------------------------------------------------------
-// The transposed M2P, and for FMM-2 the transposed near field, in one
-// compute type.
-template <typename CT>
-hipError_t adjoint_bottom_tables(fmm_plan* pl, hipStream_t s) {
-  constexpr int X = Mf<CT>::IDX;
-  const int op = pl->dl == 2 ? CV_M2PT2 : CV_M2PT;
-  hipError_t e;
-  if ((e = build_tile_table<CT>(pl, op, s)) != hipSuccess) return e;
-  if ((e = build_conv_table<CT>(pl, op, &pl->wt_m2p[X], s)) != hipSuccess) return e;
-  if (pl->dl == 2) {
-    if ((e = build_tile_table<CT>(pl, CV_P2PT2, s)) != hipSuccess) return e;
-    if ((e = build_conv_table<CT>(pl, CV_P2PT2, &pl->wt_p2p[X], s)) != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
 hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
   hipError_t e;
   const int NL = pl->NL;
@@ -1864,25 +1832,26 @@ hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
     hipLaunchKernelGGL(k_adj_coef, dim3(blocks_for(9LL * NL * 32, 256)), dim3(256), 0, s, pl->adj_l2p,
                        pl->adj_l2p2, NL);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // the transposed M2L of target levels k < klow runs in FP64, the others in
-  // the plan's compute type
+  // BF16: the transposed M2L of target levels k < klow runs in FP64
   const int klow = m2l_low_from(pl);
-  const bool lt64 = pl->F >= 3 && klow > 3, ltlow = pl->F >= klow;
-  if (lt64) {
+  if (pl->F >= 3 && klow > 3) {
     if ((e = build_conv_table<double>(pl, CV_M2LT, &pl->wt_m2l[0], s)) != hipSuccess) return e;
     if ((e = build_tile_table<double>(pl, CV_M2LT, s)) != hipSuccess) return e;
   }
-  if (ltlow) {
-    if (pl->precision == 1 && ((e = build_conv_table<float>(pl, CV_M2LT, &pl->wt_m2l[1], s)) != hipSuccess ||
-                               (e = build_tile_table<float>(pl, CV_M2LT, s)) != hipSuccess))
-      return e;
-    if (pl->precision == 2 && ((e = build_conv_table<bf16_tag>(pl, CV_M2LT, &pl->wt_m2l[2], s)) != hipSuccess ||
-                               (e = build_tile_table<bf16_tag>(pl, CV_M2LT, s)) != hipSuccess))
-      return e;
+  using CT = bf16_tag;
+  constexpr int X = Mf<CT>::IDX;
+  if (pl->F >= klow) {
+    if ((e = build_conv_table<CT>(pl, CV_M2LT, &pl->wt_m2l[X], s)) != hipSuccess) return e;
+    if ((e = build_tile_table<CT>(pl, CV_M2LT, s)) != hipSuccess) return e;
   }
-  if (!bottom_low(pl, pl->F)) return adjoint_bottom_tables<double>(pl, s);
-  if (pl->precision == 1) return adjoint_bottom_tables<float>(pl, s);
-  return adjoint_bottom_tables<bf16_tag>(pl, s);
+  const int op = pl->dl == 2 ? CV_M2PT2 : CV_M2PT;
+  if ((e = build_tile_table<CT>(pl, op, s)) != hipSuccess) return e;
+  if ((e = build_conv_table<CT>(pl, op, &pl->wt_m2p[X], s)) != hipSuccess) return e;
+  if (pl->dl == 2) {
+    if ((e = build_tile_table<CT>(pl, CV_P2PT2, s)) != hipSuccess) return e;
+    if ((e = build_conv_table<CT>(pl, CV_P2PT2, &pl->wt_p2p[X], s)) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // The backward pass of a field on the folded kernels (field 0).
@@ -1947,13 +1916,10 @@ hipError_t backward_fold(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI*
   return go(std::integral_constant<int, 1>{});
 }
 
-template <int P, typename CT, typename TI, typename TO>
-hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TO* drho, hipStream_t s) {
-  if (block_field(pl, pl->F))
-    return pl->dl == 2 ? backward_fold<P, CT, TI, 2>(pl, w, dphi, dg, drho, s)
-                       : backward_fold<P, CT, TI, 1>(pl, w, dphi, dg, drho, s);
-  if constexpr (Mf<CT>::IDX != 2) return hipErrorInvalidValue;  // FP64 and FP32 fields are all folded
-  else {
+// The backward pass of a BF16 field (field 0).
+template <int P, typename TI, typename TO>
+hipError_t backward_bf16(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TO* drho, hipStream_t s) {
+  using CT = bf16_tag;
   constexpr int NL = nterms(P);
   const int n = pl->n, F = pl->F, dl = pl->dl, nF = n >> dl;
   const double dx = pl->dx;
@@ -1986,22 +1952,16 @@ hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* d
     }
     // transposed M2L of every target level (sources k - 1 receive)
     if ((e = launch_conv<P, double, CV_M2LT>(pl, w.m2lt[0], pl->wt_m2l[0], s)) != hipSuccess) return e;
-    if constexpr (Mf<CT>::IDX == 2)
-      if ((e = launch_conv<P, CT, CV_M2LT>(pl, w.m2lt[1], pl->wt_m2l[Mf<CT>::IDX], s)) != hipSuccess) return e;
+    if ((e = launch_conv<P, CT, CV_M2LT>(pl, w.m2lt[1], pl->wt_m2l[Mf<CT>::IDX], s)) != hipSuccess) return e;
     if ((e = launch_split_reduce(pl, w.m2lt_red, s)) != hipSuccess) return e;
   }
   // transposed M2P at the finest level (and for FMM-2 the transposed near
   // field, on the same pattern over the 27 adjacent cells)
-  const bool low = bottom_low(pl, F);
   if (dl == 2) {
-    e = low ? launch_conv<P, CT, CV_M2PT2>(pl, w.m2pt, pl->wt_m2p[Mf<CT>::IDX], s)
-            : launch_conv<P, double, CV_M2PT2>(pl, w.m2pt, pl->wt_m2p[0], s);
-    if (e == hipSuccess)
-      e = low ? launch_conv<P, CT, CV_P2PT2>(pl, w.p2pt, pl->wt_p2p[Mf<CT>::IDX], s)
-              : launch_conv<P, double, CV_P2PT2>(pl, w.p2pt, pl->wt_p2p[0], s);
+    e = launch_conv<P, CT, CV_M2PT2>(pl, w.m2pt, pl->wt_m2p[Mf<CT>::IDX], s);
+    if (e == hipSuccess) e = launch_conv<P, CT, CV_P2PT2>(pl, w.p2pt, pl->wt_p2p[Mf<CT>::IDX], s);
   } else {
-    e = low ? launch_conv<P, CT, CV_M2PT>(pl, w.m2pt, pl->wt_m2p[Mf<CT>::IDX], s)
-            : launch_conv<P, double, CV_M2PT>(pl, w.m2pt, pl->wt_m2p[0], s);
+    e = launch_conv<P, CT, CV_M2PT>(pl, w.m2pt, pl->wt_m2p[Mf<CT>::IDX], s);
   }
   if (e != hipSuccess) return e;
   // transposed M2M chain, coarse to fine
@@ -2024,6 +1984,14 @@ hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* d
                      pl->NMX);
   return hipGetLastError();
   }
+
+template <int P, typename CT, typename TI, typename TO>
+hipError_t backward_ct(fmm_plan* pl, const AdjWs& w, const TI* dphi, const TI* dg, TO* drho, hipStream_t s) {
+  if (block_field(pl, pl->F))
+    return pl->dl == 2 ? backward_fold<P, CT, TI, 2>(pl, w, dphi, dg, drho, s)
+                       : backward_fold<P, CT, TI, 1>(pl, w, dphi, dg, drho, s);
+  if constexpr (Mf<CT>::IDX == 2) return backward_bf16<P>(pl, w, dphi, dg, drho, s);
+  return hipErrorInvalidValue;  // FP64 and FP32 fields are all folded
 }
 
 template <typename T>

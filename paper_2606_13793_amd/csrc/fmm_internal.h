@@ -372,7 +372,7 @@ struct fmm_plan {
   double* wshift = nullptr;         // folded fields: fragments of the shifts between levels
   fmm::SegTable s_conv[2];          // forward M2L: [0] FP64 levels, [1] low-precision levels
   fmm::SegTable s_l2l[16];          // L2L into level k (index k)
-  fmm::SegTable s_bot[2][2];        // bottom [FP64 | low][tile depth 16 | 8]
+  fmm::SegTable s_bot[2];           // BF16 bottom, tile depth 16 | 8
   fmm::SegTable s_blk[2][3];        // finest blocks [FP64 | low][1, 2 or 4 rows of blocks per tile]
   long long blk_rows[2] = {0, 0};   // their row tiles of 16 blocks
   fmm::SegTable s_m2lf[2][3];       // folded M2L [FP64 | low][1, 2 or 4 rows of octs per tile]

@@ -57,14 +57,9 @@ struct EntryGroup {
 // 16: tile m holds x = m / TPX, y = YPT (m % TPX) + i / BZ2, z = i % BZ2.
 constexpr int BX = 8, BY = 8;
 constexpr int HX = BX + 6, HY = BY + 6;
-// Waves per parity class of a bottom block: with FP64 and BF16 operands two
-// waves share a class's row tiles (1024-thread blocks), so a CU holds 16
-// waves to hide the operand latencies; FP32 keeps one and fits two 512-thread
-// blocks per CU instead.
-template <typename CT>
-constexpr int bottom_wpr() { return Mf<CT>::IDX == 1 ? 1 : 2; }
-template <typename CT>
-constexpr int bottom_threads() { return 512 * bottom_wpr<CT>(); }
+// Threads of a bottom block: two waves share a parity class's row tiles, so a CU
+// holds 16 waves to hide the operand latencies.
+constexpr int BOT_WPR = 2, BOT_THREADS = 512 * BOT_WPR;
 
 // K extent of the near-field block of FMM-1: the 6^3 unigrid cells around a
 // row's level-F cell, z padded to 8 (K step k: z run (w0, w1) = k / 8 of the
@@ -288,15 +283,12 @@ __device__ __forceinline__ void block_fill(int count, Val&& val, Put&& put) {
   }
 }
 
-// minimum waves per SIMD (the second launch bound): one 1024-thread block or
-// two 512-thread FP32 blocks per CU (4 waves per SIMD, <= 128 registers)
-template <typename CT>
-constexpr int bottom_min_waves() { return 4; }
-
+// The bottom of BF16 plans (CT = bf16_tag; FP64 and FP32 fields run k_block).
+// One block per CU: 4 waves per SIMD, <= 128 registers.
 // stamp_cnt / stamp_done (or null): per field, the finished blocks and the
 // device wall-clock time at which its last block finished.
 template <int P, typename CT, typename TI, typename TO, int BZ, int DL>
-__global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void k_bottom(
+__global__ __launch_bounds__(BOT_THREADS, 4) void k_bottom(
     const Seg* __restrict__ segs, int nseg, IoArg io, const typename Mf<CT>::H* __restrict__ Wm2p,
     const typename Mf<CT>::H* __restrict__ Wl2p, const typename Mf<CT>::H* __restrict__ Wl2p2,
     const typename Mf<CT>::H* __restrict__ Wp2p, const int* __restrict__ dlists, int nck,
@@ -308,36 +300,25 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
   using S = BotShape<BZ>;
   constexpr int BZ2 = S::BZ2, BOT_MT = S::MT, YPT = S::YPT, TPX = S::TPX;
   constexpr int KC = M::KC, OPM = M::OPM, VPL = M::VPL, EL = 64 / OPM;
-  constexpr int NM = nterms(P), NC4 = (NM + 3) / 4;
-  constexpr int NL = nterms(P);
+  static_assert(OPM == 2, "two offsets per product");
+  constexpr int NM = nterms(P), NL = nterms(P);
   constexpr int NB = 3 << DL, NNEAR = NB * NB * NB;  // near-field block: 6^3 or 12^3 unigrid cells
   constexpr int KT = 4 * VPL, NLT = (NL + KT - 1) / KT;
   constexpr int NPT = DL == 1 ? kNearK1 / KT : (NNEAR + KT - 1) / KT;
   constexpr int NCK = (NM + KC - 1) / KC;
   constexpr int NGRP = (NLIST + OPM - 1) / OPM;
-  constexpr int THREADS = bottom_threads<CT>(), MTW = BOT_MT / bottom_wpr<CT>();  // row tiles per wave
-  // mixed precision: the level-F multipoles are staged from their typed copy
-  constexpr bool TYPED = M::IDX != 0;
+  constexpr int THREADS = BOT_THREADS, MTW = BOT_MT / BOT_WPR;  // row tiles per wave
   using HL = Halo<CT, BZ>;
   __shared__ __attribute__((aligned(16))) H halo[HL::SIZE];
-  // the interaction lists of the 8 parity classes (one offset per MFMA), or
-  // the lanes' operand offsets of each offset pair (two per MFMA)
-  __shared__ int slist[OPM == 1 ? 8 * NLIST_PAD : 1];
-  __shared__ int2 spair[OPM == 2 ? 8 * (NGRP + 1) * 2 : 1];
+  // the lanes' operand offsets of each offset pair, by parity class
+  __shared__ int2 spair[8 * (NGRP + 1) * 2];
   // column of local term bt of child q in the locals' M2L layout, for the
   // tail's L2P reads (-1 past the last term)
   __shared__ int scol[8 * NLT * KT];
   // blocks walk the (order-independent) offset sum from different starting
-  // points: the lists are stored rotated (one offset per MFMA; the null entry
-  // past the end), or the pairs are taken from a rotated index (two)
-  const int rot = (int)((blockIdx.x * 37u) % (OPM == 1 ? NLIST : NGRP));
-  if constexpr (OPM == 1)
-    for (int t = threadIdx.x; t < 8 * NLIST_PAD; t += THREADS) {
-      const int cls = t / NLIST_PAD, j = t - cls * NLIST_PAD, jr = j + rot;
-      slist[t] = dlists[cls * NLIST_PAD + (j < NLIST ? (jr < NLIST ? jr : jr - NLIST) : NLIST)];
-    }
-  else
-    build_pair_table<HL>(spair, dlists, NGRP + 1, 2 * EL * VPL, THREADS);
+  // points: the pairs are taken from a rotated index
+  const int rot = (int)((blockIdx.x * 37u) % NGRP);
+  build_pair_table<HL>(spair, dlists, NGRP + 1, 2 * EL * VPL, THREADS);
   for (int t = threadIdx.x; t < 8 * NLT * KT; t += THREADS) {
     const int q = t / (NLT * KT), bt = t - q * (NLT * KT);
     const int ex = c_mi_exp[bt < NL ? bt : 0];
@@ -353,7 +334,6 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     Wl2p2 += (size_t)grp * 8 * NLT * 2 * 64 * VPL;
     Wp2p += (size_t)grp * NPT * 2 * 64 * VPL;
   }
-  const double* __restrict__ Mh = sg.a;
   const double* __restrict__ Lf = sg.c;
   const double* __restrict__ Lpar = sg.d;
   const TI* __restrict__ rho = io_rho<TI>(io, sg.field);
@@ -378,8 +358,7 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
   // per-lane part of the operand addresses: row (gyo, gz), the lane's K slice
   // and the wave's first row tile (MTW is a multiple of TPX, so the tile
   // offset splits into that of m0 and that of the tile within the wave)
-  const H* hlane = halo + 2 * gyo * HL::YS + gz * KC + lr.tic + tile_part<HL, TPX, YPT>(m0);
-  // swizzled K halves (BF16): the lane's base for swizzle bit 0 and bit 1 of
+  // swizzled K halves: the lane's base for swizzle bit 0 and bit 1 of
   // the fragment's first row (its own row is gyo rows of two further on)
   const int kh = lr.tic >> 3;
   const H* hsw0 = halo + 2 * gyo * HL::YS + gz * KC + 8 * (kh ^ (gyo & 1)) + tile_part<HL, TPX, YPT>(m0);
@@ -388,66 +367,36 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
   Acc acc[MTW][2];
 #pragma unroll
   for (int m = 0; m < MTW; ++m) acc[m][0] = acc[m][1] = Acc{0, 0, 0, 0};
-  const int* dl = slist + r * NLIST_PAD;  // visible after the first chunk's barrier
-  const int2* dp = spair + r * (NGRP + 1) * 2 + lr.sel;
-  auto entry = [&](int pos) { return dl[pos]; };  // pos < NLIST_PAD
-  // the same entry as a scalar load from the unrotated global list (pos
-  // wave-uniform): its value lands in a scalar register, so it ties up no
-  // vector register that a pending operand load could also write
-  const int* __restrict__ dg = dlists + r * NLIST_PAD;
-  auto entry_s = [&](int pos) {
-    const int jr = pos + rot;
-    return dg[pos < NLIST ? (jr < NLIST ? jr : jr - NLIST) : NLIST];
-  };
+  const int2* dp = spair + r * (NGRP + 1) * 2 + lr.sel;  // visible after the first chunk's barrier
   TypedStage<CT, BZ, THREADS> ts;
-  if constexpr (TYPED) ts.plan(nFp, tx0, ty0, tz0);
+  ts.plan(nFp, tx0, ty0, tz0);
 
   // the M2P K chunks: nck <= ceil(NM / KC), fewer when the multipoles are
   // truncated at nmax < p (the chunks past it hold only zero terms)
   for (int c = 0; c < nck; ++c) {
     __syncthreads();  // previous chunk fully consumed
-    if constexpr (TYPED)
-      ts.run(halo, (const H*)sg.t, ncellp, c);
-    else
-      stage_halo<CT, BZ, THREADS>(halo, Mh, NC4, ncellp, nFp, tx0, ty0, tz0, c);
+    ts.run(halo, (const H*)sg.t, ncellp, c);
     __syncthreads();
     const H* wc = Wm2p + (size_t)c * NSLOT * 2 * EL * VPL + lr.tl * VPL;
-    auto bload = [&](EntryGroup g, int t) {
-      if constexpr (OPM == 1)
-        return *reinterpret_cast<const AF*>(wc + ((size_t)dl_dd(g.e) * 2 + t) * EL * VPL);
-      else
-        return *reinterpret_cast<const AF*>(wc + g.boff + t * EL * VPL);
-    };
+    auto bload = [&](EntryGroup g, int t) { return *reinterpret_cast<const AF*>(wc + g.boff + t * EL * VPL); };
     // A fragments of offset group j: source halo cell of row (gx, gy, gz) is
     // 3 + 2 g + r - d.  Three register slots for the list entries, the B
     // fragments and the A fragments of groups j, j + 1, j + 2 (the loop is
     // unrolled by three, so no slot is copied): B is loaded two groups
     // ahead, A one group ahead, while the current group's products run.
     auto aload = [&](EntryGroup g, AF (&a)[MTW]) {
-      const H* base;
-      if constexpr (OPM == 1)
-        base = hlane + HL::offset_part(r0, r1, r2, dl_d0(g.e), dl_d1(g.e), dl_d2(g.e));
-      else if constexpr (HL::SWZ)
-        base = ((g.aoff & 1) ? hsw1 : hsw0) + (g.aoff & ~1);
-      else
-        base = hlane + g.aoff;
+      const H* base = ((g.aoff & 1) ? hsw1 : hsw0) + (g.aoff & ~1);
 #pragma unroll
       for (int m = 0; m < MTW; ++m)
         a[m] = *reinterpret_cast<const AF*>(base + tile_part<HL, TPX, YPT>(m));
     };
     auto group = [&](int j) {
       EntryGroup g;
-      if constexpr (OPM == 1) {
-        // FP32 keeps the entry in LDS (measured: its loop runs faster so,
-        // and without the scheduling fences below)
-        g.e = __builtin_amdgcn_readfirstlane(M::IDX == 1 ? entry(j) : entry_s(j));
-      } else {
-        const int j0 = j + rot;  // wave-uniform; past the groups, the null pair
-        const int jr = j < NGRP ? (j0 < NGRP ? j0 : j0 - NGRP) : NGRP;
-        const int2 v = dp[2 * jr];
-        g.aoff = v.x;
-        g.boff = v.y;
-      }
+      const int j0 = j + rot;  // wave-uniform; past the groups, the null pair
+      const int jr = j < NGRP ? (j0 < NGRP ? j0 : j0 - NGRP) : NGRP;
+      const int2 v = dp[2 * jr];
+      g.aoff = v.x;
+      g.boff = v.y;
       return g;
     };
     EntryGroup es[3];
@@ -461,15 +410,8 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     aload(es[0], as[0]);
     // (the list entry of a group is read three groups ahead and used one
     // group later, so the wait for it, which also covers the LDS reads in
-    // flight, finds only reads at least one group old.  FP64, BF16: a scalar
-    // load; FP32: an LDS read kept in a vector register until its use)
-    constexpr bool F32 = M::IDX == 1;
-    EntryGroup ahead{};
-    int raw = 0;
-    if constexpr (F32)
-      raw = entry(2 < NGRP ? 2 : NGRP - 1);
-    else
-      ahead = group(2);
+    // flight, finds only reads at least one group old)
+    EntryGroup ahead = group(2);
     // (the body is unrolled by three by hand; unrolling the loop itself would
     // hoist every group's table address out of the chunk loop)
     // whole unrolled iterations, the last padded with null groups (zero B
@@ -481,31 +423,20 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
 #pragma unroll
       for (int u = 0; u < 3; ++u) {
         const int jj = j + u, cur = u, nx = (u + 1) % 3, nn = (u + 2) % 3;
-        // (FP32, measured faster so, keeps a bounds test and the last real
-        // group as the prefetch past the end; for the others both are
-        // compile-time true)
-        if (!F32 || jj < NGRP) {
-          if constexpr (F32)
-            es[nn].e = __builtin_amdgcn_readfirstlane(raw);
-          else
-            es[nn] = ahead;
-          bs[nn][0] = bload(es[nn], 0);
-          bs[nn][1] = bload(es[nn], 1);
-          if constexpr (F32)
-            raw = entry(jj + 3 < NGRP ? jj + 3 : NGRP - 1);
-          else
-            ahead = group(jj + 3);
-          aload(es[nx], as[nx]);
-          // (keep the loads ahead of the products: the scheduler would move
-          // them next to their uses and expose their latency)
-          if constexpr (!F32) __builtin_amdgcn_sched_barrier(0);
+        es[nn] = ahead;
+        bs[nn][0] = bload(es[nn], 0);
+        bs[nn][1] = bload(es[nn], 1);
+        ahead = group(jj + 3);
+        aload(es[nx], as[nx]);
+        // (keep the loads ahead of the products: the scheduler would move
+        // them next to their uses and expose their latency)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int m = 0; m < MTW; ++m) {
-            acc[m][0] = M::op(as[cur][m], bs[cur][0], acc[m][0]);
-            acc[m][1] = M::op(as[cur][m], bs[cur][1], acc[m][1]);
-          }
-          if constexpr (!F32) __builtin_amdgcn_sched_barrier(0);
+        for (int m = 0; m < MTW; ++m) {
+          acc[m][0] = M::op(as[cur][m], bs[cur][0], acc[m][0]);
+          acc[m][1] = M::op(as[cur][m], bs[cur][1], acc[m][1]);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -523,7 +454,7 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
   // loaded once per step.
   constexpr int TC = BX * BY * BZ, TP = TC / 8;  // the tile's level-F cells, and their parents
   // loads in flight per thread while filling LDS (as the registers allow)
-  constexpr int FILLB = M::IDX == 0 ? 2 : 4;
+  constexpr int FILLB = 4;
   // tile-local index of the level-F cell of the lane's row in tile m, and of its parent
   auto lcell = [&](int m) { return ((2 * (m / TPX) + r0) * BY + 2 * (YPT * (m % TPX) + gyo) + r1) * BZ + 2 * gz + r2; };
   auto lpar = [&](int m) { return ((m / TPX) * (BY / 2) + YPT * (m % TPX) + gyo) * (BZ / 2) + gz; };
@@ -532,8 +463,7 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     // terms per pass (chunks of KT): the own and parent operands of TC + TP
     // cells fit the halo area; row stride KPS keeps BF16 rows 16-byte aligned
     // and spreads the rows of a fragment over the LDS banks
-    constexpr int CPP = M::IDX == 2 ? 1 : 3, KP = CPP * KT, KPS = M::IDX == 2 ? 40 : 13;
-
+    constexpr int CPP = 1, KP = CPP * KT, KPS = 40;
     static_assert((TC + TP) * KPS <= HL::SIZE, "tail operands exceed the halo area");
     H* const own = halo;
     H* const par = halo + TC * KPS;
@@ -545,12 +475,11 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     for (int c0 = 0; c0 < NLT; c0 += CPP) {
       __syncthreads();  // the area's previous contents fully consumed
       const int k0 = c0 * KT;
-      // BF16, FP32: thread t fills term k0 + t % KP of every CPR-th cell from
-      // t / KP (the lanes of a wave read consecutive columns of a row; the
-      // term's column in the M2L layout is cb + q nd for a cell that is child
-      // q of its parent), FILLB loads in flight.  FP64, whose accumulators
-      // leave fewer registers, fills one element per thread and step.
-      if constexpr (M::IDX != 0) {
+      // thread t fills term k0 + t % KP of every CPR-th cell from t / KP (the
+      // lanes of a wave read consecutive columns of a row; the term's column in
+      // the M2L layout is cb + q nd for a cell that is child q of its parent),
+      // FILLB loads in flight
+      {
         constexpr int CPR = THREADS / KP;
         const int kk = threadIdx.x % KP, cf = threadIdx.x / KP, bt = k0 + kk;
         const bool tok = cf < CPR && bt < NL;
@@ -598,36 +527,6 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
             const int pc = cf + (j + u) * CPR;
             if (cf < CPR && pc < TP) par[pc * KPS + kk] = v[u];
           }
-        }
-      } else {
-        const auto gLf = gmem(Lf);
-        const auto gLt = gmem(Lt);
-        const auto gLp = gmem(Lpar);
-        for (int e = threadIdx.x; e < TC * KP; e += THREADS) {
-          const int cell = e / KP, kk = e - cell * KP, bt = k0 + kk;
-          const int g0 = tx0 + cell / (BY * BZ), g1 = ty0 + (cell / BZ) % BY, g2 = tz0 + cell % BZ;
-          H v = H(0);
-          if (bt < NL && g0 < nF && g1 < nF && g2 < nF) {
-            const int q = ((g0 & 1) << 2) | ((g1 & 1) << 1) | (g2 & 1);
-            const long long x = (((long long)(g0 >> 1) * nP + (g1 >> 1)) * nP + (g2 >> 1)) * RS + scol[q * (NLT * KT) + bt];
-            if constexpr (M::IDX == 0)
-              v = gLf[x];
-            else
-              v = Lt ? gLt[x] : static_cast<H>(gLf[x]);
-          }
-          own[cell * KPS + kk] = v;
-        }
-        // (no parent level above F = 3: zero operands, so the products need no branch)
-        for (int e = threadIdx.x; e < TP * KP; e += THREADS) {
-          const int pc = e / KP, kk = e - pc * KP, bt = k0 + kk;
-          const int g0 = (tx0 >> 1) + pc / ((BY / 2) * (BZ / 2)), g1 = (ty0 >> 1) + (pc / (BZ / 2)) % (BY / 2),
-                    g2 = (tz0 >> 1) + pc % (BZ / 2);
-          double v = 0.0;
-          if (Lpar && bt < NL && g0 < nP && g1 < nP && g2 < nP) {
-            const int q = ((g0 & 1) << 2) | ((g1 & 1) << 1) | (g2 & 1);
-            v = gLp[(((long long)(g0 >> 1) * nPP + (g1 >> 1)) * nPP + (g2 >> 1)) * RS + scol[q * (NLT * KT) + bt]];
-          }
-          par[pc * KPS + kk] = static_cast<H>(v);
         }
       }
       __syncthreads();
@@ -680,43 +579,28 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
       return (2 * (2 * (m / TPX) + r0) * UY + 2 * (2 * (YPT * (m % TPX) + gyo) + r1)) * UZ + 2 * (2 * gz + r2);
     };
     AF bn[2], bx[2];
-    if constexpr (M::IDX != 0) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) bn[t] = *reinterpret_cast<const AF*>(Wp2p + ((size_t)t * 64 + lane) * VPL);
-    }
+    for (int t = 0; t < 2; ++t) bn[t] = *reinterpret_cast<const AF*>(Wp2p + ((size_t)t * 64 + lane) * VPL);
 #pragma unroll 1
     for (int c = 0; c < NPT; ++c) {
-      // B of step c; FP32 and BF16 also load step c + 1's ahead (FP64 has no
-      // registers for it)
-      if constexpr (M::IDX == 0) {
+      // step c + 1's B is loaded ahead
+      const int cn = c + 1 < NPT ? c + 1 : c;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) bn[t] = *reinterpret_cast<const AF*>(Wp2p + ((size_t)(c * 2 + t) * 64 + lane) * VPL);
-      } else {
-        const int cn = c + 1 < NPT ? c + 1 : c;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) bx[t] = *reinterpret_cast<const AF*>(Wp2p + ((size_t)(cn * 2 + t) * 64 + lane) * VPL);
-      }
+      for (int t = 0; t < 2; ++t) bx[t] = *reinterpret_cast<const AF*>(Wp2p + ((size_t)(cn * 2 + t) * 64 + lane) * VPL);
       const int k = KT * c + VPL * kq, run = k >> 3;
       const int koff = (run / 6) * (UY * UZ) + (run % 6) * UZ + (k & 7);
       static_for<MTW>([&](auto mi) {
         constexpr int mw = decltype(mi)::value;
         const H* src = ub + ubase(m0 + mw) + koff;
-        AF a;
-        if constexpr (VPL == 8) {
-          // 8 consecutive BF16 from an even element offset: four 4-byte reads
-          const unsigned int* s32 = reinterpret_cast<const unsigned int*>(src);
-          const u32x4 w = {s32[0], s32[1], s32[2], s32[3]};
-          a = __builtin_bit_cast(AF, w);
-        } else {
-          a = *src;
-        }
+        // 8 consecutive BF16 from an even element offset: four 4-byte reads
+        const unsigned int* s32 = reinterpret_cast<const unsigned int*>(src);
+        const u32x4 w = {s32[0], s32[1], s32[2], s32[3]};
+        const AF a = __builtin_bit_cast(AF, w);
         acc[mw][0] = M::op(a, bn[0], acc[mw][0]);
         acc[mw][1] = M::op(a, bn[1], acc[mw][1]);
       });
-      if constexpr (M::IDX != 0) {
-        bn[0] = bx[0];
-        bn[1] = bx[1];
-      }
+      bn[0] = bx[0];
+      bn[1] = bx[1];
     }
   }
   } else {
@@ -734,7 +618,7 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     // L2P K blocks of row tile m: the M2L part of the own local (stored with
     // the parent P'), then the parent level's full local; UL chunks at a time,
     // their operand loads issued together
-    constexpr int UL = M::IDX == 1 ? 2 : 1;
+    constexpr int UL = 1;
     auto tail = [&](int m, Acc (&am)[2]) __attribute__((always_inline)) {
       int c0, c1, c2;
       cell_of(m, c0, c1, c2);
@@ -786,9 +670,8 @@ __global__ __launch_bounds__(bottom_threads<CT>(), bottom_min_waves<CT>()) void 
     // FMM-2's near field, 12^3 sources per row: the B fragments of a K step
     // serve every row tile of the wave, so they are loaded once per step
     // instead of once per row tile.  Row cells packed as c0 << 16 | c1 << 8 | c2.
-    // K steps in flight, sized to the registers left: FP64 3; FP32 (8 row
-    // tiles per wave) and BF16 (8 densities per lane and tile) 1
-    constexpr int UN2 = M::IDX == 0 ? 3 : 1;
+    // (one K step in flight: 8 densities per lane and tile)
+    constexpr int UN2 = 1;
     int cpk[MTW];
 #pragma unroll
     for (int mw = 0; mw < MTW; ++mw) {
@@ -1151,24 +1034,17 @@ __global__ __launch_bounds__(M2L_THREADS, 1) void k_conv(const Seg* __restrict__
   for (int m = 0; m < CMT; ++m)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[m][t] = Acc{0, 0, 0, 0};
-  // FP64 transposes: from K chunk nar(t) on, column tile t's B entries are
-  // zero outside its first 4 columns, so those chunks run the tile as
-  // 4-column products (v_mfma_f64_4x4x4f64, four 4 x 4 blocks over the 16
-  // rows, a quarter of the 16-column product's work) into acc4, added to the
-  // tile at the end.
-  //  - transposed M2L (one tile per block): |a| + |b| <= p with |b| large;
-  //    the narrow chunks are a suffix of the tile's chunks (NARROW_C);
-  //  - transposed M2Ps: the last tile, past the last multipole term, is
-  //    narrow in every chunk; its group runs the narrow form throughout
-  //    (NARROW_G, when the group's tiles have equal chunk counts).
-  constexpr bool NARROW_C = M::IDX == 0 && OP == CV_M2LT && NT == 1;
-  constexpr bool NARROW_G = M::IDX == 0 && (OP == CV_M2PT || OP == CV_M2PT2);
+  // FP64 transposed M2L (one tile per block): from K chunk nar(t) on, column
+  // tile t's B entries are zero outside its first 4 columns (|a| + |b| <= p with
+  // |b| large), so those chunks run the tile as 4-column products
+  // (v_mfma_f64_4x4x4f64, four 4 x 4 blocks over the 16 rows, a quarter of the
+  // 16-column product's work) into acc4, added to the tile at the end.
+  constexpr bool NARROW = M::IDX == 0 && OP == CV_M2LT && NT == 1;
   const int* ntab = reinterpret_cast<const int*>(tiles) + 2 * (NTILES + 16);
-  const int nar = NARROW_C ? ntab[T0] : 1 << 30;
-  const bool gnar = NARROW_G && T0 + NT - 1 < NTILES && vt[0] > 0 && vt[NT - 1] == vt[0] && ntab[T0 + NT - 1] == 0;
-  double acc4[NARROW_C || NARROW_G ? CMT : 1];
+  const int nar = NARROW ? ntab[T0] : 1 << 30;
+  double acc4[NARROW ? CMT : 1];
 #pragma unroll
-  for (int m = 0; m < (NARROW_C || NARROW_G ? CMT : 1); ++m) acc4[m] = 0.0;
+  for (int m = 0; m < (NARROW ? CMT : 1); ++m) acc4[m] = 0.0;
 
   const int* dl = slist + r * NLIST_PAD;  // visible after the first chunk's barrier
   const int2* dp = spair + r * (NGRP + 1) * 2 + lr.sel;
@@ -1305,7 +1181,7 @@ __global__ __launch_bounds__(M2L_THREADS, 1) void k_conv(const Seg* __restrict__
         else
           stage_halo<CT, CZ, M2L_THREADS>(halo, src, NC4, ncellp, nsp, tx0, ty0, tz0, c);
         __syncthreads();
-        if constexpr (NARROW_C) {
+        if constexpr (NARROW) {
           if (c >= nar)
             offsets(pk, nac, c, std::true_type{});
           else
@@ -1321,16 +1197,11 @@ __global__ __launch_bounds__(M2L_THREADS, 1) void k_conv(const Seg* __restrict__
       chunks(std::true_type{}, std::false_type{});
     else
       chunks(std::false_type{}, std::false_type{});
-  } else if constexpr (NARROW_G) {
-    if (gnar)
-      chunks(std::false_type{}, std::true_type{});
-    else
-      chunks(std::false_type{}, std::false_type{});
   } else {
     chunks(std::false_type{}, std::false_type{});
   }
-  if constexpr (NARROW_C || NARROW_G) {
-    const int tn = NARROW_C ? (nar < vt[0] ? 0 : -1) : (gnar ? NT - 1 : -1);
+  if constexpr (NARROW) {
+    const int tn = nar < vt[0] ? 0 : -1;
     // narrow output C_b[i][j] (row 4 b + i, column j) sits in lane 16 i + 4 b + j;
     // the 16-column tile keeps row 4 v + kq, column i in element v of lane 16 kq + i
 #pragma unroll
