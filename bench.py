@@ -8,8 +8,9 @@ with the density already resident in HBM.
 
 Prints ONE JSON line on stdout; progress goes to stderr.
   value         grid cells per second (n^3 x steps / timed seconds)
-  roofline      the dominant kernel (M2P) against the FP64 matrix-core peak,
-                from HIP events recorded on the solve's stream
+  roofline      the dominant kernel (M2L; BF16: M2P) against the matrix-core
+                peak, from HIP events recorded on the solve's stream; the
+                flops are those of the products it executes
   cpu_baseline  the FP64 CPU oracle on this host, on a bounded sample (full
                 upward pass + downward pass for a slab of cells), scaled to
                 cells per second of a full solve
@@ -31,12 +32,12 @@ PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0}
 HBM_PEAK_GBS = 8000.0
 
 
-PROFILE = os.path.join(ROOT, "profiles", "k_bottom_256cubed_p6_fp64.md")
-KERNEL_SOURCES = ["fmm_impl.h", "fmm_mfma.h", "fmm_internal.h", "fmm_types.h"]
+PROFILE = os.path.join(ROOT, "profiles", "k_m2lf_256cubed_p6_fp64.md")
+KERNEL_SOURCES = ["fmm_impl.h", "fmm_fold.h", "fmm_harmonic.h", "fmm_internal.h", "fmm_types.h"]
 
 
 def profiled_traffic(n: int, p: int, prec: str, delta_l: int = 1):
-    """HBM bytes per launch of the bottom kernel from the committed rocprofv3
+    """HBM bytes per launch of the M2L kernel from the committed rocprofv3
     byte-counter summary, or None when it does not describe the current
     kernel sources or this workload."""
     import hashlib
@@ -153,7 +154,7 @@ def run_large(fi, fmm, costs, n: int = 512, p: int = 6) -> dict:
         ps = phi.reshape(-1)[idx].double().cpu().numpy()
         gs = g.reshape(3, -1)[:, idx].double().cpu().numpy()
         rec = {"ms_per_solve": ms, "cells_per_s": N / (ms * 1e-3),
-               "useful_tflops": costs.solve_flops(n, p)["total"] / (ms * 1e-3) / 1e12}
+               "tflops": (costs.solve_flops if prec == "bf16" else costs.folded_flops)(n, p)["total"] / (ms * 1e-3) / 1e12}
         if prec == "fp64":
             ref = (ps, gs)
         else:
@@ -319,7 +320,7 @@ def run_extras(args, rho64, fi, fmm, costs,
             phi = torch.empty((n, n, n), dtype=torch.float64, device="cuda")
             g = torch.empty((3, n, n, n), dtype=torch.float64, device="cuda")
             ms = _event_ms(lambda: plan.solve_into(rho64, phi, g), 5, 2)
-            # the bottom kernel's own time (HIP events per stage) against its useful flops
+            # the bottom stage's own time (HIP events per stage) against the flops it executes
             plan.profile(True)
             plan.profile_read()
             for _ in range(5):
@@ -327,7 +328,7 @@ def run_extras(args, rho64, fi, fmm, costs,
             torch.cuda.synchronize()
             bot_ms = plan.profile_read()["bottom"][0] / 5
             plan.profile(False)
-            bot_tf = costs.solve_flops(n, q, nm, delta_l=2)["bottom"] / (bot_ms * 1e-3) / 1e12
+            bot_tf = costs.folded_flops(n, q, nm, delta_l=2)["bottom"] / (bot_ms * 1e-3) / 1e12
             ps, _ = sampled(plan, rho64)
             key = f"p{q}" + ("" if nm is None else f"_nmax{nm}")
             fmm2[key] = {"ms_per_solve": ms, "cells_per_s": N / (ms * 1e-3), "phi_err_vs_direct": _rel(ps, phi_d),
@@ -485,11 +486,11 @@ def run_extras(args, rho64, fi, fmm, costs,
         singles = [fmm.Plan(m, q, "fp32") for m in sizes]
         ms_l = _event_ms(lambda: [pl.solve_into(r, ph, gg) for pl, r, ph, gg in zip(singles, rhos, phis, gs)], 3, 1)
         del singles
-        fl = sum(costs.solve_flops(m, q)["total"] for m in sizes)
+        fl = sum(costs.folded_flops(m, q)["total"] for m in sizes)
         batched[f"p{q}"] = {
             "ms_per_batch": ms_b,
             "cells_per_s": cells_b / (ms_b * 1e-3),
-            "useful_tflops": fl / (ms_b * 1e-3) / 1e12,
+            "tflops": fl / (ms_b * 1e-3) / 1e12,
             "loop_of_single_solves_ms": ms_l,
             "speedup_vs_loop": ms_l / ms_b,
             "autotuned": {"bottom_tile": info["bottom_tile"], "m2l_grouping": info["m2l_grouping"],
@@ -576,9 +577,11 @@ def main():
               "max_ms": float(per.max())}
     log(f"single solves: median {spread['median_ms']:.3f} ms, mean {spread['mean_ms']:.3f} +- {spread['std_ms']:.3f} ms")
 
-    flops = costs.solve_flops(n, p, delta_l=dl)
-    stage_flops = {"p2m": flops["p2m"], "m2m": flops["m2m"], "m2l": flops["m2l"], "bottom": flops["bottom"]}
-    if dl == 1:  # level F - 1 is formed by the P2M stage, from the density
+    # FP64 and FP32 fields run the folded kernels, BF16 ones the operators term by term
+    folded = prec != "bf16"
+    flops = (costs.folded_flops if folded else costs.solve_flops)(n, p, delta_l=dl)
+    stage_flops = {k: flops[k] for k in ("p2m", "m2m", "m2l", "bottom")}
+    if not folded and dl == 1:  # level F - 1 is formed by the P2M stage, from the density
         stage_flops["p2m"] += flops["m2m_top"]
         stage_flops["m2m"] -= flops["m2m_top"]
     stages = {}
@@ -587,22 +590,25 @@ def main():
             stages[name] = {"ms_per_step": ms / args.steps, "launches_per_step": launches / args.steps}
             if name in stage_flops and ms > 0:
                 stages[name]["tflops"] = stage_flops[name] * args.steps / (ms * 1e-3) / 1e12
-    bot_ms, bot_launches = prof["bottom"]
-    bot_avg_s = bot_ms * 1e-3 / max(bot_launches, 1)
-    bot_tflops = stage_flops["bottom"] / bot_avg_s / 1e12
+    # the dominant stage: one launch (BF16: the bottom; the M2L's sum of parts,
+    # where a launch shares its K loops, is part of its time)
+    top = "m2l" if folded and dl == 1 else "bottom"
+    top_ms = prof[top][0] / args.steps
+    top_tflops = stage_flops[top] / (top_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[prec]
     roofline = {
-        "kernel": "k_bottom: M2P + L2P + near field",
+        "kernel": ("k_m2lf: M2L of all levels" if top == "m2l" else
+                   "k_m2lf, k_block: M2P, L2P + near field" if folded else "k_bottom: M2P + L2P + near field"),
         "bound": "mfma",
-        "achieved": round(bot_tflops, 3),
+        "achieved": round(top_tflops, 3),
         "peak": peak,
         "unit": "TFLOP/s",
-        "frac": round(bot_tflops / peak, 4),
+        "frac": round(top_tflops / peak, 4),
         "traffic": profiled_traffic(n, p, prec, dl),
-        "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-        "avg_launch_ms": round(bot_avg_s * 1e3, 4),
-        "flops_per_launch": stage_flops["bottom"],
-        "m2p_pairs_per_launch": costs.m2p_pairs(n, dl),
+        "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE)",
+        "avg_launch_ms": round(top_ms, 4),
+        "flops_per_launch": stage_flops[top],
+        "flops": "executed products" if folded else "useful",
     }
     m2l_ms, m2l_launches = prof["m2l"]
     solve_tflops = flops["total"] / (elapsed / args.steps) / 1e12
@@ -612,7 +618,8 @@ def main():
                 "launches_per_step": m2l_launches / args.steps},
         "solve_tflops": round(solve_tflops, 3),
         "solve_frac_of_peak": round(solve_tflops / peak, 4),
-        "useful_flops_per_solve": flops["total"],
+        "flops_per_solve": flops["total"],
+        "flops_by_the_papers_operators": costs.solve_flops(n, p, delta_l=dl)["total"],
     }
 
     cpu = None

@@ -55,6 +55,31 @@ def test_finest_blocks(F, orc, precision, n, p, nmax, tile):
     assert e[0] <= BARS[precision][0] and e[1] <= BARS[precision][1], e
 
 
+# the shifts between levels: multipoles of one to three levels by one kernel (up
+# to 64^3) or a kernel per level, locals of the coarsest level straight from the
+# M2L, both types of a mixed plan in one M2L launch, block tiles of one column tile
+# (up to 32^3); the smallest and largest orders and truncations
+@pytest.mark.parametrize("precision,n,p,nmax,coarse", [
+    ("fp64", 16, 6, None, 4), ("fp64", 32, 1, None, 4), ("fp64", 32, 8, 3, 4), ("fp64", 64, 6, None, 4),
+    ("fp64", 64, 7, 2, 4), ("fp64", 128, 1, 0, 4), ("fp64", 128, 8, None, 4), ("fp32", 64, 5, None, 3),
+    ("fp32", 64, 8, 4, 4), ("fp32", 128, 2, None, 4),
+])
+def test_level_shifts(F, orc, precision, n, p, nmax, coarse):
+    import torch
+    print(f"case shifts {precision} n={n} p={p} nmax={nmax} coarse={coarse}", flush=True)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    rho = torch.as_tensor(fi.plummer_density(n, fi.multi_plummer_params(9, 40 + n + p))).to("cuda", dt)
+    plan = F.Plan(n, p, precision, nmax=nmax, coarse_fp64_levels=coarse)
+    phi, g = plan.solve(rho)
+    torch.cuda.synchronize()
+    corners = [0, n - 1, n * n - 1, n ** 3 - 1]
+    cells = np.unique(np.concatenate([corners, np.random.default_rng(n + p).choice(n ** 3, 48, replace=False)]))
+    phi_o, g_o = orc.solve(rho.double().cpu().numpy(), p, nmax=nmax, targets=cells)
+    e = rel(phi.double().cpu().numpy().reshape(-1)[cells], phi_o), rel(g.double().cpu().numpy().reshape(3, -1)[:, cells], g_o)
+    print(f"  phi {e[0]:.2e} g {e[1]:.2e}", flush=True)
+    assert e[0] <= BARS[precision][0] and e[1] <= BARS[precision][1], e
+
+
 # the transposes: the coarsest grids (no M2L; one M2L level), one and several
 # L2L levels, truncation, both types of a mixed plan, tiles of every height
 @pytest.mark.parametrize("precision,n,p,nmax", [
