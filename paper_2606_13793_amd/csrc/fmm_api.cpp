@@ -70,7 +70,8 @@ int validate(int n, int p, int isolated, const fmm_options* o) {
   return FMM_OK;
 }
 
-// device bytes a plan will allocate (tables once, grids per field)
+// device bytes of a plan with full expansions on every level (tables once, grids
+// per field): what FMM_TEST_MAX_WORKSPACE is compared with
 size_t plan_bytes(const std::vector<int>& ns, int p, int dl) {
   const int NM = fmm::nterms(p), NC = (NM + 3) / 4, NCL = NC, ND = fmm::nterms(p + 1);
   size_t b = (size_t)343 * 8 * ND * sizeof(double) + 8 * fmm::NLIST_PAD * sizeof(int) + 256;
@@ -388,7 +389,7 @@ namespace fmm {
 // per level for the M2M and L2L chains) covers every field of the plan.
 int build_schedule(fmm_plan* pl) {
   const int RS = loc_stride(pl->p), klow = m2l_low_from(pl);
-  SegList p2m, p2m2, p2mh, up, m2m[16], m2mf[16], conv[2], l2l[16], bot[2], blk[2][3], m2lf[2][3], m2pf[2][3], l2lf[16];
+  SegList p2m, p2m2, p2mh, up, m2m[16], m2mf[16], conv[2], l2l[16], bot[2], blk[2][2], m2lf[2][3], m2pf[2][3], l2lf[16];
   for (int f = 0; f < (int)pl->fld.size(); ++f) {
     const Field& fd = pl->fld[f];
     const int F = fd.F, nF = fd.n >> pl->dl;
@@ -535,7 +536,7 @@ int build_schedule(fmm_plan* pl) {
       b.u = F >= 3 && pl->dl == 1 ? fd.lev[F].Lw : nullptr;
       b.d = lb >= 3 ? fd.lev[lb].Lc : nullptr;
       b.c = (const double*)fd.m2p;
-      for (int v = 0; v < 3; ++v) {
+      for (int v = 0; v < 2; ++v) {
         b.tz = (int)cdiv(nb, 1 << v);
         blk[x][v].add(b, (long long)b.tpa * b.tpa * b.tz);
       }
@@ -645,8 +646,8 @@ int build_schedule(fmm_plan* pl) {
     if ((rc = upload_segs(pl, pl->s_red[x], red[x]))) return rc;
     if ((rc = upload_segs(pl, pl->s_bot[x], bot[x]))) return rc;
     for (int v = 0; v < 3; ++v)
-      if ((rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v])) || (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])) ||
-          (rc = upload_segs(pl, pl->s_m2pf[x][v], m2pf[x][v])))
+      if ((v < 2 && (rc = upload_segs(pl, pl->s_blk[x][v], blk[x][v]))) ||
+          (rc = upload_segs(pl, pl->s_m2lf[x][v], m2lf[x][v])) || (rc = upload_segs(pl, pl->s_m2pf[x][v], m2pf[x][v])))
         return rc;
   }
   return FMM_OK;

@@ -334,23 +334,28 @@ __device__ __forceinline__ void blk_images(const H* ctr, int q, const H* (&p)[4]
 // 115 for L2P at 2.4 GHz, and 949 MB of locals, 200 us of copy rate.  Blocks are
 // small so that a CU holds two (FP32: three or four): one's staging and stores
 // run beside the other's products.
+// PHI: calls for the potential alone, FP64: the 8 columns (t, phi) as products of
+// 16 x 4 x 4 (17 cycles; FP32 has none of that rate) over the same table, each
+// fragment for two row tiles, as loads bound a wave then (128^3, p = 6: 109 us with
+// the 24 columns of g, 68 without).
 // blocks (of 4 waves) per compute unit
 template <typename CT, int NX>
 constexpr int blk_occ = Mf<CT>::IDX == 0 ? 2 : NX == 2 ? 3 : 4;
-template <int P, typename CT, typename TI, typename TO, int NX, int NT, int DL>
+template <int P, typename CT, typename TI, typename TO, int NX, int NT, int DL, bool PHI>
 __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
     const Seg* __restrict__ segs, int nseg, IoArg io, const typename Mf<CT>::H* __restrict__ W,
     unsigned int* __restrict__ stamp_cnt, unsigned long long* __restrict__ stamp_done) {
   using M = Mf<CT>;
   using H = typename M::H;
-  using Acc = typename M::Acc;
+  static_assert(!PHI || (Mf<CT>::IDX == 0 && NT == 2), "FP64, all positions");
+  using Acc = std::conditional_t<PHI, H, typename M::Acc>;
   typedef H h2 __attribute__((ext_vector_type(2)));
-  constexpr int NE = 4, KS = Mf<CT>::IDX == 0 ? 2 / NX : 2, NR = NX * KS / 2, HR = hrow(P), FR = frow(P);
+  constexpr int NE = 4, KS = Mf<CT>::IDX == 0 && !PHI ? 2 / NX : 2, NR = NX * KS / 2, HR = hrow(P), FR = frow(P);
   constexpr int NLP = blk_lpairs(P), NPS = blk_psteps(P), OFF_L = blk_off_l(), OFF_P = blk_off_p(P);
   // own-local pairs of steps of the last K slice, which has one group less
   constexpr int LSPLIT = KS == 1 ? NLP : NLP < (8 + NPS + 2 * NLP) / 4 ? NLP : (8 + NPS + 2 * NLP) / 4;
   // epilogue image of the results of NXR row tiles, [slice][half][4][NXR * 16][CS]
-  constexpr int NXR = NX / NR, CS = 16 * NT + 1, ES = NXR * 16 * CS;
+  constexpr int NXR = NX / NR, CS = PHI ? 9 : 16 * NT + 1, ES = NXR * 16 * CS;
   constexpr int EP = KS * 8 * ES, TILE = blk_tile(NX), SZ = EP > TILE ? EP : TILE;
   __shared__ __attribute__((aligned(16))) H lds[SZ];
   __shared__ int spt[8 * NPS * 4];
@@ -375,14 +380,20 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
     for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[r][e][t] = Acc{0, 0, 0, 0};
+      for (int t = 0; t < NT; ++t) acc[r][e][t] = Acc{};
+  // the lane's B elements (PHI: column lane % 4 of each tile's phi)
+  const unsigned bl = PHI ? 8u * (lane & 3) + 32u * kq : 2u * lane;
+  auto mul = [](H a, H b, Acc c) {
+    if constexpr (PHI) return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+    else return M::op(a, b, c);
+  };
   auto products = [&](const H (&a)[NR][NE], const H (&b)[NE][NT]) {
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
       for (int e = 0; e < NE; ++e)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[r][e][t] = M::op(a[r][e], b[e][t], acc[r][e][t]);
+        for (int t = 0; t < NT; ++t) acc[r][e][t] = mul(a[r][e], b[e][t], acc[r][e][t]);
   };
   __syncthreads();
   // ---- the 12^3 densities
@@ -393,7 +404,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
       for (int e = 0; e < NE; ++e)
         if constexpr (NT == 2) {
-          const h2 v = *(const __attribute__((address_space(1))) h2*)(wb + s * 1024 + e * 128 + 2u * lane);
+          const h2 v = *(const __attribute__((address_space(1))) h2*)(wb + s * 1024 + e * 128 + bl);
           b[e][0] = v[0], b[e][1] = v[1];
         } else {
           b[e][0] = (wb + s * 1024 + e * 128)[2u * lane];
@@ -455,7 +466,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
       for (int v = 0; v < 2; ++v)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) y[v][t] = (wl + s * 256 + v * 128 + t)[2u * lane];
+        for (int t = 0; t < NT; ++t) y[v][t] = (wl + s * 256 + v * 128 + t)[bl];
     };
     const int s0 = KS == 1 || ks ? 0 : LSPLIT, s1 = KS == 1 || !ks ? NLP : LSPLIT;
     auto step = [&](const h8 (&x)[NR], const H (&y)[2][NT]) {
@@ -466,7 +477,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
           for (int e = 0; e < NE; ++e)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[r][e][t] = M::op(x[r][2 * e + v], y[v][t], acc[r][e][t]);
+            for (int t = 0; t < NT; ++t) acc[r][e][t] = mul(x[r][2 * e + v], y[v][t], acc[r][e][t]);
     };
     if (s0 < s1) {
       read(s0, x[0], y[0]);
@@ -504,7 +515,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
           const H a = static_cast<H>(v[e][s]);
 #pragma unroll
           for (int t = 0; t < NT; ++t)
-            acc[r][e][t] = M::op(a, (wp + (e * NPS + s) * 128 + t)[2u * lane], acc[r][e][t]);
+            acc[r][e][t] = mul(a, (wp + (e * NPS + s) * 128 + t)[bl], acc[r][e][t]);
         }
     }
   }
@@ -517,7 +528,7 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
   const int z = threadIdx.x & 15, y = threadIdx.x >> 4, qy = y & 3, qz = z & 3;
   const int uy = 4 * by0 + y, uz = 4 * bz0 + z, myz = (qy < 2) << 1 | (qz < 2);
   const int tyz = (qy == 0 || qy == 3) << 1 | (qz == 0 || qz == 3);
-  const H* const res = lds + myz * ES + (4 * (y >> 2) + (z >> 2)) * CS + 4 * tyz;
+  const H* const res = lds + myz * ES + (4 * (y >> 2) + (z >> 2)) * CS + (PHI ? 1 : 4) * tyz;
   const double sc[4] = {0.125 * sphi, 0.125 * sgr, (qy < 2 ? -0.125 : 0.125) * sgr, (qz < 2 ? -0.125 : 0.125) * sgr};
   const long long blk0 = ((long long)bx0 * nb + (uy >> 2)) * nb + (uz >> 2), pyz = qy * 4 + qz;
   const unsigned at = (unsigned)(y * n + z);
@@ -529,10 +540,15 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const H p0 = acc[R][0][t][v] + acc[R][1][t][v], m0 = acc[R][0][t][v] - acc[R][1][t][v],
-                p1 = acc[R][2][t][v] + acc[R][3][t][v], m1 = acc[R][2][t][v] - acc[R][3][t][v];
-        H* const to = lds + (ks * 2 + half) * 4 * ES + (16 * X + M::row(v, kq)) * CS + 16 * t + i;
+      for (int v = 0; v < (PHI ? 1 : 4); ++v) {
+        H x[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+          if constexpr (PHI) x[e] = acc[R][e][t];
+          else x[e] = acc[R][e][t][v];
+        const H p0 = x[0] + x[1], m0 = x[0] - x[1], p1 = x[2] + x[3], m1 = x[2] - x[3];
+        const int row = PHI ? kq + 4 * ((lane >> 2) & 3) : M::row(v, kq), col = PHI ? 4 * t + (lane & 3) : 16 * t + i;
+        H* const to = lds + (ks * 2 + half) * 4 * ES + (16 * X + row) * CS + col;
         to[0] = p0 + p1;
         to[ES] = m0 + m1;
         to[2 * ES] = p0 - p1;
@@ -543,14 +559,14 @@ __global__ __launch_bounds__(BLK_THREADS, (blk_occ<CT, NX>)) void k_block(
       static_for<4 * NXR>([&](auto xc) {
         constexpr int x = decltype(xc)::value, qx = x & 3, XT = x >> 2, XB = R + XT;
         // (column tile 1: the outer two cells along x)
-        constexpr int outer = qx == 0 || qx == 3, ro = (NT == 2 ? 16 * outer : 0) + 16 * XT * CS;
+        constexpr int outer = qx == 0 || qx == 3, ro = (PHI ? 4 : NT == 2 ? 16 : 0) * outer + 16 * XT * CS;
         if (NT == 1 && outer != t0) return;
         const int ux = 4 * (bx0 + XB) + qx;
         if (ux >= n) return;
         const long long row = ((long long)ux * n + 4 * by0) * n + 4 * bz0;  // (uniform)
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-          if (o && !g) break;
+          if (o && (PHI || !g)) break;
           H a = res[ro + o], c = res[4 * ES + ro + o];
           if constexpr (KS == 2) {
             a += res[8 * ES + ro + o];

@@ -164,11 +164,13 @@ struct Level {
   int nkp = 0;        // padded cells per axis (multipole grids: nk + 6)
   long long ncell = 0;   // nk^3
   long long ncellp = 0;  // nkp^3
-  void* M = nullptr;  // multipoles, chunked [NC][ncellp][4], zero halo of 3 cells
-  // mixed-precision plans: the same multipoles rounded to the compute type of
-  // the kernels that read this level, chunked [ceil(NM/KC)][ncellp][KC] with
-  // KC the type's K chunk (16 BF16 / 4 FP32 terms), zero halo; null where no
-  // low-precision kernel reads the level
+  // multipoles, zero halo of 3 cells: folded fields (fmm_fold.h), levels 2 ..
+  // block_level, planes of harmonic terms [term][ncellp], where the backward pass
+  // also leaves its cotangents; others chunked [NC][ncellp][4]
+  void* M = nullptr;
+  // BF16 fields: the same multipoles rounded to the compute type of
+  // the kernels that read this level, chunked [ceil(NM/16)][ncellp][16], zero
+  // halo; null where no BF16 kernel reads the level
   void* Mt = nullptr;
   // locals of level k >= 3, stored per parent cell P (level k-1) in M2L
   // column order: L[P][m2l_col(q, b)] = Lhat of child 2P + q, term b;
@@ -185,8 +187,7 @@ struct Level {
   void* Lw = nullptr;
   // levels 3 .. block_level: the complete locals' harmonic terms, [cell][hrow]
   double* Lc = nullptr;
-  // harmonic multipoles of levels 2 .. block_level, [term][ncellp] with a zero halo,
-  // in the compute type of the M2L into the next level
+  // the planes of M in FP32, where the M2L into the next level runs in it (or null)
   void* Mh = nullptr;
 };
 
@@ -195,9 +196,9 @@ struct Field {
   int n = 0, L = 0, F = 0;  // unigrid cells per axis, log2 n, finest FMM level L - 1
   double dx = 0.0;
   Level lev[16];
-  // a copy of the last solve's density (I/O type), left by the block kernel
-  // of a field with an FP64 bottom: the level-F multipoles, which that kernel
-  // never forms, are derived from it when they are asked for
+  // a copy of the last solve's density (I/O type), left by the block kernel for
+  // field 0: full multipoles, which folded fields never form, are derived from it
+  // when they are asked for
   void* rho_copy = nullptr;
   // FMM-2: M2P at the unigrid centres, [level-F cell][phi, g][4^3] in the
   // bottom's compute type, added by the block kernel
@@ -373,7 +374,7 @@ struct fmm_plan {
   fmm::SegTable s_conv[2];          // forward M2L: [0] FP64 levels, [1] low-precision levels
   fmm::SegTable s_l2l[16];          // L2L into level k (index k)
   fmm::SegTable s_bot[2];           // BF16 bottom, tile depth 16 | 8
-  fmm::SegTable s_blk[2][3];        // finest blocks [FP64 | low][1, 2 or 4 rows of blocks per tile]
+  fmm::SegTable s_blk[2][2];        // finest blocks [FP64 | FP32][1 or 2 rows of blocks per tile]
   long long blk_rows[2] = {0, 0};   // their row tiles of 16 blocks
   fmm::SegTable s_m2lf[2][3];       // folded M2L [FP64 | low][1, 2 or 4 rows of octs per tile]
   fmm::SegTable s_m2pf[2][3];       // FMM-2: folded M2P, the same

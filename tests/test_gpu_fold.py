@@ -80,6 +80,29 @@ def test_level_shifts(F, orc, precision, n, p, nmax, coarse):
     assert e[0] <= BARS[precision][0] and e[1] <= BARS[precision][1], e
 
 
+# the potential alone takes other products than phi and g: both against each other
+# and the oracle, on block tiles of one column tile, one row and two rows
+@pytest.mark.parametrize("n,p,nmax,delta_l", [
+    (16, 4, None, 1), (64, 1, None, 1), (64, 7, 3, 1), (128, 3, None, 1), (128, 8, None, 1), (64, 5, None, 2), (128, 2, None, 2),
+])
+def test_potential_alone(F, orc, n, p, nmax, delta_l):
+    import torch
+    print(f"case phi alone n={n} p={p} nmax={nmax} delta_l={delta_l}", flush=True)
+    rho = torch.as_tensor(fi.plummer_density(n, fi.multi_plummer_params(9, 70 + n + p))).cuda()
+    plan = F.Plan(n, p, "fp64", nmax=nmax, delta_l=delta_l)
+    both, _ = plan.solve(rho)
+    alone = torch.full_like(rho, float("nan"))
+    plan.solve_into(rho, alone, None)
+    torch.cuda.synchronize()
+    e = rel(alone.cpu().numpy(), both.cpu().numpy())
+    cells = np.random.default_rng(n + p).choice(n ** 3, 48, replace=False)
+    kw = {"delta_l": 2} if delta_l == 2 else {}
+    phi_o, _ = orc.solve(rho.cpu().numpy(), p, nmax=nmax, targets=cells, **kw)
+    eo = rel(alone.cpu().numpy().reshape(-1)[cells], phi_o)
+    print(f"  against phi of both {e:.2e}, oracle {eo:.2e}", flush=True)
+    assert e <= BARS["fp64"][0] and eo <= BARS["fp64"][0], (e, eo)
+
+
 # the transposes: the coarsest grids (no M2L; one M2L level), one and several
 # L2L levels, truncation, both types of a mixed plan, tiles of every height
 @pytest.mark.parametrize("precision,n,p,nmax", [
