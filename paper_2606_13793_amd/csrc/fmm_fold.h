@@ -86,12 +86,6 @@ constexpr __host__ __device__ int blk_psteps(int P) {
   }
   return (most + 3) / 4;
 }
-// the k-th reduced term of parity e, or -1
-constexpr __host__ __device__ int blk_pterm(int P, int e, int k) {
-  for (int i = 0; i < hterms(P); ++i)
-    if (h_parity(i) == e && k-- == 0) return i;
-  return -1;
-}
 // table layout (elements): the folded stencil [54][8][64][2 column tiles], the
 // own locals [steps][64][2], the level F-1 locals [8][steps][64][2]
 constexpr __host__ __device__ int blk_off_l() { return BLK_STEPS * 8 * 2 * 64; }
@@ -141,35 +135,6 @@ __device__ __forceinline__ double blk_l2p(int bt, int t, int o, int dl) {
   return l2p_w_coef(bt, w, 1.0, 1.0, o);
 }
 
-// The block kernel's B table in the compute type (layout above); lane = j +
-// 16 kq, column 16 tile + j = (t, o).  The 1/8 of the inverse Walsh sum is
-// left to the epilogue.
-template <typename H>
-__global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int P, int dl) {
-  const int id = blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= blk_table(P)) return;
-  const int lane = (id >> 1) & 63, tile = id & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
-  const int t = col >> 2, o = col & 3;
-  double x = 0.0;
-  if (id < blk_off_l()) {
-    const int e = (id >> 7) & 7, st = id >> 10, pair = 4 * (st / 6) + kq;
-    const int jj[3] = {pair / 6, pair % 6, st % 6};
-    for (int minus = 0; minus < 8; ++minus) {
-      int v = 0;
-      for (int a = 0; a < 3; ++a) v = v * 12 + (((minus >> (2 - a)) & 1) ? 5 - jj[a] : 6 + jj[a]);
-      x += chi(e, minus) * G[((size_t)t * 1728 + v) * 4 + o];
-    }
-  } else if (id < blk_off_p(P)) {
-    const int st = (id - blk_off_l()) >> 7, b = 8 * (st >> 1) + 2 * kq + (st & 1);
-    if (b < hterms(P)) x = h_reduce(b, [&](int bt) { return l2p_coef(bt, t, o); });
-  } else {
-    const int s = (id - blk_off_p(P)) >> 7, np = blk_psteps(P), e = s / np;
-    const int b = blk_pterm(P, e, 4 * (s % np) + kq);
-    if (b >= 0) x = 8.0 * h_reduce(b, [&](int bt) { return blk_l2p(bt, t, o, dl); });
-  }
-  W[id] = static_cast<H>(x);
-}
-
 // (pattern, term) of column col of the transpose's K order (sorted by the degree
 // of the term, the pattern slow inside a degree), packed pattern << 8 | term; -1
 // past the last
@@ -186,7 +151,7 @@ struct FoldTab {
   unsigned char par[hterms(P)];         // its parity pattern
   unsigned char deg[hterms(P)];         // its degree
   unsigned char idx[hterms(P)];         // its place among the terms of that pattern
-  signed char pt[8][4 * blk_psteps(P)];  // blk_pterm
+  signed char pt[8][4 * blk_psteps(P)];  // the terms of each pattern, -1 past the last
   constexpr FoldTab() : col(), full(), par(), deg(), idx(), pt() {
     for (int i = 0; i < 8 * hterms(P); ++i) col[i] = (short)m2lf_col(P, i);
     int cnt[8] = {};
@@ -212,6 +177,38 @@ struct BlkPlaces {
   __device__ int operator[](int i) const { return v[i]; }
 };
 __constant__ const BlkPlaces c_blk_place = BlkPlaces();
+
+// The block kernel's B table in the compute type (layout above); lane = j +
+// 16 kq, column 16 tile + j = (t, o).  The 1/8 of the inverse Walsh sum is
+// left to the epilogue.
+// (The order is a template parameter so that the offsets and class tables are
+// constants: 137 us of plan creation at p = 6 before.)
+template <int P, typename H>
+__global__ void k_blk_table(const double* __restrict__ G, H* __restrict__ W, int dl) {
+  constexpr int OFF_L = blk_off_l(), OFF_P = blk_off_p(P), END = blk_table(P), np = blk_psteps(P);
+  const int id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= END) return;
+  const int lane = (id >> 1) & 63, tile = id & 1, j = lane & 15, kq = lane >> 4, col = 16 * tile + j;
+  const int t = col >> 2, o = col & 3;
+  double x = 0.0;
+  if (id < OFF_L) {
+    const int e = (id >> 7) & 7, st = id >> 10, pair = 4 * (st / 6) + kq;
+    const int jj[3] = {pair / 6, pair % 6, st % 6};
+    for (int minus = 0; minus < 8; ++minus) {
+      int v = 0;
+      for (int a = 0; a < 3; ++a) v = v * 12 + (((minus >> (2 - a)) & 1) ? 5 - jj[a] : 6 + jj[a]);
+      x += chi(e, minus) * G[((size_t)t * 1728 + v) * 4 + o];
+    }
+  } else if (id < OFF_P) {
+    const int st = (id - OFF_L) >> 7, b = 8 * (st >> 1) + 2 * kq + (st & 1);
+    if (b < hterms(P)) x = h_reduce(b, [&](int bt) { return l2p_coef(bt, t, o); });
+  } else {
+    const int s = (id - OFF_P) >> 7, e = s / np;
+    const int b = c_ft<P>.pt[e][4 * (s % np) + kq];
+    if (b >= 0) x = 8.0 * h_reduce(b, [&](int bt) { return blk_l2p(bt, t, o, dl); });
+  }
+  W[id] = static_cast<H>(x);
+}
 
 // in-place Walsh transform of 8 values
 template <typename H>

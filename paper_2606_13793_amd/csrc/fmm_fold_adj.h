@@ -28,13 +28,16 @@ constexpr __host__ __device__ int blka_ltiles(int P) { return (hterms(P) + 15) /
 constexpr __host__ __device__ int blka_off_lp(int P) { return blka_off_l(P) + 8 * blka_ltiles(P) * 64; }
 constexpr __host__ __device__ int blka_table(int P) { return blka_off_lp(P) + 64 * 64; }
 
-__global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int P, int nmax, int dl) {
+template <int P>
+__global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict__ W, int nmax, int dl) {
+  constexpr int OFF_P = blka_off_p(), OFF_L = blka_off_l(P), OFF_LP = blka_off_lp(P), END = blka_table(P), np = blk_psteps(P),
+                LT = blka_ltiles(P);
   const int id = blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= blka_table(P)) return;
-  const bool quads = id < blka_off_l(P);
+  if (id >= END) return;
+  const bool quads = id < OFF_L;
   const int lane = id & 63, j = quads ? ((id >> 1) & 3) + 4 * (id & 1) : lane & 15, kq = quads ? (id >> 3) & 3 : lane >> 4;
   double x = 0.0;
-  if (id < blka_off_p()) {
+  if (id < OFF_P) {
     // source sp of the positive octant, targets at y = the 8 images of u
     const int e = (id >> 5) & 7, st = (id >> 8) % BLK_STEPS, o = (id >> 8) / BLK_STEPS, pair = 4 * (st / 6) + kq;
     const int jj[3] = {pair / 6, pair % 6, st % 6};
@@ -52,9 +55,9 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
       const int eo = o ? 8 >> o : 0;  // the axis of output o
       x += chi(e, minus) * chi(eo, minus) * chi(eo, neg) * G[((size_t)t * 1728 + v) * 4 + o];
     }
-  } else if (id < blka_off_l(P)) {
-    const int s = (id - blka_off_p()) >> 5, np = blk_psteps(P), e = s / np;
-    const int b = blk_pterm(P, e, 4 * (s % np) + kq);
+  } else if (id < OFF_L) {
+    const int s = (id - OFF_P) >> 5, e = s / np;
+    const int b = c_ft<P>.pt[e][4 * (s % np) + kq];
     if (b >= 0 && h_degree(b) <= nmax) {
       // P2M weights w^a / a!, w = -(1/8 or 3/8)
       const double w[3] = {(j & 4) ? -0.375 : -0.125, (j & 2) ? -0.375 : -0.125, (j & 1) ? -0.375 : -0.125};
@@ -67,12 +70,12 @@ __global__ void k_blk_adj_table(const double* __restrict__ G, double* __restrict
             return m;
           });
     }
-  } else if (id < blka_off_lp(P)) {
-    const int f = (id - blka_off_l(P)) >> 6, s = f / blka_ltiles(P), b = 16 * (f % blka_ltiles(P)) + j;
+  } else if (id < OFF_LP) {
+    const int f = (id - OFF_L) >> 6, s = f / LT, b = 16 * (f % LT) + j;
     if (b < hterms(P)) x = 0.125 * h_reduce(b, [&](int bt) { return l2p_coef(bt, s, kq); });
   } else {
-    const int f = (id - blka_off_lp(P)) >> 6, e = f >> 3, s = f & 7;
-    const int b = blk_pterm(P, e, j);
+    const int f = (id - OFF_LP) >> 6, e = f >> 3, s = f & 7;
+    const int b = j < 4 * np ? c_ft<P>.pt[e][j] : -1;
     if (b >= 0) x = h_reduce(b, [&](int bt) { return blk_l2p(bt, s, kq, dl); });
   }
   W[id] = x;

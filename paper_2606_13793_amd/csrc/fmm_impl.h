@@ -1455,11 +1455,9 @@ hipError_t tables_all(fmm_plan* pl, hipStream_t s) {
       if ((e = hipMalloc(&pl->wblk[x], b)) != hipSuccess) break;
       pl->bytes += b;
       if (x)
-        hipLaunchKernelGGL(k_blk_table<float>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (float*)pl->wblk[x], pl->p,
-                           pl->dl);
+        hipLaunchKernelGGL((k_blk_table<P, float>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (float*)pl->wblk[x], pl->dl);
       else
-        hipLaunchKernelGGL(k_blk_table<double>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (double*)pl->wblk[x], pl->p,
-                           pl->dl);
+        hipLaunchKernelGGL((k_blk_table<P, double>), dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, (double*)pl->wblk[x], pl->dl);
       e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1810,6 +1808,7 @@ hipError_t solve_ct(fmm_plan* pl, IoArg io, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // adjoint solve (field 0)
 // ---------------------------------------------------------------------------
+template <int P>
 hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
   hipError_t e;
   const int NL = pl->NL;
@@ -1825,8 +1824,7 @@ hipError_t adjoint_tables_all(fmm_plan* pl, hipStream_t s) {
     if ((e = hipMalloc(&G, 8 * 1728 * 4 * sizeof(double))) != hipSuccess) return e;
     hipLaunchKernelGGL(k_blk_green, dim3(blocks_for(8 * 1728 * 4, 256)), dim3(256), 0, s, pl->dtab, G, pl->NMX, pl->ND,
                        pl->dl);
-    hipLaunchKernelGGL(k_blk_adj_table, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, pl->wblk_adj, pl->p, pl->nmax,
-                       pl->dl);
+    hipLaunchKernelGGL(k_blk_adj_table<P>, dim3(blocks_for(cnt, 256)), dim3(256), 0, s, G, pl->wblk_adj, pl->nmax, pl->dl);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(G);
@@ -2046,7 +2044,7 @@ hipError_t Impl<P>::backward(fmm_plan* pl, const AdjWs& w, const void* dphi, con
 
 template <int P>
 hipError_t Impl<P>::adjoint_tables(fmm_plan* pl, hipStream_t s) {
-  return adjoint_tables_all(pl, s);
+  return adjoint_tables_all<P>(pl, s);
 }
 
 // L2L into the finest level of field 0 (the solve leaves Lam_F without it)
