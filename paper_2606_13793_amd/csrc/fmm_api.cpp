@@ -401,7 +401,8 @@ int build_schedule(fmm_plan* pl) {
       // Small fields form three levels at once (k_up): its 4 x 4 x 4 cells write
       // quarter lines, which costs large ones more than the launches it saves
       // (64^3, p = 5: 8 + 6 + 6 us -> 11; the whole call at 256^3, p = 6: + 130 us)
-      const bool fused = (1LL << (3 * (top - 2))) <= pl->cus;
+      // (top < 2, 8^3 under FMM-1: no level is formed)
+      const bool fused = top >= 2 && (1LL << (3 * (top - 2))) <= pl->cus;
       const int ups = top < 2 ? 0 : fused ? std::min(3, top - 1) : 1;
       if (ups && !fused) {
         Seg s2{};
