@@ -226,8 +226,10 @@ int fmm_last_status(void);
  * only its M2L part during a solve), so call it only between solves on the
  * null stream's device.  Copies to HOST
  * memory `out`, as double, the scaled expansions (FP64 and FP32 levels keep
- * them in harmonic terms only: full multipoles are then formed on the host from
- * the plan's copy of the density, full locals by Laplace's equation):
+ * them in harmonic terms only, which the export returns as they are; what those
+ * leave open of full multipoles, and the whole of the finest level's under
+ * FMM-1, is formed from the plan's copy of the last density, full locals by
+ * Laplace's equation):
  *   which = 0: multipoles of level `level` (2 <= level <= F), nterms(nmax) per cell,
  *              Mhat[a] = (-1)^|a| M[a] / (a! h^|a| dx^3), M[a] = sum m (x - c)^a
  *   which = 1: locals of level `level` (3 <= level <= F),

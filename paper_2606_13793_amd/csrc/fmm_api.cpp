@@ -1774,6 +1774,23 @@ int fmm_fd_force(int n, const double* phi, double* f, void* stream) {
   return ok();
 }
 
+// One of the plan's exports over a level, nt terms per cell, a bounded number of
+// cells at a time.
+static int export_level(fmm_plan* plan, decltype(fmm_plan::export_multipoles) fn, int level, int nt, double* out) {
+  const long long ncell = plan->lev[level].ncell, step = std::min(ncell, (64LL << 20) / (8 * nt));
+  double* dev = nullptr;
+  hipError_t e = hipMalloc(&dev, (size_t)step * nt * sizeof(double));
+  for (long long c = 0; c < ncell && e == hipSuccess; c += step) {
+    const long long cnt = std::min(step, ncell - c);
+    if ((e = fn(plan, level, c, cnt, dev, nullptr)) == hipSuccess)
+      e = hipMemcpy(out + c * nt, dev, (size_t)cnt * nt * sizeof(double), hipMemcpyDeviceToHost);
+  }
+  if (dev) (void)hipFree(dev);
+  if (e == hipSuccess) return ok();
+  (void)hipGetLastError();
+  return fail(e == hipErrorOutOfMemory ? FMM_ERR_OUT_OF_MEMORY : FMM_ERR_DEVICE, "export failed: %s", hipGetErrorString(e));
+}
+
 // The complete locals of one level of a field on the folded kernels, [cell]
 // [full term]: the harmonic terms the plan keeps, and the others by Laplace's
 // equation.  The finest level keeps its M2L part only, Walsh-folded over each
@@ -1857,51 +1874,7 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   const int nch = (nt + 3) / 4;
   if (!out || count < (size_t)lv.ncell * nt) return fail(FMM_ERR_INVALID_ARG, "out must hold %lld doubles", lv.ncell * nt);
   const int nk = lv.nk;
-  if (which == 0 && fmm::block_field(plan, plan->F)) {
-    // a folded field keeps harmonic terms only: derive the full ones from the
-    // copy of the density it left, sum_s rho_s w_s^a / a!, w the place of a
-    // unigrid cell in units of two cells, summed along z, y and x in turn
-    const int n = plan->n, m = n >> level, p = plan->p;
-    const size_t N = (size_t)n * n * n;
-    std::vector<double> rho(N);
-    hipError_t e;
-    if (plan->precision == 0) {
-      e = hipMemcpy(rho.data(), plan->fld[0].rho_copy, N * sizeof(double), hipMemcpyDeviceToHost);
-    } else {
-      std::vector<float> r32(N);
-      e = hipMemcpy(r32.data(), plan->fld[0].rho_copy, N * sizeof(float), hipMemcpyDeviceToHost);
-      std::copy(r32.begin(), r32.end(), rho.begin());
-    }
-    if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
-    std::vector<int> mi(3 * fmm::nterms(p));
-    fmm_multi_index(p, mi.data(), mi.size());
-    std::vector<double> pw((size_t)(p + 1) * m), zs(p + 1), yz((size_t)(p + 1) * (p + 1)), xyz((size_t)(p + 1) * (p + 1) * (p + 1));
-    for (int i = 0; i < m; ++i) {
-      double f = 1.0;
-      for (int k = 0; k <= p; ++k, f *= (m - 1 - 2 * i) / (2.0 * m * k)) pw[(size_t)k * m + i] = f;
-    }
-    for (long long cidx = 0; cidx < lv.ncell; ++cidx) {
-      const int c2 = (int)(cidx % nk), c1 = (int)((cidx / nk) % nk), c0 = (int)(cidx / ((long long)nk * nk));
-      std::fill(xyz.begin(), xyz.end(), 0.0);
-      for (int x = 0; x < m; ++x) {
-        std::fill(yz.begin(), yz.end(), 0.0);
-        for (int y = 0; y < m; ++y) {
-          std::fill(zs.begin(), zs.end(), 0.0);
-          const double* row = &rho[((size_t)(m * c0 + x) * n + m * c1 + y) * n + m * c2];
-          for (int z = 0; z < m; ++z)
-            for (int k = 0; k <= p; ++k) zs[k] += pw[(size_t)k * m + z] * row[z];
-          for (int j = 0; j <= p; ++j)
-            for (int k = 0; j + k <= p; ++k) yz[j * (p + 1) + k] += pw[(size_t)j * m + y] * zs[k];
-        }
-        for (int i = 0; i <= p; ++i)
-          for (int j = 0; i + j <= p; ++j)
-            for (int k = 0; i + j + k <= p; ++k)
-              xyz[(i * (p + 1) + j) * (p + 1) + k] += pw[(size_t)i * m + x] * yz[j * (p + 1) + k];
-      }
-      for (int t = 0; t < nt; ++t) out[cidx * nt + t] = xyz[(mi[3 * t] * (p + 1) + mi[3 * t + 1]) * (p + 1) + mi[3 * t + 2]];
-    }
-    return ok();
-  }
+  if (which == 0 && fmm::block_field(plan, plan->F)) return export_level(plan, plan->export_multipoles, level, nt, out);
   if (which == 0) {
     std::vector<double> host((size_t)nch * lv.ncellp * 4);
     hipError_t e = hipMemcpy(host.data(), lv.M, host.size() * sizeof(double), hipMemcpyDeviceToHost);

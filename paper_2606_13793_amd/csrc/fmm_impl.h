@@ -607,6 +607,7 @@ __device__ __forceinline__ double p2p2_coef(int k, int grp, int q, int o) {
 #include "fmm_fold.h"
 #include "fmm_shift.h"
 #include "fmm_fold_adj.h"
+#include "fmm_export.h"
 
 // ---------------------------------------------------------------------------
 // L2L, eq. (L2L), for one level k: Lhat_k[T] += shift of Lhat_{k-1}[parent(T)]
@@ -2017,6 +2018,7 @@ hipError_t Impl<P>::upload_constants() {
 
 template <int P>
 hipError_t Impl<P>::tables(fmm_plan* pl, hipStream_t s) {
+  pl->export_multipoles = export_multipoles<P>;
   const hipError_t e = alloc_m2lf_part<P>(pl);
   return e == hipSuccess ? tables_all<P>(pl, s) : e;
 }

@@ -197,8 +197,8 @@ struct Field {
   double dx = 0.0;
   Level lev[16];
   // a copy of the last solve's density (I/O type), left by the block kernel for
-  // field 0: full multipoles, which folded fields never form, are derived from it
-  // when they are asked for
+  // field 0: the export takes from it what harmonic terms leave open of full
+  // multipoles (fmm_export.h)
   void* rho_copy = nullptr;
   // FMM-2: M2P at the unigrid centres, [level-F cell][phi, g][4^3] in the
   // bottom's compute type, added by the block kernel
@@ -410,6 +410,10 @@ struct fmm_plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   size_t bytes = 0;
+  // folded fields: writes the full multipoles of cnt cells of a level of field 0,
+  // from the first-th in C order, to dev [cell][term] (set with the order's tables)
+  hipError_t (*export_multipoles)(const fmm_plan*, int level, long long first, long long cnt, double* dev,
+                                  hipStream_t) = nullptr;
   // stage profiling
   int profiling = 0;
   std::vector<fmm::StageRec> recs;
