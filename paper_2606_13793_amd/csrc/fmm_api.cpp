@@ -1791,77 +1791,6 @@ static int export_level(fmm_plan* plan, decltype(fmm_plan::export_multipoles) fn
   return fail(e == hipErrorOutOfMemory ? FMM_ERR_OUT_OF_MEMORY : FMM_ERR_DEVICE, "export failed: %s", hipGetErrorString(e));
 }
 
-// The complete locals of one level of a field on the folded kernels, [cell]
-// [full term]: the harmonic terms the plan keeps, and the others by Laplace's
-// equation.  The finest level keeps its M2L part only, Walsh-folded over each
-// parent's children: unfolded here, plus the shift of the level above.
-static int export_harmonic_locals(fmm_plan* plan, int level, double* out) {
-  const fmm::Level& lv = plan->lev[level];
-  const int p = plan->p, nk = lv.nk, ht = (p + 1) * (p + 1), hr = (ht + 3) / 4 * 4, fr = (ht + 1) / 2 * 16, nl = plan->NL;
-  auto hidx = [](int x, int y, int z) { return (x + y + z) * (x + y + z) + (z ? x + y + z + 1 + x : x); };
-  auto choose = [](int n, int k) { double b = 1; for (int i = 1; i <= k; ++i) b = b * (n - k + i) / i; return b; };
-  std::vector<int> mi(3 * nl);
-  fmm_multi_index(p, mi.data(), mi.size());
-  auto full = [&](const double* h, double* f) {
-    for (int t = 0; t < nl; ++t) {
-      const int x = mi[3 * t], y = mi[3 * t + 1], z = mi[3 * t + 2], k = z >> 1;
-      double v = 0.0;
-      for (int l = 0; l <= k; ++l) v += choose(k, l) * h[hidx(x + 2 * l, y + 2 * (k - l), z & 1)];
-      f[t] = k & 1 ? -v : v;
-    }
-  };
-  auto fetch = [&](const void* dev, size_t cnt, bool f32, std::vector<double>* v) {
-    v->resize(cnt);
-    if (!f32) return hipMemcpy(v->data(), dev, cnt * sizeof(double), hipMemcpyDeviceToHost);
-    std::vector<float> w(cnt);
-    const hipError_t e = hipMemcpy(w.data(), dev, cnt * sizeof(float), hipMemcpyDeviceToHost);
-    std::copy(w.begin(), w.end(), v->begin());
-    return e;
-  };
-  std::vector<double> own, par;
-  const bool finest = level > fmm::block_level(plan, plan->F);
-  hipError_t e = hipDeviceSynchronize();
-  if (e == hipSuccess)
-    e = fetch(finest ? lv.Lw : lv.Lc, finest ? (size_t)(lv.ncell / 8) * fr : (size_t)lv.ncell * hr, finest && fmm::bottom_low(plan, plan->F), &own);
-  if (e == hipSuccess && finest && level > 3)
-    e = fetch(plan->lev[level - 1].Lc, (size_t)plan->lev[level - 1].ncell * hr, false, &par);
-  if (e != hipSuccess) return fail(FMM_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
-  std::vector<double> h(hr), pf(nl);
-  const int np = nk / 2;
-  for (long long c = 0; c < lv.ncell; ++c) {
-    if (!finest) {
-      full(&own[(size_t)c * hr], out + c * nl);
-      continue;
-    }
-    const int c2 = (int)(c % nk), c1 = (int)((c / nk) % nk), c0 = (int)(c / ((long long)nk * nk));
-    const size_t P = ((size_t)(c0 >> 1) * np + (c1 >> 1)) * np + (c2 >> 1);
-    const int minus = 7 - (((c0 & 1) << 2) | ((c1 & 1) << 1) | (c2 & 1));
-    auto odd = [](int b) { b ^= b >> 2; return (b ^ (b >> 1)) & 1; };
-    for (int z = 0; z < 2; ++z)
-      for (int x = 0; x <= p; ++x)
-        for (int y = 0; x + y + z <= p; ++y) {
-          const int b = hidx(x, y, z), pb = ((x & 1) << 2) | ((y & 1) << 1) | (z & 1);
-          double v = 0.0;
-          for (int k = 0; k < 8; ++k) v += (odd((k ^ pb) & minus) ? -0.125 : 0.125) * own[P * fr + 16 * (b >> 1) + 2 * k + (b & 1)];
-          h[b] = v;
-        }
-    full(h.data(), out + c * nl);
-    if (level <= 3) continue;
-    full(&par[P * hr], pf.data());
-    auto fact = [](int k) { double f = 1; for (int i = 2; i <= k; ++i) f *= i; return f; };
-    for (int t = 0; t < nl; ++t)
-      for (int s = t; s < nl; ++s) {
-        const int gx = mi[3 * s] - mi[3 * t], gy = mi[3 * s + 1] - mi[3 * t + 1], gz = mi[3 * s + 2] - mi[3 * t + 2];
-        if (gx < 0 || gy < 0 || gz < 0) continue;
-        const int mt = mi[3 * t] + mi[3 * t + 1] + mi[3 * t + 2];
-        const int neg = odd((((gx & 1) << 2) | ((gy & 1) << 1) | (gz & 1)) & minus);
-        const double w = std::ldexp(1.0 / (fact(gx) * fact(gy) * fact(gz)), -(mt + 1) - 2 * (gx + gy + gz));
-        out[c * nl + t] += (neg ? -w : w) * pf[s];
-      }
-  }
-  return ok();
-}
-
 int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size_t count) {
   if (!plan) return fail(FMM_ERR_INVALID_ARG, "plan is NULL");
   if (which != 0 && which != 1) return fail(FMM_ERR_INVALID_ARG, "which must be 0 or 1");
@@ -1888,7 +1817,7 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   }
   if (level == plan->F && (fmm::block_field(plan, plan->F) ? fmm::finest_locals_typed(plan, plan->fld[0]) : plan->lt_live))
     return fail(FMM_ERR_UNSUPPORTED, "a low-precision bottom keeps the level-%d locals in its compute type only", level);
-  if (fmm::block_field(plan, plan->F)) return export_harmonic_locals(plan, level, out);
+  if (fmm::block_field(plan, plan->F)) return export_level(plan, plan->export_locals, level, nt, out);
   hipError_t fe = fmm::finish_locals(plan, level, nullptr);
   if (fe == hipSuccess) fe = hipDeviceSynchronize();
   if (fe != hipSuccess) return fail(FMM_ERR_DEVICE, "completing locals failed: %s", hipGetErrorString(fe));

@@ -2019,6 +2019,7 @@ hipError_t Impl<P>::upload_constants() {
 template <int P>
 hipError_t Impl<P>::tables(fmm_plan* pl, hipStream_t s) {
   pl->export_multipoles = export_multipoles<P>;
+  pl->export_locals = export_locals<P>;
   const hipError_t e = alloc_m2lf_part<P>(pl);
   return e == hipSuccess ? tables_all<P>(pl, s) : e;
 }

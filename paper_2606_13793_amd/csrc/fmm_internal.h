@@ -410,10 +410,11 @@ struct fmm_plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   size_t bytes = 0;
-  // folded fields: writes the full multipoles of cnt cells of a level of field 0,
+  // folded fields: write the full expansions of cnt cells of a level of field 0,
   // from the first-th in C order, to dev [cell][term] (set with the order's tables)
   hipError_t (*export_multipoles)(const fmm_plan*, int level, long long first, long long cnt, double* dev,
                                   hipStream_t) = nullptr;
+  decltype(export_multipoles) export_locals = nullptr;
   // stage profiling
   int profiling = 0;
   std::vector<fmm::StageRec> recs;

@@ -85,3 +85,42 @@ def test_stored_multipoles(F, orc, precision, n, p, nmax, delta_l):
     torch.cuda.synchronize()
     for level in levels:
         assert np.array_equal(plan.expansions("M", level), first[level]), level
+
+
+# the finest level alone and with a parent, levels kept complete, FMM-2, the finest
+# level in FP32 (bar: FP32 phi's 1e-5)
+@pytest.mark.parametrize("precision,n,p,delta_l", [
+    ("fp64", 16, 8, 1), ("fp64", 32, 1, 1), ("fp64", 64, 7, 1), ("fp64", 64, 4, 2), ("fp32", 64, 6, 1), ("fp32", 16, 3, 1),
+])
+def test_stored_locals(F, orc, precision, n, p, delta_l):
+    import torch
+    print(f"case stored locals {precision} n={n} p={p} delta_l={delta_l}", flush=True)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    rho = torch.as_tensor(fi.plummer_density(n, fi.multi_plummer_params(8, 650 + n + p))).to("cuda", dt)
+    plan = F.Plan(n, p, precision, delta_l=delta_l, coarse_fp64_levels=2)
+    plan.solve(rho)
+    torch.cuda.synchronize()
+    for level in range(3, plan.finest_level + 1):
+        e = rel(plan.expansions("L", level), oracle_expansions(orc, F, rho.double().cpu().numpy(), p, "L", level))
+        assert e <= (TOL64 if precision == "fp64" else 1e-5), (level, e)
+
+
+def test_locals_cost_what_multipoles_cost(F):
+    """Both exports of the finest level write the same number of values."""
+    import time
+    import torch
+    plan = F.Plan(128, 6)
+    plan.solve(torch.ones((128,) * 3, dtype=torch.float64, device="cuda"))
+    torch.cuda.synchronize()
+
+    def best(which):
+        times = []
+        for _ in range(3):
+            t = time.perf_counter()
+            plan.expansions(which, 6)
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    m, l = best("M"), best("L")
+    print(f"multipoles {m:.3f} s, locals {l:.3f} s", flush=True)
+    assert l <= 8 * m, (l, m)
