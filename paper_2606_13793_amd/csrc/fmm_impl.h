@@ -1574,20 +1574,22 @@ M2lGrid m2lf_grid(const fmm_plan* pl, int T) {
   const long long lim = std::max<long long>(27, total * T / pl->cus / ((OP & 1) && V ? 1 : 2));
   for (int i = 0; i < g.ng; ++i) {
     const long long chunks = (longest[i] + 26) / 27, want = (cost[i] + lim - 1) / lim;
-    g.parts[i] = (int)std::max<long long>(1, std::min<long long>({want, chunks, 32}));
+    // (costs and chunks fall from group to group, so the shared ones are the first)
+    g.parts[i] = g.shared < i ? 1 : (int)std::max<long long>(1, std::min<long long>({want, chunks, 32}));
     g.shared += g.parts[i] > 1;
     g.first[i] = (int)g.blocks;
     g.blocks += (long long)T * g.parts[i];
   }
   return g;
 }
-// doubles of partial sums of such a launch
+// doubles of partial sums of such a launch: those of its shared groups
 template <int P, int OP, int V, int X>
 void m2lf_need_x(const fmm_plan* pl, int T, size_t* part) {
   using S = M2lShape<OP, V, X>;
   const M2lGrid g = m2lf_grid<P, OP, V, X>(pl, T);
   if (!g.shared) return;
-  *part = std::max(*part, (size_t)g.blocks * S::MT * 16 * 16 * S::NT * 8);
+  const long long blocks = g.shared < g.ng ? g.first[g.shared] : g.blocks;
+  *part = std::max(*part, (size_t)blocks * S::MT * 16 * 16 * S::NT * 8);
 }
 template <int P, int OP, int V>
 void m2lf_need(const fmm_plan* pl, int x, int T, size_t* part) {

@@ -286,7 +286,7 @@ struct M2lGrid {
   int first[kM2lGroups] = {};
   int parts[kM2lGroups] = {};
   long long blocks = 0;
-  int shared = 0;  // groups with more than one part
+  int shared = 0;  // groups with more than one part: the first ones, which alone have partial sums
 };
 // One compute type's share of such a launch.
 struct M2lArgs {
