@@ -237,11 +237,11 @@ int fmm_last_status(void);
  * with h = 2^-level the cell size and dx = 1/n.  Layout out[cell][term] with
  * cells of the level in C order and terms in the order of
  * fmm_multi_index().  `count` is the number of doubles `out` holds.
- * A plan whose finest level runs M2P in FP32 or BF16 (delta_l = 1) keeps
- * that level's multipoles and the M2L part of its locals in the compute type
- * only (the level below is formed from the density directly): level F
- * returns FMM_ERR_UNSUPPORTED there, for which = 0 and, unless the M2L of
- * that level splits its offset sums (small grids), for which = 1.
+ * Level F of a plan whose finest level runs in FP32 or BF16 (delta_l = 1)
+ * returns FMM_ERR_UNSUPPORTED for which = 0: FP32 plans form no multipoles there,
+ * BF16 ones keep them in BF16 only.  For which = 1 it does
+ * unless the low-precision levels are small (single fields: n < 256): BF16 plans
+ * then have that level's locals in FP64, FP32 plans return them as rounded to FP32.
  */
 int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size_t count);
 

@@ -352,7 +352,8 @@ long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 // Tiles of M2L launch site x (0: FP64 target levels, 1: low-precision ones)
 // over every field, 8-deep when all its row grids are at most 8 cells deep,
 // as build_schedule lays them out; a site under 128 tiles splits each tile's
-// offset sum over several blocks.
+// offset sum over several blocks.  (FP32 plans have no such launch: for them it is
+// the size from which the finest locals are not exported.)
 long long conv_site_tiles(const fmm_plan* pl, int x) {
   const int klow = fmm::m2l_low_from(pl);
   bool any = false, shallow = true;
@@ -375,12 +376,11 @@ long long conv_site_tiles(const fmm_plan* pl, int x) {
 }  // namespace
 
 namespace fmm {
-// Whether the finest locals of field fd live only in the compute type
-// (Level::Lt): an FMM-1 field whose bottom kernel runs in FP32/BF16, when the
-// low-precision M2L launch does not split its offset sums (split partial sums
-// are FP64).  Then no FP64 locals are allocated for that level.
+// Whether the finest locals of field fd live only in BF16 (Level::Lt): an FMM-1
+// field on k_bottom, when the BF16 M2L launch does not split its offset sums
+// (split partial sums are FP64).  Then no FP64 locals are allocated for that level.
 bool finest_locals_typed(const fmm_plan* pl, const Field& fd) {
-  return pl->dl == 1 && fd.F >= 3 && bottom_low(pl, fd.F) && conv_site_tiles(pl, 1) >= 128;
+  return !block_field(pl, fd.F) && pl->dl == 1 && fd.F >= 3 && conv_site_tiles(pl, 1) >= 128;
 }
 }  // namespace fmm
 
@@ -1045,9 +1045,8 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
         }
       }
       if (fmm::typed_level(pl, fd.F, k)) {
-        // the copy in the compute type: BF16 chunks of 16 terms, FP32 of 4
-        const int kc = pl->precision == 2 ? 16 : 4;
-        const size_t tb = (size_t)((pl->NM + kc - 1) / kc) * kc * lv.ncellp * (pl->precision == 2 ? 2 : 4);
+        // the copy in BF16, chunks of 16 terms
+        const size_t tb = (size_t)((pl->NM + 15) / 16) * 16 * lv.ncellp * 2;
         if (dev_alloc(pl, &lv.Mt, tb)) return bail();
         if (hipMemset(lv.Mt, 0, tb) != hipSuccess) {
           fail(FMM_ERR_DEVICE, "hipMemset failed");
@@ -1055,11 +1054,9 @@ fmm_plan* create_plan(const std::vector<int>& ns, int p, const fmm_options& o, i
         }
       }
       if (k >= 3 && !fmm::block_field(pl, fd.F)) {
-        // the finest level of a low-precision bottom keeps its locals in the
-        // compute type only (Level::Lt)
+        // (finest locals kept in BF16 only: Level::Lt)
         const bool typed = k == fd.F && fmm::finest_locals_typed(pl, fd);
-        const size_t lb = (size_t)(lv.ncell / 8) * fmm::loc_stride(p) *
-                          (!typed ? sizeof(double) : pl->precision == 2 ? 2 : 4);
+        const size_t lb = (size_t)(lv.ncell / 8) * fmm::loc_stride(p) * (typed ? 2 : sizeof(double));
         void*& dst = typed ? lv.Lt : lv.L;
         if (dev_alloc(pl, &dst, lb)) return bail();
         if (hipMemset(dst, 0, lb) != hipSuccess) {
@@ -1797,7 +1794,10 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
   const int lo = which == 0 ? 2 : 3;
   if (level < lo || level > plan->F) return fail(FMM_ERR_INVALID_ARG, "level %d outside [%d, %d]", level, lo, plan->F);
   if (which == 0 && level == plan->F && plan->dl == 1 && fmm::bottom_low(plan, plan->F))
-    return fail(FMM_ERR_UNSUPPORTED, "a low-precision bottom keeps the level-%d multipoles in its compute type only", level);
+    return fail(FMM_ERR_UNSUPPORTED,
+                fmm::block_field(plan, plan->F) ? "an FP32 plan forms no level-%d multipoles"
+                                                : "a BF16 plan keeps the level-%d multipoles in BF16 only",
+                level);
   const fmm::Level& lv = plan->lev[level];
   const int nt = which == 0 ? plan->NMX : plan->NL;
   const int nch = (nt + 3) / 4;
@@ -1815,9 +1815,15 @@ int fmm_debug_expansions(fmm_plan* plan, int which, int level, double* out, size
     }
     return ok();
   }
-  if (level == plan->F && (fmm::block_field(plan, plan->F) ? fmm::finest_locals_typed(plan, plan->fld[0]) : plan->lt_live))
-    return fail(FMM_ERR_UNSUPPORTED, "a low-precision bottom keeps the level-%d locals in its compute type only", level);
-  if (fmm::block_field(plan, plan->F)) return export_level(plan, plan->export_locals, level, nt, out);
+  if (fmm::block_field(plan, plan->F)) {
+    // FP32 plans keep the finest locals in FP32 at every size; they are exported
+    // from the sizes at which BF16 plans have them in FP64 (finest_locals_typed)
+    if (level == plan->F && plan->dl == 1 && fmm::bottom_low(plan, plan->F) && conv_site_tiles(plan, 1) >= 128)
+      return fail(FMM_ERR_UNSUPPORTED, "an FP32 plan of this size does not export the level-%d locals, kept in FP32 only", level);
+    return export_level(plan, plan->export_locals, level, nt, out);
+  }
+  if (level == plan->F && plan->lt_live)
+    return fail(FMM_ERR_UNSUPPORTED, "a BF16 plan of this size keeps the level-%d locals in BF16 only", level);
   hipError_t fe = fmm::finish_locals(plan, level, nullptr);
   if (fe == hipSuccess) fe = hipDeviceSynchronize();
   if (fe != hipSuccess) return fail(FMM_ERR_DEVICE, "completing locals failed: %s", hipGetErrorString(fe));

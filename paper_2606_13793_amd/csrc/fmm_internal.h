@@ -495,10 +495,8 @@ inline int fold_variant(const fmm_plan* pl, int op, long long large) {
   return large >= pl->cus / ((op & 1) ? 8 : 4) ? 1 : 0;
 }
 // whether the multipoles of level k (of a field with finest level F) get a
-// copy in the compute type: the low-precision bottom reads level F, the
-// low-precision M2L into level k + 1 reads level k
+// copy in BF16: k_bottom reads level F, the BF16 M2L into level k + 1 reads level k
 inline bool typed_level(const fmm_plan* pl, int F, int k) {
-  if (pl->precision == 0) return false;
   if (block_field(pl, F)) return false;
   return (k == F && bottom_low(pl, F)) || (k < F && k + 1 >= m2l_low_from(pl));
 }

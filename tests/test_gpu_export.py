@@ -124,3 +124,20 @@ def test_locals_cost_what_multipoles_cost(F):
     m, l = best("M"), best("L")
     print(f"multipoles {m:.3f} s, locals {l:.3f} s", flush=True)
     assert l <= 8 * m, (l, m)
+
+
+def test_refused_exports_say_why(F):
+    """The finest level of an FP32 plan: no multipoles are formed there, at any
+    size; its locals are exported from small grids."""
+    plan = F.Plan(64, 3, "fp32")
+    with pytest.raises(F.FmmError, match="forms no level-5 multipoles") as e:
+        plan.expansions("M", 5)
+    assert e.value.code == F.FMM_ERR_UNSUPPORTED
+    for n, fine in ((64, True), (128, True), (256, False)):
+        plan = F.Plan(n, 1, "fp32")
+        if fine:
+            plan.expansions("L", plan.finest_level)
+            continue
+        with pytest.raises(F.FmmError, match="kept in FP32 only") as e:
+            plan.expansions("L", plan.finest_level)
+        assert e.value.code == F.FMM_ERR_UNSUPPORTED
