@@ -226,8 +226,8 @@ __device__ __forceinline__ void walsh8(H (&y)[8]) {
 
 // Walsh sums of the 8 mirror images r[minus bits] for the NE patterns
 // NE eg .. NE eg + NE - 1: s = the weight of the minus images along each axis,
-// chi of the axis where eg fixes it (x for NE <= 4; y for NE <= 2; z for NE = 1) times the
-// images' own sign.
+// chi of the axis where eg fixes it (x for NE <= 4; y for NE = 2) times the images'
+// own sign.
 template <int NE, typename H>
 __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[NE]) {
   H x[4];
@@ -252,13 +252,10 @@ __device__ __forceinline__ void fold8(const H (&r)[8], H sx, H sy, H sz, H (&a)[
     a[2] = fma(sz, m1, m0);
     a[3] = fma(-sz, m1, m0);
   } else {
+    static_assert(NE == 2, "2, 4 or 8 patterns");
     const H y0 = fma(sy, x[2], x[0]), y1 = fma(sy, x[3], x[1]);
-    if constexpr (NE == 2) {
-      a[0] = fma(sz, y1, y0);
-      a[1] = fma(-sz, y1, y0);
-    } else {
-      a[0] = fma(sz, y1, y0);
-    }
+    a[0] = fma(sz, y1, y0);
+    a[1] = fma(-sz, y1, y0);
   }
 }
 
@@ -699,7 +696,7 @@ __global__ void k_m2lf_table(const double* __restrict__ Dtab, const int2* __rest
 // and the next chunk's planes are read beside the products.  Two blocks run per
 // compute unit, so that one's staging and stores lie beside the other's
 // products.  At 64^3 source cells, p = 6 (the finest level of a 256^3 grid):
-// FP64 1785 us -> 1460 us (835 us of products at 2.4 GHz), FP32 1216 -> 885 us,
+// FP64 1785 us -> 1436 us (835 us of products at 2.4 GHz), FP32 1216 -> 885 us,
 // of which the 839 (420) MB of results are 180 (90) us of copy rate.
 //
 // LDS tile of k_m2lf: rows of 12 cells along z, the even cells first (the 16
@@ -790,7 +787,7 @@ __device__ __forceinline__ void m2lf_put(const Seg& sg, int cb, int ox0, int oy0
 template <int NT>
 constexpr int m2lf_nte = NT % 2 ? NT : NT / 2;
 // Tile shapes of the folded M2L by variant (rows of octs, column tiles per
-// group, patterns per wave, K slices): forward, and transposes, whose few
+// group, patterns per wave, waves): forward, and transposes, whose few
 // column tiles are dominated by the first.
 // X: FP32 products, which take half the time, so that folding an operand has to
 // serve more of them.
@@ -922,14 +919,13 @@ __device__ __forceinline__ void m2lf_run(const M2lArgs& args, int block, char* s
         for (int t = 0; t < decltype(nac)::value; ++t) acc[m][e][t] = M::op(a[m][e], b[e][t], acc[m][e][t]);
   };
   // chi of the axes the wave's patterns share
-  const H cx = NE <= 4 && (e0 & 4) ? H(-1) : H(1), cy = NE <= 2 && (e0 & 2) ? H(-1) : H(1),
-          cz = NE == 1 && (e0 & 1) ? H(-1) : H(1);
+  const H cx = NE <= 4 && (e0 & 4) ? H(-1) : H(1), cy = NE <= 2 && (e0 & 2) ? H(-1) : H(1);
   // the 27 sources of chunk c
   auto run = [&](auto nac, int c, bool more) {
     constexpr int NA = decltype(nac)::value;
     const int t = (HEAD ? 1 : 0) + 4 * c + kq;  // the lane's term, and the signs of its minus images
     const int par = t >= NTERM ? 0 : OP == 3 ? t >> 5 : OP == 1 ? c_ft<P>.col[t] >> 8 : c_ft<P>.par[t];
-    const H gx = par & 4 ? -cx : cx, gy = par & 2 ? -cy : cy, gz = par & 1 ? -cz : cz;
+    const H gx = par & 4 ? -cx : cx, gy = par & 2 ? -cy : cy, gz = par & 1 ? H(-1) : H(1);
     const int base = (HEAD ? FOLD_HEAD : 0) + 27 * c;
     const H* const pl = oct + kq * CELLS;
     const H* p[4];
@@ -1009,7 +1005,7 @@ __device__ __forceinline__ void m2lf_run(const M2lArgs& args, int block, char* s
       __builtin_amdgcn_sched_barrier(0);
       H a[NR][NE];
 #pragma unroll
-      for (int m = 0; m < NR; ++m) fold8<NE>(r[m], cx, cy, cz, a[m]);
+      for (int m = 0; m < NR; ++m) fold8<NE>(r[m], cx, cy, H(1), a[m]);
       products(std::integral_constant<int, NT>{}, a, b[u & 1]);
       __builtin_amdgcn_sched_barrier(0);
     });

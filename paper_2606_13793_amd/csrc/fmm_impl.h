@@ -404,7 +404,6 @@ __global__ __launch_bounds__(M2MShape<PO>::THREADS) void k_m2m(const Seg* __rest
   __shared__ int sstart[NM + 1];
   __shared__ int soff[NE];
   __shared__ double scoef[NE];
-  __shared__ double out[M2M_PAR * NM];
   const Seg& sg = find_seg(segs, nseg, blockIdx.x);
   const double* __restrict__ Mc = sg.a;
   double* __restrict__ Mp = sg.b;
@@ -464,27 +463,11 @@ __global__ __launch_bounds__(M2MShape<PO>::THREADS) void k_m2m(const Seg* __rest
     const int p2 = (int)(P % np), p1 = (int)((P / np) % np), p0 = (int)(P / ((long long)np * np));
     const long long cp = ((long long)(p0 + 3) * npp + (p1 + 3)) * npp + (p2 + 3);
     const double v = al < nmx ? acc : 0.0;  // truncation at nmax
-    out[pl * NM + al] = v;
     Mp[((al >> 2) * ncp_p + cp) * 4 + (al & 3)] = v;
     if constexpr (Mf<CT>::IDX != 0) {
       constexpr int KC = Mf<CT>::KC;
       if (sg.t) ((typename Mf<CT>::H*)sg.t)[((al / KC) * ncp_p + cp) * KC + al % KC] = static_cast<typename Mf<CT>::H>(v);
     }
-  }
-  if (!sg.u) return;
-  // the harmonic terms
-  __syncthreads();
-  for (int w = threadIdx.x; w < M2M_PAR * hterms(PO); w += M2M_THREADS) {
-    const int pl = w % M2M_PAR, i = w / M2M_PAR;
-    const long long P = P0 + pl;
-    if (P >= nP) continue;
-    const double v = h_reduce(i, [&](int al) { return out[pl * NM + al]; });
-    const int p2 = (int)(P % np), p1 = (int)((P / np) % np), p0 = (int)(P / ((long long)np * np));
-    const long long x = i * ncp_p + ((long long)(p0 + 3) * npp + (p1 + 3)) * npp + (p2 + 3);
-    if (sg.split)
-      static_cast<float*>(sg.u)[x] = (float)v;
-    else
-      static_cast<double*>(sg.u)[x] = v;
   }
 }
 

@@ -131,16 +131,6 @@ constexpr int conv_group_end(int op, int P, int t0, int KC, int MAXT, int MAXB) 
   }
   return t;
 }
-constexpr int conv_group_start(int op, int P, int g, int KC, int MAXT, int MAXB) {
-  int t = 0;
-  for (int i = 0; i < g; ++i) t = conv_group_end(op, P, t, KC, MAXT, MAXB);
-  return t;
-}
-constexpr int conv_ngroups(int op, int P, int KC, int MAXT, int MAXB) {
-  int g = 0, t = 0;
-  while (t < conv_ntiles(op, P)) { t = conv_group_end(op, P, t, KC, MAXT, MAXB); ++g; }
-  return g;
-}
 
 // number of interaction-list offsets per parity class (6^3 - 3^3); the
 // device lists hold NLIST_PAD entries per class, entry NLIST being a null
@@ -265,7 +255,7 @@ struct AdjWs {
   void* lb[16] = {};     // level k: the M2L rows' cotangents, planes [8 (p+1)^2][(2^(k-1)+6)^3] in the M2L's type
   double* lc[16] = {};   // level k < F: the complete locals' cotangents, [cell][hrow]
   SegTable m2ltf[2];     // folded transposed M2L [FP64 | FP32]
-  int m2ltf_v[2] = {0, 0};  // and its tile (rows of octs: 1, 2 or 4)
+  int m2ltf_v[2] = {0, 0};  // and its variant (fold_variant)
   void* yb = nullptr;    // FMM-2: folded cotangents of the level-F cells, planes [256][(2^F+6)^3] in the M2P's type
   SegTable m2ptf;        // FMM-2: folded transposed M2P
   int m2ptf_v = 0;

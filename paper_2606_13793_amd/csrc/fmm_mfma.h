@@ -126,9 +126,9 @@ __device__ __forceinline__ void stage_halo(typename Mf<CT>::H* __restrict__ halo
   using HL = Halo<CT, BZ>;
   constexpr int S4 = Mf<CT>::KC / 4;
   constexpr int HZ = BotShape<BZ>::HZ, NH = HX * HY * HZ, NIT = (NH + NTHR - 1) / NTHR;
-  // cells per batch, sized to the registers the kernels leave free: FP64
-  // 5 (40 registers in flight), FP32 2 (16), BF16 1 (the 4 loads of a cell)
-  constexpr int BATCH = Mf<CT>::IDX == 0 ? 3 : (Mf<CT>::IDX == 1 ? 2 : 1);
+  // cells per batch, sized to the registers the kernels leave free: FP64 3,
+  // BF16 1 (the 4 loads of a cell)
+  constexpr int BATCH = Mf<CT>::IDX == 0 ? 3 : 1;
   const __attribute__((address_space(1))) d4* g = gmem(reinterpret_cast<const d4*>(src));
 #pragma unroll 1
   for (int b0 = 0; b0 < NIT; b0 += BATCH) {
@@ -1059,7 +1059,7 @@ __global__ __launch_bounds__(M2L_THREADS, 1) void k_conv(const Seg* __restrict__
   };
   // Packed groups: M2L column tiles of degree p need the single multipole
   // term a = 0, so one K chunk would carry one useful term in KC.  With one
-  // offset per MFMA (FP64, FP32) such a group instead packs four offsets into
+  // offset per MFMA (FP64) such a group instead packs four offsets into
   // K: lane k-group kq takes offset 4 j + kq, term 0, and its B value from
   // the k-group-0 lane of that offset's fragment.
   constexpr bool CAN_PACK = OPM == 1 && OP == CV_M2L;
