@@ -145,7 +145,7 @@ int fmm_solve_backward(fmm_plan* plan, const void* dphi, const void* dg, void* d
  * the array it uses, writes its launch tables there and runs the backward
  * pass.  Plans whose workspace does not fit are rejected with
  * FMM_ERR_INVALID_ARG before anything is enqueued: with m = n / 2^delta_l
- * it needs
+ * it is counted (as BF16 plans lay it out; FP64 and FP32 ones need no more) as
  *   4096 + ceil256(8^delta_l (m+6)^3 32) + sum_{k=3..F} ceil256(S (2^(k-1)+6)^3 8)
  *   (+ ceil256(16 (m+6)^3 32) for delta_l = 2)
  * bytes, S = 16 ceil(8 nterms(p) / 16), which fits n <= 32 at every p and

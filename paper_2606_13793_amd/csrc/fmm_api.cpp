@@ -1581,10 +1581,12 @@ int fmm_solve_backward(fmm_plan* plan, const void* dphi, const void* dg, void* d
 }
 
 // The backward pass with its workspace laid out in the library's static
-// device array instead of plan memory: [segment tables | Ybar | adjoint
-// locals of levels F..3], each part 256-byte aligned, zeroed by a kernel on
-// `stream` at every call; the transposed M2L writes its adjoint multipoles
-// in place (no split partial sums).  Only kernels are enqueued.
+// device array instead of plan memory, each part 256-byte aligned and zeroed by a
+// kernel on `stream` at every call: [segment tables | AdjWs, as fmm_solve_backward
+// allocates it].  Folded fields run the same launches as there (their shared K
+// loops add through the plan's m2lf_part); BF16 ones write the transposed M2L's
+// adjoint multipoles in place, without split partial sums.  Only kernels are
+// enqueued.
 int fmm_solve_backward_noalloc(fmm_plan* plan, const void* dphi, const void* dg, void* drho, void* stream) {
   if (int rc = check_backward_args(plan, dphi, dg, drho)) return rc;
   hipStream_t s = (hipStream_t)stream;
